@@ -138,7 +138,7 @@ def prepare(case, seed):
         LSE = torch.empty((B, H, n), dtype=torch.float32, device=dev)
         ws = torch.empty(max(256, bb.bigbird_attn_workspace_bytes(B, H, n, DIM, BLOCK, g, case["w"], r)),
                          dtype=torch.uint8, device=dev)
-        state["out"] = (O, LSE)
+        state["out"], state["workspace"] = (O, LSE), ws
         state["call"] = bb.prepare_attn_fwd(Q, K, V, state["rand_idx"], O, LSE, ws, **args)
     return state
 
