@@ -186,8 +186,8 @@ def forward_line(bb, torch, dev, name: str, batches: int, skip_padded_query_bloc
 def etc_forward_lines(bb, torch, dev, batches: int):
     """Forward timings of the ETC construction (Sec. 2: extra global tokens in front) at b = 64, total
     length 4096, 12 heads, window of 3 blocks, no random blocks: 256 global tokens (four leading
-    global blocks) and 230 (App. E's NaturalQ figure: the fourth block padded with a key mask,
-    which sends every item through the per-key masking path)."""
+    global blocks) and 230 (App. E's NaturalQ figure: the fourth block padded with a key mask, so
+    that every row attends a block with padded keys inside)."""
     import oracle
     out = []
     B, H, n, b, w, scale = 4, 12, 4096, 64, 3, 0.125

@@ -199,9 +199,8 @@ int bigbird_attn_bwd(const void* Q, const void* K, const void* V, const void* O,
  * else); p_drop == 0 is the plain call, bit for bit.  Use a new seed for every step and layer.
  *
  * bigbird_attn_fwd_dropout: arguments, checks and outputs of bigbird_attn_fwd, plus p_drop and
- * seed.  The bf16 path applies the mask on its per-item path (the one that also serves
- * blocks with padded keys inside), not in the pipelined one: expect about half the
- * throughput of the plain call.
+ * seed.  The bf16 path applies the mask on its per-item path, not in the pipelined one: expect
+ * about half the throughput of the plain call.
  */
 int bigbird_attn_fwd_dropout(const void* Q, const void* K, const void* V, void* O, float* LSE,
                              const int32_t* rand_idx, const uint8_t* key_padding_mask,

@@ -20,8 +20,7 @@
 //     reference of 0 is exact as long as the row sum stays inside [2^-40, 2^60]; a wave
 //     checks that at the end of its item and, if a row left the range (logits beyond about
 //     +-28 in natural units), puts the item on a list that it works off afterwards with the
-//     classical running-maximum recurrence (slow_item), as it does with items that have
-//     padded keys inside a block.  Both paths give the same un-normalised (reference, sum,
+//     classical running-maximum recurrence (slow_item).  Both paths give the same un-normalised (reference, sum,
 //     O~) triple to the common epilogue.  (Folding the factor into the query operand would
 //     save the multiplication, but the operand would have to be rounded to bf16 again: that
 //     perturbs a logit by up to 2^-9 of its size, four times the error of everything else in
@@ -44,10 +43,16 @@
 //     three quarters of a block pair to land.
 //   * V^T operands come from the transposing LDS read; the LDS layout is swizzled so
 //     that neither read pattern has bank conflicts.
+//   * A block with padded keys inside takes the same body: after the conversion the padded keys'
+//     probabilities are cleared (drop_padded_keys), behind a scalar branch per slot.  What bounds
+//     such batches is the pipelined body as ever: 8 sequences of 1024 .. 4096 valid positions
+//     (12 heads, n = 4096) 72 us against 84 when items with such a block went to the per-item list,
+//     57 against 101 with their padded query blocks skipped; 230 leading global tokens (every row
+//     attends a cut block, 4 sequences) 47 against 75.
 //   * The two waves of a SIMD get their issue priority from the pairs they still have to
 //     do, so that they finish together (set_issue_priority).
-//   * Two instances of the kernel.  fwd_kernel_bf16<false> is everything above and nothing else.
-//     fwd_kernel_bf16<true> is launched only when a call asks for attention dropout (every item
+//   * Three instances of the kernel: without a padding mask (everything above and nothing else),
+//     with one, and kOptions, launched only when a call asks for attention dropout (every item
 //     then takes the per-item path, in a plain loop, where the keep mask of dropout.h is applied
 //     to the probabilities that multiply V), or for fully padded query blocks to be skipped
 //     (BB_SKIP_PADDED_QUERY_BLOCKS: their rows are written as zeros and the waves claim the
@@ -68,6 +73,10 @@ constexpr int kFwdWaves = 4;
 constexpr int kFwdThreads = 64 * kFwdWaves;  // four independent wavefronts, one work item each
 constexpr int kTile = kBlk * kDim * 2;       // 8 KB
 constexpr int kHalfTile = kTile / 2;         // 32 rows
+
+// Instances of the kernel: no padding mask; a padding mask; a padding mask or none, and attention
+// dropout or skipped query blocks.
+enum { kPlain = 0, kMasked = 1, kOptions = 2 };
 
 // Row sums of the reference-free path must stay inside [kSumLo, kSumHi] (see the file header).
 constexpr float kSumLo = 0x1p-40f;
@@ -209,7 +218,7 @@ __device__ __forceinline__ int finish_key_list_sparse(const Pattern& pat, int r,
 // was requested three slots earlier; the request for the half after that follows as soon as the
 // read has returned.  Tile loads outstanding at the start of a pair, oldest first:
 // K(i+1).t0 and V(i).t1 (8 instructions).
-// Blocks with padded keys inside never come here: such items take the slow path.
+// A block with padded keys inside comes with the validity bits of its keys (key_bits, LDS).
 struct PairCtx {
   const char* lds_k;   // this wave's K and V tile buffers
   const char* lds_v;
@@ -314,6 +323,28 @@ __device__ __forceinline__ void pin_slot() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Padded keys of a unit leave the probabilities here, after the conversion and before the P V and
+// row-sum products of the next slot see them (their scores may be anything, also not a number).
+// bits: validity of the 32 keys of the unit, in key order.  Element kk of operand sgl belongs to key
+// 16 sgl + 8 (kk / 4) + 4 hf + kk % 4 (acc_row).  Three instructions per packed pair on the vector port --
+// only block pairs with padded keys inside pay them: the other pairs take one scalar branch per slot.
+__device__ __forceinline__ void drop_padded_keys(uint32_t bits, int hf, bf16x8 (&pb)[2]) {
+  const int b = static_cast<int>(bits >> (4 * hf));
+#pragma unroll
+  for (int sgl = 0; sgl < 2; ++sgl) {
+    union { bf16x8 v; uint32_t d[4]; } u;
+    u.v = pb[sgl];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int key = acc_row(sgl * 8 + 2 * m, 0);
+      const uint32_t even = static_cast<uint32_t>(__builtin_amdgcn_sbfe(b, key, 1));      // 0 or ~0
+      const uint32_t odd = static_cast<uint32_t>(__builtin_amdgcn_sbfe(b, key + 1, 1));
+      u.d[m] &= (even & 0xffffu) | (odd & 0xffff0000u);
+    }
+    pb[sgl] = u.v;
+  }
+}
+
 // One block pair.  The arithmetic and the memory requests are the same for every pair, so that
 // one straight-line body serves them all: the first pair of an item finishes a predecessor that
 // does not exist (p3 = 0 on entry, V fragments zeroed), the last one starts a successor that does
@@ -322,11 +353,13 @@ __device__ __forceinline__ void pin_slot() {
 // delivers a tile nobody uses (see TileStreams).
 // k1 / v1: global address of the tile that follows this pair's in the K / V stream; k2: the one
 // after that in the K stream.
+template <int kMode>
 __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
                                           const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], bf16x8 (&va)[2][2][2],
                                           f32x16& sA, bf16x8 (&p3)[2], f32x16 (&o)[2][2],
                                           const RowSumOperand& ones, f32x4 (&ls)[2],
-                                          const char* k1, const char* v1, const char* k2) {
+                                          const char* k1, const char* v1, const char* k2,
+                                          const uint32_t* key_bits = nullptr) {
   f32x16 sB, sC, sD;
   bf16x8 p0[2], p1[2], p2[2];
 
@@ -338,6 +371,7 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   unit_pv(va[1], p3, o[1], ones, ls[1]);
   unit_probs(sA, cx.c, p0);
   pin_slot<0>();
+  if (kMode != kPlain && key_bits) drop_padded_keys(key_bits[0], cx.hf, p0);
 
   // ---- slot 1: K(i+1).t0 and V(i).t1 have landed
   wait_tile_loads<8>();
@@ -347,6 +381,7 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   unit_pv(va[0], p0, o[0], ones, ls[0]);
   unit_probs(sB, cx.c, p1);
   pin_slot<12>();
+  if (kMode != kPlain && key_bits) drop_padded_keys(key_bits[0], cx.hf, p1);
 
   // ---- slot 2
   wait_lds_reads();
@@ -356,6 +391,7 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   unit_pv(va[0], p1, o[1], ones, ls[1]);
   unit_probs(sC, cx.c, p2);
   pin_slot<0>();
+  if (kMode != kPlain && key_bits) drop_padded_keys(key_bits[1], cx.hf, p2);
 
   // ---- slot 3: K(i+1).t1 and V(i+1).t0 have landed
   wait_tile_loads<8>();
@@ -365,11 +401,15 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   unit_pv(va[1], p2, o[0], ones, ls[0]);
   unit_probs(sD, cx.c, p3);
   pin_slot<12>();
+  if (kMode != kPlain && key_bits) drop_padded_keys(key_bits[1], cx.hf, p3);
 }
 
 // LDS of a workgroup (at namespace scope: the cold paths below are separate functions).
 __shared__ __attribute__((aligned(1024))) char lds_all[kFwdWaves][2 * kTile];  // per wave: K tile, V tile
 __shared__ int klist_all[kFwdWaves][kGlobalWaveLen];
+// validity bits of the keys of listed blocks that have padded keys inside, for the three items a wave
+// knows at a time (the one in work, the next, the one after)
+__shared__ uint32_t key_bits_all[kFwdWaves][3][kGlobalWaveLen][2];
 __shared__ float mrg_m[kFwdWaves][kBlk], mrg_l[kFwdWaves][kBlk];  // global rows: per-wave exponent, sum
 
 // What a wave knows about itself and its LDS.
@@ -434,7 +474,8 @@ struct Item {
   int slot;            // partial-result slot (nchunks > 1)
   int cnt;             // key blocks in this slice
   int kl;              // the list: lane t holds entry t % 16
-  bool any_partial;    // some listed block has padded keys inside
+  unsigned partial;    // bit t: entry t has padded keys inside (its validity bits are in the wave's key_bits)
+  bool per_item;       // not for the pipelined path (see make_item)
   bool skipped;        // query block without a valid position, not to be computed (cnt = 0)
 };
 
@@ -503,7 +544,7 @@ __device__ __forceinline__ bool block_any_valid_scalar(const uint8_t* kmask, int
 // the row).  All loads here are waited for before the function returns (scalar loads inside
 // their asm statement, the others by the compiler), so tile loads in flight are at most delayed.
 // Its first part: which row, which slice of the row's list (arithmetic only, no memory access).
-template <bool kX>
+template <int kMode>
 __device__ __forceinline__ void item_coords(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
                                             int& list_lo, int& list_len, bool& row_global) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
@@ -539,22 +580,25 @@ __device__ __forceinline__ const char* query_tile(const FwdParams& p, int bh, in
   return static_cast<const char*>(p.Q) + (static_cast<size_t>(bh) * p.n + static_cast<size_t>(j) * kBlk) * (kDim * 2);
 }
 
-// kX (here and below): the instance of the kernel that serves attention dropout and skipped query
-// blocks.  The plain instance holds none of that code, so its registers and schedule are its own.
-template <bool kX>
-__device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it) {
+// kMode (here and below): the instance of the kernel.  kPlain knows no padding mask, kMasked does,
+// kOptions also serves attention dropout and skipped query blocks.  An instance holds no code of the
+// others, so its registers and schedule are its own.
+template <int kMode>
+__device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
+                                          int bits_slot) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   const int lane = lane_again(w.lane);
   int list_lo, list_len;
   bool row_global;
-  item_coords<kX>(p, w, sc, t, it, list_lo, list_len, row_global);
+  item_coords<kMode>(p, w, sc, t, it, list_lo, list_len, row_global);
   const int bi = it.bh / p.H, h = it.bh % p.H;
   it.skipped = false;
-  if (kX && p.skip_q && !block_any_valid_scalar(p.kmask, __builtin_amdgcn_readfirstlane(bi), p.n, __builtin_amdgcn_readfirstlane(it.j))) {
+  if (kMode == kOptions && p.skip_q && !block_any_valid_scalar(p.kmask, __builtin_amdgcn_readfirstlane(bi), p.n, __builtin_amdgcn_readfirstlane(it.j))) {
     // the caller reads the mask as a query mask too, and no position of this block is valid:
     // an item without key blocks (O = 0, LSE = -inf)
     it.skipped = true;
-    it.any_partial = false;
+    it.partial = 0;
+    it.per_item = false;
     it.kl = 0;
     it.bh = __builtin_amdgcn_readfirstlane(it.bh);
     it.j = __builtin_amdgcn_readfirstlane(it.j);
@@ -592,20 +636,47 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
   asm volatile("" ::: "memory");
   it.kl = w.klist[lane & (kGlobalWaveLen - 1)];
   asm volatile("" ::: "memory");
-  it.any_partial = kX && p.drop.thr != 0;  // attention dropout is applied on the slow path only
-  if (p.kmask) {
+  it.per_item = kMode == kOptions && p.drop.thr != 0;  // attention dropout is applied on the per-item path only
+  it.partial = 0;
+  if (kMode != kPlain && p.kmask) {
     bool any_valid = false, any_padded = false;
     if (lane < it.cnt) block_mask_flags(p.kmask, bi, p.n, it.kl, any_valid, any_padded);
+    const uint64_t m = __ballot(any_valid);
+    const int entry = fast_list ? mask_rank(m) : lane;
+    const int kb = it.kl;
     if (fast_list) {
       // drop the blocks without a valid key (the general builder has done that already)
-      const uint64_t m = __ballot(any_valid);
-      if (any_valid) w.klist[mask_rank(m)] = it.kl;
+      if (any_valid) w.klist[entry] = kb;
       it.cnt = static_cast<int>(__popcll(m));
+    }
+    const bool cut = any_valid && any_padded;
+    if (__any(cut)) {
+      if (cut) {
+        uint32_t bits[2];
+        block_key_bits(p.kmask, bi, p.n, kb, bits);
+        key_bits_all[w.wv][bits_slot][entry][0] = bits[0];
+        key_bits_all[w.wv][bits_slot][entry][1] = bits[1];
+      }
+      // entries are in lane order, so the flags of the kept lanes, closed up, are the flags of the list
+      uint64_t rest = m, flags = __ballot(cut);
+      if (fast_list) {
+        unsigned closed = 0;
+        for (int e = 0; rest; ++e, rest &= rest - 1)
+          closed |= ((flags >> __builtin_ctzll(rest)) & 1) ? 1u << e : 0u;
+        it.partial = closed;
+      } else {
+        it.partial = static_cast<unsigned>(flags);
+      }
+      // No block without padded keys: a row may have a key or two, whose rounded probabilities are a
+      // row sum that is off by up to 2^-9 (over 64 keys and more the roundings average out) -- the
+      // recurrence sums them before the rounding.
+      it.per_item |= it.partial == (1u << it.cnt) - 1;
+    }
+    if (fast_list) {
       asm volatile("" ::: "memory");
       it.kl = w.klist[lane & (kGlobalWaveLen - 1)];
       asm volatile("" ::: "memory");
     }
-    it.any_partial |= __any(any_valid && any_padded) != 0;
   }
   // all of these are wave uniform; saying so keeps them (and what is computed from them) in
   // scalar registers
@@ -615,7 +686,8 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
   it.nchunks = __builtin_amdgcn_readfirstlane(it.nchunks);
   it.slot = __builtin_amdgcn_readfirstlane(it.slot);
   it.cnt = __builtin_amdgcn_readfirstlane(it.cnt);
-  it.any_partial = __builtin_amdgcn_readfirstlane(static_cast<int>(it.any_partial)) != 0;
+  it.partial = __builtin_amdgcn_readfirstlane(it.partial);
+  it.per_item = __builtin_amdgcn_readfirstlane(static_cast<int>(it.per_item)) != 0;
 }
 
 // First tiles of an item that nobody has fetched ahead.  The query block takes the same road as a
@@ -687,10 +759,11 @@ struct TileStreams {
 // one more tile of the K stream, its first K tile as one more of the V stream, so that both are
 // in LDS when this item's last pair is done (they are read as K / V fragments by the pairs'
 // regular reads, which nothing uses).
+template <int kMode>
 __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
                                           const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], const FwdParams& p,
                                           const Item& item, const Item* next, bool fresh,
-                                          f32x16 (&o)[2][2], float (&l_tot)[2]) {
+                                          const uint32_t* key_bits, f32x16 (&o)[2][2], float (&l_tot)[2]) {
   bf16x8 va[2][2][2], p3[2];
   f32x16 sA;
   const RowSumOperand ones(lane_id());
@@ -722,7 +795,8 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
   unit_scores(ka[0], qb[0], sA);
 
   for (int i = 0; i < cnt; ++i)
-    pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
+    pair_step<kMode>(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2),
+                     (item.partial >> i) & 1 ? key_bits + 2 * i : nullptr);
   if (!next) wait_tile_loads<0>();  // requests past the end of the streams
   // the last unit's share of O and of the row sums
   unit_pv(va[1], p3, o[1], ones, ls[1]);
@@ -731,10 +805,10 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
 }
 
 // The classical recurrence (running maximum, rescale on every block), one block pair at a time
-// with synchronous tile loads: the path of items with padded keys inside a block and the
+// the path of attention dropout, of items whose every block has padded keys inside and the
 // fallback for items whose row sums left the safe range of the reference-free path.  Leaves m_ref (exponent
 // units), this lane's share of the row sums and O~.  Any load still in flight lands first.
-template <bool kX>
+template <int kMode>
 __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
                                           const bf16x8 (&qb)[2][4], const FwdParams& p, const Item& item,
                                           f32x16 (&o)[2][2], float (&l_run)[2], float (&m_ref)[2]) {
@@ -749,7 +823,7 @@ __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffse
   // attention dropout (all items of a call with dropout come here): the keys of this lane's two
   // rows of the keep mask
   uint32_t drop_rk[2] = {0u, 0u};
-  if (kX && p.drop.thr) {
+  if (kMode == kOptions && p.drop.thr) {
     const uint32_t row0 = static_cast<uint32_t>(item.bh) * static_cast<uint32_t>(p.n) + item.j * kBlk + (lane_id() & 31);
 #pragma unroll
     for (int q = 0; q < 2; ++q) drop_rk[q] = drop_row_key(p.drop, row0 + q * 32);
@@ -813,7 +887,7 @@ __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffse
             const float p0 = fast_exp2(s[t][r] - m_use), p1 = fast_exp2(s[t][r + 1] - m_use);
             bf16x2 pk = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
             l_run[q] += p0 + p1;  // (the row sums are those of the undropped probabilities)
-            if (kX && p.drop.thr) {
+            if (kMode == kOptions && p.drop.thr) {
               // registers r, r + 1 are keys 2m, 2m + 1: one word of the mask
               const uint32_t key = static_cast<uint32_t>(kblock * kBlk + t * 32 + acc_row(r, cx.hf));
               const uint32_t wd = drop_word(drop_rk[q], key >> 1);
@@ -941,9 +1015,9 @@ __device__ __forceinline__ const void* kernel_kernargs() {
 }
 
 // One non-global item by the classical recurrence, from its first load to its last store: the path
-// of items with padded keys inside a block or without any key block, and of items whose row sums
+// of items without any key block or with padded keys inside every block, of items whose row sums
 // left the safe range of the pipelined path, and of every item under attention dropout.
-template <bool kX>
+template <int kMode>
 __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
   const WaveCtx w(p.c);
   Sched sc(p);
@@ -951,7 +1025,7 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
   const StraightOffsets so(w.lane);
   const TransposedOffsets to(w.lane);
   Item it;
-  make_item<kX>(p, w, sc, t, it);
+  make_item<kMode>(p, w, sc, t, it, 0);
   wait_tile_loads<0>();
   bf16x8 qb[2][4];
   f32x16 o[2][2];
@@ -962,14 +1036,14 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
     so.read(w.lds_v, qb);
     wait_lds_reads();
     }
-  slow_item<kX>(w.cx, so, to, qb, p, it, o, l_run, m_ref);
+  slow_item<kMode>(w.cx, so, to, qb, p, it, o, l_run, m_ref);
 #pragma unroll
   for (int q = 0; q < 2; ++q) l_tot[q] = half_sum(l_run[q]);
   if (it.nchunks == 1) {
     float inv[2], lse[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      inv[q] = l_tot[q] > 0.f ? (kX ? p.drop.rs : 1.f) / l_tot[q] : 0.f;  // (rs: 1, or the dropout scale)
+      inv[q] = l_tot[q] > 0.f ? (kMode == kOptions ? p.drop.rs : 1.f) / l_tot[q] : 0.f;  // (rs: 1, or the dropout scale)
       lse[q] = l_tot[q] > 0.f ? (m_ref[q] + fast_log2(l_tot[q])) * kLn2 : neg_inf();
     }
     store_rows_bf16(p, w, it, o, inv, lse);
@@ -982,10 +1056,10 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
 // function: its registers are not that loop's problem.  One call for the whole list: a call saves
 // and restores the callee-saved registers in scratch memory, about 50 KB per wave, which per item
 // was most of the time of launches in which many items come here.
-template <bool kX>
+template <int kMode>
 __device__ __attribute__((noinline)) void redo_items(const void* kernargs, int redo, int n_redo) {
   const FwdParams p = params_from(kernargs);
-  for (int u = 0; u < n_redo; ++u) item_by_recurrence<kX>(p, __builtin_amdgcn_readlane(redo, u));
+  for (int u = 0; u < n_redo; ++u) item_by_recurrence<kMode>(p, __builtin_amdgcn_readlane(redo, u));
 }
 
 // One global query block by a whole workgroup: 16 key blocks per wave, the four waves' (m, l, O~)
@@ -993,7 +1067,7 @@ __device__ __attribute__((noinline)) void redo_items(const void* kernargs, int r
 // real call would start by saving a hundred callee-saved vector registers to scratch memory
 // (11 MB of HBM writes per launch at the BERT-base size, measured) for a caller that has nothing
 // in them.
-template <bool kX>
+template <int kMode>
 __device__ __forceinline__ void global_row_workgroup(const FwdParams& p) {
   const WaveCtx w(p.c);
   const Sched sc(p);
@@ -1004,7 +1078,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p) {
   const long long rt0 = __builtin_amdgcn_s_memrealtime();
 #endif
   Item cur;
-  make_item<kX>(p, w, sc, 0, cur);
+  make_item<kMode>(p, w, sc, 0, cur, 0);
   bf16x8 qb[2][4], ka[2][4];
   f32x16 o[2][2];
   float m_ref[2] = {0.f, 0.f};  // reference exponents (base-2 units); halves agree
@@ -1014,14 +1088,14 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p) {
   if (cur.cnt > 0) {
     fresh_start(p, w, so, cur, qb);
     float l_run[2] = {0.f, 0.f};
-    bool bad = cur.any_partial;  // per-key masking is only in the slow path
-    if (!cur.any_partial) {
-      fast_item(w.cx, so, to, qb, ka, p, cur, nullptr, true, o, l_tot);
+    bool bad = cur.per_item;
+    if (!bad) {
+      fast_item<kMode>(w.cx, so, to, qb, ka, p, cur, nullptr, true, key_bits_all[w.wv][0][0], o, l_tot);
 #pragma unroll
       for (int q = 0; q < 2; ++q) bad |= !(l_tot[q] >= kSumLo && l_tot[q] <= kSumHi);
     }
     if (__any(bad)) {
-      slow_item<kX>(w.cx, so, to, qb, p, cur, o, l_run, m_ref);
+      slow_item<kMode>(w.cx, so, to, qb, p, cur, o, l_run, m_ref);
 #pragma unroll
       for (int q = 0; q < 2; ++q) l_tot[q] = half_sum(l_run[q]);
     }
@@ -1084,7 +1158,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p) {
   }
   const size_t row = row_blk + q;
   if (cur.nchunks == 1) {
-    const float inv = L > 0.f ? (kX ? p.drop.rs : 1.f) / L : 0.f;  // (rs: 1, or the dropout scale)
+    const float inv = L > 0.f ? (kMode == kOptions ? p.drop.rs : 1.f) / L : 0.f;  // (rs: 1, or the dropout scale)
     if (part == 0) p.LSE[row] = L > 0.f ? (M + fast_log2(L)) * kLn2 : neg_inf();
     bf16x8 v0, v1;
 #pragma unroll
@@ -1119,7 +1193,7 @@ __global__ void zero_counters_kernel(int* counters) {
   if (threadIdx.x < kXcd) counters[threadIdx.x * kCounterStride] = 0;
 }
 
-template <bool kX>
+template <int kMode>
 __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void fwd_kernel_bf16(FwdParams p) {
   Sched sc(p);
@@ -1127,10 +1201,10 @@ void fwd_kernel_bf16(FwdParams p) {
   // the launch) instead of taking every wave_stride-th one: with a padding mask items differ in
   // length and some are not computed at all.  The waves of a global-row workgroup then join in
   // when their row is done.
-  const bool dyn = kX && p.dyn != 0;
+  const bool dyn = kMode == kOptions && p.dyn != 0;
   const bool was_global = sc.global_wg;
   if (sc.global_wg) {
-    if ((sc.wg / p.geo.g_wgs) * kXcd + sc.xcd < static_cast<unsigned>(p.BH)) global_row_workgroup<kX>(p);
+    if ((sc.wg / p.geo.g_wgs) * kXcd + sc.xcd < static_cast<unsigned>(p.BH)) global_row_workgroup<kMode>(p);
     if (!dyn) return;
     __syncthreads();  // the merge has read the other waves' LDS regions; from here on each wave's is its own
     sc.global_wg = false;
@@ -1155,11 +1229,11 @@ void fwd_kernel_bf16(FwdParams p) {
     // (a counter that has run far past the end must not wrap the sum)
     return c < n_items_die ? wave_stride + c : n_items_die;
   };
-  if (kX && p.drop.thr != 0) {
+  if (kMode == kOptions && p.drop.thr != 0) {
     // attention dropout: every item takes the per-item path, so there is no stream to run and no
     // list to keep -- wave w does the die's items w, w + wave_stride, ... one after the other
     for (int t = static_cast<int>(sc.wg - sc.n_gpart) * kFwdWaves + w.wv; t < n_items_die; t += wave_stride)
-      item_by_recurrence<kX>(p, __builtin_amdgcn_readfirstlane(t));
+      item_by_recurrence<kMode>(p, __builtin_amdgcn_readfirstlane(t));
     return;
   }
   int t_first = static_cast<int>(sc.wg - sc.n_gpart) * kFwdWaves + w.wv;  // first item of this wave
@@ -1186,7 +1260,7 @@ void fwd_kernel_bf16(FwdParams p) {
 #define BB_STAMP(i)
 #endif
   // ---- persistent wave: the die's non-global items t_item, t_item + wave_stride, ...
-  // Items that cannot take the pipelined path (padded keys inside a block, no key block at all,
+  // Items that cannot take the pipelined path (no key block at all, padded keys inside every block,
   // or -- found out afterwards -- row sums outside the safe range) are put on a list and done
   // by the classical recurrence when the stream has ended; the host sizes the grid so that a
   // wave has at most 64 items (a lane of `redo` each).
@@ -1197,15 +1271,15 @@ void fwd_kernel_bf16(FwdParams p) {
     n_redo = __builtin_amdgcn_readfirstlane(n_redo + 1);
   };
   // the next item at or after t that takes the pipelined path (others go to the list)
-  auto next_fast = [&](int t, Item& it) {
+  auto next_fast = [&](int t, Item& it, int bits_slot) {
     int found = -1;
     while (t < n_items_die) {
-      make_item<kX>(p, w, sc, t, it);
-      if (it.cnt > 0 && !it.any_partial) {
+      make_item<kMode>(p, w, sc, t, it, bits_slot);
+      if (it.cnt > 0 && !it.per_item) {
         found = t;
         break;
       }
-      if (kX && it.skipped && it.nchunks == 1) {  // nothing to compute: its rows are written here
+      if (kMode == kOptions && it.skipped && it.nchunks == 1) {  // nothing to compute: its rows are written here
         store_zero_rows_bf16(p, it);
       } else {
         push_redo(t);
@@ -1230,11 +1304,11 @@ void fwd_kernel_bf16(FwdParams p) {
   {
     int lo_, len_;
     bool rg_;
-    item_coords<kX>(p, w, sc, t_item, cur, lo_, len_, rg_);
+    item_coords<kMode>(p, w, sc, t_item, cur, lo_, len_, rg_);
     tile_load_async_wave(query_tile(p, __builtin_amdgcn_readfirstlane(cur.bh), __builtin_amdgcn_readfirstlane(cur.j)),
                          cx.lds_k_a, cx.voff);
   }
-  int t_cur = next_fast(t_item, cur);
+  int t_cur = next_fast(t_item, cur, 0);
   int t_nxt = -1;
 #ifdef BB_STAMPS
   st_t[0] = __builtin_readcyclecounter() - tprev;
@@ -1284,7 +1358,7 @@ void fwd_kernel_bf16(FwdParams p) {
 #ifdef BB_STAMPS
     st_t[2] = __builtin_readcyclecounter() - tprev;
 #endif
-    t_nxt = next_fast(successor(t_cur), nxt);  // (scalar loads only, unless there is a padding mask)
+    t_nxt = next_fast(successor(t_cur), nxt, 1);  // (scalar loads only, unless there is a padding mask)
     TileStreams ts(p, cur, t_nxt >= 0 ? &nxt : nullptr, lane_again(lane));
     int cnt = __builtin_amdgcn_readfirstlane(cur.cnt);  // pairs of the item in work
       reset_item_state();
@@ -1301,9 +1375,11 @@ void fwd_kernel_bf16(FwdParams p) {
     unit_scores(ka[0], qb[0], sA);
     BB_STAMP(0);
 
+    int bits_cur = 0;  // where cur's validity bits are (nxt's: the next of the three places, cyclically)
     for (int i = 0;;) {
       if ((rem_pairs & 3) == 3 || i == 0) set_issue_priority(rem_pairs);
-      pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
+      pair_step<kMode>(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2),
+                       (cur.partial >> i) & 1 ? key_bits_all[w.wv][bits_cur][i] : nullptr);
       rem_pairs = __builtin_amdgcn_readfirstlane(rem_pairs - 1);
       i = __builtin_amdgcn_readfirstlane(i + 1);
       if (__builtin_expect(i < cnt, 1)) continue;  // (the register allocator should favour the pairs)
@@ -1329,7 +1405,7 @@ void fwd_kernel_bf16(FwdParams p) {
       int t_nn = -1;
       BB_STAMP(2);
       if (t_nxt >= 0) {
-        t_nn = next_fast(successor(t_nxt), nn);
+        t_nn = next_fast(successor(t_nxt), nn, bits_cur == 0 ? 2 : bits_cur - 1);
         BB_STAMP(3);
         // The next item's query tile is in the K buffer, its first K tile in the V buffer (the
         // second half may still be landing).  Both go to registers, its first V tile is requested,
@@ -1362,7 +1438,8 @@ void fwd_kernel_bf16(FwdParams p) {
       if (t_nxt < 0) break;
 
       // ---- the next item's stream starts (its K(0) fragments are in registers, V(0) is in flight)
-          cur = nxt;
+      cur = nxt;
+      bits_cur = __builtin_amdgcn_readfirstlane(bits_cur == 2 ? 0 : bits_cur + 1);
       t_cur = t_nxt;
       nxt = nn;
       t_nxt = t_nn;
@@ -1392,7 +1469,7 @@ void fwd_kernel_bf16(FwdParams p) {
 #endif
 
   // ---- the listed items, by the classical recurrence
-  if (n_redo > 0) redo_items<kX>(kernel_kernargs(), redo, n_redo);
+  if (n_redo > 0) redo_items<kMode>(kernel_kernargs(), redo, n_redo);
 }
 
 int launch_fwd_bf16_main(const FwdParams& p, hipStream_t stream) {
@@ -1403,9 +1480,11 @@ int launch_fwd_bf16_main(const FwdParams& p, hipStream_t stream) {
     if (hipGetLastError() != hipSuccess) return BB_ERR_LAUNCH;
   }
   if (p.drop.thr != 0 || p.skip_q || p.dyn)
-    hipLaunchKernelGGL(fwd_kernel_bf16<true>, dim3(grid), dim3(kFwdThreads), 0, stream, p);
+    hipLaunchKernelGGL(fwd_kernel_bf16<kOptions>, dim3(grid), dim3(kFwdThreads), 0, stream, p);
+  else if (p.kmask)
+    hipLaunchKernelGGL(fwd_kernel_bf16<kMasked>, dim3(grid), dim3(kFwdThreads), 0, stream, p);
   else
-    hipLaunchKernelGGL(fwd_kernel_bf16<false>, dim3(grid), dim3(kFwdThreads), 0, stream, p);
+    hipLaunchKernelGGL(fwd_kernel_bf16<kPlain>, dim3(grid), dim3(kFwdThreads), 0, stream, p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     fprintf(stderr, "bigbird: launch of fwd_kernel_bf16 failed: %s\n", hipGetErrorString(e));

@@ -182,6 +182,22 @@ __device__ __forceinline__ void block_mask_flags(const uint8_t* kmask, int bi, i
   any_padded = zero_byte != 0;
 }
 
+// The same 64 bytes as bits (bit t of bits[0] / bits[1]: key t / 32 + t of the block is valid).
+__device__ __forceinline__ void block_key_bits(const uint8_t* kmask, int bi, int n, int k, uint32_t (&bits)[2]) {
+  const u32x4* p = reinterpret_cast<const u32x4*>(kmask + static_cast<size_t>(bi) * n + k * kBlk);
+  bits[0] = bits[1] = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const u32x4 v = p[i];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t set = ((((v[e] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v[e]) >> 7) & 0x01010101u;  // byte != 0
+      // bits 0, 8, 16, 24 -> bits 24 .. 27 (no two products meet)
+      bits[i >> 1] |= ((set * 0x01020408u) >> 24 & 15u) << ((i & 1) * 16 + e * 4);
+    }
+  }
+}
+
 // Key blocks attended by query block j of head h (App. D items 1-3 as a set
 // union, minus blocks without a valid key), slice `chunk` (see WorkItem) of the
 // ascending-by-candidate list: entries [lo, lo+len).  Every lane of the calling wave takes

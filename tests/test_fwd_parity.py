@@ -147,6 +147,36 @@ def test_key_padding_unaligned_and_empty_rows(dtype):
     assert (to_host(O)[2] == 0).all() and np.isneginf(to_host(LSE)[2]).all()
 
 
+@pytest.mark.parametrize("tail", [1, 2, 31, 32, 33, 63])
+@pytest.mark.parametrize("mode,g,r", [(bb.BB_GLOBAL_FIRST_LAST, 2, 3), (bb.BB_GLOBAL_LEADING, 3, 0)])
+def test_blocks_with_padded_keys_inside(tail, mode, g, r):
+    """bf16: validity ends `tail` keys into a block, at the edges of the 32-key units; a hole of every
+    residue; a whole sequence of `tail` keys (rows with no full block); mask bytes of any non-zero value;
+    K rows of padded keys hold NaN.  (Same tolerance as everywhere: the keys left out change nothing else.)"""
+    torch = torch_mod()
+    B, H, n, w = 3, 2, 1024, 3
+    t = inp.make_tensors(B, H, n, 64, 40 + tail, "bf16")
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 6, mode)
+    km = np.full((B, n), 0x80, dtype=np.uint8)
+    km[0, 640 + tail:] = 0
+    km[1, 128:128 + tail] = 0
+    km[1, 300:300 + 2 * tail] = 0
+    km[2, tail:] = 0
+    Oref, Lref = oracle.attn_fwd(t["Q"], t["K"], t["V"], ridx, 64, g, w, 0.125, key_mask=(km != 0).astype(np.uint8),
+                                 global_mode=mode)
+    Q, K, V = device_qkv(t, "bf16")
+    kmd = torch.from_numpy(km).to("cuda:0")
+    K.masked_fill_((kmd == 0)[:, None, :, None], float("nan"))
+    O, LSE = bb.bigbird_attn_fwd(Q, K, V, torch.from_numpy(ridx).to("cuda:0"), g=g, w=w, scale=0.125,
+                                 key_padding_mask=kmd, global_mode=mode)
+    Oh, Lh = to_host(O), to_host(LSE)
+    fin = np.isfinite(Lref)
+    assert (np.isneginf(Lh) == ~fin).all()
+    err_o, err_l = np.abs(Oh - Oref).max(), np.abs(Lh[fin] - Lref[fin]).max()
+    print(f"tail {tail} mode {mode}: max|dO|={err_o:.3e} max|dLSE|={err_l:.3e}")
+    assert err_o <= TOL["bf16"] and err_l <= TOL["bf16"]
+
+
 def test_zero_queries_closed_form_and_pattern_readback():
     """Q = 0 => O_i = mean of V over N(i), LSE_i = ln|N(i)|; V one-hot per key block spells out
     the neighbour set the kernel used, which must be the table's."""
