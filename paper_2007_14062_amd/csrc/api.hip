@@ -3,6 +3,7 @@
 #include "bwd_kernels.h"
 #include "fwd_kernels.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <mutex>
@@ -36,8 +37,12 @@ int check_attn_shape(int B, int H, int n, int d, int b, int g, int w, int r, int
 WorkspaceLayout make_layout(int B, int H, int n, int b, int g, int w, int r, int need_bwd) {
   WorkspaceLayout L;
   const int BH = B * H, nb = n / b;
-  const bb::RowSplit s = bb::make_row_split(BH, nb, g, w, r);
-  const size_t slots = static_cast<size_t>(BH) * s.slots_per_bh;
+  // (the same buffer serves both storage types: the larger need counts)
+  const int fine = bb::fine_slice_f32(BH, nb, g, w, r);
+  const int fwd_fine = nb > bb::kChunkGlobal ? fine : 0;
+  size_t slots = static_cast<size_t>(BH) * bb::make_row_split(BH, nb, g, w, r).slots_per_bh;
+  if (fwd_fine)
+    slots = std::max(slots, static_cast<size_t>(BH) * bb::make_row_split(BH, nb, g, w, r, fwd_fine).slots_per_bh);
   size_t off = 0;
   L.part_o = off;
   off += round_up(slots * bb::kBlk * bb::kDim * sizeof(float));
@@ -52,8 +57,9 @@ WorkspaceLayout make_layout(int B, int H, int n, int b, int g, int w, int r, int
   L.total = off;
   if (need_bwd) {
     const size_t rows = static_cast<size_t>(BH) * n;
-    const int cq = (nb + bb::kChunk - 1) / bb::kChunk;
-    const size_t kv_slots = cq > 1 ? static_cast<size_t>(BH) * g * cq : 0;
+    if (fine) slots = std::max(slots, static_cast<size_t>(BH) * bb::make_row_split(BH, nb, g, w, r, fine).slots_per_bh);
+    size_t kv_slots = static_cast<size_t>(BH) * bb::make_key_split(nb, g, w, r).slots_per_bh;
+    if (fine) kv_slots = std::max(kv_slots, static_cast<size_t>(BH) * bb::make_key_split(nb, g, w, r, fine).slots_per_bh);
     size_t o2 = 0;
     L.dvec = o2;
     o2 += round_up(rows * sizeof(float));
@@ -140,7 +146,9 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
   // slow path.)
   p.counters = L.has_counters ? reinterpret_cast<int*>(ws + L.counters) : nullptr;
   p.dyn = (dtype == BB_BF16 && p.skip_q && drop.thr == 0 && p.counters) ? 1 : 0;
-  p.split = bb::make_row_split(p.BH, p.nb, g, w, r);
+  // (at up to 8 blocks no row is split and the forward needs no workspace: that stays so)
+  const bool fine = dtype == BB_F32 && p.nb > bb::kChunkGlobal;
+  p.split = bb::make_row_split(p.BH, p.nb, g, w, r, fine ? bb::fine_slice_f32(p.BH, p.nb, g, w, r) : 0);
   if (dtype == BB_BF16) {
     bb::Bf16Geom& q = p.geo;
     {
@@ -339,9 +347,9 @@ int attn_bwd_impl(const void* Q, const void* K, const void* V, const void* O,
   p.scale = scale;
   p.drop = drop;
   p.skip_q = (skip_q && key_padding_mask) ? 1 : 0;
-  p.split = bb::make_row_split(p.BH, p.nb, g, w, r);
-  p.cq = (p.nb + bb::kChunk - 1) / bb::kChunk;
-  p.kv_items_per_bh = g * p.cq + (p.nb - g);
+  const int fine = dtype == BB_F32 ? bb::fine_slice_f32(p.BH, p.nb, g, w, r) : 0;
+  p.split = bb::make_row_split(p.BH, p.nb, g, w, r, fine);
+  p.kv = bb::make_key_split(p.nb, g, w, r, fine);
   if (dtype == BB_F32) return bb::launch_bwd_f32(p, static_cast<hipStream_t>(hip_stream));
   return bb::launch_bwd_bf16(p, static_cast<hipStream_t>(hip_stream));
 }

@@ -1,12 +1,19 @@
-// Backward kernels, fp32 end to end: the correctness configuration of the backward pass
-// (plain vector arithmetic, no matrix instructions, not tuned).  Same calculus as the
-// bf16 kernels (eq. (AT) of Sec. 2 differentiated on the blocked pattern of App. D):
+// Backward kernels, fp32 end to end.  Same calculus as the bf16 kernels (eq. (AT) of Sec. 2
+// differentiated on the blocked pattern of App. D):
 //   dV = P^T dO;  dP = dO V^T;  D_i = sum_c dO_ic O_ic;  dS = P o (dP - D);
 //   dQ = scale dS K;  dK = scale dS^T Q,
-// with P recomputed from Q, K and the forward's LSE.  No atomics and no partial results:
-// one workgroup owns one query block (dQ) or one key block (dK, dV) and walks its whole
-// list, so the summation order is fixed.
+// with P recomputed from Q, K and the forward's LSE.  No atomics: a work item is a slice of a query
+// block's key-block list (dQ) or of a key block's query-block list (dK, dV); where a list has several
+// slices, bwd_reduce_kernel adds their partial sums in slice order.
+//
+// fp32 MFMA 32x32x2 throughout, four waves per item, a wave per 32x32 quarter of every block pair
+// (f32_ops.h).  What bounds them is the fp32 matrix rate (a block pair is 96 / 128 MFMAs of 64 cycles per
+// wave) and, at small sizes, the longest slice: hence slices down to a single pair (fine_slice_f32).
+// n = 1024, 2 heads: dQ 18 us, dK/dV 27 us, reduction 4 us, where one workgroup per block with vector
+// arithmetic took 313 and 358; n = 4096, 24 slices, forward and backward: 0.73 ms against 10.7.
+// (dK/dV is held to two waves per SIMD: 29 registers spilled, but 0.73 against 0.78 ms.)
 #include "bwd_kernels.h"
+#include "f32_ops.h"
 
 #include <cstdio>
 
@@ -14,280 +21,266 @@ namespace bb {
 
 namespace {
 
-constexpr int kF32Threads = 256;
-constexpr int kTileStride = kDim + 4;  // floats per LDS row of a [64][64] tile: 16-byte rows, shifted banks
-constexpr int kListChunk = 64;         // list entries built at a time
-
-// [64][64] fp32 rows from global memory into an LDS tile, by the whole workgroup.
-__device__ __forceinline__ void load_tile_f32(const float* src, float* dst) {
-  for (int e = threadIdx.x; e < kBlk * kDim / 4; e += kF32Threads) {
-    const int row = e >> 4, c4 = e & 15;
-    *reinterpret_cast<f32x4*>(dst + row * kTileStride + c4 * 4) =
-        *reinterpret_cast<const f32x4*>(src + row * kDim + c4 * 4);
-  }
+// [64 x 32] accumulator pair (rows d, column = this lane's sequence position) -> dst_row[d].
+__device__ __forceinline__ void store_rows_f32(float* dst_row, const f32x16 (&a)[2], int hf) {
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      f32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = a[dt][r4 * 4 + e];
+      *reinterpret_cast<f32x4*>(dst_row + dt * 32 + acc_row(r4 * 4, hf)) = v;
+    }
 }
 
-__device__ __forceinline__ float dot_row(const float (&a)[kDim], const float* row) {
-  float s = 0.f;
+// Accumulators of one wave to another through LDS, register by register (2048 floats).
+__device__ __forceinline__ void hand_over(float* slot, int lane, const f32x16 (&a)[2]) {
 #pragma unroll
-  for (int c4 = 0; c4 < kDim / 4; ++c4) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(row + c4 * 4);
+  for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s = __builtin_fmaf(a[c4 * 4 + e], v[e], s);
-  }
-  return s;
+    for (int r = 0; r < 16; ++r) slot[(dt * 16 + r) * 64 + lane] = a[dt][r];
+}
+__device__ __forceinline__ void take_over(const float* slot, int lane, f32x16 (&a)[2]) {
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a[dt][r] += slot[(dt * 16 + r) * 64 + lane];
+}
+
+__device__ __forceinline__ void clear(f32x16 (&a)[2]) {
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a[dt][r] = 0.f;
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------------------------------
-// dQ (and the row sums D): one workgroup per (batch*head, query block).  Thread t: query
-// t % 64 of the block, keys 16 (t / 64) .. + 15 of every key block of the row's list.
+// dQ (and the row sums D): one work item = (batch*head, query block, slice of its key-block list).
+// Wave (qh, kh): 32 queries against 32 keys of every block; S^T, dP^T, dS^T are [keys x queries],
+// dQ^T += K^T dS^T; the two key halves' shares are added in LDS.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kF32Threads) void bwd_f32_dq_kernel(BwdParams p) {
-  __shared__ __attribute__((aligned(16))) float lds_k[kBlk * kTileStride];
-  __shared__ __attribute__((aligned(16))) float lds_v[kBlk * kTileStride];
-  __shared__ __attribute__((aligned(16))) float lds_red[kBlk * (kDim + 1)];
-  __shared__ int klist[kListChunk];
-  __shared__ int kcount;
+__global__ __launch_bounds__(kThreadsF32) void bwd_f32_dq_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(16))) float lds_k[kBlk * kF32Stride];
+  __shared__ __attribute__((aligned(16))) float lds_v[kBlk * kF32Stride];
+  __shared__ int klist[kChunkMax];
 
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
-  const int bh = blockIdx.x / p.nb, j = blockIdx.x % p.nb;
-  const int bi = bh / p.H, h = bh % p.H;
-  const int i = threadIdx.x & 63, kg = threadIdx.x >> 6;
-  const size_t bh_row0 = static_cast<size_t>(bh) * p.n;
-  const size_t qrow = bh_row0 + static_cast<size_t>(j) * kBlk + i;
-  const float* Q = static_cast<const float*>(p.Q);
-  const float* K = static_cast<const float*>(p.K);
-  const float* V = static_cast<const float*>(p.V);
-  const float* O = static_cast<const float*>(p.O);
-  const float* dO = static_cast<const float*>(p.dO);
+  WorkItem it;
+  if (!decode_item(p.split, pat, p.BH, blockIdx.x, &it)) return;
+  const int bi = it.bh / p.H, h = it.bh % p.H;
+  const int lane = lane_id(), wv = threadIdx.x >> 6;
+  const int hf = lane >> 5, col = lane & 31;
+  const int qh = wv & 1, kh = wv >> 1;
+  const size_t bh_row0 = static_cast<size_t>(it.bh) * p.n;
+  const size_t qrow = bh_row0 + static_cast<size_t>(it.j) * kBlk + qh * 32 + col;
+  const float* Kp = static_cast<const float*>(p.K);
+  const float* Vp = static_cast<const float*>(p.V);
 
-  float q[kDim], go[kDim], dq[kDim];
-  float dsum = 0.f;
+  f32x4 qf[8], gf[8];  // Q and dO rows of this lane's query, half of d each
+  row_fragments_f32(static_cast<const float*>(p.Q) + qrow * kDim, hf, qf);
+  row_fragments_f32(static_cast<const float*>(p.dO) + qrow * kDim, hf, gf);
+  // a query block that was skipped (no valid position) behaves like rows without a valid key
+  const bool skip = p.skip_q && key_valid_bits(p.kmask, bi, p.n, it.j) == 0;
+  float dsum, lse2;
+  {
+    f32x4 of[8];
+    row_fragments_f32(static_cast<const float*>(p.O) + qrow * kDim, hf, of);
+    float part = 0.f;
 #pragma unroll
-  for (int c4 = 0; c4 < kDim / 4; ++c4) {
-    const f32x4 qv = *reinterpret_cast<const f32x4*>(Q + qrow * kDim + c4 * 4);
-    const f32x4 gv = *reinterpret_cast<const f32x4*>(dO + qrow * kDim + c4 * 4);
-    const f32x4 ov = *reinterpret_cast<const f32x4*>(O + qrow * kDim + c4 * 4);
+    for (int u = 0; u < 8; ++u)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      q[c4 * 4 + e] = qv[e];
-      go[c4 * 4 + e] = gv[e];
-      dq[c4 * 4 + e] = 0.f;
-      dsum = __builtin_fmaf(gv[e], ov[e], dsum);
+      for (int e = 0; e < 4; ++e) part = __builtin_fmaf(gf[u][e], of[u][e], part);
+    dsum = half_sum(part);
+    if (skip) dsum = 0.f;
+    const float lse = p.LSE[qrow];
+    lse2 = (skip || lse == neg_inf()) ? __builtin_inff() : lse * kLog2e;  // no valid key: every P is 0
+    if (it.chunk == 0 && kh == 0 && hf == 0) {
+      p.Dvec[qrow] = dsum;
+      p.Lvec[qrow] = lse2;
     }
   }
-  // a query block that was skipped (no valid position) behaves like rows without a valid key
-  const bool skip = p.skip_q && !block_has_valid_key(p.kmask, bi, p.n, j);
-  if (skip) dsum = 0.f;
-  const float lse = p.LSE[qrow];
-  const float lse2 = (skip || lse == neg_inf()) ? __builtin_inff() : lse * kLog2e;  // no valid key: every P is 0
-  if (kg == 0) {
-    p.Dvec[qrow] = dsum;
-    p.Lvec[qrow] = lse2;
-  }
+  const int cnt = skip ? 0 : build_key_list(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it, klist);
+  __syncthreads();
+
   const float c = p.c;
-  const bool row_global = pat.is_global(j);
   // attention dropout: dP = M / (1 - p) o (dO V^T), M this row of the keep mask
   const uint32_t drop_rk = p.drop.thr ? drop_row_key(p.drop, static_cast<uint32_t>(qrow)) : 0u;
-
-  for (int lo = 0;; lo += kListChunk) {
-    __syncthreads();  // the previous chunk's list and tiles are no longer read
-    if (threadIdx.x < 64) {
-      const int cnt = build_key_list_range(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, j, row_global, lo,
-                                           kListChunk, klist);
-      if (threadIdx.x == 0) kcount = cnt;
-    }
+  f32x16 dq[2];
+  clear(dq);
+  f32x4 kreg[kVecPerThreadF32], vreg[kVecPerThreadF32];
+  if (cnt > 0) {
+    const size_t row0 = bh_row0 + static_cast<size_t>(klist[0]) * kBlk;
+    tile_fetch_f32(Kp + row0 * kDim, kreg);
+    tile_fetch_f32(Vp + row0 * kDim, vreg);
+  }
+  for (int i = 0; i < cnt; ++i) {
+    const int kb = klist[i];
+    __syncthreads();  // everyone is done reading the previous tiles
+    tile_store_f32(lds_k, kreg);
+    tile_store_f32(lds_v, vreg);
     __syncthreads();
-    const int cnt = kcount;
-    for (int u = 0; u < cnt; ++u) {
-      const int kb = klist[u];
-      __syncthreads();  // tiles of the previous key block are no longer read
-      load_tile_f32(K + (bh_row0 + static_cast<size_t>(kb) * kBlk) * kDim, lds_k);
-      load_tile_f32(V + (bh_row0 + static_cast<size_t>(kb) * kBlk) * kDim, lds_v);
-      __syncthreads();
-      for (int t = 0; t < 16; ++t) {
-        const int kk = kg * 16 + t;
-        const bool valid = !p.kmask || p.kmask[static_cast<size_t>(bi) * p.n + kb * kBlk + kk] != 0;
-        const float* krow = lds_k + kk * kTileStride;
-        const float s = dot_row(q, krow);
-        float dp = dot_row(go, lds_v + kk * kTileStride);
-        if (p.drop.thr) {
-          const uint32_t key = static_cast<uint32_t>(kb * kBlk + kk);
-          const uint32_t wd = drop_word(drop_rk, key >> 1);
-          const bool keep = (key & 1u) ? drop_keep_odd(wd, p.drop.thr) : drop_keep_even(wd, p.drop.thr);
-          dp = keep ? dp * p.drop.rs : 0.f;
-        }
-        const float pr = valid ? fast_exp2(__builtin_fmaf(s, c, -lse2)) : 0.f;
-        const float ds = pr * (dp - dsum);
+    if (i + 1 < cnt) {
+      const size_t row0 = bh_row0 + static_cast<size_t>(klist[i + 1]) * kBlk;
+      tile_fetch_f32(Kp + row0 * kDim, kreg);
+      tile_fetch_f32(Vp + row0 * kDim, vreg);
+    }
+    uint32_t valid = ~0u;  // bit acc_row(r, 0): this lane's r-th key
+    if (p.kmask) valid = static_cast<uint32_t>(key_valid_bits(p.kmask, bi, p.n, kb) >> (kh * 32)) >> (hf * 4);
+
+    f32x16 s, dp;
+    mfma_rows_f32(lds_k + (kh * 32 + col) * kF32Stride, hf, qf, s);
+    mfma_rows_f32(lds_v + (kh * 32 + col) * kF32Stride, hf, gf, dp);
+    if (p.drop.thr) {
 #pragma unroll
-        for (int c4 = 0; c4 < kDim / 4; ++c4) {
-          const f32x4 kv = *reinterpret_cast<const f32x4*>(krow + c4 * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dq[c4 * 4 + e] = __builtin_fmaf(ds, kv[e], dq[c4 * 4 + e]);
-        }
+      for (int r = 0; r < 16; r += 2) {
+        const uint32_t key = static_cast<uint32_t>(kb * kBlk + kh * 32 + acc_row(r, hf));
+        const uint32_t wd = drop_word(drop_rk, key >> 1);
+        dp[r] = drop_keep_even(wd, p.drop.thr) ? dp[r] * p.drop.rs : 0.f;
+        dp[r + 1] = drop_keep_odd(wd, p.drop.thr) ? dp[r + 1] * p.drop.rs : 0.f;
       }
     }
-    if (cnt < kListChunk) break;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float ds = fast_exp2(__builtin_fmaf(s[r], c, -lse2)) * (dp[r] - dsum);
+      s[r] = (valid >> acc_row(r, 0)) & 1 ? ds : 0.f;
+    }
+    mfma_columns_f32(lds_k + kh * 32 * kF32Stride, hf, col, s, dq);
   }
 
-  // the four key groups' shares of dQ, added in group order
-  for (int gsrc = 1; gsrc < 4; ++gsrc) {
-    __syncthreads();
-    if (kg == gsrc)
+  __syncthreads();  // the tiles are no longer read
+  float* const slot = lds_k + qh * (32 * 64);
+  if (kh == 1) hand_over(slot, lane, dq);
+  __syncthreads();
+  if (kh == 1) return;
+  take_over(slot, lane, dq);
 #pragma unroll
-      for (int d = 0; d < kDim; ++d) lds_red[i * (kDim + 1) + d] = dq[d];
-    __syncthreads();
-    if (kg == 0)
+  for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-      for (int d = 0; d < kDim; ++d) dq[d] += lds_red[i * (kDim + 1) + d];
-  }
-  if (kg == 0) {
-#pragma unroll
-    for (int c4 = 0; c4 < kDim / 4; ++c4) {
-      f32x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = dq[c4 * 4 + e] * p.scale;
-      *reinterpret_cast<f32x4*>(p.dQ + qrow * kDim + c4 * 4) = v;
-    }
-  }
+    for (int r = 0; r < 16; ++r) dq[dt][r] *= p.scale;
+  if (it.nchunks == 1)
+    store_rows_f32(p.dQ + qrow * kDim, dq, hf);
+  else
+    store_rows_f32(p.part_dq + static_cast<size_t>(it.slot) * (kBlk * kDim) + (qh * 32 + col) * kDim, dq, hf);
 }
 
 // ---------------------------------------------------------------------------------------
-// dK, dV: one workgroup per (batch*head, key block k), over every query block that attends k
-// (the inverse of the pattern: every block if k is global; else the global query blocks, the
-// window and the rows of rand_idx that name k).  Per query block, first thread t computes
-// P and dS for key t % 64 and queries 16 (t / 64) .. + 15 into LDS, then thread t adds the
-// products into d columns 16 (t / 64) .. + 15 of key t % 64.
+// dK, dV: one work item = (batch*head, key block k, slice of its query-block list).  Slice u of ns takes
+// entries u, u + ns, ... of the list (a non-global key block's list can be of any length: the rows of
+// rand_idx that name it).  Wave (qh, kh): 32 queries against 32 keys, S, dP, dS are [queries x keys],
+// dV^T += dO^T P and dK^T += Q^T dS; the two query halves' shares are added in LDS.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kF32Threads) void bwd_f32_dkv_kernel(BwdParams p) {
-  __shared__ __attribute__((aligned(16))) float lds_q[kBlk * kTileStride];
-  __shared__ __attribute__((aligned(16))) float lds_do[kBlk * kTileStride];
-  __shared__ float lds_p[kBlk * (kBlk + 1)];   // [query][key]
-  __shared__ float lds_ds[kBlk * (kBlk + 1)];
-  __shared__ float lds_lse[kBlk], lds_d[kBlk];
-  __shared__ int jlist[kListChunk];
-  __shared__ int jcount;
+__global__ __launch_bounds__(kThreadsF32) __attribute__((amdgpu_waves_per_eu(2))) void bwd_f32_dkv_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(16))) float lds_q[kBlk * kF32Stride];
+  __shared__ __attribute__((aligned(16))) float lds_do[kBlk * kF32Stride];
+  __shared__ __attribute__((aligned(16))) float lds_lse[kBlk], lds_d[kBlk];
+  __shared__ int jlist[kMaxBwdBlocks];
 
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
-  const int nb = p.nb;
-  const int bh = blockIdx.x / nb, k = blockIdx.x % nb;
-  const int bi = bh / p.H, h = bh % p.H;
-  const int kk = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const size_t bh_row0 = static_cast<size_t>(bh) * p.n;
-  const size_t krow = bh_row0 + static_cast<size_t>(k) * kBlk + kk;
-  const float* Q = static_cast<const float*>(p.Q);
-  const float* K = static_cast<const float*>(p.K);
-  const float* V = static_cast<const float*>(p.V);
-  const float* dO = static_cast<const float*>(p.dO);
+  KeyItem it;
+  if (!decode_key_item(p, pat, blockIdx.x, &it)) return;
+  const int bi = it.bh / p.H, h = it.bh % p.H;
+  const int lane = lane_id(), wv = threadIdx.x >> 6;
+  const int hf = lane >> 5, col = lane & 31;
+  const int qh = wv & 1, kh = wv >> 1;
+  const size_t bh_row0 = static_cast<size_t>(it.bh) * p.n;
+  const size_t krow = bh_row0 + static_cast<size_t>(it.k) * kBlk + kh * 32 + col;
+  const float* Qp = static_cast<const float*>(p.Q);
+  const float* Gp = static_cast<const float*>(p.dO);
 
-  float kr[kDim], vr[kDim];
-#pragma unroll
-  for (int c4 = 0; c4 < kDim / 4; ++c4) {
-    const f32x4 kv = *reinterpret_cast<const f32x4*>(K + krow * kDim + c4 * 4);
-    const f32x4 vv = *reinterpret_cast<const f32x4*>(V + krow * kDim + c4 * 4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      kr[c4 * 4 + e] = kv[e];
-      vr[c4 * 4 + e] = vv[e];
-    }
-  }
-  const bool key_valid = !p.kmask || p.kmask[static_cast<size_t>(bi) * p.n + k * kBlk + kk] != 0;
-  const bool key_global = pat.is_global(k);
-  const int32_t* tbl = p.rand_idx ? p.rand_idx + static_cast<size_t>(h) * nb * p.r : nullptr;
+  f32x4 kf[8], vf[8];
+  row_fragments_f32(static_cast<const float*>(p.K) + krow * kDim, hf, kf);
+  row_fragments_f32(static_cast<const float*>(p.V) + krow * kDim, hf, vf);
+  const bool key_valid = !p.kmask || p.kmask[static_cast<size_t>(bi) * p.n + it.k * kBlk + kh * 32 + col] != 0;
+  const int total = build_query_list(p, pat, bi, h, it.k, jlist, wv == 0);
+  __syncthreads();
+
   const float c = p.c;
-  float dk[16], dv[16];
-#pragma unroll
-  for (int d = 0; d < 16; ++d) dk[d] = dv[d] = 0.f;
-
-  for (int j0 = 0; j0 < nb; j0 += kListChunk) {
-    __syncthreads();  // the previous chunk's list is no longer read
-    if (threadIdx.x < 64) {
-      // query blocks j0 .. j0+63 that attend k, in ascending order
-      const int j = j0 + threadIdx.x;
-      bool att = false;
-      if (j < nb) {
-        att = key_global || pat.is_global(j) || pat.in_window(j, k);
-        if (!att && tbl)
-          for (int t = 0; t < p.r; ++t) att |= tbl[static_cast<size_t>(j) * p.r + t] == k;
-      }
-      const uint64_t m = __ballot(att);
-      if (att) jlist[mask_rank(m)] = j;
-      if (threadIdx.x == 0) jcount = static_cast<int>(__popcll(m));
-    }
+  f32x16 dk[2], dv[2];
+  clear(dk);
+  clear(dv);
+  f32x4 qreg[kVecPerThreadF32], greg[kVecPerThreadF32];
+  float lreg = 0.f;  // threads 0 .. 63: LSE of row tid of the list entry, 64 .. 127: D
+  auto fetch = [&](int u) {
+    const size_t row0 = bh_row0 + static_cast<size_t>(jlist[u]) * kBlk;
+    tile_fetch_f32(Qp + row0 * kDim, qreg);
+    tile_fetch_f32(Gp + row0 * kDim, greg);
+    if (wv < 2) lreg = (wv == 0 ? p.Lvec : p.Dvec)[row0 + lane];
+  };
+  if (it.chunk < total) fetch(it.chunk);
+  for (int u = it.chunk; u < total; u += it.nchunks) {
+    const int j = jlist[u];
+    __syncthreads();  // everyone is done reading the previous tiles
+    tile_store_f32(lds_q, qreg);
+    tile_store_f32(lds_do, greg);
+    if (wv < 2) (wv == 0 ? lds_lse : lds_d)[lane] = lreg;
     __syncthreads();
-    const int cnt = jcount;
-    for (int u = 0; u < cnt; ++u) {
-      const int j = jlist[u];
-      __syncthreads();  // tiles and products of the previous query block are no longer read
-      const size_t jrow0 = bh_row0 + static_cast<size_t>(j) * kBlk;
-      load_tile_f32(Q + jrow0 * kDim, lds_q);
-      load_tile_f32(dO + jrow0 * kDim, lds_do);
-      if (threadIdx.x < 64) {
-        lds_lse[threadIdx.x] = p.Lvec[jrow0 + threadIdx.x];
-        lds_d[threadIdx.x] = p.Dvec[jrow0 + threadIdx.x];
-      }
-      __syncthreads();
-      for (int t = 0; t < 16; ++t) {
-        const int i = part * 16 + t;
-        const float s = dot_row(kr, lds_q + i * kTileStride);
-        const float dp = dot_row(vr, lds_do + i * kTileStride);
-        const float pr = key_valid ? fast_exp2(__builtin_fmaf(s, c, -lds_lse[i])) : 0.f;
+    if (u + it.nchunks < total) fetch(u + it.nchunks);
+
+    f32x16 s, dp;
+    mfma_rows_f32(lds_q + (qh * 32 + col) * kF32Stride, hf, kf, s);
+    mfma_rows_f32(lds_do + (qh * 32 + col) * kF32Stride, hf, vf, dp);
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const f32x4 l4 = *reinterpret_cast<const f32x4*>(lds_lse + qh * 32 + acc_row(r4 * 4, hf));
+      const f32x4 d4 = *reinterpret_cast<const f32x4*>(lds_d + qh * 32 + acc_row(r4 * 4, hf));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = r4 * 4 + e;
+        const float pr = fast_exp2(__builtin_fmaf(s[r], c, -l4[e]));
         // attention dropout: dV takes the kept, rescaled probabilities; dP is masked the same way
         float mr = 1.f;
         if (p.drop.thr)
-          mr = drop_keep(p.drop, static_cast<uint32_t>(jrow0 + i), static_cast<uint32_t>(k * kBlk + kk))
+          mr = drop_keep(p.drop, static_cast<uint32_t>(bh_row0 + j * kBlk + qh * 32 + acc_row(r, hf)),
+                         static_cast<uint32_t>(it.k * kBlk + kh * 32 + col))
                    ? p.drop.rs : 0.f;
-        lds_p[i * (kBlk + 1) + kk] = pr * mr;
-        lds_ds[i * (kBlk + 1) + kk] = pr * (dp * mr - lds_d[i]);
-      }
-      __syncthreads();
-      for (int i = 0; i < kBlk; ++i) {
-        const float pr = lds_p[i * (kBlk + 1) + kk];
-        const float ds = lds_ds[i * (kBlk + 1) + kk];
-        const float* qrow = lds_q + i * kTileStride + part * 16;
-        const float* grow = lds_do + i * kTileStride + part * 16;
-#pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
-          const f32x4 qv = *reinterpret_cast<const f32x4*>(qrow + c4 * 4);
-          const f32x4 gv = *reinterpret_cast<const f32x4*>(grow + c4 * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            dk[c4 * 4 + e] = __builtin_fmaf(ds, qv[e], dk[c4 * 4 + e]);
-            dv[c4 * 4 + e] = __builtin_fmaf(pr, gv[e], dv[c4 * 4 + e]);
-          }
-        }
+        s[r] = pr * mr;
+        dp[r] = pr * (dp[r] * mr - d4[e]);
       }
     }
+    mfma_columns_f32(lds_do + qh * 32 * kF32Stride, hf, col, s, dv);
+    mfma_columns_f32(lds_q + qh * 32 * kF32Stride, hf, col, dp, dk);
   }
+
+  __syncthreads();  // the tiles are no longer read
+  if (qh == 1) {
+    hand_over(lds_q + kh * (32 * 64), lane, dk);
+    hand_over(lds_do + kh * (32 * 64), lane, dv);
+  }
+  __syncthreads();
+  if (qh == 1) return;
+  take_over(lds_q + kh * (32 * 64), lane, dk);
+  take_over(lds_do + kh * (32 * 64), lane, dv);
+  // gradients of a padded key are exactly 0 (selected, not multiplied: its K row may hold anything)
 #pragma unroll
-  for (int c4 = 0; c4 < 4; ++c4) {
-    f32x4 a, b;
+  for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      a[e] = dk[c4 * 4 + e] * p.scale;
-      b[e] = dv[c4 * 4 + e];
+    for (int r = 0; r < 16; ++r) {
+      dk[dt][r] = key_valid ? dk[dt][r] * p.scale : 0.f;
+      dv[dt][r] = key_valid ? dv[dt][r] : 0.f;
     }
-    *reinterpret_cast<f32x4*>(p.dK + krow * kDim + part * 16 + c4 * 4) = a;
-    *reinterpret_cast<f32x4*>(p.dV + krow * kDim + part * 16 + c4 * 4) = b;
-  }
+  const size_t off = it.nchunks == 1 ? krow * kDim
+                                     : static_cast<size_t>(it.slot) * (kBlk * kDim) + (kh * 32 + col) * kDim;
+  store_rows_f32((it.nchunks == 1 ? p.dK : p.part_dk) + off, dk, hf);
+  store_rows_f32((it.nchunks == 1 ? p.dV : p.part_dv) + off, dv, hf);
 }
 
 int launch_bwd_f32(const BwdParams& p, hipStream_t stream) {
-  const unsigned grid = static_cast<unsigned>(p.BH) * p.nb;
-  if (grid == 0) return BB_OK;
-  hipLaunchKernelGGL(bwd_f32_dq_kernel, dim3(grid), dim3(kF32Threads), 0, stream, p);
+  const unsigned qgrid = DieItems(p.BH, p.split.items_per_bh).grid();
+  const unsigned kvgrid = DieItems(p.BH, p.kv.items_per_bh).grid();
+  hipLaunchKernelGGL(bwd_f32_dq_kernel, dim3(qgrid), dim3(kThreadsF32), 0, stream, p);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(bwd_f32_dkv_kernel, dim3(grid), dim3(kF32Threads), 0, stream, p);
+    hipLaunchKernelGGL(bwd_f32_dkv_kernel, dim3(kvgrid), dim3(kThreadsF32), 0, stream, p);
     e = hipGetLastError();
   }
   if (e != hipSuccess) {
     fprintf(stderr, "bigbird: launch of the fp32 backward kernels failed: %s\n", hipGetErrorString(e));
     return BB_ERR_LAUNCH;
   }
-  return BB_OK;
+  return launch_bwd_reduce(p, stream);
 }
 
 }  // namespace bb

@@ -10,6 +10,26 @@ namespace bb {
 constexpr int kMaxBwdBlocks = 256;  // longest query-block list a key block can have (LDS list): n <= 16 384,
                                     // the longest sequence the backward is verified on in full
 
+// dK/dV launch geometry: the query-block list of a global key block is cut into cg slices, that of
+// another one into cs slices; slice u of c takes entries u, u + c, ... of the list.
+struct KeySplit {
+  int cg, cs;
+  int items_per_bh;  // g*cg + (nb-g)*cs
+  int slots_per_bh;  // partial slots: (cg>1 ? g*cg : 0) + (cs>1 ? (nb-g)*cs : 0)
+};
+
+// len: list entries per slice of every key block (of an average list where its length is not known);
+// 0: kChunk for a global key block, one slice for the others.
+inline KeySplit make_key_split(int nb, int g, int w, int r, int len = 0) {
+  KeySplit s;
+  s.cg = (nb + (len > 0 ? len : kChunk) - 1) / (len > 0 ? len : kChunk);
+  s.cs = len > 0 ? (longest_sparse_list(nb, g, w, r) + len - 1) / len : 1;
+  if (s.cs < 1) s.cs = 1;
+  s.items_per_bh = g * s.cg + (nb - g) * s.cs;
+  s.slots_per_bh = (s.cg > 1 ? g * s.cg : 0) + (s.cs > 1 ? (nb - g) * s.cs : 0);
+  return s;
+}
+
 struct BwdParams {
   const void* Q;
   const void* K;
@@ -25,25 +45,92 @@ struct BwdParams {
   float* Dvec;     // [B*H*n]  -D_i, D_i = sum_c dO_ic O_ic (written by the dQ kernel)
   float* Lvec;     // [B*H*n]  LSE_i * log2(e); +inf for rows without a valid key
   float* part_dq;  // [slots][64][64] partial dQ of split rows (slots as in the forward)
-  float* part_dk;  // [B*H*g*cq][64][64] partial dK of global key blocks
+  float* part_dk;  // [slots][64][64] partial dK of split key blocks (slots: see KeySplit)
   float* part_dv;  // same for dV
   int B, H, BH, n, nb, g, w, r, global_mode;
   float c;      // scale * log2(e)
   float scale;
   RowSplit split;  // query-row decomposition (dQ kernel), as in the forward
-  int cq;          // slices of the query-block list of a global key block: ceil(nb / 8)
-  int kv_items_per_bh;  // g*cq + (nb - g)
+  KeySplit kv;     // key-block decomposition (dK/dV kernel)
   Dropout drop;    // attention dropout of the forward these gradients belong to (thr == 0: none)
   int skip_q;      // query blocks without a valid position (in kmask) were not computed: no gradient through them
 };
+
+// One item of the dK/dV kernels.
+struct KeyItem {
+  int bh, k;
+  int chunk, nchunks, slot;
+  bool key_global;
+};
+
+// Workgroup id -> item (see decode_item).  False: no such item.
+__device__ __forceinline__ bool decode_key_item(const BwdParams& p, const Pattern& pat, unsigned wg, KeyItem* it) {
+  int item;
+  if (!DieItems(p.BH, p.kv.items_per_bh).decode(wg, &it->bh, &item)) return false;
+  const int nglob = p.g * p.kv.cg;
+  it->key_global = item < nglob;
+  if (it->key_global) {
+    it->k = pat.global_block(item / p.kv.cg);
+    it->chunk = item % p.kv.cg;
+    it->nchunks = p.kv.cg;
+    it->slot = it->bh * p.kv.slots_per_bh + item;
+  } else {
+    const int t = item - nglob;
+    it->k = pat.sparse_block(t / p.kv.cs);
+    it->chunk = t % p.kv.cs;
+    it->nchunks = p.kv.cs;
+    it->slot = it->bh * p.kv.slots_per_bh + (p.kv.cg > 1 ? nglob : 0) + t;
+  }
+  return true;
+}
+
+// Query blocks that attend key block k, by the whole calling wave: every block if k is global (Sec. 2:
+// A(:, i) = 1 for i in G); else the global query blocks, the window, and the rows of rand_idx that name
+// k (a ballot scan of the head's table).  Without the query blocks that were not computed (skip_q).
+// Returns the count; one wave per workgroup writes the list.
+__device__ __forceinline__ int build_query_list(const BwdParams& p, const Pattern& pat, int bi, int h, int k,
+                                                int* jlist, bool write) {
+  const int lane = lane_id();
+  const bool key_global = pat.is_global(k);
+  int cnt = 0;
+  auto take = [&](bool valid, int j) {
+    if (p.skip_q && valid) valid = block_has_valid_key(p.kmask, bi, p.n, j);
+    const uint64_t m = __ballot(valid);
+    const int rank = cnt + mask_rank(m);
+    if (valid && write && rank < kMaxBwdBlocks) jlist[rank] = j;
+    cnt += static_cast<int>(__popcll(m));
+  };
+  if (key_global) {
+    for (int j0 = 0; j0 < p.nb; j0 += 64) take(j0 + lane < p.nb, j0 + lane);
+  } else {
+    for (int c0 = 0; c0 < p.g + p.w; c0 += 64) {
+      const int ci = c0 + lane;
+      const int j = ci < p.g ? pat.global_block(ci) : k - pat.half() + (ci - p.g);
+      take(ci < p.g || (ci < p.g + p.w && j >= 0 && j < p.nb && !pat.is_global(j)), j);
+    }
+    if (p.rand_idx) {
+      const int32_t* tbl = p.rand_idx + static_cast<size_t>(h) * p.nb * p.r;
+      for (int j0 = 0; j0 < p.nb; j0 += 64) {
+        const int j = j0 + lane;
+        bool valid = false;
+        if (j < p.nb && !pat.is_global(j) && !pat.in_window(j, k))
+          for (int t = 0; t < p.r; ++t) valid |= tbl[static_cast<size_t>(j) * p.r + t] == k;
+        take(valid, j);
+      }
+    }
+  }
+  return cnt < kMaxBwdBlocks ? cnt : kMaxBwdBlocks;  // (never more: the host bounds nb, a block is listed once)
+}
 
 // Enqueues: the dQ kernel (which also computes the row sums D), the dK/dV kernel and the
 // fixed-order reductions.
 int launch_bwd_bf16(const BwdParams& p, hipStream_t stream);
 
-// The same for fp32 tensors (Q, K, V, O, dO fp32): two plain kernels, one workgroup per query
-// block and per key block, no partial results (correctness configuration, not tuned).
+// The same for fp32 tensors (Q, K, V, O, dO fp32).
 int launch_bwd_f32(const BwdParams& p, hipStream_t stream);
+
+// Fixed-order sums of the partial gradients of both (nothing if no row and no column is split).
+int launch_bwd_reduce(const BwdParams& p, hipStream_t stream);
 
 }  // namespace bb
 #endif  // BB_BWD_KERNELS_H_

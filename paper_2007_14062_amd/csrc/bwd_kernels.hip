@@ -73,8 +73,7 @@ void bwd_dq_kernel(BwdParams p) {
   // a query block that the forward did not compute (no valid position, and the caller asked for
   // such blocks to be skipped): no key block, D = 0, probabilities 0
   const bool skip = p.skip_q && key_valid_bits(p.kmask, bi, p.n, it.j) == 0;
-  const int cnt = skip ? 0 : build_key_list(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, it.row_global,
-                                            it.chunk, klist);
+  const int cnt = skip ? 0 : build_key_list(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it, klist);
   __syncthreads();
   const int kl = klist[lane & (kChunkMax - 1)];
   auto key_block = [&](int i) { return __builtin_amdgcn_readlane(kl, i); };
@@ -261,28 +260,14 @@ void bwd_dkv_kernel(BwdParams p) {
   __shared__ int jlist[kMaxBwdBlocks];
 
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
-  const int nb = p.nb;
-  // workgroup id -> (batch*head, item); id % 8 is the die, as in the forward
-  const int xcd = blockIdx.x % kXcd;
-  const unsigned qidx = blockIdx.x / kXcd;
-  const int bh = (qidx / p.kv_items_per_bh) * kXcd + xcd;
-  if (bh >= p.BH) return;
-  const int item = qidx % p.kv_items_per_bh;
+  KeyItem it;
+  if (!decode_key_item(p, pat, blockIdx.x, &it)) return;
+  const int bh = it.bh, k = it.k;
   const int bi = bh / p.H, h = bh % p.H;
   const int lane = lane_id(), wv = threadIdx.x >> 6;
   const int hf = lane >> 5, col = lane & 31;
-
-  const int nglob = p.g * p.cq;
-  const bool key_global = item < nglob;
-  int k, chunk = 0, slot = 0;
-  if (key_global) {
-    k = pat.global_block(item / p.cq);
-    chunk = item % p.cq;
-    slot = (bh * p.g + item / p.cq) * p.cq + chunk;
-  } else {
-    k = pat.sparse_block(item - nglob);
-  }
-  const bool split = key_global && p.cq > 1;
+  const bool split = it.nchunks > 1;
+  const int slot = it.slot;
 
   const size_t bh_row0 = static_cast<size_t>(bh) * p.n;
   const size_t krow = bh_row0 + k * kBlk + wv * 32 + col;  // this lane's key
@@ -304,58 +289,9 @@ void bwd_dkv_kernel(BwdParams p) {
   }
   const bool key_valid = (vbits >> (wv * 32 + col)) & 1;
 
-  // ---- query blocks that attend key block k
-  int cnt = 0;
-  if (key_global) {
-    // every query block attends a global key block (Sec. 2: A(:, i) = 1 for i in G)
-    const int lo = chunk * kChunk;
-    cnt = nb - lo < kChunk ? nb - lo : kChunk;
-    if (cnt < 0) cnt = 0;
-    if (!p.skip_q) {
-      if (threadIdx.x < kChunk) jlist[threadIdx.x] = lo + threadIdx.x;
-    } else {
-      // without the query blocks that were not computed (both waves count, wave 0 writes)
-      const bool valid = lane < cnt && block_has_valid_key(p.kmask, bi, p.n, lo + lane);
-      const uint64_t m = __ballot(valid);
-      if (valid && wv == 0) jlist[mask_rank(m)] = lo + lane;
-      cnt = static_cast<int>(__popcll(m));
-    }
-  } else {
-    // global query blocks, then the window, then rows of rand_idx that name k
-    const int32_t* tbl = p.rand_idx ? p.rand_idx + static_cast<size_t>(h) * nb * p.r : nullptr;
-    for (int c0 = 0; c0 < p.g + p.w && cnt < kMaxBwdBlocks; c0 += 64) {
-      const int ci = c0 + lane;
-      bool valid = false;
-      int j = -1;
-      if (ci < p.g) {
-        j = pat.global_block(ci);
-        valid = true;
-      } else if (ci < p.g + p.w) {
-        j = k - pat.half() + (ci - p.g);
-        valid = j >= 0 && j < nb && !pat.is_global(j);
-      }
-      if (p.skip_q && valid) valid = block_has_valid_key(p.kmask, bi, p.n, j);
-      const uint64_t m = __ballot(valid);
-      const int rank = cnt + mask_rank(m);
-      if (valid && rank < kMaxBwdBlocks && wv == 0) jlist[rank] = j;
-      cnt += __popcll(m);
-    }
-    if (tbl) {
-      for (int j0 = 0; j0 < nb && cnt < kMaxBwdBlocks; j0 += 64) {
-        const int j = j0 + lane;
-        bool valid = false;
-        if (j < nb && !pat.is_global(j) && !pat.in_window(j, k)) {
-          for (int t = 0; t < p.r; ++t) valid |= tbl[static_cast<size_t>(j) * p.r + t] == k;
-        }
-        if (p.skip_q && valid) valid = block_has_valid_key(p.kmask, bi, p.n, j);
-        const uint64_t m = __ballot(valid);
-        const int rank = cnt + mask_rank(m);
-        if (valid && rank < kMaxBwdBlocks && wv == 0) jlist[rank] = j;
-        cnt += __popcll(m);
-      }
-    }
-    if (cnt > kMaxBwdBlocks) cnt = kMaxBwdBlocks;  // unreachable: the host bounds nb
-  }
+  const int total = build_query_list(p, pat, bi, h, k, jlist, wv == 0);
+  // this slice's share: entries chunk, chunk + nchunks, ... of the list
+  const int cnt = it.chunk < total ? (total - it.chunk + it.nchunks - 1) / it.nchunks : 0;
   __syncthreads();
 
   const char* qbase = static_cast<const char*>(p.Q) + bh_row0 * (kDim * 2);
@@ -369,7 +305,7 @@ void bwd_dkv_kernel(BwdParams p) {
   const unsigned lds_d_a = __builtin_amdgcn_readfirstlane(lds_addr(lds_d));
   // wave 0 brings LSE_j, wave 1 brings D_j (256 bytes each)
   auto stage = [&](int i, int buf) {
-    const int j = __builtin_amdgcn_readfirstlane(jlist[i]);
+    const int j = __builtin_amdgcn_readfirstlane(jlist[it.chunk + i * it.nchunks]);
     const size_t off = static_cast<size_t>(j) * kTile;
     tile_load_async(qbase + off, lds_q_wave + buf * kTile, voff);
     tile_load_async(dobase + off, lds_do_wave + buf * kTile, voff);
@@ -528,7 +464,7 @@ void bwd_dkv_kernel(BwdParams p) {
 // Fixed-order sums of the partial gradients of split rows (dQ) and split columns (dK, dV)
 // ---------------------------------------------------------------------------------------
 // One launch covers all three: blocks [0, nq) are the dQ blocks of split query rows, then
-// come the dK and the dV blocks of the global key blocks.  Four workgroups per 64x64 block,
+// come the dK and the dV blocks of split key blocks.  Four workgroups per 64x64 block,
 // thread t owns 4 columns of row part*16 + t/16.
 __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdParams p, int nq_blocks, int nkv_blocks) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
@@ -560,11 +496,23 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdParams p, int nq_blo
     blk -= nq_blocks;
     const bool is_dv = blk >= nkv_blocks;
     if (is_dv) blk -= nkv_blocks;
-    const int bh = blk / p.g, gi = blk % p.g;
-    nslices = p.cq;
-    const size_t slot0 = static_cast<size_t>(bh * p.g + gi) * p.cq;
-    src = (is_dv ? p.part_dv : p.part_dk) + slot0 * (kBlk * kDim);
-    dst = (is_dv ? p.dV : p.dK) + (static_cast<size_t>(bh) * p.n + pat.global_block(gi) * kBlk) * kDim;
+    const KeySplit& s = p.kv;
+    const int nglob_cols = s.cg > 1 ? p.g : 0;
+    const int cols_per_bh = nglob_cols + (s.cs > 1 ? p.nb - p.g : 0);
+    const int bh = blk / cols_per_bh, cc = blk % cols_per_bh;
+    int k, slot0;
+    if (cc < nglob_cols) {
+      k = pat.global_block(cc);
+      nslices = s.cg;
+      slot0 = bh * s.slots_per_bh + cc * s.cg;
+    } else {
+      const int t = cc - nglob_cols;
+      k = pat.sparse_block(t);
+      nslices = s.cs;
+      slot0 = bh * s.slots_per_bh + (s.cg > 1 ? p.g * s.cg : 0) + t * s.cs;
+    }
+    src = (is_dv ? p.part_dv : p.part_dk) + static_cast<size_t>(slot0) * (kBlk * kDim);
+    dst = (is_dv ? p.dV : p.dK) + (static_cast<size_t>(bh) * p.n + k * kBlk) * kDim;
   }
   const int off = (part * 16 + (threadIdx.x >> 4)) * kDim + (threadIdx.x & 15) * 4;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -596,25 +544,28 @@ bool launch_failed(const char* what) {
 }  // namespace
 
 int launch_bwd_bf16(const BwdParams& p, hipStream_t stream) {
-  const RowSplit& s = p.split;
-  const unsigned qgrid = static_cast<unsigned>(kXcd) * s.bh_rounds * s.items_per_bh;
+  const unsigned qgrid = DieItems(p.BH, p.split.items_per_bh).grid();
   const bool drop = p.drop.thr != 0;
   if (drop)
     hipLaunchKernelGGL(bwd_dq_kernel<true>, dim3(qgrid), dim3(kThreads), 0, stream, p);
   else
     hipLaunchKernelGGL(bwd_dq_kernel<false>, dim3(qgrid), dim3(kThreads), 0, stream, p);
   if (launch_failed("bwd_dq_kernel")) return BB_ERR_LAUNCH;
-  const unsigned kvgrid = static_cast<unsigned>(kXcd) * s.bh_rounds * p.kv_items_per_bh;
+  const unsigned kvgrid = DieItems(p.BH, p.kv.items_per_bh).grid();
   if (drop)
     hipLaunchKernelGGL(bwd_dkv_kernel<true>, dim3(kvgrid), dim3(kThreads), 0, stream, p);
   else
     hipLaunchKernelGGL(bwd_dkv_kernel<false>, dim3(kvgrid), dim3(kThreads), 0, stream, p);
   if (launch_failed("bwd_dkv_kernel")) return BB_ERR_LAUNCH;
 
-  // one reduction launch for the split dQ rows and the split dK / dV columns
+  return launch_bwd_reduce(p, stream);
+}
+
+int launch_bwd_reduce(const BwdParams& p, hipStream_t stream) {
+  const RowSplit& s = p.split;
   const int rows_per_bh = (s.cg > 1 ? p.g : 0) + (s.cs > 1 ? p.nb - p.g : 0);
-  const int nq_blocks = p.BH * rows_per_bh;
-  const int nkv_blocks = (p.g > 0 && p.cq > 1) ? p.BH * p.g : 0;
+  const int cols_per_bh = (p.kv.cg > 1 ? p.g : 0) + (p.kv.cs > 1 ? p.nb - p.g : 0);
+  const int nq_blocks = p.BH * rows_per_bh, nkv_blocks = p.BH * cols_per_bh;
   const int total = nq_blocks + 2 * nkv_blocks;
   if (total > 0) {
     hipLaunchKernelGGL(bwd_reduce_kernel, dim3(static_cast<unsigned>(total) * 4), dim3(256), 0, stream, p,

@@ -10,45 +10,23 @@
 // halves, and the probabilities sit in registers exactly where the second MFMA
 // wants its B operand (the contraction order over keys is free, so V^T is read
 // from LDS in the matching permuted key order).
+#include "f32_ops.h"
 #include "fwd_epilogue.h"
 
 #include <cstdio>
 
 namespace bb {
 
-namespace {
-
-constexpr int kTileBytesF32 = kBlk * kF32Stride * 4;            // 17 KB, rows padded to 68 floats
-constexpr int kVecPerThreadF32 = kBlk * kDim * 4 / 16 / kThreads;  // 8 x 16 bytes per thread
-
-// Global -> registers: one 64x64 fp32 tile of K or V, 16 bytes per lane per step, coalesced.
-__device__ __forceinline__ void tile_fetch_f32(const float* base, size_t row0, u32x4* regs) {
-  const int tid = threadIdx.x;
-  const char* p = reinterpret_cast<const char*>(base + row0 * kDim);
-#pragma unroll
-  for (int i = 0; i < kVecPerThreadF32; ++i) {
-    const int idx = i * kThreads + tid;
-    regs[i] = *reinterpret_cast<const u32x4*>(p + (idx >> 4) * 256 + (idx & 15) * 16);
-  }
-}
-
-// Registers -> LDS, rows padded so that the column reads of the MFMA operands spread over banks.
-__device__ __forceinline__ void tile_store_f32(char* lds, const u32x4* regs) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < kVecPerThreadF32; ++i) {
-    const int idx = i * kThreads + tid;
-    *reinterpret_cast<u32x4*>(lds + ((idx >> 4) * kF32Stride + (idx & 15) * 4) * 4) = regs[i];
-  }
-}
-
-}  // namespace
-
-// fp32 end to end (the small correctness workload): fp32 MFMA 32x32x2, tiles staged
-// through registers into one LDS buffer each, plain online softmax.
-__global__ __launch_bounds__(kThreads) void fwd_kernel_f32(FwdParams p) {
-  __shared__ __attribute__((aligned(16))) char lds_k[kTileBytesF32];
-  __shared__ __attribute__((aligned(16))) char lds_v[kTileBytesF32];
+// fp32 end to end: fp32 MFMA 32x32x2.  Four waves per work item; wave (qh, kh) takes 32 queries against
+// 32 of the 64 keys of every block with an online softmax of its own, and the two key halves are merged
+// in LDS at the end.  What bounds it is the fp32 matrix rate (a block pair is 64 MFMAs of 64 cycles per
+// wave: 2 us) and, at small sizes, the length of the longest slice: hence the fine slices
+// (fine_slice_f32).  n = 1024, 2 heads: 20 us a call with the merge launch; two waves over slices of 8
+// blocks took 44.  n = 2048, 12 heads: 50 against 92.
+__global__ __launch_bounds__(kThreadsF32) void fwd_kernel_f32(FwdParams p) {
+  __shared__ __attribute__((aligned(16))) float lds_k[kBlk * kF32Stride];
+  __shared__ __attribute__((aligned(16))) float lds_v[kBlk * kF32Stride];
+  __shared__ float mrg_m[kBlk], mrg_l[kBlk];
   __shared__ int klist[kChunkMax];
 
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
@@ -57,26 +35,22 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel_f32(FwdParams p) {
   const int bi = it.bh / p.H, h = it.bh % p.H;
   const int lane = lane_id(), wv = threadIdx.x >> 6;
   const int hf = lane >> 5, col = lane & 31;
-
-  // (a query block without a valid position, if the caller asked for those to be skipped, is an
-  // empty row: O = 0, LSE = -inf through the usual end of an item)
-  const bool skip = p.skip_q && key_valid_bits(p.kmask, bi, p.n, it.j) == 0;
-  const int cnt = skip ? 0 : build_key_list(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, it.row_global,
-                                            it.chunk, klist);
-  __syncthreads();
+  const int qh = wv & 1, kh = wv >> 1;
 
   const size_t bh_row0 = static_cast<size_t>(it.bh) * p.n;    // first row of this (batch, head)
-  const size_t qrow = bh_row0 + it.j * kBlk + wv * 32 + col;  // this lane's query row
+  const size_t qrow = bh_row0 + it.j * kBlk + qh * 32 + col;  // this lane's query row
   const float* Kp = static_cast<const float*>(p.K);
   const float* Vp = static_cast<const float*>(p.V);
 
   // Q^T operand: MFMA contraction slot hf of step (u, e) is d = 8u + 4hf + e.
   f32x4 qf[8];
-  {
-    const f32x4* qp = reinterpret_cast<const f32x4*>(static_cast<const float*>(p.Q) + qrow * kDim);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) qf[u] = qp[u * 2 + hf];
-  }
+  row_fragments_f32(static_cast<const float*>(p.Q) + qrow * kDim, hf, qf);
+
+  // (a query block without a valid position, if the caller asked for those to be skipped, is an
+  // empty row: O = 0, LSE = -inf through the usual end of an item)
+  const bool skip = p.skip_q && key_valid_bits(p.kmask, bi, p.n, it.j) == 0;
+  const int cnt = skip ? 0 : build_key_list(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it, klist);
+  __syncthreads();
 
   f32x16 o[2];
 #pragma unroll
@@ -85,15 +59,15 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel_f32(FwdParams p) {
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
   // attention dropout: the key of this lane's row of the keep mask
   const uint32_t drop_rk = p.drop.thr ? drop_row_key(p.drop, static_cast<uint32_t>(qrow)) : 0u;
-  float m_run = neg_inf();  // running maximum of the raw scores q.k (both halves agree)
+  float m_run = neg_inf();  // running maximum of the raw scores q.k (both lane halves agree)
   float l_run = 0.f;        // this lane's share of the running sum of 2^((q.k - m) c)
   const float c = p.c;
 
-  u32x4 kreg[kVecPerThreadF32], vreg[kVecPerThreadF32];
+  f32x4 kreg[kVecPerThreadF32], vreg[kVecPerThreadF32];
   if (cnt > 0) {
     const size_t krow0 = bh_row0 + static_cast<size_t>(klist[0]) * kBlk;
-    tile_fetch_f32(Kp, krow0, kreg);
-    tile_fetch_f32(Vp, krow0, vreg);
+    tile_fetch_f32(Kp + krow0 * kDim, kreg);
+    tile_fetch_f32(Vp + krow0 * kDim, vreg);
   }
 
   for (int i = 0; i < cnt; ++i) {
@@ -104,44 +78,28 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel_f32(FwdParams p) {
     __syncthreads();
     if (i + 1 < cnt) {
       const size_t krow0 = bh_row0 + static_cast<size_t>(klist[i + 1]) * kBlk;
-      tile_fetch_f32(Kp, krow0, kreg);
-      tile_fetch_f32(Vp, krow0, vreg);
+      tile_fetch_f32(Kp + krow0 * kDim, kreg);
+      tile_fetch_f32(Vp + krow0 * kDim, vreg);
     }
     uint64_t vbits = ~0ull;
     if (p.kmask) vbits = key_valid_bits(p.kmask, bi, p.n, kb);
 
-    // ---- S^T tile: rows = 64 keys (two 32-row MFMA tiles), columns = this wave's 32 queries
-    f32x16 s[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
-      const float* kr = reinterpret_cast<const float*>(lds_k) + (t * 32 + col) * kF32Stride + hf * 4;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(kr + u * 8);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          s[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], qf[u][e], s[t], 0, 0, 0);
-      }
-    }
+    // ---- S^T: rows = this wave's 32 keys, columns = its 32 queries
+    f32x16 s;
+    mfma_rows_f32(lds_k + (kh * 32 + col) * kF32Stride, hf, qf, s);
 
     // ---- padded keys -> -inf (only blocks that are partly padded take this path)
     if (vbits != ~0ull) {
-      const uint64_t mine = vbits >> (hf * 4);
+      const uint32_t mine = static_cast<uint32_t>(vbits >> (kh * 32)) >> (hf * 4);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (!((mine >> (t * 32 + acc_row(r, 0))) & 1)) s[t][r] = neg_inf();
+      for (int r = 0; r < 16; ++r)
+        if (!((mine >> acc_row(r, 0)) & 1)) s[r] = neg_inf();
     }
 
     // ---- online softmax (base 2, scale folded into c)
     float mloc = neg_inf();
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s[t][r]);
+    for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s[r]);
     mloc = half_max(mloc);
     const float m_new = fmaxf(m_run, mloc);
     const float m_use = (m_new == neg_inf()) ? 0.f : m_new;
@@ -149,13 +107,11 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel_f32(FwdParams p) {
     const float mc = m_use * c;
     float lsum = 0.f;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float pv = fast_exp2(__builtin_fmaf(s[t][r], c, -mc));
-        s[t][r] = pv;
-        lsum += pv;
-      }
+    for (int r = 0; r < 16; ++r) {
+      const float pv = fast_exp2(__builtin_fmaf(s[r], c, -mc));
+      s[r] = pv;
+      lsum += pv;
+    }
     l_run = l_run * alpha + lsum;
     m_run = m_new;
 #pragma unroll
@@ -167,33 +123,44 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel_f32(FwdParams p) {
     // multiplies V is the kept part (registers r, r+1 are keys 2m, 2m+1: one word of the mask)
     if (p.drop.thr) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          const uint32_t key = static_cast<uint32_t>(kb * kBlk + t * 32 + acc_row(r, hf));
-          const uint32_t wd = drop_word(drop_rk, key >> 1);
-          if (!drop_keep_even(wd, p.drop.thr)) s[t][r] = 0.f;
-          if (!drop_keep_odd(wd, p.drop.thr)) s[t][r + 1] = 0.f;
-        }
+      for (int r = 0; r < 16; r += 2) {
+        const uint32_t key = static_cast<uint32_t>(kb * kBlk + kh * 32 + acc_row(r, hf));
+        const uint32_t wd = drop_word(drop_rk, key >> 1);
+        if (!drop_keep_even(wd, p.drop.thr)) s[r] = 0.f;
+        if (!drop_keep_odd(wd, p.drop.thr)) s[r + 1] = 0.f;
+      }
     }
 
-    // ---- O^T += V^T P^T: the S^T accumulator is the B operand as it stands; slot hf of
-    // register r is key 32t + acc_row(r, hf), and V is read in that same key order.
-    const float* vbase = reinterpret_cast<const float*>(lds_v);
+    // ---- O^T += V^T P^T: the S^T accumulator is the B operand as it stands
+    mfma_columns_f32(lds_v + kh * 32 * kF32Stride, hf, col, s, o);
+  }
+
+  // ---- merge the two key halves: waves kh = 1 hand over, waves kh = 0 finish
+  float l_tot = half_sum(l_run);
+  __syncthreads();  // the tiles are no longer read
+  float* const slot = lds_k + qh * (32 * 64);
+  if (kh == 1) {
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = t * 32 + acc_row(r, hf);
-          const float a = vbase[key * kF32Stride + dt * 32 + col];
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, s[t][r], o[dt], 0, 0, 0);
-        }
+      for (int r = 0; r < 16; ++r) slot[(dt * 16 + r) * 64 + lane] = o[dt][r];
+    if (hf == 0) {
+      mrg_m[qh * 32 + col] = m_run;
+      mrg_l[qh * 32 + col] = l_tot;
+    }
   }
-
-  const float l_tot = half_sum(l_run);
-  fwd_store<false>(p, it, o, m_run, l_tot, c, qrow, wv * 32 + col, hf);
+  __syncthreads();
+  if (kh == 1) return;
+  const float m1 = mrg_m[qh * 32 + col], l1 = mrg_l[qh * 32 + col];
+  const float m_all = fmaxf(m_run, m1);
+  const float m_ref = m_all == neg_inf() ? 0.f : m_all;
+  const float w0 = fast_exp2((m_run - m_ref) * c), w1 = fast_exp2((m1 - m_ref) * c);
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[dt][r] = o[dt][r] * w0 + slot[(dt * 16 + r) * 64 + lane] * w1;
+  l_tot = l_tot * w0 + l1 * w1;
+  fwd_store<false>(p, it, o, m_all, l_tot, c, qrow, qh * 32 + col, hf);
 }
 
 // Merge the slices of a split row: M = max m_c, L = sum l_c 2^(m_c - M),
@@ -224,29 +191,36 @@ __global__ __launch_bounds__(kCombineThreads) void fwd_combine_kernel(FwdParams 
   const int q = part * 16 + (threadIdx.x >> 4), d0 = (threadIdx.x & 15) * 4;
   const float* ml = p.part_ml + static_cast<size_t>(slot0) * (2 * kBlk) + q;
   const float* po = p.part_o + static_cast<size_t>(slot0) * (kBlk * kDim) + q * kDim + d0;
-  float M = neg_inf();
-  for (int cidx = 0; cidx < nchunks; ++cidx) M = fmaxf(M, ml[cidx * (2 * kBlk)]);
+  // One pass with a running maximum, eight partials and their (m, l) requested together: a trip to
+  // memory per eight slices, not one per slice.
+  float M = neg_inf(), L = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  float L = 0.f;
-  if (M != neg_inf()) {
-    constexpr int U = 8;  // partials in flight per thread
-    for (int c0 = 0; c0 < nchunks; c0 += U) {
-      f32x4 v[U];
-      float wgt[U], lc[U];
+  constexpr int U = 8;
+  for (int c0 = 0; c0 < nchunks; c0 += U) {
+    f32x4 v[U];
+    float mc[U], lc[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int cidx = c0 + u < nchunks ? c0 + u : nchunks - 1;
-        v[u] = *reinterpret_cast<const f32x4*>(po + static_cast<size_t>(cidx) * (kBlk * kDim));
-        const float mcur = ml[cidx * (2 * kBlk)];
-        lc[u] = ml[cidx * (2 * kBlk) + kBlk];
-        wgt[u] = (c0 + u < nchunks && mcur != neg_inf()) ? fast_exp2(mcur - M) : 0.f;
-      }
+    for (int u = 0; u < U; ++u) {
+      const int cidx = c0 + u < nchunks ? c0 + u : nchunks - 1;
+      v[u] = *reinterpret_cast<const f32x4*>(po + static_cast<size_t>(cidx) * (kBlk * kDim));
+      mc[u] = ml[cidx * (2 * kBlk)];
+      lc[u] = ml[cidx * (2 * kBlk) + kBlk];
+    }
+    float m_new = M;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        L += lc[u] * wgt[u];
+    for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, mc[u]);
+    if (m_new == neg_inf()) continue;  // nothing but empty slices so far
+    const float alpha = fast_exp2(M - m_new);
+    M = m_new;
+    L *= alpha;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] += v[u][e] * wgt[u];
-      }
+    for (int e = 0; e < 4; ++e) acc[e] *= alpha;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float wgt = c0 + u < nchunks && mc[u] != neg_inf() ? fast_exp2(mc[u] - M) : 0.f;
+      L += lc[u] * wgt;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += v[u][e] * wgt;
     }
   }
   const float inv = L > 0.f ? p.drop.rs / L : 0.f;  // (rs: 1, or the dropout scale)
@@ -280,10 +254,9 @@ int launch_fwd(const FwdParams& p, bool bf16, hipStream_t stream) {
     const int st = launch_fwd_bf16_main(p, stream);
     if (st != BB_OK) return st;
   } else {
-    const RowSplit& s = p.split;
-    const unsigned grid = static_cast<unsigned>(kXcd) * s.bh_rounds * s.items_per_bh;
+    const unsigned grid = DieItems(p.BH, p.split.items_per_bh).grid();
     if (grid == 0) return BB_OK;
-    hipLaunchKernelGGL(fwd_kernel_f32, dim3(grid), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL(fwd_kernel_f32, dim3(grid), dim3(kThreadsF32), 0, stream, p);
     if (launch_failed("fwd_kernel_f32")) return BB_ERR_LAUNCH;
   }
   const int rows_per_bh = p.cmb_g_rows + p.cmb_s_rows;

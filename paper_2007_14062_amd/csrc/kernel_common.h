@@ -94,8 +94,8 @@ constexpr int kF32Stride = 68;  // floats per row of an fp32 tile in LDS (64 + 4
 struct WorkItem {
   int bh;       // batch * H + head
   int j;        // query block
-  int chunk;    // slice number: entries [chunk*len, (chunk+1)*len) of the row's key-block list,
-                // len = kChunkGlobal for a global row, kSparseChunk otherwise
+  int chunk;    // slice number: entries [chunk*len, (chunk+1)*len) of the row's key-block list
+  int len;      // RowSplit::lg for a global row, RowSplit::ls otherwise
   int nchunks;  // slices this row is split into
   int slot;     // partial-result slot (valid when nchunks > 1)
   bool row_global;
@@ -104,18 +104,38 @@ struct WorkItem {
 // Launch geometry shared by forward and dQ: rows of global query blocks are split
 // into cg slices, other rows into cs slices; global rows come first (longest first).
 struct RowSplit {
+  int lg, ls;         // key blocks per slice of a global / of a non-global row
   int cg, cs;         // slices per global / per non-global row
   int items_per_bh;   // g*cg + (nb-g)*cs
   int slots_per_bh;   // partial slots: (cg>1 ? g*cg : 0) + (cs>1 ? (nb-g)*cs : 0)
   int bh_rounds;      // ceil(B*H / 8)
 };
 
-inline RowSplit make_row_split(int BH, int nb, int g, int w, int r) {
+// Longest key-block list of a non-global row.
+inline int longest_sparse_list(int nb, int g, int w, int r) {
+  const long long ub = static_cast<long long>(g) + w + r;
+  return ub < nb ? static_cast<int>(ub) : nb;
+}
+
+// Key blocks per slice of the fp32 kernels.  A block pair keeps a workgroup's matrix pipes busy for
+// 2 .. 4 us there, so a launch that would have fewer than two 8-block slices per compute unit is cut finer,
+// down to one pair per workgroup (n = 1024, 2 heads: forward 42 us with slices of 8, backward kernels
+// 38 and 52; 13, 18 and 27 with slices of one).  0: use the standard slices.
+inline int fine_slice_f32(int BH, int nb, int g, int w, int r) {
+  const long long pairs =
+      static_cast<long long>(BH) * (static_cast<long long>(g) * nb + static_cast<long long>(nb - g) * longest_sparse_list(nb, g, w, r));
+  const long long len = (pairs + 511) / 512;
+  return len < kChunkGlobal ? static_cast<int>(len < 1 ? 1 : len) : 0;
+}
+
+// len: key blocks per slice of every row; 0: kChunkGlobal / kSparseChunk.
+inline RowSplit make_row_split(int BH, int nb, int g, int w, int r, int len = 0) {
   RowSplit s;
-  int sparse_ub = g + w + r;
-  if (sparse_ub > nb) sparse_ub = nb;
-  s.cg = (nb + kChunkGlobal - 1) / kChunkGlobal;
-  s.cs = (sparse_ub + kSparseChunk - 1) / kSparseChunk;
+  const int sparse_ub = longest_sparse_list(nb, g, w, r);
+  s.lg = len > 0 ? len : kChunkGlobal;
+  s.ls = len > 0 ? len : kSparseChunk;
+  s.cg = (nb + s.lg - 1) / s.lg;
+  s.cs = (sparse_ub + s.ls - 1) / s.ls;
   if (s.cs < 1) s.cs = 1;
   s.items_per_bh = g * s.cg + (nb - g) * s.cs;
   s.slots_per_bh = (s.cg > 1 ? g * s.cg : 0) + (s.cs > 1 ? (nb - g) * s.cs : 0);
@@ -123,20 +143,48 @@ inline RowSplit make_row_split(int BH, int nb, int g, int w, int r) {
   return s;
 }
 
-// Workgroup id -> work item.  Hardware hands consecutive workgroup ids to the 8
-// dies round robin, so id % 8 picks the die and all items of one (batch, head)
-// are given to one die: its K and V (1 MB at n = 4096) stay in that die's L2.
+// Hardware hands consecutive workgroup ids to the 8 dies round robin, so id % 8 picks the die.  Die x
+// gets the (batch, head) slices x, x + 8, ... whole, so that a slice's K and V (1 MB at n = 4096) stay in
+// its L2 and the sequences of a padded batch are spread over the dies; the items of the last B * H mod 8
+// slices are cut into eight equal runs: whole slices would leave six dies idle at B * H = 2 (fp32
+// forward at n = 1024, one pair per item: 25 us against 13) and give four of them twice the work of
+// the others at 12 (bf16 dQ and dK/dV kernels at n = 1088: 16 and 21 us against 13 and 18).
+struct DieItems {
+  unsigned rounds;   // whole slices per die
+  unsigned per_bh;   // items per slice
+  unsigned total;    // items of the slices left over
+  unsigned run;      // of these per die
+  __host__ __device__ DieItems(int BH, int items_per_bh) {
+    rounds = BH / kXcd;
+    per_bh = items_per_bh;
+    total = (BH % kXcd) * per_bh;
+    run = (total + kXcd - 1) / kXcd;
+  }
+  unsigned grid() const { return kXcd * (rounds * per_bh + run); }
+  // workgroup -> (slice, item); false: none
+  __device__ __forceinline__ bool decode(unsigned wg, int* bh, int* item) const {
+    const unsigned xcd = wg % kXcd, u = wg / kXcd;
+    if (u < rounds * per_bh) {
+      *bh = static_cast<int>(u / per_bh * kXcd + xcd);
+      *item = static_cast<int>(u % per_bh);
+      return true;
+    }
+    const unsigned t = xcd * run + (u - rounds * per_bh);
+    *bh = static_cast<int>(rounds * kXcd + t / per_bh);
+    *item = static_cast<int>(t % per_bh);
+    return t < total;
+  }
+};
+
+// Workgroup id -> work item.
 __device__ __forceinline__ bool decode_item(const RowSplit& s, const Pattern& pat, int BH,
                                             unsigned wg, WorkItem* it) {
-  const int xcd = wg % kXcd;
-  const unsigned q = wg / kXcd;
-  const int round = q / s.items_per_bh;
-  const int item = q % s.items_per_bh;
-  it->bh = round * kXcd + xcd;
-  if (it->bh >= BH) return false;
+  int item;
+  if (!DieItems(BH, s.items_per_bh).decode(wg, &it->bh, &item)) return false;
   const int nglob = pat.g * s.cg;
   if (item < nglob) {
     it->row_global = true;
+    it->len = s.lg;
     it->j = pat.global_block(item / s.cg);
     it->chunk = item % s.cg;
     it->nchunks = s.cg;
@@ -144,6 +192,7 @@ __device__ __forceinline__ bool decode_item(const RowSplit& s, const Pattern& pa
   } else {
     const int t = item - nglob;
     it->row_global = false;
+    it->len = s.ls;
     it->j = pat.sparse_block(t / s.cs);
     it->chunk = t % s.cs;
     it->nchunks = s.cs;
@@ -245,12 +294,11 @@ __device__ __forceinline__ int build_key_list_range(const Pattern& pat, const in
   return cnt;
 }
 
-// The same with the slice given by its number (see WorkItem).
+// The same for a work item's slice.
 __device__ __forceinline__ int build_key_list(const Pattern& pat, const int32_t* rand_idx, int r,
-                                              const uint8_t* kmask, int n, int bi, int h, int j,
-                                              bool row_global, int chunk, int* klist) {
-  const int len = row_global ? kChunkGlobal : kSparseChunk;
-  return build_key_list_range(pat, rand_idx, r, kmask, n, bi, h, j, row_global, chunk * len, len, klist);
+                                              const uint8_t* kmask, int n, int bi, int h, const WorkItem& it,
+                                              int* klist) {
+  return build_key_list_range(pat, rand_idx, r, kmask, n, bi, h, it.j, it.row_global, it.chunk * it.len, it.len, klist);
 }
 
 // 64-bit validity mask of the keys of block k (bit t = key k*64+t is valid).

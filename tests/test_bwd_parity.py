@@ -299,3 +299,25 @@ def test_seeded_sweep_of_small_configurations():
         check_full(t, ridx, 64, g, w, 0.125, key_mask=km, mode=mode,
                    tag=f"bwd sweep {done}: B{B} H{H} nb{nb} g{g} w{w} r{r} mode{mode} pad{km is not None}")
         done += 1
+
+
+@pytest.mark.parametrize("B,H,nb,g,w,r", [
+    (1, 1, 1, 0, 1, 0),     # a single pair
+    (1, 1, 9, 2, 3, 3),     # one pair per slice, one slice of batch * heads
+    (1, 6, 17, 2, 3, 3),    # two pairs per slice, odd number of blocks
+    (2, 9, 21, 3, 5, 2),    # slices of 7: remainders in every list
+    (3, 10, 16, 2, 3, 3),   # just past the fine slices
+    (1, 2, 20, 1, 1, 17),   # lists of 19, inverse lists of any length
+])
+def test_fp32_slices(B, H, nb, g, w, r):
+    """fp32 forward and backward at the edges of the slicing rule (bar 1e-4: fp32 sums of up to
+    64 * nb terms of order one)."""
+    n = nb * 64
+    t = inp.make_tensors(B, H, n, 64, 50 + nb, "f32", with_dO=True)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 5)
+    km = None
+    if nb > 1:
+        km = np.ones((B, n), dtype=np.uint8)
+        km[0, n - 70:] = 0
+        km[B - 1, 33:64] = 0
+    check_full_f32(t, ridx, 64, g, w, 0.125, key_mask=km, tag=f"fp32 slices B{B} H{H} nb{nb}")
