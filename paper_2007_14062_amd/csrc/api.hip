@@ -19,7 +19,7 @@ struct WorkspaceLayout {
   bool has_counters = false;
   size_t fwd_total = 0;
   // backward (its own carving of the same buffer): row sums, scaled LSE, partial gradients
-  size_t dvec = 0, lvec = 0, part_dq = 0, part_dk = 0, part_dv = 0;
+  size_t dvec = 0, lvec = 0, part_dq = 0, part_dk = 0, part_dv = 0, inverse = 0;
   size_t bwd_total = 0;
   size_t total = 0;
 };
@@ -71,6 +71,8 @@ WorkspaceLayout make_layout(int B, int H, int n, int b, int g, int w, int r, int
     o2 += round_up(kv_slots * bb::kBlk * bb::kDim * sizeof(float));
     L.part_dv = o2;
     o2 += round_up(kv_slots * bb::kBlk * bb::kDim * sizeof(float));
+    L.inverse = o2;  // inverse of the pattern: sets, order
+    o2 += round_up(static_cast<size_t>(H) * nb * (bb::kSetWords + 1) * sizeof(int));
     L.bwd_total = o2;
     if (o2 > L.total) L.total = o2;
   }
@@ -343,6 +345,9 @@ int attn_bwd_impl(const void* Q, const void* K, const void* V, const void* O,
   p.part_dv = reinterpret_cast<float*>(ws + L.part_dv);
   p.B = B; p.H = H; p.BH = B * H; p.n = n; p.nb = n / b;
   p.g = g; p.w = w; p.r = r; p.global_mode = global_mode;
+  p.query_sets = reinterpret_cast<uint32_t*>(ws + L.inverse);
+  p.key_order = reinterpret_cast<int*>(p.query_sets + static_cast<size_t>(H) * p.nb * bb::kSetWords);
+  p.inverse_wgs = (static_cast<unsigned>(H) * ((p.nb + 63) / 64) + bb::kXcd - 1) / bb::kXcd * bb::kXcd;
   p.c = scale * bb::kLog2e;
   p.scale = scale;
   p.drop = drop;

@@ -30,6 +30,8 @@ inline KeySplit make_key_split(int nb, int g, int w, int r, int len = 0) {
   return s;
 }
 
+constexpr int kSetWords = kMaxBwdBlocks / 32;
+
 struct BwdParams {
   const void* Q;
   const void* K;
@@ -42,8 +44,12 @@ struct BwdParams {
   float* dV;
   const int32_t* rand_idx;
   const uint8_t* kmask;
-  float* Dvec;     // [B*H*n]  -D_i, D_i = sum_c dO_ic O_ic (written by the dQ kernel)
-  float* Lvec;     // [B*H*n]  LSE_i * log2(e); +inf for rows without a valid key
+  // written by the dQ kernel for the dK/dV kernel
+  float* Dvec;     // [B*H*n]  bf16: -D_i, D_i = sum_c dO_ic O_ic; fp32: D_i
+  float* Lvec;     // [B*H*n]  bf16: -LSE_i / scale, -inf for rows without a valid key; fp32: LSE_i * log2(e), +inf
+  int* key_order;  // bf16: [H][nb] non-global key blocks by falling length of their query-block lists
+  uint32_t* query_sets;  // bf16: [H][nb][kSetWords] query blocks that attend a non-global key block, as bits
+  unsigned inverse_wgs;  // bf16: workgroups of the dQ launch that make these (a multiple of the dies)
   float* part_dq;  // [slots][64][64] partial dQ of split rows (slots as in the forward)
   float* part_dk;  // [slots][64][64] partial dK of split key blocks (slots: see KeySplit)
   float* part_dv;  // same for dV
@@ -63,10 +69,13 @@ struct KeyItem {
   bool key_global;
 };
 
-// Workgroup id -> item (see decode_item).  False: no such item.
+// Workgroup id -> item (see decode_item).  False: no such item.  As many slices at
+// a time as have their Q and dO (256 n bytes each) in an L2 together: with the longest lists of all of them
+// first the bf16 kernel ends sooner (24 slices, n = 4096: 43 -> 42 us; 48 padded ones, n = 3072, dropout: 64 -> 60),
+// but two slices of n = 16384 alternating miss the L2 (104 -> 111).
 __device__ __forceinline__ bool decode_key_item(const BwdParams& p, const Pattern& pat, unsigned wg, KeyItem* it) {
   int item;
-  if (!DieItems(p.BH, p.kv.items_per_bh).decode(wg, &it->bh, &item)) return false;
+  if (!DieItems(p.BH, p.kv.items_per_bh).decode(wg, &it->bh, &item, p.n < 16384 ? 16384 / p.n : 1)) return false;
   const int nglob = p.g * p.kv.cg;
   it->key_global = item < nglob;
   if (it->key_global) {

@@ -10,21 +10,20 @@
 //     query, and dQ^T += K^T dS^T.  It also computes the row sums D (and leaves them
 //     in the workspace for the second kernel).
 //   * bwd_dkv_kernel walks the query-block list of a key block -- the inverse of the
-//     pattern: the global query blocks, the window, and the rows of rand_idx that
-//     name this key block (found by scanning the head's table) -- with S, dP, dS as
+//     pattern (invert_pattern, part of the dQ launch) -- with S, dP, dS as
 //     [queries x keys] tiles, one lane per key, dV^T += dO^T P and dK^T += Q^T dS.
 // Rows / columns of global blocks are cut into slices of 8 blocks whose partial sums
 // are added in slice order by bwd_reduce_kernel (bit-reproducible).
 #include "bwd_kernels.h"
+#include "key_list.h"
 #include "tile_ops.h"
 
 #include <cstdio>
+#include <type_traits>
 
 namespace bb {
 
 namespace {
-
-constexpr int kTile = kBlk * kDim * 2;  // one 64x64 bf16 tile: 8 KB
 
 __device__ __forceinline__ void zero_acc(f32x16 (&a)[2]) {
 #pragma unroll
@@ -33,431 +32,686 @@ __device__ __forceinline__ void zero_acc(f32x16 (&a)[2]) {
     for (int r = 0; r < 16; ++r) a[t][r] = 0.f;
 }
 
-// Stores a [64 x 32] accumulator pair whose rows are d and whose column is this lane's
-// sequence position `row` (a query for dQ, a key for dK/dV): dst[row][d0 .. d0+3].
-__device__ __forceinline__ void store_acc_rows(float* dst_row, const f32x16 (&a)[2], int hf) {
-#pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      f32x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = a[dt][r4 * 4 + e];
-      *reinterpret_cast<f32x4*>(dst_row + dt * 32 + acc_row(r4 * 4, hf)) = v;
+// Sum over each group of eight lanes, in all of them.
+__device__ __forceinline__ float add_over_8_lanes(float x) {
+  auto moved = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  x += moved(x, std::integral_constant<int, 0xB1>{});   // quad_perm [1, 0, 3, 2]
+  x += moved(x, std::integral_constant<int, 0x4E>{});   // quad_perm [2, 3, 0, 1]
+  x += moved(x, std::integral_constant<int, 0x141>{});  // row_half_mirror: the other four of the eight
+  return x;
+}
+
+// The inverse of the pattern for one head and 64 key blocks: for a non-global key block the set of query
+// blocks that attend it, as bits, and its place in the order of falling list length.  One wave; it runs
+// beside the first dQ items, under whose time its own (5 us at nb = 64) disappears.  lds: 9 * kMaxBwdBlocks words.
+__device__ __forceinline__ void invert_pattern(const BwdParams& p, const Pattern& pat, unsigned wg, uint32_t* lds) {
+  const int groups = (p.nb + 63) / 64;
+  const int h = wg / groups, group = wg % groups, lane = lane_id();
+  if (h >= p.H) return;
+  auto low_bits = [](int n) { return n <= 0 ? 0u : n >= 32 ? ~0u : (1u << n) - 1u; };
+  uint32_t* const bits = lds;                                 // [key block][kSetWords]
+  int* const len = reinterpret_cast<int*>(lds) + kMaxBwdBlocks * kSetWords;  // of its list; 0: global, or past the end
+  const int first = pat.lead(), end = p.nb - pat.trail();     // non-global blocks
+  for (int i = lane; i < kMaxBwdBlocks * kSetWords; i += 64) bits[i] = 0u;
+  for (int i = lane; i < kMaxBwdBlocks; i += 64) len[i] = 0;
+  asm volatile("" ::: "memory");
+  // a lane per query block
+  for (int j = lane; j < p.nb; j += 64) {
+    const uint32_t bit = 1u << (j & 31);
+    uint32_t* const col = bits + (j >> 5);
+    if (!pat.is_global(j)) {
+      const int lo = j - pat.half() > first ? j - pat.half() : first, hi = j + pat.half() < end - 1 ? j + pat.half() : end - 1;
+      for (int k = lo; k <= hi; ++k) atomicOr(col + k * kSetWords, bit);
+      if (p.rand_idx) {
+        const int32_t* row = p.rand_idx + (static_cast<size_t>(h) * p.nb + j) * p.r;
+#pragma unroll 4
+        for (int t = 0; t < p.r; ++t) {
+          const int k = row[t];
+          if (k >= first && k < end) atomicOr(col + k * kSetWords, bit);
+        }
+      }
     }
+  }
+  asm volatile("" ::: "memory");
+  for (int k = first + lane; k < end; k += 64) {
+    int n = 0;
+#pragma unroll
+    for (int w = 0; w < kSetWords; ++w) {
+      // the global query blocks: [0, first) and [end, nb)
+      const uint32_t set = bits[k * kSetWords + w] | (low_bits(first - 32 * w) | (low_bits(p.nb - 32 * w) & ~low_bits(end - 32 * w)));
+      bits[k * kSetWords + w] = set;
+      n += __popc(set);
+    }
+    len[k] = n;
+  }
+  asm volatile("" ::: "memory");
+  const int k = group * 64 + lane;
+  const bool mine = k >= first && k < end;
+  const int my_len = mine ? len[k] : 0;
+  int rank = 0;
+#pragma unroll 4
+  for (int k4 = 0; k4 < p.nb; k4 += 4) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(len + k4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) rank += static_cast<int>(v[u]) + (k4 + u < k ? 1 : 0) > my_len ? 1 : 0;  // longer, or as long and before
+  }
+  if (mine) {
+    p.key_order[h * p.nb + rank] = k;
+    u32x4* dst = reinterpret_cast<u32x4*>(p.query_sets + (static_cast<size_t>(h) * p.nb + k) * kSetWords);
+#pragma unroll
+    for (int w = 0; w < kSetWords / 4; ++w) dst[w] = *reinterpret_cast<const u32x4*>(bits + k * kSetWords + w * 4);
+  }
+}
+
+// Query blocks that attend key block k, by both waves of a workgroup (wave 0 writes the list), in
+// ascending order: every block if k is global (Sec. 2: A(:, i) = 1 for i in G); else the set that
+// invert_pattern left.  Without the query blocks that were not computed (skip_q).
+__device__ __forceinline__ int query_list(const BwdParams& p, const Pattern& pat, int bi, int h, int k, int* jlist,
+                                          bool write) {
+  const int lane = lane_id();
+  const bool key_global = pat.is_global(k);
+  const uint32_t* set = p.query_sets + (static_cast<size_t>(h) * p.nb + k) * kSetWords;
+  int cnt = 0;
+  for (int j0 = 0; j0 < p.nb; j0 += 64) {
+    const int j = j0 + lane;
+    bool valid = j < p.nb;
+    if (!key_global) valid = (set[j >> 5] >> (j & 31)) & 1;  // (bits past nb are 0)
+    if (p.skip_q && valid) valid = block_has_valid_key(p.kmask, bi, p.n, j);
+    const uint64_t m = __ballot(valid);
+    if (valid && write) jlist[cnt + mask_rank(m)] = j;
+    cnt += static_cast<int>(__popcll(m));
+  }
+  return cnt;
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------------------------------
-// dQ: one work item = (batch*head, query block j, slice of <= 8 key blocks of j's list)
+// dQ: one work item = (batch*head, query block j, slice of j's key-block list), one wavefront per item
 // ---------------------------------------------------------------------------------------
+// A block pair is four units: 32 keys x 32 queries (query tile A or B), key half by key half.  Stages
+// of unit u, in the order the wave issues them:
+//   a(u)  S^T = K Q^T on the matrix pipe (4 MFMAs), beside dS(u-1) = P o (dP - D) and its conversion
+//   b(u)  dP^T = V dO^T and dQ^T += K^T dS^T of unit u-1 (8 MFMAs), beside P = 2^(S^T c - LSE log2e)
+// so that both pipes always have independent work, within the wave and between the two waves of a SIMD,
+// which never wait for each other.
+// Why this split: per block pair and compute unit the three products take the matrix pipes 384 cycles.
+// Operands come from LDS, 128 bytes per cycle: a wave with 32 queries (two waves sharing the tiles, as
+// this kernel was before) reads 48 KB per pair, 384 cycles more that nothing hid.  With 64 queries per
+// wave every K, V and K^T fragment feeds two MFMAs: 24 KB.  Key halves, not whole blocks, because 64
+// keys' worth of fragments do not fit beside Q, dO and dQ (128 registers).
+// What bounds it now: issue slots of the vector port (an MFMA takes 17 cycles of it, an exponential 7 to 9,
+// a conversion 5, other instructions 3, measured with two waves per SIMD: 2080 per block pair and SIMD
+// against 1536 of the matrix pipe; 2300 are reached) and, with all waves of a launch of 1872 items resident
+// at once, the start: Q, dO, O tiles of every item together, 9 k of a wave's 41 k cycles.
+// 24 slices, n = 4096: 40 -> 35 us; 16 of n = 16384: 97 -> 82; n = 3072, 48 slices, dropout: 53 -> 47.
+struct DqState {
+  bf16x8 qb[2][4], dob[2][4];  // B operands of the item: Q^T, dO^T (lane = query, d = 16ks + 8hf .. +8)
+  f32x16 dq[2][2];             // [query tile][d tile]
+  bf16x8 ka[4], va[4];         // straight fragments of the key half in work
+  bf16x8 kt[2][2];             // its transposed K fragments (until the next half's arrive)
+  f32x16 s, dp;                // the unit in work
+  float lse2[2], d[2];         // per query tile: LSE log2(e) of this lane's query, its row sum D
+};
+
 // kDrop: attention dropout, dP = M / (1 - p) o (dO V^T) with M the keep mask (a second instance of
 // the kernel, so that the one without dropout keeps its registers and its schedule).
+
+// dS of the previous unit (query tile q), packed as B operand.
 template <bool kDrop>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
+__device__ __forceinline__ void dq_ds(const DqState& st, const f32x16& p, const f32x16& dp, int q,
+                                      const Dropout& drop, uint32_t drop_rk, uint32_t key0, int hf,
+                                      bf16x8 (&dsb)[2]) {
+  const float d = st.d[q];
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    float x0, x1;
+    if constexpr (kDrop) {
+      // registers r, r + 1 are keys 2m, 2m + 1: one word of the mask
+      const uint32_t wd = drop_word(drop_rk, (key0 + acc_row(r, hf)) >> 1);
+      x0 = drop_keep_even(wd, drop.thr) ? __builtin_fmaf(dp[r], drop.rs, -d) : -d;
+      x1 = drop_keep_odd(wd, drop.thr) ? __builtin_fmaf(dp[r + 1], drop.rs, -d) : -d;
+    } else {
+      x0 = dp[r] - d;
+      x1 = dp[r + 1] - d;
+    }
+    const bf16x2 pk = {static_cast<__bf16>(p[r] * x0), static_cast<__bf16>(p[r + 1] * x1)};
+    dsb[r >> 3][r & 7] = pk[0];
+    dsb[r >> 3][(r & 7) + 1] = pk[1];
+  }
+}
+
+// Issue order of stage a: per MFMA a quarter of the vector work and of the LDS reads; of stage b: per
+// MFMA two exponentials.
+template <int DS_READS, int VALU>
+__device__ __forceinline__ void pin_a() {
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, DS_READS / 4, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <int DS_READS>
+__device__ __forceinline__ void pin_b() {
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    if (u < DS_READS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <bool kDrop>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_dq_kernel(BwdParams p) {
-  __shared__ __attribute__((aligned(1024))) char lds_k[2 * kTile];
-  __shared__ __attribute__((aligned(1024))) char lds_v[2 * kTile];
-  // The key list lives in the second V buffer, which is not written before the first barrier of
-  // the loop; by then every lane holds its entry in a register.
-  int* const klist = reinterpret_cast<int*>(lds_v + kTile);
+  // K and V tiles of the block in work, then swapped: what takes a half's place is requested as soon as
+  // the half sits in registers, the next block's K half where the V half was (free first) and its V half
+  // where the K half was, so that every request has one and a half halves of a block to land
+  __shared__ __attribute__((aligned(1024))) char lds[2][kTile];
+  __shared__ int klist[kChunkMax];
+  __shared__ uint32_t key_bits[kChunkMax][2];  // validity of the keys of blocks with padded keys inside
+  __shared__ float dvals[kBlk];
 
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   WorkItem it;
-  if (!decode_item(p.split, pat, p.BH, blockIdx.x, &it)) return;
+  // the first workgroups make the inverse of the pattern for the dK/dV kernel, which runs after this one
+  if (blockIdx.x < p.inverse_wgs) {
+    invert_pattern(p, pat, blockIdx.x, reinterpret_cast<uint32_t*>(lds));
+    return;
+  }
+  if (!decode_item(p.split, pat, p.BH, blockIdx.x - p.inverse_wgs, &it)) return;
   const int bi = it.bh / p.H, h = it.bh % p.H;
-  const int lane = lane_id(), wv = threadIdx.x >> 6;
+  const int lane = lane_id();
   const int hf = lane >> 5, col = lane & 31;
+  const size_t bh_row0 = static_cast<size_t>(it.bh) * p.n;
+
+  // Q and dO tiles into LDS, the O tile into registers (8 lanes a row), all in one trip to memory, whole
+  // rows at a time: fetched in operand layout these loads touch every row in each instruction, and all
+  // waves of the launch start with them.
+  const unsigned lds_a = __builtin_amdgcn_readfirstlane(lds_addr(lds[0]));
+  unsigned voff[2];
+  half_load_offsets(lane, voff);
+  const size_t row0 = bh_row0 + static_cast<size_t>(it.j) * kBlk;
+  tile_load_async_wave(static_cast<const char*>(p.Q) + row0 * (kDim * 2), lds_a, voff);
+  tile_load_async_wave(static_cast<const char*>(p.dO) + row0 * (kDim * 2), lds_a + kTile, voff);
+  bf16x8 orow[8];  // rows 8 ii + lane / 8, columns 8 (lane % 8) .. + 7
+#pragma unroll
+  for (int ii = 0; ii < 8; ++ii)
+    orow[ii] = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(p.O) + row0 * kDim)[ii * 64 + lane];
+  float lse = p.LSE[row0 + lane];
 
   // a query block that the forward did not compute (no valid position, and the caller asked for
   // such blocks to be skipped): no key block, D = 0, probabilities 0
-  const bool skip = p.skip_q && key_valid_bits(p.kmask, bi, p.n, it.j) == 0;
-  const int cnt = skip ? 0 : build_key_list(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it, klist);
-  __syncthreads();
-  const int kl = klist[lane & (kChunkMax - 1)];
-  auto key_block = [&](int i) { return __builtin_amdgcn_readlane(kl, i); };
+  const bool skip = p.skip_q && !block_any_valid_scalar(p.kmask, bi, p.n, it.j);
+  KeyList list = item_key_list<true>(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, it.row_global, it.chunk * it.len,
+                                     it.len, lane, klist, key_bits);
+  const int cnt = __builtin_amdgcn_readfirstlane(skip ? 0 : list.cnt);
+  const int kl = list.entry;
+  const unsigned partial = __builtin_amdgcn_readfirstlane(list.partial);
 
-  const size_t bh_row0 = static_cast<size_t>(it.bh) * p.n;
-  const size_t qrow = bh_row0 + it.j * kBlk + wv * 32 + col;
   const char* kbase = static_cast<const char*>(p.K) + bh_row0 * (kDim * 2);
   const char* vbase = static_cast<const char*>(p.V) + bh_row0 * (kDim * 2);
-  const unsigned voff = tile_load_lane_offset(wv, lane);
-  const unsigned lds_k_wave = __builtin_amdgcn_readfirstlane(lds_addr(lds_k) + wv * 1024);
-  const unsigned lds_v_wave = __builtin_amdgcn_readfirstlane(lds_addr(lds_v) + wv * 1024);
-  auto tile_off = [&](int i) { return static_cast<size_t>(key_block(i)) * kTile; };
-
-  if (cnt > 0) {
-    tile_load_async(kbase + tile_off(0), lds_k_wave, voff);
-    tile_load_async(vbase + tile_off(0), lds_v_wave, voff);
-  }
-
-  // B operands kept for the whole item: Q^T and dO^T, lane = query `col`, d = 16ks + 8hf .. +8
-  bf16x8 qb[4], dob[4];
-  {
-    const bf16x8* qp = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(p.Q) + qrow * kDim);
-    const bf16x8* dp = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(p.dO) + qrow * kDim);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      qb[ks] = qp[ks * 2 + hf];
-      dob[ks] = dp[ks * 2 + hf];
-    }
-  }
-  // D_i = sum_c dO_ic O_ic and LSE_i log2(e) of this lane's query (+inf where the forward found
-  // no valid key, so that the recomputed probabilities of such a row are 0).  The lane pair
-  // (l, l+32) shares a query and holds complementary halves of its d range.  The first slice of
-  // a row also leaves both values in the workspace for the dK/dV kernel, which runs after this one.
-  float dsum, lse2;
-  {
-    const bf16x8* op = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(p.O) + qrow * kDim);
-    float part = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const bf16x8 ob = op[ks * 2 + hf];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) part += static_cast<float>(dob[ks][e]) * static_cast<float>(ob[e]);
-    }
-    dsum = skip ? 0.f : half_sum(part);
-    const float lse = p.LSE[qrow];
-    lse2 = (skip || lse == neg_inf()) ? __builtin_inff() : lse * kLog2e;
-    if (it.chunk == 0 && hf == 0) {
-      p.Dvec[qrow] = -dsum;  // negated: the other kernel starts its dP accumulators from it
-      p.Lvec[qrow] = lse2;
-    }
-  }
-  // let the compiler settle these loads here, not inside the loop (see the forward kernel)
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(qb[ks]), "+v"(dob[ks]));
-  asm volatile("" : "+v"(lse2), "+v"(dsum));
+  // (past the end of the list: its last block again, which nobody uses)
+  auto tile_off = [&](int i) {
+    return static_cast<size_t>(__builtin_amdgcn_readlane(kl, i < cnt ? i : cnt - 1)) * kTile;
+  };
 
   const StraightOffsets so(lane);
-  const TransposedOffsets to(lane);
-  f32x16 dq[2];
-  zero_acc(dq);
-  const float c = p.c;
-  f32x16 neg_d;
+  DqState st;
+  wait_tile_loads<0>();
+  so.read(lds[0], st.qb);
+  so.read(lds[1], st.dob);
+  // D_i = sum_c dO_ic O_ic: row by row, an eighth of a row per lane, added up over the eight lanes
+  float dsum = 0.f;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) neg_d[r] = kDrop ? 0.f : -dsum;  // (with dropout D is subtracted after the mask)
-  uint32_t drop_rk = 0u;
-  if constexpr (kDrop) drop_rk = drop_row_key(p.drop, static_cast<uint32_t>(qrow));
-
-  for (int i = 0; i < cnt; ++i) {
-    const int buf = i & 1;
-    const int kb = key_block(i);
-    uint64_t vbits = ~0ull;
-    if (p.kmask) vbits = key_valid_bits(p.kmask, bi, p.n, kb);
-
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // K(i), V(i) landed
-    __builtin_amdgcn_s_waitcnt(kLgkmcnt0);     // our reads of the other buffers are done
-    BB_BARRIER();
-    if (i + 1 < cnt) {
-      tile_load_async(kbase + tile_off(i + 1), lds_k_wave + (buf ^ 1) * kTile, voff);
-      tile_load_async(vbase + tile_off(i + 1), lds_v_wave + (buf ^ 1) * kTile, voff);
+  for (int ii = 0; ii < 8; ++ii) {
+    const bf16x8 g = *reinterpret_cast<const bf16x8*>(lds[1] + tile_off_bf16(ii * 8 + (lane >> 3), lane & 7));
+    float part = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part = __builtin_fmaf(static_cast<float>(g[e]), static_cast<float>(orow[ii][e]), part);
+    part = add_over_8_lanes(part);
+    if ((lane & 7) == ii) dsum = part;
+  }
+  wait_lds_reads();
+  if (cnt > 0) {
+    const size_t off = tile_off(0);
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      half_load_async(kbase + off, lds_a, hh, voff);
+      half_load_async(vbase + off, lds_a + kTile, hh, voff);
     }
-    const char* kt = lds_k + buf * kTile;
-    const char* vt = lds_v + buf * kTile;
-
-    // S^T = K Q^T and dP^T = V dO^T: rows = 64 keys, columns = this wave's 32 queries
-    // (dP^T starts from -D: every element of a lane's accumulators belongs to the lane's query,
-    // so the subtraction in dS = P o (dP - D) costs no vector instruction)
-    f32x16 s[2], dp[2];
-    zero_acc(s);
-    dp[0] = neg_d;
-    dp[1] = neg_d;
-    bf16x8 ka[2][4], va[2][4];
-    so.read(kt, ka);
-    so.read(vt, va);
+  }
+  // (+inf where the forward found no valid key, so that the recomputed probabilities of such a row are
+  // 0.)  The first slice of a row also leaves D and LSE log2(e) in the workspace for the dK/dV kernel,
+  // which runs after this one.
+  if (skip) dsum = 0.f;
+  lse = (skip || lse == neg_inf()) ? __builtin_inff() : lse * kLog2e;
+  dvals[(lane & 7) * 8 + (lane >> 3)] = dsum;
+  asm volatile("" ::: "memory");
+  if (it.chunk == 0) {
+    p.Dvec[row0 + lane] = -dvals[lane];  // negated: the other kernel starts its dP accumulators from it
+    p.Lvec[row0 + lane] = lse == __builtin_inff() ? neg_inf() : -lse / p.c;  // (its S accumulators: from this)
+  }
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+  for (int q = 0; q < 2; ++q) {
+    st.d[q] = dvals[q * 32 + col];
+    st.lse2[q] = __shfl(lse, q * 32 + col);
+    zero_acc(st.dq[q]);
+  }
+  asm volatile("" : "+v"(st.d[0]), "+v"(st.d[1]), "+v"(st.lse2[0]), "+v"(st.lse2[1]));
+  uint32_t drop_rk[2] = {0u, 0u};
+  if constexpr (kDrop) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[t][ks], qb[ks], s[t], 0, 0, 0);
-    if (vbits != ~0ull) {  // partly padded block: masked keys get probability 0
-      const uint64_t mine = vbits >> (hf * 4);
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (!((mine >> (t * 32 + acc_row(r, 0))) & 1)) s[t][r] = neg_inf();
-    }
-    // P^T = 2^(S^T c - LSE log2e) on the vector ALU while the matrix pipe computes dP^T (the issue
-    // order "one MFMA, eight vector instructions" is pinned: left alone the compiler queues the
-    // MFMAs first, and the wave can issue nothing else meanwhile)
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-        dp[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t][ks], dob[ks], dp[t], 0, 0, 0);
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[t][r] = fast_exp2(__builtin_fmaf(s[t][r], c, -lse2));
-        asm volatile("" : "+v"(s[t][r]));  // computed here, beside the MFMAs, not where it is used
-      }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x402, 8, 0);
-    }
-    if constexpr (kDrop) {
-      // registers r, r + 1 are keys 2m, 2m + 1: one word of the mask
-      const float rs = p.drop.rs, nd = -dsum;
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          const uint32_t key = static_cast<uint32_t>(kb * kBlk + t * 32 + acc_row(r, hf));
-          const uint32_t wd = drop_word(drop_rk, key >> 1);
-          dp[t][r] = drop_keep_even(wd, p.drop.thr) ? __builtin_fmaf(dp[t][r], rs, nd) : nd;
-          dp[t][r + 1] = drop_keep_odd(wd, p.drop.thr) ? __builtin_fmaf(dp[t][r + 1], rs, nd) : nd;
-        }
-    }
-    // dS^T = P^T o (dP^T - D)
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[t][r] *= dp[t][r];
-    bf16x8 dsb[4];
-    pack_acc_bf16(s, dsb);
-
-    // dQ^T += K^T dS^T: rows = d, columns = queries, contraction over the 64 keys
-    bf16x8 kta[2][4];
-    to.read(kt, kta);
-#pragma unroll
-    for (int sg = 0; sg < 4; ++sg)
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt)
-        dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kta[dt][sg], dsb[sg], dq[dt], 0, 0, 0);
+    for (int q = 0; q < 2; ++q) drop_rk[q] = drop_row_key(p.drop, static_cast<uint32_t>(row0 + q * 32 + col));
   }
 
+  const TransposedOffsets to(lane);
+  const float c = p.c;
+
+  if (cnt > 0) {
+    // what the first unit "finishes": nothing
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
+    for (int r = 0; r < 16; ++r) st.s[r] = st.dp[r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dq[dt][r] *= p.scale;
-  if (it.nchunks == 1) {
-    store_acc_rows(p.dQ + qrow * kDim, dq, hf);
-  } else {
-    float* po = p.part_dq + static_cast<size_t>(it.slot) * (kBlk * kDim);
-    store_acc_rows(po + (wv * 32 + col) * kDim, dq, hf);
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) st.kt[a][b][e] = static_cast<__bf16>(0.f);
+    wait_tile_loads<8>();  // K(0).h0, V(0).h0 (each request is four loads)
+    read_straight_half(so, lds[0], 0, st.ka);
+
+    // dS of the last unit, its share of dQ in stage b of the next
+    bf16x8 dsb[2];
+    auto mask_ds = [&](int i, int hh) {
+      if ((partial >> i) & 1) drop_padded_keys(key_bits[i][hh], hf, dsb);
+    };
+    auto dq_update = [&](int q) {
+#pragma unroll
+      for (int sgl = 0; sgl < 2; ++sgl)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+          st.dq[q][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.kt[dt][sgl], dsb[sgl], st.dq[q][dt], 0, 0, 0);
+    };
+    auto products = [&](const bf16x8 (&a)[4], const bf16x8 (&b)[4], f32x16& acc) {
+      f32x16 z;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z[r] = 0.f;
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], z, 0, 0, 0);
+#pragma unroll
+      for (int ks = 1; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], b[ks], acc, 0, 0, 0);
+    };
+    // dP of query tile q beside the dQ products of the other one, alternating: an MFMA that adds to the
+    // result of the one before it waits for it
+    auto products_and_update = [&](int q, int qu) {
+      f32x16 z;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        st.dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.va[ks], st.dob[q][ks], ks == 0 ? z : st.dp, 0, 0, 0);
+        st.dq[qu][ks & 1] =
+            __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.kt[ks & 1][ks >> 1], dsb[ks >> 1], st.dq[qu][ks & 1], 0, 0, 0);
+      }
+    };
+    auto probabilities = [&](int q) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st.s[r] = fast_exp2(__builtin_fmaf(st.s[r], c, -st.lse2[q]));
+    };
+
+    // block i; its K tile is lds[X], its V tile lds[X ^ 1]
+    auto block = [&](int i, auto X) {
+      constexpr int kx = decltype(X)::value;
+      const int kb = __builtin_amdgcn_readlane(kl, i);
+      const int kprev = __builtin_amdgcn_readlane(kl, i > 0 ? i - 1 : 0);
+      const size_t off1 = tile_off(i + 1);
+      const char* k1 = kbase + off1;
+      const char* v1 = vbase + off1;
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        // key number of the first key of the previous unit's half (tile B of the half before this one)
+        const uint32_t key_prev = static_cast<uint32_t>((hh ? kb : kprev) * kBlk + (hh ^ 1) * 32);
+        const uint32_t key_cur = static_cast<uint32_t>(kb * kBlk + hh * 32);
+        f32x16 s_new;
+        // ---- a(A): V fragments of this half (the two requests after it are still out)
+        wait_tile_loads<8>();
+        read_straight_half(so, lds[kx ^ 1], hh, st.va);
+        products(st.ka, st.qb[0], s_new);
+        dq_ds<kDrop>(st, st.s, st.dp, 1, p.drop, drop_rk[1], key_prev, hf, dsb);
+        pin_a<4, 10>();
+        mask_ds(hh ? i : (i > 0 ? i - 1 : 0), hh ^ 1);
+        st.s = s_new;
+        // ---- b(A): the V half is in registers, its place takes the next block's K half
+        wait_lds_reads();
+        half_load_async(k1, lds_a + (kx ^ 1) * kTile, hh, voff);
+        products_and_update(0, 1);
+        probabilities(0);
+        pin_b<0>();
+        // ---- a(B)
+        read_transposed_half(to, lds[kx], hh, st.kt);
+        products(st.ka, st.qb[1], s_new);
+        dq_ds<kDrop>(st, st.s, st.dp, 0, p.drop, drop_rk[0], key_cur, hf, dsb);
+        pin_a<8, 10>();
+        mask_ds(i, hh);
+        st.s = s_new;
+        // ---- b(B): the K half likewise; the next half's K has landed (two younger requests)
+        wait_lds_reads();
+        wait_tile_loads<8>();
+        half_load_async(v1, lds_a + kx * kTile, hh, voff);
+        read_straight_half(so, lds[hh ? kx ^ 1 : kx], hh ^ 1, st.ka);
+        products_and_update(1, 0);
+        probabilities(1);
+        pin_b<4>();
+      }
+    };
+    for (int i = 0; i < cnt; i += 2) {
+      block(i, std::integral_constant<int, 0>{});
+      if (i + 1 < cnt) block(i + 1, std::integral_constant<int, 1>{});
+    }
+    // the last unit's dS and its share of dQ
+    {
+      const int kb = __builtin_amdgcn_readlane(kl, cnt - 1);
+      dq_ds<kDrop>(st, st.s, st.dp, 1, p.drop, drop_rk[1], static_cast<uint32_t>(kb * kBlk + 32), hf, dsb);
+      mask_ds(cnt - 1, 1);
+      dq_update(1);
+    }
+    wait_tile_loads<0>();  // requests past the end of the list
+  }
+
+  // dQ^T accumulators, turned through LDS so that memory sees whole rows
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = st.dq[q][dt][r4 * 4 + e] * p.scale;
+        *reinterpret_cast<f32x4*>(lds[dt] + tile_off_bf16(q * 32 + col, r4 * 2 + hf)) = v;
+      }
+  wait_lds_reads();
+  float* dst = it.nchunks == 1 ? p.dQ + row0 * kDim : p.part_dq + static_cast<size_t>(it.slot) * (kBlk * kDim);
+#pragma unroll
+  for (int ii = 0; ii < 16; ++ii) {
+    const int row = ii * 4 + (lane >> 4), cc = lane & 15;
+    const f32x4 v = *reinterpret_cast<const f32x4*>(lds[cc >> 3] + tile_off_bf16(row, cc & 7));
+    *reinterpret_cast<f32x4*>(dst + row * kDim + cc * 4) = v;
   }
 }
 
 // ---------------------------------------------------------------------------------------
-// dK, dV: one work item = (batch*head, key block k[, slice of its query-block list])
+// dK, dV: one work item = (batch*head, key block k[, slice of its query-block list]), two waves
 // ---------------------------------------------------------------------------------------
+// Wave wv owns 32 keys of the block; the list's Q and dO tiles come in halves of 32 queries through a ring
+// of four places in LDS that both waves read, one barrier per half.  Stages of half h, in issue order:
+//   A(h)  dK^T += Q^T dS of half h-1 and dP = dO V^T (8 MFMAs), beside P = 2^(S c) and its conversion
+//   B(h)  dV^T += dO^T P and S = Q K^T of half h+1 (8 MFMAs), beside dS = P o dP and its conversion
+// S starts from -LSE / scale and dP from -D, staged with the tiles (element r of an accumulator belongs to
+// query row acc_row(r)), so neither subtraction costs a vector instruction.  Operands are read from LDS one
+// stage before their use; a half is requested three halves ahead.
+// What bounds it: issue slots of the vector port, where an MFMA takes 17 cycles, an exponential 7 to 9, a
+// conversion 5 and other instructions 3 (measured, two waves per SIMD): 2340 cycles per block pair and
+// SIMD against 2048 of the matrix pipe.  One wave alone reaches
+// 1950, two on a SIMD 2700 (per pair; 3220 when a pair was one stage after the other).
+// Items run longest list first (key_order of the workspace): the lists of the non-global key blocks hold 5
+// to 16 query blocks at the base pattern, and in the order of the sequence the launch ended on whichever
+// came last.  24 slices, n = 4096: 50 -> 42 us; 16 of n = 16384: 124 -> 104; 48 of n = 3072 with padding and
+// dropout: 64 -> 60.
+//
 // kDrop: attention dropout (see bwd_dq_kernel): dV takes the kept probabilities (rescaled at the
-// end), dP is masked and rescaled before D is subtracted.  The row keys of the mask for the 64
-// queries of a list entry are staged in LDS beside LSE and D.
+// end), dP is masked and rescaled before D is subtracted.  The row keys of the mask for the queries of a
+// half are staged in LDS beside LSE and D.
+constexpr int kRing = 4;
+constexpr int kDkvThreads = 128;
+
+template <int DS_READS, int VALU>
+__device__ __forceinline__ void pin_half_stage() {
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, DS_READS / 8, 0);
+    if (VALU == 0)
+      __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);  // two exponentials
+    else
+      __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 template <bool kDrop>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(kDkvThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_dkv_kernel(BwdParams p) {
-  __shared__ __attribute__((aligned(256))) uint32_t lds_rk[kDrop ? 2 * kBlk : 4];
-  __shared__ __attribute__((aligned(1024))) char lds_q[2 * kTile];
-  __shared__ __attribute__((aligned(1024))) char lds_do[2 * kTile];
-  __shared__ __attribute__((aligned(256))) float lds_lse[2 * kBlk];
-  __shared__ __attribute__((aligned(256))) float lds_d[2 * kBlk];
+  __shared__ __attribute__((aligned(1024))) char ring[kRing][2][kHalfTile];  // Q half, dO half
+  __shared__ __attribute__((aligned(256))) float lds_l[kRing][kBlk];         // -LSE / scale of the whole block
+  __shared__ __attribute__((aligned(256))) float lds_d[kRing][kBlk];         // -D
+  __shared__ __attribute__((aligned(256))) uint32_t lds_rk[kDrop ? kRing : 1][kBlk];
   __shared__ int jlist[kMaxBwdBlocks];
 
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   KeyItem it;
   if (!decode_key_item(p, pat, blockIdx.x, &it)) return;
-  const int bh = it.bh, k = it.k;
+  const int bh = it.bh;
   const int bi = bh / p.H, h = bh % p.H;
-  const int lane = lane_id(), wv = threadIdx.x >> 6;
+  const int lane = lane_id();
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int hf = lane >> 5, col = lane & 31;
-  const bool split = it.nchunks > 1;
-  const int slot = it.slot;
+  if (!it.key_global) it.k = p.key_order[h * p.nb + it.k - pat.lead()];
+  const int k = __builtin_amdgcn_readfirstlane(it.k);
 
   const size_t bh_row0 = static_cast<size_t>(bh) * p.n;
-  const size_t krow = bh_row0 + k * kBlk + wv * 32 + col;  // this lane's key
-  float* dk_dst = split ? p.part_dk + static_cast<size_t>(slot) * (kBlk * kDim) + (wv * 32 + col) * kDim
-                        : p.dK + krow * kDim;
-  float* dv_dst = split ? p.part_dv + static_cast<size_t>(slot) * (kBlk * kDim) + (wv * 32 + col) * kDim
-                        : p.dV + krow * kDim;
+  const size_t krow0 = bh_row0 + static_cast<size_t>(k) * kBlk + wv * 32;  // first of this wave's keys
+  float* dk_dst = it.nchunks == 1 ? p.dK + krow0 * kDim
+                                  : p.part_dk + static_cast<size_t>(it.slot) * (kBlk * kDim) + wv * 32 * kDim;
+  float* dv_dst = it.nchunks == 1 ? p.dV + krow0 * kDim
+                                  : p.part_dv + static_cast<size_t>(it.slot) * (kBlk * kDim) + wv * 32 * kDim;
+
+  unsigned voff[2];
+  half_load_offsets(lane, voff);
+  const unsigned ring_a = __builtin_amdgcn_readfirstlane(lds_addr(ring));
+  // this wave's keys' K and V rows, through places 2 and 3 of the ring (whole rows at a time)
+  {
+    const size_t off = krow0 * (kDim * 2);
+    half_load_async(static_cast<const char*>(p.K) + off, ring_a + (2 * 2 + wv) * kHalfTile, 0, voff);
+    half_load_async(static_cast<const char*>(p.V) + off, ring_a + (3 * 2 + wv) * kHalfTile, 0, voff);
+  }
+  uint64_t vbits = ~0ull;
+  if (p.kmask) vbits = key_valid_bits(p.kmask, bi, p.n, k);
+  const int total = vbits == 0 ? 0 : query_list(p, pat, bi, h, k, jlist, wv == 0);
+  // this slice's share: entries chunk, chunk + nchunks, ... of the list
+  const int cnt = __builtin_amdgcn_readfirstlane(it.chunk < total ? (total - it.chunk + it.nchunks - 1) / it.nchunks : 0);
+  __syncthreads();
 
   f32x16 dk[2], dv[2];
   zero_acc(dk);
   zero_acc(dv);
+  if (cnt > 0) {
+    const char* qbase = static_cast<const char*>(p.Q) + bh_row0 * (kDim * 2);
+    const char* dobase = static_cast<const char*>(p.dO) + bh_row0 * (kDim * 2);
+    const char* tbase = wv == 0 ? qbase : dobase;  // wave 0 brings the Q halves and LSE, wave 1 dO and D
+    const float* vecbase = (wv == 0 ? p.Lvec : p.Dvec) + bh_row0;
+    const unsigned vec_a = __builtin_amdgcn_readfirstlane(wv == 0 ? lds_addr(lds_l) : lds_addr(lds_d));
+    // (past the end of the list: its last entry again, which nobody uses)
+    auto entry = [&](int hh) {
+      const int i = hh >> 1;
+      return jlist[it.chunk + (i < cnt ? i : cnt - 1) * it.nchunks];
+    };
+    // five loads per wave and half
+    auto request = [&](int hh, int j_, int place) {
+      const int j = __builtin_amdgcn_readfirstlane(j_);
+      half_load_async(tbase + static_cast<size_t>(j) * kTile + (hh & 1) * kHalfTile, ring_a + (place * 2 + wv) * kHalfTile, 0,
+                      voff);
+      vec_load_async(vecbase + static_cast<size_t>(j) * kBlk, vec_a + place * (kBlk * 4), lane);
+      if constexpr (kDrop) {
+        if (wv == 0)
+          lds_rk[place][lane] = drop_row_key(p.drop, static_cast<uint32_t>(bh_row0 + static_cast<size_t>(j) * kBlk + lane));
+      }
+    };
+    request(0, entry(0), 0);
+    request(1, entry(1), 1);
 
-  uint64_t vbits = ~0ull;
-  if (p.kmask) vbits = key_valid_bits(p.kmask, bi, p.n, k);
-  if (vbits == 0) {  // fully padded key block: gradients are exactly 0
-    store_acc_rows(dk_dst, dk, hf);
-    store_acc_rows(dv_dst, dv, hf);
-    return;
-  }
-  const bool key_valid = (vbits >> (wv * 32 + col)) & 1;
-
-  const int total = build_query_list(p, pat, bi, h, k, jlist, wv == 0);
-  // this slice's share: entries chunk, chunk + nchunks, ... of the list
-  const int cnt = it.chunk < total ? (total - it.chunk + it.nchunks - 1) / it.nchunks : 0;
-  __syncthreads();
-
-  const char* qbase = static_cast<const char*>(p.Q) + bh_row0 * (kDim * 2);
-  const char* dobase = static_cast<const char*>(p.dO) + bh_row0 * (kDim * 2);
-  const float* lbase = p.Lvec + bh_row0;
-  const float* dbase = p.Dvec + bh_row0;
-  const unsigned voff = tile_load_lane_offset(wv, lane);
-  const unsigned lds_q_wave = __builtin_amdgcn_readfirstlane(lds_addr(lds_q) + wv * 1024);
-  const unsigned lds_do_wave = __builtin_amdgcn_readfirstlane(lds_addr(lds_do) + wv * 1024);
-  const unsigned lds_lse_a = __builtin_amdgcn_readfirstlane(lds_addr(lds_lse));
-  const unsigned lds_d_a = __builtin_amdgcn_readfirstlane(lds_addr(lds_d));
-  // wave 0 brings LSE_j, wave 1 brings D_j (256 bytes each)
-  auto stage = [&](int i, int buf) {
-    const int j = __builtin_amdgcn_readfirstlane(jlist[it.chunk + i * it.nchunks]);
-    const size_t off = static_cast<size_t>(j) * kTile;
-    tile_load_async(qbase + off, lds_q_wave + buf * kTile, voff);
-    tile_load_async(dobase + off, lds_do_wave + buf * kTile, voff);
-    if (wv == 0)
-      vec_load_async(lbase + static_cast<size_t>(j) * kBlk, lds_lse_a + buf * (kBlk * 4), lane);
-    else
-      vec_load_async(dbase + static_cast<size_t>(j) * kBlk, lds_d_a + buf * (kBlk * 4), lane);
-    if constexpr (kDrop) {
-      if (wv == 0)
-        lds_rk[buf * kBlk + lane] = drop_row_key(p.drop, static_cast<uint32_t>(bh_row0 + static_cast<size_t>(j) * kBlk + lane));
-    }
-  };
-  if (cnt > 0) stage(0, 0);
-
-  // B operands kept for the whole item: K^T and V^T, lane = key `col`, d = 16ks + 8hf .. +8
-  bf16x8 kb[4], vb[4];
-  {
-    const bf16x8* kp = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(p.K) + krow * kDim);
-    const bf16x8* vp = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(p.V) + krow * kDim);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      kb[ks] = kp[ks * 2 + hf];
-      vb[ks] = vp[ks * 2 + hf];
-    }
-  }
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(kb[ks]), "+v"(vb[ks]));
-
-  const StraightOffsets so(lane);
-  const TransposedOffsets to(lane);
-  const float c = p.c;
-
-  for (int i = 0; i < cnt; ++i) {
-    const int buf = i & 1;
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __builtin_amdgcn_s_waitcnt(kLgkmcnt0);
+    // B operands kept for the whole item: K^T and V^T, lane = key `col`, d = 16ks + 8hf .. +8
+    const StraightOffsets so(lane);
+    const TransposedOffsets to(lane);
+    bf16x8 kb[4], vb[4];
+    wait_tile_loads<10>();
+    read_straight_half(so, ring[2][wv], 0, kb);
+    read_straight_half(so, ring[3][wv], 0, vb);
+    wait_lds_reads();
+    wait_tile_loads<5>();
     BB_BARRIER();
-    if (i + 1 < cnt) stage(i + 1, buf ^ 1);
-    const char* qt = lds_q + buf * kTile;
-    const char* dot = lds_do + buf * kTile;
+    request(2, entry(2), 2);
 
-    // S = Q K^T and dP = dO V^T: rows = 64 queries of block j, columns = this wave's 32 keys
-    // (dP starts from -D_q, staged with the tiles: element r of an accumulator belongs to query
-    // row acc_row(r), so dS = P o (dP - D) needs no subtraction afterwards)
-    const float* lq = lds_lse + buf * kBlk;
-    const float* dq = lds_d + buf * kBlk;
-    f32x16 s[2], dp[2];
-    zero_acc(s);
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
+    const float c = p.c;
+    bf16x8 qs[4], dos[4], qt[2][2], dot[2][2], pb[2], dsb[2];
+    f32x16 s, dp;
+    // rows of an accumulator that starts from a staged vector
+    auto start_from = [&](const float* vec, f32x16& acc) {
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
-        const f32x4 d4 = *reinterpret_cast<const f32x4*>(dq + t * 32 + acc_row(r4 * 4, hf));
+        const f32x4 v = *reinterpret_cast<const f32x4*>(vec + acc_row(r4 * 4, hf));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dp[t][r4 * 4 + e] = kDrop ? 0.f : d4[e];
+        for (int e = 0; e < 4; ++e) acc[r4 * 4 + e] = v[e];
       }
-    {
-      bf16x8 qa[2][4];
-      so.read(qt, qa);
+    };
+    auto add_products = [&](const bf16x8 (&a)[4], const bf16x8 (&b)[4], f32x16& acc) {
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+      for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], b[ks], acc, 0, 0, 0);
+    };
+    auto add_transposed = [&](const bf16x8 (&a)[2][2], const bf16x8 (&b)[2], f32x16 (&acc)[2]) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-          s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[t][ks], kb[ks], s[t], 0, 0, 0);
+      for (int sgl = 0; sgl < 2; ++sgl)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+          acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[dt][sgl], b[sgl], acc[dt], 0, 0, 0);
+    };
+    auto pack = [&](const f32x16& x, bf16x8 (&b)[2]) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) b[r >> 3][r & 7] = static_cast<__bf16>(x[r]);
+    };
+    // S of half 0; what A(0) "finishes": nothing
+    read_straight_half(so, ring[0][0], 0, qs);
+    start_from(lds_l[0], s);
+    add_products(qs, kb, s);
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dsb[a][e] = static_cast<__bf16>(0.f);
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qt[a][b][e] = static_cast<__bf16>(0.f);
     }
-    bf16x8 pb[4], dsb[4];
-    {
-      bf16x8 da[2][4];
-      so.read(dot, da);
+    const uint32_t my_pair = static_cast<uint32_t>(k * kBlk + wv * 32 + col) >> 1;  // (dropout) this lane's key
+    const uint32_t my_shift = (col & 1) ? 16u : 0u;
+
+    int j_next = entry(3);
+    auto half = [&](int hh, auto P) {
+      constexpr int here = decltype(P)::value, next = (here + 1) % kRing, row = (here & 1) * 32, row1 = row ^ 32;
+      // everything this wave read of half h-1 is in registers and its share of half h+1 has landed; after
+      // the barrier that holds for both waves, and half h+3 takes the place of half h-1
+      wait_lds_reads();
+      wait_tile_loads<5>();
+      BB_BARRIER();
+      request(hh + 3, j_next, (here + 3) % kRing);
+
+      // ---- A(h)
+      read_straight_half(so, ring[here][1], 0, dos);
+      if constexpr (kDrop) {
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+        for (int r = 0; r < 16; ++r) dp[r] = 0.f;
+      } else {
+        start_from(lds_d[here] + row, dp);
+      }
+      read_transposed_half(to, ring[here][1], 0, dot);
+      add_transposed(qt, dsb, dk);
+      add_products(dos, vb, dp);
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-          dp[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[t][ks], vb[ks], dp[t], 0, 0, 0);
-      // P = 2^(S c - LSE_q log2e) beside the dP MFMAs; q runs along the rows.  (A padded key's
-      // column is not set to 0 here: a lane's key only reaches that key's own columns of dK and
-      // dV, which are cleared at the end.)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int r = 0; r < 16; ++r) s[r] = fast_exp2(s[r] * c);
+      if constexpr (kDrop) {
+        // this lane's key against the queries of its accumulator rows: the kept probabilities go to dV,
+        // and dP becomes M / (1 - p) o dP - D  (the staged vector holds -D)
+        __builtin_amdgcn_sched_barrier(0);
+        const float rs = p.drop.rs;
+        f32x16 sk;
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(lq + t * 32 + acc_row(r4 * 4, hf));
+          const u32x4 k4 = *reinterpret_cast<const u32x4*>(lds_rk[here] + row + acc_row(r4 * 4, hf));
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(lds_d[here] + row + acc_row(r4 * 4, hf));
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            s[t][r4 * 4 + e] = fast_exp2(__builtin_fmaf(s[t][r4 * 4 + e], c, -l4[e]));
+            const uint32_t wd = drop_word(k4[e], my_pair);
+            const bool keep = ((wd >> my_shift) & 0x7fffu) >= p.drop.thr;
+            sk[r4 * 4 + e] = keep ? s[r4 * 4 + e] : 0.f;
+            dp[r4 * 4 + e] = keep ? __builtin_fmaf(dp[r4 * 4 + e], rs, d4[e]) : d4[e];
           }
         }
-      if constexpr (kDrop) {
-        // this lane's key against the 32 queries of its accumulator rows: the kept probabilities
-        // go to dV, and dP becomes M / (1 - p) o dP - D  (the staged vector holds -D)
-        const uint32_t* rkq = lds_rk + buf * kBlk;
-        const uint32_t my_pair = static_cast<uint32_t>(k * kBlk + wv * 32 + col) >> 1;
-        const uint32_t my_shift = (col & 1) ? 16u : 0u;
-        const float rs = p.drop.rs;
-        f32x16 sk[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4) {
-            const u32x4 k4 = *reinterpret_cast<const u32x4*>(rkq + t * 32 + acc_row(r4 * 4, hf));
-            const f32x4 d4 = *reinterpret_cast<const f32x4*>(dq + t * 32 + acc_row(r4 * 4, hf));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const uint32_t wd = drop_word(k4[e], my_pair);
-              const bool keep = ((wd >> my_shift) & 0x7fffu) >= p.drop.thr;
-              sk[t][r4 * 4 + e] = keep ? s[t][r4 * 4 + e] : 0.f;
-              dp[t][r4 * 4 + e] = keep ? __builtin_fmaf(dp[t][r4 * 4 + e], rs, d4[e]) : d4[e];
-            }
-          }
-        pack_acc_bf16(sk, pb);
+        pack(sk, pb);
+        __builtin_amdgcn_sched_barrier(0);
       } else {
-        pack_acc_bf16(s, pb);
+        pack(s, pb);
+        pin_half_stage<16, 0>();
+      }
+
+      // ---- B(h)
+      f32x16 s_new;
+      read_straight_half(so, ring[next][0], 0, qs);
+      start_from(lds_l[next] + row1, s_new);
+      read_transposed_half(to, ring[here][0], 0, qt);
+      j_next = entry(hh + 4);
+      add_transposed(dot, pb, dv);
+      add_products(qs, kb, s_new);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dp[r] *= s[r];
+      pack(dp, dsb);
+      pin_half_stage<16, 3>();
+      s = s_new;
+    };
+    for (int hh = 0; hh < 2 * cnt; hh += 4) {
+      half(hh, std::integral_constant<int, 0>{});
+      half(hh + 1, std::integral_constant<int, 1>{});
+      if (hh + 2 < 2 * cnt) {
+        half(hh + 2, std::integral_constant<int, 2>{});
+        half(hh + 3, std::integral_constant<int, 3>{});
       }
     }
-
-    // dV^T += dO^T P and dK^T += Q^T dS: rows = d, columns = keys, contraction over the 64 queries;
-    // dS = P o (dP - D_q) and its conversion beside the dV MFMAs
-    {
-      bf16x8 dta[2][4];
-      to.read(dot, dta);
-#pragma unroll
-      for (int sg = 0; sg < 4; ++sg)
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dta[dt][sg], pb[sg], dv[dt], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dp[t][r] *= s[t][r];
-      pack_acc_bf16(dp, dsb);
-    }
-    {
-      bf16x8 qta[2][4];
-      to.read(qt, qta);
-#pragma unroll
-      for (int sg = 0; sg < 4; ++sg)
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qta[dt][sg], dsb[sg], dk[dt], 0, 0, 0);
-    }
+    add_transposed(qt, dsb, dk);  // the last half's share
   }
+  wait_tile_loads<0>();  // requests past the end of the list (with an empty one: K and V)
+  __syncthreads();       // nobody reads the ring any more
 
-  // gradients of a padded key are exactly 0 (selected, not multiplied: its K row may hold anything)
+  // gradients of a padded key are exactly 0 (selected, not multiplied: its K row may hold anything); turned
+  // through LDS so that memory sees whole rows: this wave's 32 rows of dK, then of dV, d 0 .. 31 and 32 .. 63
+  const bool key_valid = (vbits >> (wv * 32 + col)) & 1;
+  const float vscale = kDrop ? p.drop.rs : 1.f;
+  char* const out = &ring[0][0][0] + wv * (4 * kHalfTile);
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      dk[dt][r] = key_valid ? dk[dt][r] * p.scale : 0.f;
-      dv[dt][r] = key_valid ? (kDrop ? dv[dt][r] * p.drop.rs : dv[dt][r]) : 0.f;
+    for (int r4 = 0; r4 < 4; ++r4) {
+      f32x4 a, b;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        a[e] = key_valid ? dk[dt][r4 * 4 + e] * p.scale : 0.f;
+        b[e] = key_valid ? dv[dt][r4 * 4 + e] * vscale : 0.f;
+      }
+      const int off = tile_off_bf16(col, r4 * 2 + hf);
+      *reinterpret_cast<f32x4*>(out + dt * kHalfTile + off) = a;
+      *reinterpret_cast<f32x4*>(out + (2 + dt) * kHalfTile + off) = b;
     }
-  store_acc_rows(dk_dst, dk, hf);
-  store_acc_rows(dv_dst, dv, hf);
+  wait_lds_reads();
+#pragma unroll
+  for (int ii = 0; ii < 8; ++ii) {
+    const int row = ii * 4 + (lane >> 4), cc = lane & 15;
+    const char* src = out + (cc >> 3) * kHalfTile + tile_off_bf16(row, cc & 7);
+    *reinterpret_cast<f32x4*>(dk_dst + row * kDim + cc * 4) = *reinterpret_cast<const f32x4*>(src);
+    *reinterpret_cast<f32x4*>(dv_dst + row * kDim + cc * 4) = *reinterpret_cast<const f32x4*>(src + 2 * kHalfTile);
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -544,18 +798,18 @@ bool launch_failed(const char* what) {
 }  // namespace
 
 int launch_bwd_bf16(const BwdParams& p, hipStream_t stream) {
-  const unsigned qgrid = DieItems(p.BH, p.split.items_per_bh).grid();
+  const unsigned qgrid = p.inverse_wgs + DieItems(p.BH, p.split.items_per_bh).grid();
   const bool drop = p.drop.thr != 0;
   if (drop)
-    hipLaunchKernelGGL(bwd_dq_kernel<true>, dim3(qgrid), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL(bwd_dq_kernel<true>, dim3(qgrid), dim3(64), 0, stream, p);
   else
-    hipLaunchKernelGGL(bwd_dq_kernel<false>, dim3(qgrid), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL(bwd_dq_kernel<false>, dim3(qgrid), dim3(64), 0, stream, p);
   if (launch_failed("bwd_dq_kernel")) return BB_ERR_LAUNCH;
   const unsigned kvgrid = DieItems(p.BH, p.kv.items_per_bh).grid();
   if (drop)
-    hipLaunchKernelGGL(bwd_dkv_kernel<true>, dim3(kvgrid), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL(bwd_dkv_kernel<true>, dim3(kvgrid), dim3(kDkvThreads), 0, stream, p);
   else
-    hipLaunchKernelGGL(bwd_dkv_kernel<false>, dim3(kvgrid), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL(bwd_dkv_kernel<false>, dim3(kvgrid), dim3(kDkvThreads), 0, stream, p);
   if (launch_failed("bwd_dkv_kernel")) return BB_ERR_LAUNCH;
 
   return launch_bwd_reduce(p, stream);

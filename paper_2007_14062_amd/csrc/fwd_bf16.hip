@@ -61,6 +61,7 @@
 // partial-result workspace (which must then hold 128 bytes per wave of the launch); the
 // library proper is built without it.
 #include "fwd_epilogue.h"
+#include "key_list.h"
 #include "tile_ops.h"
 
 #include <cstdio>
@@ -71,8 +72,6 @@ namespace {
 
 constexpr int kFwdWaves = 4;
 constexpr int kFwdThreads = 64 * kFwdWaves;  // four independent wavefronts, one work item each
-constexpr int kTile = kBlk * kDim * 2;       // 8 KB
-constexpr int kHalfTile = kTile / 2;         // 32 rows
 
 // Instances of the kernel: no padding mask; a padding mask; a padding mask or none, and attention
 // dropout or skipped query blocks.
@@ -90,65 +89,6 @@ __device__ __forceinline__ void zero_acc(f32x16 (&a)[2]) {
 }
 
 
-__device__ __forceinline__ const char* uniform_ptr(const char* p) {
-  const uintptr_t v = reinterpret_cast<uintptr_t>(p);
-  const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v));
-  const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));
-  return reinterpret_cast<const char*>((static_cast<uintptr_t>(hi) << 32) | lo);
-}
-
-// Half of a 64x64 bf16 tile (rows 32*hh .. +32), global -> LDS, by one wave: four
-// instructions of 64 lanes x 16 bytes.  Instruction ii fills LDS rows 8*ii .. 8*ii+7 of
-// the half linearly (lane l lands on row l/8, chunk position l%8) and fetches, for that
-// place, the chunk the swizzle stores there.  The swizzle depends on row bits 1..3, i.e. on
-// l/8 and on the parity of ii: voff[0] / voff[1] are the per-lane byte offsets for even /
-// odd ii.  The instruction's immediate offset moves the global and the LDS address alike,
-// so the four instructions share one base pair (M0, scalar address).
-__device__ __forceinline__ void half_load_async(const char* gtile_, unsigned lds, int hh,
-                                                const unsigned (&voff)[2]) {
-  const char* gtile = uniform_ptr(gtile_);  // wave uniform by construction: it has to sit in scalar registers
-  asm volatile(
-      "s_mov_b32 m0, %3\n\t"
-      "s_nop 4\n\t"  // wait states the compiler cannot see to from outside: M0 written by a scalar instruction (1) and an
-                       // address register pair that a vector instruction (v_readlane) may just have written (5)
-      "global_load_lds_dwordx4 %0, %2\n\t"
-      "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
-      "global_load_lds_dwordx4 %0, %2 offset:2048\n\t"
-      "global_load_lds_dwordx4 %1, %2 offset:3072"
-      :
-      : "v"(voff[0]), "v"(voff[1]), "s"(gtile + hh * kHalfTile), "s"(lds + hh * kHalfTile)
-      : "memory");  // M0 is written here; it is a reserved register that the compiler only sets right before
-                    // instructions of its own that read it, and this kernel has none
-}
-
-__device__ __forceinline__ void tile_load_async_wave(const char* gtile_, unsigned lds, const unsigned (&voff)[2]) {
-  const char* gtile = uniform_ptr(gtile_);  // wave-uniform by construction: keep it in scalar registers
-  half_load_async(gtile, lds, 0, voff);
-  half_load_async(gtile, lds, 1, voff);
-}
-
-// The lane number again, as a value the compiler cannot trace back.  Addresses and masks computed
-// from it are then computed where they are used; computed from the known lane number they would
-// be hoisted out of the item loop and carried through the pair loop, which has no register to
-// spare (spilled, they come back one scratch load and one full memory wait at a time).
-__device__ __forceinline__ int lane_again(int lane) {
-  asm volatile("" : "+v"(lane));
-  return lane;
-}
-
-// Waits and compiler fences.  The tile loads are invisible to the compiler's wait-count
-// bookkeeping (inline asm), so every wait for them is written out; loads return in order,
-// which makes "all but the N youngest" exact.
-template <int N>
-__device__ __forceinline__ void wait_tile_loads() {
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(N));
-  asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ void wait_lds_reads() {
-  __builtin_amdgcn_s_waitcnt(kLgkmcnt0);
-  asm volatile("" ::: "memory");
-}
-
 // Issue priority of the wave by the block pairs it still has to do, in steps of four pairs: the
 // two waves of a SIMD would otherwise be served oldest first, the older one would finish pairs
 // ahead of the younger, and the younger would do its last pairs alone at a little more than half
@@ -164,40 +104,6 @@ __device__ __forceinline__ void set_issue_priority(int remaining_pairs) {
   } else {
     __builtin_amdgcn_s_setprio(0);
   }
-}
-
-// Key-block list of a non-global row without a padding mask, from the row of the pattern table
-// that lanes 0 .. r-1 already hold in `rnd` (one entry per lane).  Same candidate order and
-// rules as build_key_list_range: global blocks, window blocks, random blocks; a candidate is
-// dropped if an earlier component already holds it.  Entries [lo, lo+len) go to klist.
-__device__ __forceinline__ int finish_key_list_sparse(const Pattern& pat, int r, int j, int rnd, int lo,
-                                                       int len, int* klist) {
-  const int lane = lane_id();
-  const int nb = pat.nb;
-  const int ncand = pat.g + pat.w + r;  // <= 64 (checked by the caller)
-  bool valid = false;
-  int k = -1;
-  const int t = lane - pat.g - pat.w;
-  const int mine = __shfl(rnd, t < 0 ? 0 : t);  // entry t of the row, for the lanes that stand for it
-  if (lane < pat.g) {
-    k = pat.global_block(lane);
-    valid = true;
-  } else if (lane < pat.g + pat.w) {
-    k = j - pat.half() + (lane - pat.g);
-    valid = k >= 0 && k < nb && !pat.is_global(k);
-  } else if (lane < ncand) {
-    k = mine;
-    valid = k >= 0 && k < nb && !pat.is_global(k) && !pat.in_window(j, k);
-  }
-  for (int u = 0; u < r; ++u) {
-    const int ku = __builtin_amdgcn_readlane(rnd, u);
-    if (u < t && ku == k) valid = false;
-  }
-  const uint64_t m = __ballot(valid);
-  const int rank = mask_rank(m);
-  if (valid && rank >= lo && rank < lo + len) klist[rank - lo] = k;
-  int cnt = static_cast<int>(__popcll(m)) - lo;
-  return cnt < 0 ? 0 : (cnt > len ? len : cnt);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -227,19 +133,6 @@ struct PairCtx {
   int hf;
   float c;  // scale * log2(e)
 };
-
-__device__ __forceinline__ void read_k_half(const StraightOffsets& so, const char* tile, int t, bf16x8 (&f)[4]) {
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) f[ks] = *reinterpret_cast<const bf16x8*>(tile + so.off[ks] + t * kHalfTile);
-}
-
-__device__ __forceinline__ void read_v_half(const TransposedOffsets& to, const char* tile, int t,
-                                            bf16x8 (&f)[2][2]) {
-#pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-    for (int sgl = 0; sgl < 2; ++sgl) f[dt][sgl] = to.read_one(tile, dt, 2 * t + sgl);
-}
 
 __device__ __forceinline__ void unit_scores(const bf16x8 (&k)[4], const bf16x8 (&q)[4], f32x16& s) {
   f32x16 z;
@@ -323,28 +216,6 @@ __device__ __forceinline__ void pin_slot() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// Padded keys of a unit leave the probabilities here, after the conversion and before the P V and
-// row-sum products of the next slot see them (their scores may be anything, also not a number).
-// bits: validity of the 32 keys of the unit, in key order.  Element kk of operand sgl belongs to key
-// 16 sgl + 8 (kk / 4) + 4 hf + kk % 4 (acc_row).  Three instructions per packed pair on the vector port --
-// only block pairs with padded keys inside pay them: the other pairs take one scalar branch per slot.
-__device__ __forceinline__ void drop_padded_keys(uint32_t bits, int hf, bf16x8 (&pb)[2]) {
-  const int b = static_cast<int>(bits >> (4 * hf));
-#pragma unroll
-  for (int sgl = 0; sgl < 2; ++sgl) {
-    union { bf16x8 v; uint32_t d[4]; } u;
-    u.v = pb[sgl];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int key = acc_row(sgl * 8 + 2 * m, 0);
-      const uint32_t even = static_cast<uint32_t>(__builtin_amdgcn_sbfe(b, key, 1));      // 0 or ~0
-      const uint32_t odd = static_cast<uint32_t>(__builtin_amdgcn_sbfe(b, key + 1, 1));
-      u.d[m] &= (even & 0xffffu) | (odd & 0xffff0000u);
-    }
-    pb[sgl] = u.v;
-  }
-}
-
 // One block pair.  The arithmetic and the memory requests are the same for every pair, so that
 // one straight-line body serves them all: the first pair of an item finishes a predecessor that
 // does not exist (p3 = 0 on entry, V fragments zeroed), the last one starts a successor that does
@@ -375,8 +246,8 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
 
   // ---- slot 1: K(i+1).t0 and V(i).t1 have landed
   wait_tile_loads<8>();
-  read_k_half(so, cx.lds_k, 0, ka[0]);
-  read_v_half(to, cx.lds_v, 1, va[1]);
+  read_straight_half(so, cx.lds_k, 0, ka[0]);
+  read_transposed_half(to, cx.lds_v, 1, va[1]);
   unit_scores(ka[1], qb[0], sC);
   unit_pv(va[0], p0, o[0], ones, ls[0]);
   unit_probs(sB, cx.c, p1);
@@ -395,8 +266,8 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
 
   // ---- slot 3: K(i+1).t1 and V(i+1).t0 have landed
   wait_tile_loads<8>();
-  read_k_half(so, cx.lds_k, 1, ka[1]);
-  read_v_half(to, cx.lds_v, 0, va[0]);
+  read_straight_half(so, cx.lds_k, 1, ka[1]);
+  read_transposed_half(to, cx.lds_v, 0, va[0]);
   unit_scores(ka[0], qb[0], sA);
   unit_pv(va[1], p2, o[0], ones, ls[0]);
   unit_probs(sD, cx.c, p3);
@@ -433,11 +304,7 @@ struct WaveCtx {
     cx.lds_v = lds_v;
     cx.hf = hf;
     cx.c = c;
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int row = par * 8 + (lane >> 3);
-      cx.voff[par] = (lane >> 3) * 128 + (((lane & 7) ^ tile_swizzle(row)) << 4);
-    }
+    half_load_offsets(lane, cx.voff);
     cx.lds_k_a = __builtin_amdgcn_readfirstlane(lds_addr(lds_k));
     cx.lds_v_a = __builtin_amdgcn_readfirstlane(lds_addr(lds_v));
   }
@@ -499,46 +366,6 @@ struct ItemTiles {
     return vbase + static_cast<size_t>(__builtin_amdgcn_readlane(kl, i)) * kTile;
   }
 };
-
-// Up to four entries of a pattern-table row through the scalar data path: request and wait sit
-// in one asm statement (the compiler sees the registers only once the values are in them), and
-// the wait is on the scalar/LDS counter, which the tile loads in flight do not touch.
-__device__ __forceinline__ void scalar_load4(const int32_t* row_, int o0, int o1, int o2, int o3, int (&e)[4]) {
-  // wave uniform by construction; made so explicitly, or the operands may arrive in vector registers
-  const int32_t* row = reinterpret_cast<const int32_t*>(uniform_ptr(reinterpret_cast<const char*>(row_)));
-  o0 = __builtin_amdgcn_readfirstlane(o0);
-  o1 = __builtin_amdgcn_readfirstlane(o1);
-  o2 = __builtin_amdgcn_readfirstlane(o2);
-  o3 = __builtin_amdgcn_readfirstlane(o3);
-  asm volatile(
-      "s_load_dword %0, %4, %5\n\t"
-      "s_load_dword %1, %4, %6\n\t"
-      "s_load_dword %2, %4, %7\n\t"
-      "s_load_dword %3, %4, %8\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&s"(e[0]), "=&s"(e[1]), "=&s"(e[2]), "=&s"(e[3])
-      : "s"(row), "s"(o0 * 4), "s"(o1 * 4), "s"(o2 * 4), "s"(o3 * 4)
-      : "memory");
-}
-
-// Does block j of batch entry bi hold a valid position?  The 64 mask bytes come through the scalar
-// data path (request and wait in one statement, on the scalar counter): no vector memory wait, which
-// would also wait for the tile loads in flight and for the stores of rows just written.
-__device__ __forceinline__ bool block_any_valid_scalar(const uint8_t* kmask, int bi, int n, int j) {
-  typedef __attribute__((ext_vector_type(16))) unsigned int u32x16;
-  const char* ptr = uniform_ptr(reinterpret_cast<const char*>(kmask) + static_cast<size_t>(bi) * n + static_cast<size_t>(j) * kBlk);
-  u32x16 v;
-  asm volatile(
-      "s_load_dwordx16 %0, %1, 0x0\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&s"(v)
-      : "s"(ptr)
-      : "memory");
-  unsigned any = 0;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) any |= v[e];
-  return any != 0;
-}
 
 // Item number -> item with its key-block list (for a global-row workgroup: the wave's share of
 // the row).  All loads here are waited for before the function returns (scalar loads inside
@@ -608,76 +435,17 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
     it.cnt = 0;
     return;
   }
-  // Non-global rows: the table row comes through the scalar data path and the list is made
-  // without a vector memory access.  A padding mask is then applied to the finished list, lane i
-  // looking at block i (one round trip to memory for the whole list) -- for rows of one slice,
-  // where dropping blocks afterwards cannot move a slice boundary.  Everything else takes the
-  // general builder.
-  const bool fast_list = !row_global && p.rand_idx && p.r > 0 &&
-                         p.g + p.w + p.r <= (p.kmask ? kGlobalWaveLen : 64);
-  if (fast_list) {
-    const int32_t* rrow = p.rand_idx + (static_cast<size_t>(h) * p.nb + it.j) * p.r;
-    int rnd = -1;
-    for (int u0 = 0; u0 < p.r; u0 += 4) {
-      int e[4];
-      const int last = p.r - 1;
-      scalar_load4(rrow, u0, u0 + 1 < last ? u0 + 1 : last, u0 + 2 < last ? u0 + 2 : last,
-                   u0 + 3 < last ? u0 + 3 : last, e);
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (lane == u0 + k && u0 + k < p.r) rnd = e[k];
-    }
-    it.cnt = finish_key_list_sparse(pat, p.r, it.j, rnd, list_lo, list_len, w.klist);
-  } else {
-    it.cnt = build_key_list_range(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, row_global, list_lo,
-                                  list_len, w.klist);
-  }
-  // same wave wrote and reads the list: LDS keeps a wave's accesses in order, the compiler must too
-  asm volatile("" ::: "memory");
-  it.kl = w.klist[lane & (kGlobalWaveLen - 1)];
-  asm volatile("" ::: "memory");
-  it.per_item = kMode == kOptions && p.drop.thr != 0;  // attention dropout is applied on the per-item path only
-  it.partial = 0;
-  if (kMode != kPlain && p.kmask) {
-    bool any_valid = false, any_padded = false;
-    if (lane < it.cnt) block_mask_flags(p.kmask, bi, p.n, it.kl, any_valid, any_padded);
-    const uint64_t m = __ballot(any_valid);
-    const int entry = fast_list ? mask_rank(m) : lane;
-    const int kb = it.kl;
-    if (fast_list) {
-      // drop the blocks without a valid key (the general builder has done that already)
-      if (any_valid) w.klist[entry] = kb;
-      it.cnt = static_cast<int>(__popcll(m));
-    }
-    const bool cut = any_valid && any_padded;
-    if (__any(cut)) {
-      if (cut) {
-        uint32_t bits[2];
-        block_key_bits(p.kmask, bi, p.n, kb, bits);
-        key_bits_all[w.wv][bits_slot][entry][0] = bits[0];
-        key_bits_all[w.wv][bits_slot][entry][1] = bits[1];
-      }
-      // entries are in lane order, so the flags of the kept lanes, closed up, are the flags of the list
-      uint64_t rest = m, flags = __ballot(cut);
-      if (fast_list) {
-        unsigned closed = 0;
-        for (int e = 0; rest; ++e, rest &= rest - 1)
-          closed |= ((flags >> __builtin_ctzll(rest)) & 1) ? 1u << e : 0u;
-        it.partial = closed;
-      } else {
-        it.partial = static_cast<unsigned>(flags);
-      }
-      // No block without padded keys: a row may have a key or two, whose rounded probabilities are a
-      // row sum that is off by up to 2^-9 (over 64 keys and more the roundings average out) -- the
-      // recurrence sums them before the rounding.
-      it.per_item |= it.partial == (1u << it.cnt) - 1;
-    }
-    if (fast_list) {
-      asm volatile("" ::: "memory");
-      it.kl = w.klist[lane & (kGlobalWaveLen - 1)];
-      asm volatile("" ::: "memory");
-    }
-  }
+  const KeyList kl = item_key_list<kMode != kPlain>(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, row_global, list_lo,
+                                                    list_len, lane, w.klist, key_bits_all[w.wv][bits_slot]);
+  it.cnt = kl.cnt;
+  it.kl = kl.entry;
+  it.partial = kl.partial;
+  // attention dropout is applied on the per-item path only
+  it.per_item = kMode == kOptions && p.drop.thr != 0;
+  // No block without padded keys: a row may have a key or two, whose rounded probabilities are a
+  // row sum that is off by up to 2^-9 (over 64 keys and more the roundings average out) -- the
+  // recurrence sums them before the rounding.
+  if (kMode != kPlain && it.partial) it.per_item |= it.partial == (1u << it.cnt) - 1;
   // all of these are wave uniform; saying so keeps them (and what is computed from them) in
   // scalar registers
   it.bh = __builtin_amdgcn_readfirstlane(it.bh);
@@ -782,8 +550,8 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
 
   // start of the streams: K(0) -> registers, then the loads a pair expects to find outstanding
   if (fresh) {
-    read_k_half(so, cx.lds_k, 0, ka[0]);
-    read_k_half(so, cx.lds_k, 1, ka[1]);
+    read_straight_half(so, cx.lds_k, 0, ka[0]);
+    read_straight_half(so, cx.lds_k, 1, ka[1]);
     wait_lds_reads();
     half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
     half_load_async(ts.v(0), cx.lds_v_a, 1, cx.voff);
@@ -791,7 +559,7 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
     half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
   }
   wait_tile_loads<8>();
-  read_v_half(to, cx.lds_v, 0, va[0]);
+  read_transposed_half(to, cx.lds_v, 0, va[0]);
   unit_scores(ka[0], qb[0], sA);
 
   for (int i = 0; i < cnt; ++i)
@@ -845,10 +613,10 @@ __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffse
     if (p.kmask) vbits = key_valid_bits(p.kmask, item.bh / p.H, p.n, kblock);
     wait_tile_loads<0>();
     bf16x8 ka[2][4], va[2][2][2];
-    read_k_half(so, cx.lds_k, 0, ka[0]);
-    read_k_half(so, cx.lds_k, 1, ka[1]);
-    read_v_half(to, cx.lds_v, 0, va[0]);
-    read_v_half(to, cx.lds_v, 1, va[1]);
+    read_straight_half(so, cx.lds_k, 0, ka[0]);
+    read_straight_half(so, cx.lds_k, 1, ka[1]);
+    read_transposed_half(to, cx.lds_v, 0, va[0]);
+    read_transposed_half(to, cx.lds_v, 1, va[1]);
     wait_lds_reads();  // the buffers are free again
     if (i + 1 < item.cnt) request_tiles(i + 1);
 #pragma unroll
@@ -1366,12 +1134,12 @@ void fwd_kernel_bf16(FwdParams p) {
     st_t[1] = __builtin_readcyclecounter() - tprev;
 #endif
     wait_tile_loads<8>();  // K(0)
-    read_k_half(so, lds_k, 0, ka[0]);
-    read_k_half(so, lds_k, 1, ka[1]);
+    read_straight_half(so, lds_k, 0, ka[0]);
+    read_straight_half(so, lds_k, 1, ka[1]);
     wait_lds_reads();
     half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
     wait_tile_loads<8>();  // V(0).t0
-    read_v_half(to, lds_v, 0, va[0]);
+    read_transposed_half(to, lds_v, 0, va[0]);
     unit_scores(ka[0], qb[0], sA);
     BB_STAMP(0);
 
@@ -1412,8 +1180,8 @@ void fwd_kernel_bf16(FwdParams p) {
         // and this item's output is written under that flight.
         wait_tile_loads<0>();
         so.read(lds_k, qb);
-        read_k_half(so, lds_v, 0, ka[0]);
-        read_k_half(so, lds_v, 1, ka[1]);
+        read_straight_half(so, lds_v, 0, ka[0]);
+        read_straight_half(so, lds_v, 1, ka[1]);
         wait_lds_reads();
         const char* v0 = uniform_ptr(ItemTiles(p, nxt).vtile(0));
         half_load_async(v0, cx.lds_v_a, 0, cx.voff);
@@ -1448,7 +1216,7 @@ void fwd_kernel_bf16(FwdParams p) {
       cnt = __builtin_amdgcn_readfirstlane(cur.cnt);
       half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
       wait_tile_loads<8>();
-      read_v_half(to, lds_v, 0, va[0]);
+      read_transposed_half(to, lds_v, 0, va[0]);
       unit_scores(ka[0], qb[0], sA);
       i = 0;
       BB_STAMP(6);

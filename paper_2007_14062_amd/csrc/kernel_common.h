@@ -13,10 +13,8 @@ constexpr int kBlk = 64;      // block length b (App. E.1: 64 for every ITC mode
 constexpr int kDim = 64;      // head width d
 constexpr int kChunk = 8;     // list entries per slice of a global row / global key column
 constexpr int kSparseChunk = 16;  // most key blocks per work item of a non-global row (the ITC base pattern has g+w+r = 8)
-constexpr int kChunkGlobal = 8;  // key blocks per work item of a global row (equal to kChunk; 16 measured the same backward time)
+constexpr int kChunkGlobal = 8;  // key blocks per work item of a global row
 constexpr int kChunkMax = kChunkGlobal > kSparseChunk ? kChunkGlobal : kSparseChunk;
-constexpr int kWaves = 2;     // one wave owns 32 query rows of the 64-row block
-constexpr int kThreads = 64 * kWaves;
 constexpr int kXcd = 8;       // accelerator dies; workgroup id modulo 8 selects the die
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -71,14 +69,6 @@ __device__ __forceinline__ int tile_swizzle(int row) { return (((row >> 1) & 1) 
 // Byte offset of 16-byte chunk c of row `row` in such a tile.
 __device__ __forceinline__ int tile_off_bf16(int row, int chunk) {
   return row * 128 + ((chunk ^ tile_swizzle(row)) << 4);
-}
-
-// Per-lane byte offset inside a tile for the asynchronous tile loads: instruction ii of
-// wave wv fills rows 16*ii + 8*wv .. +8 linearly, lane l landing on row l/8, chunk
-// position l%8, so it must fetch the chunk that the swizzle stores there.
-__device__ __forceinline__ unsigned tile_load_lane_offset(int wv, int lane) {
-  const int row = wv * 8 + (lane >> 3);  // + 16*ii: bits 1..3 of the row do not depend on ii
-  return row * 128 + (((lane & 7) ^ tile_swizzle(row)) << 4);
 }
 
 // ds_read_b64_tr_b16: inside each group of 16 lanes, lane i passes the address of
@@ -161,18 +151,22 @@ struct DieItems {
     run = (total + kXcd - 1) / kXcd;
   }
   unsigned grid() const { return kXcd * (rounds * per_bh + run); }
-  // workgroup -> (slice, item); false: none
-  __device__ __forceinline__ bool decode(unsigned wg, int* bh, int* item) const {
+  // workgroup -> (slice, item); false: none.  interleaved: the items of up to `interleaved` of the die's
+  // slices alternate (for items that come longest first), instead of slice after slice.
+  __device__ __forceinline__ bool decode(unsigned wg, int* bh, int* item, unsigned interleaved = 1) const {
     const unsigned xcd = wg % kXcd, u = wg / kXcd;
     if (u < rounds * per_bh) {
-      *bh = static_cast<int>(u / per_bh * kXcd + xcd);
-      *item = static_cast<int>(u % per_bh);
+      const unsigned groups = (rounds + interleaved - 1) / interleaved, size = (rounds + groups - 1) / groups;
+      const unsigned base = u / per_bh / size * size, n = rounds - base < size ? rounds - base : size;
+      const unsigned v = u - base * per_bh;
+      *bh = static_cast<int>((base + v % n) * kXcd + xcd);
+      *item = static_cast<int>(v / n);
       return true;
     }
     const unsigned t = xcd * run + (u - rounds * per_bh);
     *bh = static_cast<int>(rounds * kXcd + t / per_bh);
     *item = static_cast<int>(t % per_bh);
-    return t < total;
+    return u < rounds * per_bh + run && t < total;
   }
 };
 

@@ -6,34 +6,72 @@
 
 namespace bb {
 
+constexpr int kTile = kBlk * kDim * 2;  // one 64x64 bf16 tile: 8 KB
+constexpr int kHalfTile = kTile / 2;    // 32 rows
+
 // s_waitcnt immediate that waits for all but `n` vector-memory loads (gfx9 encoding:
 // vmcnt in bits 3:0 and 15:14, other counters left at their maxima).
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 constexpr int kLgkmcnt0 = 15 | (3 << 14) | (7 << 4);  // wait for all LDS reads, nothing else
 
-// Enqueue this wave's half of a 64x64 bf16 tile: global -> LDS, 16 bytes per lane,
-// four instructions per wave.  Instruction ii of wave wv fills LDS rows
-// 8*(2*ii+wv) .. +8 linearly (the hardware places lane l at M0 + 16*l), so the XOR
-// swizzle is applied on the global side: the lane that lands on chunk position p of
-// row r fetches chunk p ^ tile_swizzle(r).  `voff` is that per-lane byte offset inside
-// the tile (tile_load_lane_offset, fixed for the kernel), `gtile` the wave-uniform tile
-// address, `lds` the LDS byte address of this wave's first 1 KB slot.
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const uintptr_t v = reinterpret_cast<uintptr_t>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v));
+  const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));
+  return reinterpret_cast<const char*>((static_cast<uintptr_t>(hi) << 32) | lo);
+}
+
+// Per-lane byte offsets of half_load_async.
+__device__ __forceinline__ void half_load_offsets(int lane, unsigned (&voff)[2]) {
+#pragma unroll
+  for (int par = 0; par < 2; ++par)
+    voff[par] = (lane >> 3) * 128 + (((lane & 7) ^ tile_swizzle(par * 8 + (lane >> 3))) << 4);
+}
+
+// Half of a 64x64 bf16 tile (rows 32*hh .. +32), global -> LDS, by one wave: four
+// instructions of 64 lanes x 16 bytes.  Instruction ii fills LDS rows 8*ii .. 8*ii+7 of
+// the half linearly (lane l lands on row l/8, chunk position l%8) and fetches, for that
+// place, the chunk the swizzle stores there.  The swizzle depends on row bits 1..3, i.e. on
+// l/8 and on the parity of ii: voff[0] / voff[1] are the per-lane byte offsets for even /
+// odd ii.  The instruction's immediate offset moves the global and the LDS address alike,
+// so the four instructions share one base pair (M0, scalar address).
 // Written as inline asm so that the compiler's wait-count bookkeeping does not see
 // these loads: it would otherwise drain them before every LDS read.  The waits
 // are placed by hand (loads return in order, so vmcnt(N) is exact).
-__device__ __forceinline__ void tile_load_async(const char* gtile, unsigned lds, unsigned voff) {
-  // the instruction offset moves the global and the LDS address alike: two base pairs per tile
-#pragma unroll
-  for (int hh = 0; hh < 2; ++hh)
-    asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 4\n\t"  // wait states the compiler cannot see to from outside: M0 written by a scalar instruction (1) and an
+__device__ __forceinline__ void half_load_async(const char* gtile_, unsigned lds, int hh,
+                                                const unsigned (&voff)[2]) {
+  const char* gtile = uniform_ptr(gtile_);  // wave uniform by construction: it has to sit in scalar registers
+  asm volatile(
+      "s_mov_b32 m0, %3\n\t"
+      "s_nop 4\n\t"  // wait states the compiler cannot see to from outside: M0 written by a scalar instruction (1) and an
                        // address register pair that a vector instruction (v_readlane) may just have written (5)
-        "global_load_lds_dwordx4 %0, %1\n\t"
-        "global_load_lds_dwordx4 %0, %1 offset:2048"
-        :
-        : "v"(voff), "s"(gtile + hh * 4096), "s"(lds + hh * 4096)
-        : "memory");  // M0 is written here; nothing else in this kernel reads M0
+      "global_load_lds_dwordx4 %0, %2\n\t"
+      "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+      "global_load_lds_dwordx4 %0, %2 offset:2048\n\t"
+      "global_load_lds_dwordx4 %1, %2 offset:3072"
+      :
+      : "v"(voff[0]), "v"(voff[1]), "s"(gtile + hh * kHalfTile), "s"(lds + hh * kHalfTile)
+      : "memory");  // M0 is written here; it is a reserved register that the compiler only sets right before
+                    // instructions of its own that read it, and this kernel has none
+}
+
+__device__ __forceinline__ void tile_load_async_wave(const char* gtile_, unsigned lds, const unsigned (&voff)[2]) {
+  const char* gtile = uniform_ptr(gtile_);  // wave-uniform by construction: keep it in scalar registers
+  half_load_async(gtile, lds, 0, voff);
+  half_load_async(gtile, lds, 1, voff);
+}
+
+// Waits and compiler fences.  The tile loads are invisible to the compiler's wait-count
+// bookkeeping (inline asm), so every wait for them is written out; loads return in order,
+// which makes "all but the N youngest" exact.
+template <int N>
+__device__ __forceinline__ void wait_tile_loads() {
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(N));
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lds_reads() {
+  __builtin_amdgcn_s_waitcnt(kLgkmcnt0);
+  asm volatile("" ::: "memory");
 }
 
 __device__ __forceinline__ unsigned lds_addr(const void* p) {
@@ -100,21 +138,42 @@ struct TransposedOffsets {
     u.h2.b = hi;
     return u.v;
   }
-  __device__ __forceinline__ void read(const char* tile, bf16x8 (&f)[2][4]) const {
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-      for (int sg = 0; sg < 4; ++sg) f[dt][sg] = read_one(tile, dt, sg);
-  }
 };
 
-// Accumulator tile pair [2][16] (rows 64 x this lane's column) -> the four bf16 B-operand
-// fragments of the next MFMA (slot order as in TransposedOffsets).
-__device__ __forceinline__ void pack_acc_bf16(const f32x16 (&a)[2], bf16x8 (&b)[4]) {
+// One half (32 rows) of either kind, by one wave.
+__device__ __forceinline__ void read_straight_half(const StraightOffsets& so, const char* tile, int t, bf16x8 (&f)[4]) {
 #pragma unroll
-  for (int sg = 0; sg < 4; ++sg)
+  for (int ks = 0; ks < 4; ++ks) f[ks] = *reinterpret_cast<const bf16x8*>(tile + so.off[ks] + t * kHalfTile);
+}
+
+__device__ __forceinline__ void read_transposed_half(const TransposedOffsets& to, const char* tile, int t,
+                                            bf16x8 (&f)[2][2]) {
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) b[sg][kk] = static_cast<__bf16>(a[sg >> 1][(sg & 1) * 8 + kk]);
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int sgl = 0; sgl < 2; ++sgl) f[dt][sgl] = to.read_one(tile, dt, 2 * t + sgl);
+}
+
+// Padded keys of a unit (32 keys x 32 queries, a lane per query) leave its packed probabilities, or dS
+// values, here: after the conversion and before a product sees them (they may be anything, also not a
+// number).  bits: validity of the 32 keys of the unit, in key order.  Element kk of operand sgl belongs to key
+// 16 sgl + 8 (kk / 4) + 4 hf + kk % 4 (acc_row).  Three instructions per packed pair on the vector port --
+// only block pairs with padded keys inside pay them: the others take one scalar branch per unit.
+__device__ __forceinline__ void drop_padded_keys(uint32_t bits, int hf, bf16x8 (&pb)[2]) {
+  const int b = static_cast<int>(bits >> (4 * hf));
+#pragma unroll
+  for (int sgl = 0; sgl < 2; ++sgl) {
+    union { bf16x8 v; uint32_t d[4]; } u;
+    u.v = pb[sgl];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int key = acc_row(sgl * 8 + 2 * m, 0);
+      const uint32_t even = static_cast<uint32_t>(__builtin_amdgcn_sbfe(b, key, 1));      // 0 or ~0
+      const uint32_t odd = static_cast<uint32_t>(__builtin_amdgcn_sbfe(b, key + 1, 1));
+      u.d[m] &= (even & 0xffffu) | (odd & 0xffff0000u);
+    }
+    pb[sgl] = u.v;
+  }
 }
 
 }  // namespace bb

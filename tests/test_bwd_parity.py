@@ -321,3 +321,21 @@ def test_fp32_slices(B, H, nb, g, w, r):
         km[0, n - 70:] = 0
         km[B - 1, 33:64] = 0
     check_full_f32(t, ridx, 64, g, w, 0.125, key_mask=km, tag=f"fp32 slices B{B} H{H} nb{nb}")
+
+
+@pytest.mark.parametrize("nb,g,w,r", [(1, 0, 1, 0), (2, 1, 1, 0), (3, 0, 3, 0), (7, 0, 1, 1), (65, 2, 3, 3), (66, 1, 5, 17)])
+def test_list_lengths(nb, g, w, r):
+    """Key lists of 1, 2, 3 ... blocks and across a 16-block slice, inverse lists of 0 .. nb blocks: every row
+    of one head names the same blocks, in another head no row names any."""
+    B, H, n = 1, 3, nb * 64
+    t = inp.make_tensors(B, H, n, 64, 60 + nb, "bf16", with_dO=True)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 5)
+    if r:
+        ridx[1] = np.arange(r, dtype=np.int32) + nb // 2   # (window and global ones among them do not count)
+        ridx[1, nb // 3] = nb // 2                          # r equal entries
+        ridx[2] = -1
+    km = None
+    if nb > 3:
+        km = np.ones((B, n), dtype=np.uint8)
+        km[0, n - 70:] = 0
+    check_full(t, ridx, 64, g, w, 0.125, key_mask=km, tag=f"bwd lists nb{nb} g{g} w{w} r{r}")
