@@ -155,8 +155,7 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
     bb::Bf16Geom& q = p.geo;
     {
       // a wave takes up to 16 key blocks of a non-global row; wider patterns are sliced
-      int sparse_ub = g + w + r;
-      if (sparse_ub > p.nb) sparse_ub = p.nb;
+      const int sparse_ub = bb::longest_sparse_list(p.nb, g, w, r);
       q.cs = (sparse_ub + bb::kGlobalWaveLen - 1) / bb::kGlobalWaveLen;
       if (q.cs < 1) q.cs = 1;
     }
@@ -167,7 +166,7 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
     // workgroup of the launch is resident at once (two per CU, 32 CUs per die) the longest
     // workgroup sets the run time, so the global rows are then cut twice as fine, into
     // workgroups whose partial results the merge kernel combines -- if that finer grid still fits.
-    q.gw_len = bb::kGlobalWaveLen;
+    q.gw_len = p.nb < 4 * bb::kGlobalWaveLen ? (p.nb + 3) / 4 : bb::kGlobalWaveLen;
     q.ng = (p.nb + 4 * q.gw_len - 1) / (4 * q.gw_len);
     {
       const int slots_per_die = 64;
@@ -179,6 +178,22 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
       }
     }
     q.g_wgs = g * q.ng;
+    // Small launches, about a workgroup per CU: all rows that way, the key list of each dealt out to four
+    // waves.  12 heads, n = 512 / 1024 / 1536: 12.2 -> 7.2, 12.4 -> 8.7, 12.5 -> 11.9 us; past that CUs have
+    // two such workgroups and single waves with whole rows win (n = 2048, 384 rows: 12.7 against 17.5).
+    q.by_row = 0;
+    q.sw_len = 0;
+    {
+      const int sparse_ub = bb::longest_sparse_list(p.nb, g, w, r);
+      const long long rows = static_cast<long long>(p.BH) * (q.g_wgs + p.nb - g);
+      if (rows <= 288 && sparse_ub <= 4 * bb::kGlobalWaveLen) {
+        q.by_row = 1;
+        q.sw_len = sparse_ub > 4 ? (sparse_ub + 3) / 4 : 1;
+        q.g_wgs += p.nb - g;
+        q.cs = 1;
+        p.dyn = 0;  // (nothing is claimed)
+      }
+    }
     {
       // Persistent workgroups: as many as stay resident beside the global-row workgroups (a die
       // holds 64 workgroups of this kernel: two per CU), at most one wave per item.

@@ -320,14 +320,28 @@ struct Sched {
   int xcd;
   unsigned wg;        // workgroup number inside the die
   unsigned n_gpart;   // global-row workgroups of the die
-  bool global_wg;
+  bool by_row;        // a constant of the kernel
+  bool global_wg;     // a row by the whole workgroup (global rows; by_row: every row)
+  int row_bh, row_idx;  // which one
+  bool row_ok;
   int n_items_die;    // non-global items of the die
   int wave_stride;    // persistent waves of the die
-  __device__ __forceinline__ explicit Sched(const FwdParams& p) {
+  __device__ __forceinline__ explicit Sched(const FwdParams& p, bool by_row) {
     xcd = blockIdx.x % kXcd;
     wg = blockIdx.x / kXcd;
     n_gpart = static_cast<unsigned>(p.geo.bh_rounds) * p.geo.g_wgs;
-    global_wg = wg < n_gpart;
+    this->by_row = by_row;
+    if (by_row) {
+      global_wg = true;
+      row_ok = DieItems(p.BH, p.geo.g_wgs).decode(blockIdx.x, &row_bh, &row_idx);
+    } else {
+      global_wg = wg < n_gpart;
+      if (global_wg) {  // (two divisions that the other waves' first loads need not wait for)
+        row_bh = static_cast<int>(wg / p.geo.g_wgs * kXcd + xcd);
+        row_idx = static_cast<int>(wg % p.geo.g_wgs);
+        row_ok = row_bh < p.BH;
+      }
+    }
     const int n_bh_die = xcd < p.BH ? (p.BH - xcd + kXcd - 1) / kXcd : 0;
     n_items_die = n_bh_die * p.geo.n_sitems;
     wave_stride = p.geo.p_wgs * kFwdWaves;
@@ -377,9 +391,19 @@ __device__ __forceinline__ void item_coords(const FwdParams& p, const WaveCtx& w
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   const Bf16Geom& geo = p.geo;
   if (sc.global_wg) {
-    it.bh = (sc.wg / geo.g_wgs) * kXcd + sc.xcd;
-    const int gidx = sc.wg % geo.g_wgs;
-    const int row = gidx / geo.ng, u = gidx % geo.ng;
+    it.bh = sc.row_bh;
+    const int n_glob = pat.g * geo.ng;
+    if (sc.by_row && sc.row_idx >= n_glob) {
+      row_global = false;
+      it.j = pat.sparse_block(sc.row_idx - n_glob);
+      it.chunk = 0;
+      it.nchunks = 1;
+      it.slot = 0;
+      list_lo = w.wv * geo.sw_len;
+      list_len = geo.sw_len;
+      return;
+    }
+    const int row = sc.row_idx / geo.ng, u = sc.row_idx % geo.ng;
     row_global = true;
     it.j = pat.global_block(row);
     it.chunk = u;
@@ -788,7 +812,7 @@ __device__ __forceinline__ const void* kernel_kernargs() {
 template <int kMode>
 __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
   const WaveCtx w(p.c);
-  Sched sc(p);
+  Sched sc(p, false);
   sc.global_wg = false;  // (a wave of a global-row workgroup that went on to claim other items)
   const StraightOffsets so(w.lane);
   const TransposedOffsets to(w.lane);
@@ -830,15 +854,14 @@ __device__ __attribute__((noinline)) void redo_items(const void* kernargs, int r
   for (int u = 0; u < n_redo; ++u) item_by_recurrence<kMode>(p, __builtin_amdgcn_readlane(redo, u));
 }
 
-// One global query block by a whole workgroup: 16 key blocks per wave, the four waves' (m, l, O~)
-// merged in LDS.  Inlined into the kernel, as the branch taken by the die's first workgroups: a
+// One query block by a whole workgroup: its key list dealt out to the four waves (up to 16 key blocks
+// each), their (m, l, O~) merged in LDS.  Inlined into the kernel, as the branch taken by the die's first workgroups: a
 // real call would start by saving a hundred callee-saved vector registers to scratch memory
 // (11 MB of HBM writes per launch at the BERT-base size, measured) for a caller that has nothing
 // in them.
 template <int kMode>
-__device__ __forceinline__ void global_row_workgroup(const FwdParams& p) {
+__device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const Sched& sc) {
   const WaveCtx w(p.c);
-  const Sched sc(p);
   const StraightOffsets so(w.lane);
   const TransposedOffsets to(w.lane);
   const int lane = w.lane, wv = w.wv, hf = w.hf, col = w.col;
@@ -961,10 +984,19 @@ __global__ void zero_counters_kernel(int* counters) {
   if (threadIdx.x < kXcd) counters[threadIdx.x * kCounterStride] = 0;
 }
 
+// Small launches: a workgroup per row (a kernel of its own, so that the other one keeps its registers
+// and schedule).
+template <int kMode>
+__global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void fwd_rows_bf16(FwdParams p) {
+  const Sched sc(p, true);
+  if (sc.row_ok) global_row_workgroup<kMode>(p, sc);
+}
+
 template <int kMode>
 __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void fwd_kernel_bf16(FwdParams p) {
-  Sched sc(p);
+  Sched sc(p, false);
   // dyn: after its first piece of work a wave claims items from its die's counter (zeroed before
   // the launch) instead of taking every wave_stride-th one: with a padding mask items differ in
   // length and some are not computed at all.  The waves of a global-row workgroup then join in
@@ -972,7 +1004,7 @@ void fwd_kernel_bf16(FwdParams p) {
   const bool dyn = kMode == kOptions && p.dyn != 0;
   const bool was_global = sc.global_wg;
   if (sc.global_wg) {
-    if ((sc.wg / p.geo.g_wgs) * kXcd + sc.xcd < static_cast<unsigned>(p.BH)) global_row_workgroup<kMode>(p);
+    if (sc.row_ok) global_row_workgroup<kMode>(p, sc);
     if (!dyn) return;
     __syncthreads();  // the merge has read the other waves' LDS regions; from here on each wave's is its own
     sc.global_wg = false;
@@ -1241,18 +1273,17 @@ void fwd_kernel_bf16(FwdParams p) {
 }
 
 int launch_fwd_bf16_main(const FwdParams& p, hipStream_t stream) {
-  const unsigned grid = static_cast<unsigned>(kXcd) * (p.geo.bh_rounds * p.geo.g_wgs + p.geo.p_wgs);
+  const unsigned grid = p.geo.by_row ? DieItems(p.BH, p.geo.g_wgs).grid()
+                                     : static_cast<unsigned>(kXcd) * (p.geo.bh_rounds * p.geo.g_wgs + p.geo.p_wgs);
   if (grid == 0) return BB_OK;
   if (p.dyn) {
     hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, stream, p.counters);
     if (hipGetLastError() != hipSuccess) return BB_ERR_LAUNCH;
   }
-  if (p.drop.thr != 0 || p.skip_q || p.dyn)
-    hipLaunchKernelGGL(fwd_kernel_bf16<kOptions>, dim3(grid), dim3(kFwdThreads), 0, stream, p);
-  else if (p.kmask)
-    hipLaunchKernelGGL(fwd_kernel_bf16<kMasked>, dim3(grid), dim3(kFwdThreads), 0, stream, p);
-  else
-    hipLaunchKernelGGL(fwd_kernel_bf16<kPlain>, dim3(grid), dim3(kFwdThreads), 0, stream, p);
+  const bool options = p.drop.thr != 0 || p.skip_q || p.dyn;
+  auto kernel = p.geo.by_row ? (options ? fwd_rows_bf16<kOptions> : p.kmask ? fwd_rows_bf16<kMasked> : fwd_rows_bf16<kPlain>)
+                             : (options ? fwd_kernel_bf16<kOptions> : p.kmask ? fwd_kernel_bf16<kMasked> : fwd_kernel_bf16<kPlain>);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kFwdThreads), 0, stream, p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     fprintf(stderr, "bigbird: launch of fwd_kernel_bf16 failed: %s\n", hipGetErrorString(e));

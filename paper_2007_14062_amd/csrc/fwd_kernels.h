@@ -16,14 +16,17 @@ namespace bb {
 constexpr int kGlobalWaveLen = 16;  // most key blocks a wave of a global workgroup takes
 constexpr int kCounterStride = 32;  // ints between the item counters of two dies (a 128-byte line each)
 struct Bf16Geom {
-  int gw_len;    // key blocks per wave of a global workgroup: 16, or 8 when the whole grid fits
-                 // the chip at once (then the global rows alone would set the run time)
+  int by_row;    // small launches: every row is done the way global rows are, a workgroup per row; no
+                 // persistent workgroups
+  int sw_len;    // by_row: key blocks per wave of a non-global row
+  int gw_len;    // key blocks per wave of a global workgroup: a quarter of the row, at most 16, or 8 when the
+                 // whole grid fits the chip at once (then the global rows alone would set the run time)
   int ng;        // workgroups per global row: ceil(nb / (4 * gw_len))
   int cs;        // slices per non-global row: ceil(min(g + w + r, nb) / 16)
   int n_sitems;  // (nb - g) * cs
   int s_wgs;     // ceil(n_sitems / 4): workgroups the non-global items of one (batch, head) would fill
   int p_wgs;     // persistent workgroups per die: their waves share out the die's non-global items
-  int g_wgs;     // global workgroups per (batch, head): g * ng
+  int g_wgs;     // row workgroups per (batch, head): g * ng of global rows, then, by_row, the other rows
   int bh_rounds; // ceil(B*H / 8)
 };
 

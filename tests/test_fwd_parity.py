@@ -177,6 +177,24 @@ def test_blocks_with_padded_keys_inside(tail, mode, g, r):
     assert err_o <= TOL["bf16"] and err_l <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("B,H,nb,g,w,r", [
+    (1, 1, 1, 1, 1, 0), (1, 1, 3, 0, 1, 0), (1, 3, 9, 2, 3, 3), (1, 16, 18, 2, 3, 3), (1, 17, 17, 2, 3, 3),
+    (1, 2, 66, 1, 3, 60), (1, 2, 70, 1, 3, 61), (1, 1, 130, 2, 3, 12)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_rows_by_workgroup(B, H, nb, g, w, r, masked):
+    """Small launches (a workgroup per row) and the first ones past the limit of 288 rows; key lists of 1, 2, 3,
+    9, 16, 64 and 65 blocks dealt out to four waves; global rows of one and of several workgroups; a mask
+    that leaves waves without a block."""
+    n = nb * 64
+    t = inp.make_tensors(B, H, n, 64, 70 + nb, "bf16")
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 8)
+    km = None
+    if masked:
+        km = np.zeros((B, n), dtype=np.uint8)
+        km[:, n // 2 - 5:n // 2 + 60] = 1
+    check_full(t, ridx, "bf16", 64, g, w, 0.125, key_mask=km, tag=f"rows B{B} H{H} nb{nb} r{r} mask{masked}")
+
+
 def test_zero_queries_closed_form_and_pattern_readback():
     """Q = 0 => O_i = mean of V over N(i), LSE_i = ln|N(i)|; V one-hot per key block spells out
     the neighbour set the kernel used, which must be the table's."""
