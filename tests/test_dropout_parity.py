@@ -158,3 +158,37 @@ def test_training_shape_sampled_rows_and_gradient_properties():
     errs = [np.abs(to_host(x[bi, h]) - r).max() for x, r in zip(grads, ref)]
     print(f"dropout cfg4: forward rows {worst:.3e}; slice ({bi},{h}) gradients {errs}")
     assert max(errs) <= TOL["bf16"], errs
+
+
+@pytest.mark.parametrize("n,skip,spread", [
+    (1024, False, 1.0),   # every row by a workgroup
+    (1664, False, 1.0),   # items in waves' streams (12 slices, 26 blocks)
+    (1664, True, 1.0),
+    (1664, False, 40.0),  # row sums that leave the range of the fixed reference: the recurrence
+])
+def test_pipelined_forward_with_padding(n, skip, spread):
+    """Forward under dropout on masked batches: a block cut inside, holes, a single valid key, against the
+    oracle; rows of every query block."""
+    torch = torch_mod()
+    B, H = 2, 6
+    t = inp.make_tensors(B, H, n, 64, 307, "bf16")
+    if spread != 1.0:  # exact in bf16: a power of two
+        f = 2.0 ** round(np.log2(spread))
+        t["Q"] = t["Q"] * np.float32(f)
+    ridx_h = bb.bigbird_make_rand_idx(H, n, 64, 2, 3, 3, 13)
+    km = inp.lengths_to_key_mask(np.array([n - 100, 333]), n)
+    km[0, 640:760] = 0
+    km[1, 333:] = 0
+    km[1, 900] = 1
+    Q, K, V = (torch.from_numpy(np.ascontiguousarray(t[x], dtype=np.float32)).to("cuda:0").to(torch.bfloat16) for x in ("Q", "K", "V"))
+    O, LSE = bb.bigbird_attn_fwd_dropout(Q, K, V, torch.from_numpy(ridx_h).to("cuda:0"), g=2, w=3, scale=0.125,
+                                         p_drop=0.1, seed=77, key_padding_mask=torch.from_numpy(km).to("cuda:0"),
+                                         global_mode=bb.BB_SKIP_PADDED_QUERY_BLOCKS if skip else 0)
+    torch.cuda.synchronize()
+    Oo, Lo = oracle.attn_fwd_dropout(t["Q"], t["K"], t["V"], ridx_h, 64, 2, 3, 0.125, 0.1, 77, key_mask=km,
+                                     skip_padded_query_blocks=skip)
+    fin = np.isfinite(Lo)
+    assert (to_host(LSE)[~fin] == -np.inf).all() and (to_host(O)[~fin] == 0).all()
+    # (one key can hold all of a row: its probability and the output are rounded to 2^-9 of at most 5)
+    assert np.abs(to_host(O) - Oo).max() <= TOL["bf16"]
+    assert np.abs(to_host(LSE)[fin] - Lo[fin]).max() <= (1e-4 if spread == 1.0 else TOL["bf16"])
