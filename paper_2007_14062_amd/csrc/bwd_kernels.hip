@@ -462,7 +462,8 @@ void bwd_dq_kernel(BwdParams p) {
 // Items run longest list first (key_order of the workspace): the lists of the non-global key blocks hold 5
 // to 16 query blocks at the base pattern, and in the order of the sequence the launch ended on whichever
 // came last.  24 slices, n = 4096: 50 -> 42 us; 16 of n = 16384: 124 -> 104; 48 of n = 3072 with padding and
-// dropout: 64 -> 60.
+// dropout: 64 -> 60; there
+// two neighbouring keys share the words of the keep mask (one per 2 x 1 elements): 63 -> 59.
 //
 // kDrop: attention dropout (see bwd_dq_kernel): dV takes the kept probabilities (rescaled at the
 // end), dP is masked and rescaled before D is subtracted.  The row keys of the mask for the queries of a
@@ -607,8 +608,24 @@ void bwd_dkv_kernel(BwdParams p) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) qt[a][b][e] = static_cast<__bf16>(0.f);
     }
-    const uint32_t my_pair = static_cast<uint32_t>(k * kBlk + wv * 32 + col) >> 1;  // (dropout) this lane's key
-    const uint32_t my_shift = (col & 1) ? 16u : 0u;
+    // (dropout) this lane's key: its pair's share of the words' argument, its half of a word
+    const uint32_t my_pair = (static_cast<uint32_t>(k * kBlk + wv * 32 + col) >> 1) * kDropPairStep;
+    const int odd = col & 1, my_shift = odd * 16;
+    const uint32_t drop_thr = kDrop ? drop_pair_threshold(p.drop) : 0u;
+    // keep bits of this lane's key, bit r: the query of accumulator register r.  A word of the mask serves two
+    // keys, neighbouring lanes: the even one makes those of registers 0 .. 7, the odd one those of 8 .. 15
+    auto keep_bits = [&](const uint32_t* row_keys) {
+      uint32_t both = 0;  // bit i: even key, 16 + i: odd key
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const u32x4 k4 = *reinterpret_cast<const u32x4*>(row_keys + odd * 16 + acc_row(u * 4, hf));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) both |= drop_keep_pair(drop_mix(k4[e] ^ my_pair), drop_thr) & (0x00010001u << (u * 4 + e));
+      }
+      const uint32_t other = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(both), 0xB1, 0xf, 0xf, true));  // quad_perm [1, 0, 3, 2]
+      const uint32_t mine = (both >> my_shift) & 0xffu, theirs = (other >> my_shift) & 0xffu;
+      return odd ? theirs | mine << 8 : mine | theirs << 8;
+    };
 
     int j_next = entry(3);
     auto half = [&](int hh, auto P) {
@@ -638,17 +655,16 @@ void bwd_dkv_kernel(BwdParams p) {
         // and dP becomes M / (1 - p) o dP - D  (the staged vector holds -D)
         __builtin_amdgcn_sched_barrier(0);
         const float rs = p.drop.rs;
+        const int keep = static_cast<int>(keep_bits(lds_rk[here] + row));
         f32x16 sk;
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-          const u32x4 k4 = *reinterpret_cast<const u32x4*>(lds_rk[here] + row + acc_row(r4 * 4, hf));
           const f32x4 d4 = *reinterpret_cast<const f32x4*>(lds_d[here] + row + acc_row(r4 * 4, hf));
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const uint32_t wd = drop_word(k4[e], my_pair);
-            const bool keep = ((wd >> my_shift) & 0x7fffu) >= p.drop.thr;
-            sk[r4 * 4 + e] = keep ? s[r4 * 4 + e] : 0.f;
-            dp[r4 * 4 + e] = keep ? __builtin_fmaf(dp[r4 * 4 + e], rs, d4[e]) : d4[e];
+            const int m = __builtin_amdgcn_sbfe(keep, r4 * 4 + e, 1);  // 0 or ~0
+            sk[r4 * 4 + e] = __int_as_float(__float_as_int(s[r4 * 4 + e]) & m);
+            dp[r4 * 4 + e] = __builtin_fmaf(__int_as_float(__float_as_int(dp[r4 * 4 + e]) & m), rs, d4[e]);
           }
         }
         pack(sk, pb);
