@@ -370,6 +370,11 @@ int attn_bwd_impl(const void* Q, const void* K, const void* V, const void* O,
   const int fine = dtype == BB_F32 ? bb::fine_slice_f32(p.BH, p.nb, g, w, r) : 0;
   p.split = bb::make_row_split(p.BH, p.nb, g, w, r, fine);
   p.kv = bb::make_key_split(p.nb, g, w, r, fine);
+  p.by_row = dtype == BB_BF16 && bb::bwd_by_row(p.BH, p.nb, g, w, r);
+  if (p.by_row) {  // (never more slots than the workspace is sized for: longer slices)
+    p.split = bb::make_row_split_by_row(p.BH, p.nb, g, w, r);
+    p.kv = bb::make_key_split_by_row(p.nb, g);
+  }
   if (dtype == BB_F32) return bb::launch_bwd_f32(p, static_cast<hipStream_t>(hip_stream));
   return bb::launch_bwd_bf16(p, static_cast<hipStream_t>(hip_stream));
 }

@@ -30,6 +30,46 @@ inline KeySplit make_key_split(int nb, int g, int w, int r, int len = 0) {
   return s;
 }
 
+// Small bf16 launches: a workgroup per query block (dQ) and per key block (dK/dV) that deals out the block's
+// list to four waves or pairs of waves.  Otherwise most of the chip is idle behind lists of eight pairs in
+// series.
+constexpr int kRowWaves = 4;
+// Entries per wave (pair of waves) of a global block's list: all of it in one workgroup up to 8 each, which
+// saves the reduction launch; longer lists in several workgroups of 4 each, so that they end with the others (2 heads,
+// n = 4096: 25 us, with 16 each 43).
+inline int by_row_share(int nb) {
+  const int quarter = (nb + kRowWaves - 1) / kRowWaves;
+  return quarter <= 8 ? quarter : 4;
+}
+// dQ items then; a non-global row whole.
+inline RowSplit make_row_split_by_row(int BH, int nb, int g, int w, int r) {
+  RowSplit s = make_row_split(BH, nb, g, w, r);
+  const int sparse = (longest_sparse_list(nb, g, w, r) + kRowWaves - 1) / kRowWaves;
+  s.lg = kRowWaves * by_row_share(nb);
+  s.ls = kRowWaves * (sparse > 1 ? sparse : 1);
+  s.cg = (nb + s.lg - 1) / s.lg;
+  s.cs = 1;
+  s.items_per_bh = g * s.cg + nb - g;
+  s.slots_per_bh = s.cg > 1 ? g * s.cg : 0;
+  return s;
+}
+// dK/dV items.
+inline KeySplit make_key_split_by_row(int nb, int g) {
+  KeySplit s;
+  s.cg = (nb + kRowWaves * by_row_share(nb) - 1) / (kRowWaves * by_row_share(nb));
+  s.cs = 1;
+  s.items_per_bh = g * s.cg + nb - g;
+  s.slots_per_bh = s.cg > 1 ? g * s.cg : 0;
+  return s;
+}
+// Where that wins: up to a dK/dV workgroup per compute unit.  12 heads, n = 512 / 1088 / 1344, whole backward:
+// 25.5 -> 18.1, 32.5 -> 24.7, 32.9 -> 27.5 us; 2 heads, n = 4096: 32.0 -> 24.9.  Past that some units have two, one
+// after the other: 4 slices of n = 4096 (280 workgroups) 34.0 -> 34.2, one of n = 16384 (286) 37.4 -> 39.7.
+inline bool bwd_by_row(int BH, int nb, int g, int w, int r) {
+  return static_cast<long long>(BH) * make_key_split_by_row(nb, g).items_per_bh <= 256 &&
+         longest_sparse_list(nb, g, w, r) <= kRowWaves * kChunkMax;
+}
+
 constexpr int kSetWords = kMaxBwdBlocks / 32;
 
 struct BwdParams {
@@ -56,6 +96,7 @@ struct BwdParams {
   int B, H, BH, n, nb, g, w, r, global_mode;
   float c;      // scale * log2(e)
   float scale;
+  int by_row;      // bf16: a workgroup per block (bwd_by_row)
   RowSplit split;  // query-row decomposition (dQ kernel), as in the forward
   KeySplit kv;     // key-block decomposition (dK/dV kernel)
   Dropout drop;    // attention dropout of the forward these gradients belong to (thr == 0: none)

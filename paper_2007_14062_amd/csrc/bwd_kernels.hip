@@ -206,22 +206,29 @@ __device__ __forceinline__ void pin_b() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <bool kDrop>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+// kWaves: waves of a workgroup.  Large launches: 1, every wave an item of its own.  Small ones: 4 (p.by_row),
+// which deal out the list of one item among themselves and add their shares of dQ in LDS.
+template <bool kDrop, int kWaves>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_dq_kernel(BwdParams p) {
   // K and V tiles of the block in work, then swapped: what takes a half's place is requested as soon as
   // the half sits in registers, the next block's K half where the V half was (free first) and its V half
   // where the K half was, so that every request has one and a half halves of a block to land
-  __shared__ __attribute__((aligned(1024))) char lds[2][kTile];
-  __shared__ int klist[kChunkMax];
-  __shared__ uint32_t key_bits[kChunkMax][2];  // validity of the keys of blocks with padded keys inside
-  __shared__ float dvals[kBlk];
+  __shared__ __attribute__((aligned(1024))) char lds_all[kWaves][2][kTile];
+  __shared__ int klist_all[kWaves][kChunkMax];
+  __shared__ uint32_t key_bits_all[kWaves][kChunkMax][2];  // validity of the keys of blocks with padded keys inside
+  __shared__ float dvals_all[kWaves][kBlk];
+  const int wv = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char (&lds)[2][kTile] = lds_all[wv];
+  int* const klist = klist_all[wv];
+  uint32_t (*const key_bits)[2] = key_bits_all[wv];
+  float* const dvals = dvals_all[wv];
 
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   WorkItem it;
   // the first workgroups make the inverse of the pattern for the dK/dV kernel, which runs after this one
   if (blockIdx.x < p.inverse_wgs) {
-    invert_pattern(p, pat, blockIdx.x, reinterpret_cast<uint32_t*>(lds));
+    if (wv == 0) invert_pattern(p, pat, blockIdx.x, reinterpret_cast<uint32_t*>(lds));
     return;
   }
   if (!decode_item(p.split, pat, p.BH, blockIdx.x - p.inverse_wgs, &it)) return;
@@ -248,8 +255,8 @@ void bwd_dq_kernel(BwdParams p) {
   // a query block that the forward did not compute (no valid position, and the caller asked for
   // such blocks to be skipped): no key block, D = 0, probabilities 0
   const bool skip = p.skip_q && !block_any_valid_scalar(p.kmask, bi, p.n, it.j);
-  KeyList list = item_key_list<true>(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, it.row_global, it.chunk * it.len,
-                                     it.len, lane, klist, key_bits);
+  KeyList list = item_key_list<true>(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, it.row_global,
+                                     it.chunk * it.len + wv * (it.len / kWaves), it.len / kWaves, lane, klist, key_bits);
   const int cnt = __builtin_amdgcn_readfirstlane(skip ? 0 : list.cnt);
   const int kl = list.entry;
   const unsigned partial = __builtin_amdgcn_readfirstlane(list.partial);
@@ -293,7 +300,7 @@ void bwd_dq_kernel(BwdParams p) {
   lse = (skip || lse == neg_inf()) ? __builtin_inff() : lse * kLog2e;
   dvals[(lane & 7) * 8 + (lane >> 3)] = dsum;
   asm volatile("" ::: "memory");
-  if (it.chunk == 0) {
+  if (it.chunk == 0 && wv == 0) {
     p.Dvec[row0 + lane] = -dvals[lane];  // negated: the other kernel starts its dP accumulators from it
     p.Lvec[row0 + lane] = lse == __builtin_inff() ? neg_inf() : -lse / p.c;  // (its S accumulators: from this)
   }
@@ -436,11 +443,18 @@ void bwd_dq_kernel(BwdParams p) {
         *reinterpret_cast<f32x4*>(lds[dt] + tile_off_bf16(q * 32 + col, r4 * 2 + hf)) = v;
       }
   wait_lds_reads();
+  if constexpr (kWaves > 1) __syncthreads();
   float* dst = it.nchunks == 1 ? p.dQ + row0 * kDim : p.part_dq + static_cast<size_t>(it.slot) * (kBlk * kDim);
 #pragma unroll
-  for (int ii = 0; ii < 16; ++ii) {
-    const int row = ii * 4 + (lane >> 4), cc = lane & 15;
-    const f32x4 v = *reinterpret_cast<const f32x4*>(lds[cc >> 3] + tile_off_bf16(row, cc & 7));
+  for (int ii = 0; ii < 16 / kWaves; ++ii) {
+    const int row = (wv * (16 / kWaves) + ii) * 4 + (lane >> 4), cc = lane & 15;
+    f32x4 v = *reinterpret_cast<const f32x4*>(lds_all[0][cc >> 3] + tile_off_bf16(row, cc & 7));
+#pragma unroll
+    for (int u = 1; u < kWaves; ++u) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(lds_all[u][cc >> 3] + tile_off_bf16(row, cc & 7));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += x[e];
+    }
     *reinterpret_cast<f32x4*>(dst + row * kDim + cc * 4) = v;
   }
 }
@@ -485,13 +499,15 @@ __device__ __forceinline__ void pin_half_stage() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <bool kDrop>
-__global__ __launch_bounds__(kDkvThreads) __attribute__((amdgpu_waves_per_eu(2)))
+// kTeams: pairs of waves of a workgroup, each with a ring of its own.  Large launches: 1.  Small ones: 4
+// (p.by_row), which deal out the item's list and add their shares of dK and dV in LDS.
+template <bool kDrop, int kTeams>
+__global__ __launch_bounds__(kDkvThreads * kTeams) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_dkv_kernel(BwdParams p) {
-  __shared__ __attribute__((aligned(1024))) char ring[kRing][2][kHalfTile];  // Q half, dO half
-  __shared__ __attribute__((aligned(256))) float lds_l[kRing][kBlk];         // -LSE / scale of the whole block
-  __shared__ __attribute__((aligned(256))) float lds_d[kRing][kBlk];         // -D
-  __shared__ __attribute__((aligned(256))) uint32_t lds_rk[kDrop ? kRing : 1][kBlk];
+  __shared__ __attribute__((aligned(1024))) char ring_all[kTeams][kRing][2][kHalfTile];  // Q half, dO half
+  __shared__ __attribute__((aligned(256))) float lds_l_all[kTeams][kRing][kBlk];         // -LSE / scale of the whole block
+  __shared__ __attribute__((aligned(256))) float lds_d_all[kTeams][kRing][kBlk];         // -D
+  __shared__ __attribute__((aligned(256))) uint32_t lds_rk_all[kTeams][kDrop ? kRing : 1][kBlk];
   __shared__ int jlist[kMaxBwdBlocks];
 
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
@@ -500,7 +516,12 @@ void bwd_dkv_kernel(BwdParams p) {
   const int bh = it.bh;
   const int bi = bh / p.H, h = bh % p.H;
   const int lane = lane_id();
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wv = wave & 1, team = kTeams == 1 ? 0 : wave >> 1;
+  auto& ring = ring_all[team];
+  auto& lds_l = lds_l_all[team];
+  auto& lds_d = lds_d_all[team];
+  auto& lds_rk = lds_rk_all[team];
   const int hf = lane >> 5, col = lane & 31;
   if (!it.key_global) it.k = p.key_order[h * p.nb + it.k - pat.lead()];
   const int k = __builtin_amdgcn_readfirstlane(it.k);
@@ -523,9 +544,11 @@ void bwd_dkv_kernel(BwdParams p) {
   }
   uint64_t vbits = ~0ull;
   if (p.kmask) vbits = key_valid_bits(p.kmask, bi, p.n, k);
-  const int total = vbits == 0 ? 0 : query_list(p, pat, bi, h, k, jlist, wv == 0);
-  // this slice's share: entries chunk, chunk + nchunks, ... of the list
-  const int cnt = __builtin_amdgcn_readfirstlane(it.chunk < total ? (total - it.chunk + it.nchunks - 1) / it.nchunks : 0);
+  const int total = vbits == 0 ? 0 : query_list(p, pat, bi, h, k, jlist, wave == 0);
+  // this team's share: entries chunk, chunk + nchunks, ... of the list
+  const int chunk = it.chunk * kTeams + team, nchunks = it.nchunks * kTeams;
+  auto share = [&](int c) { return __builtin_amdgcn_readfirstlane(c < total ? (total - c + nchunks - 1) / nchunks : 0); };
+  const int cnt = share(chunk);
   __syncthreads();
 
   f32x16 dk[2], dv[2];
@@ -540,7 +563,7 @@ void bwd_dkv_kernel(BwdParams p) {
     // (past the end of the list: its last entry again, which nobody uses)
     auto entry = [&](int hh) {
       const int i = hh >> 1;
-      return jlist[it.chunk + (i < cnt ? i : cnt - 1) * it.nchunks];
+      return jlist[chunk + (i < cnt ? i : cnt - 1) * nchunks];
     };
     // five loads per wave and half
     auto request = [&](int hh, int j_, int place) {
@@ -698,6 +721,10 @@ void bwd_dkv_kernel(BwdParams p) {
     }
     add_transposed(qt, dsb, dk);  // the last half's share
   }
+  if constexpr (kTeams > 1) {  // the barriers of the team with the most entries, the first
+    const int most = share(it.chunk * kTeams);
+    for (int u = cnt > 0 ? 2 * cnt : (most > 0 ? -1 : 0); u < 2 * most; ++u) BB_BARRIER();
+  }
   wait_tile_loads<0>();  // requests past the end of the list (with an empty one: K and V)
   __syncthreads();       // nobody reads the ring any more
 
@@ -705,7 +732,7 @@ void bwd_dkv_kernel(BwdParams p) {
   // through LDS so that memory sees whole rows: this wave's 32 rows of dK, then of dV, d 0 .. 31 and 32 .. 63
   const bool key_valid = (vbits >> (wv * 32 + col)) & 1;
   const float vscale = kDrop ? p.drop.rs : 1.f;
-  char* const out = &ring[0][0][0] + wv * (4 * kHalfTile);
+  char* const out = &ring[0][0][0] + wv * (4 * kHalfTile);  // a team's ring is twice that
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
@@ -721,12 +748,28 @@ void bwd_dkv_kernel(BwdParams p) {
       *reinterpret_cast<f32x4*>(out + (2 + dt) * kHalfTile + off) = b;
     }
   wait_lds_reads();
+  if constexpr (kTeams > 1) __syncthreads();
 #pragma unroll
-  for (int ii = 0; ii < 8; ++ii) {
-    const int row = ii * 4 + (lane >> 4), cc = lane & 15;
-    const char* src = out + (cc >> 3) * kHalfTile + tile_off_bf16(row, cc & 7);
-    *reinterpret_cast<f32x4*>(dk_dst + row * kDim + cc * 4) = *reinterpret_cast<const f32x4*>(src);
-    *reinterpret_cast<f32x4*>(dv_dst + row * kDim + cc * 4) = *reinterpret_cast<const f32x4*>(src + 2 * kHalfTile);
+  for (int ii = 0; ii < 8 / kTeams; ++ii) {
+    const int row = (team * (8 / kTeams) + ii) * 4 + (lane >> 4), cc = lane & 15;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+#pragma unroll
+    for (int u = 0; u < kTeams; ++u) {
+      const char* src = &ring_all[u][0][0][0] + wv * (4 * kHalfTile) + (cc >> 3) * kHalfTile + tile_off_bf16(row, cc & 7);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(src), y = *reinterpret_cast<const f32x4*>(src + 2 * kHalfTile);
+      if (u == 0) {
+        a = x;
+        b = y;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          a[e] += x[e];
+          b[e] += y[e];
+        }
+      }
+    }
+    *reinterpret_cast<f32x4*>(dk_dst + row * kDim + cc * 4) = a;
+    *reinterpret_cast<f32x4*>(dv_dst + row * kDim + cc * 4) = b;
   }
 }
 
@@ -816,16 +859,14 @@ bool launch_failed(const char* what) {
 int launch_bwd_bf16(const BwdParams& p, hipStream_t stream) {
   const unsigned qgrid = p.inverse_wgs + DieItems(p.BH, p.split.items_per_bh).grid();
   const bool drop = p.drop.thr != 0;
-  if (drop)
-    hipLaunchKernelGGL(bwd_dq_kernel<true>, dim3(qgrid), dim3(64), 0, stream, p);
-  else
-    hipLaunchKernelGGL(bwd_dq_kernel<false>, dim3(qgrid), dim3(64), 0, stream, p);
+  const auto dq = p.by_row ? (drop ? bwd_dq_kernel<true, kRowWaves> : bwd_dq_kernel<false, kRowWaves>)
+                           : (drop ? bwd_dq_kernel<true, 1> : bwd_dq_kernel<false, 1>);
+  hipLaunchKernelGGL(dq, dim3(qgrid), dim3(p.by_row ? 64 * kRowWaves : 64), 0, stream, p);
   if (launch_failed("bwd_dq_kernel")) return BB_ERR_LAUNCH;
   const unsigned kvgrid = DieItems(p.BH, p.kv.items_per_bh).grid();
-  if (drop)
-    hipLaunchKernelGGL(bwd_dkv_kernel<true>, dim3(kvgrid), dim3(kDkvThreads), 0, stream, p);
-  else
-    hipLaunchKernelGGL(bwd_dkv_kernel<false>, dim3(kvgrid), dim3(kDkvThreads), 0, stream, p);
+  const auto dkv = p.by_row ? (drop ? bwd_dkv_kernel<true, kRowWaves> : bwd_dkv_kernel<false, kRowWaves>)
+                            : (drop ? bwd_dkv_kernel<true, 1> : bwd_dkv_kernel<false, 1>);
+  hipLaunchKernelGGL(dkv, dim3(kvgrid), dim3(p.by_row ? kDkvThreads * kRowWaves : kDkvThreads), 0, stream, p);
   if (launch_failed("bwd_dkv_kernel")) return BB_ERR_LAUNCH;
 
   return launch_bwd_reduce(p, stream);

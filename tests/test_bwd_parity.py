@@ -339,3 +339,36 @@ def test_list_lengths(nb, g, w, r):
         km = np.ones((B, n), dtype=np.uint8)
         km[0, n - 70:] = 0
     check_full(t, ridx, 64, g, w, 0.125, key_mask=km, tag=f"bwd lists nb{nb} g{g} w{w} r{r}")
+
+
+@pytest.mark.parametrize("B,H,n,g,w,r,drop", [
+    (1, 2, 64, 0, 1, 0, 0.0),      # one block: three of the four waves have nothing
+    (1, 3, 640, 2, 3, 3, 0.0),     # lists shorter and longer than a multiple of four
+    (2, 1, 1088, 2, 3, 3, 0.1),
+    (1, 1, 4160, 2, 3, 3, 0.0),    # 65 blocks: the list of a global block by several workgroups
+    (1, 2, 1536, 3, 13, 8, 0.0),   # lists of up to 24 blocks: six per wave
+    (1, 12, 1600, 2, 3, 3, 0.0),   # 300 blocks: past the line, a wave or a pair of waves per item
+])
+@pytest.mark.parametrize("padded", [False, True])
+def test_small_launches_by_blocks_bf16(B, H, n, g, w, r, drop, padded):
+    """Backward of small launches, where a workgroup deals out a block's list to its waves: every length of
+    the shares, key blocks without a query block, split global blocks."""
+    torch = torch_mod()
+    t = inp.make_tensors(B, H, n, 64, 611 + n, "bf16", with_dO=True)
+    ridx_h = oracle.make_rand_idx(H, n, 64, g, w, r, 5)
+    km = None
+    if padded:
+        km = np.ones((B, n), dtype=np.uint8)
+        km[0, n - n // 3 - 5:] = 0
+        km[-1, n // 4:n // 4 + 100] = 0
+    Q, K, V, dO = (device_tensor(t, x, "bf16") for x in ("Q", "K", "V", "dO"))
+    ridx = torch.from_numpy(np.ascontiguousarray(ridx_h)).to("cuda:0")
+    kw = dict(g=g, w=w, scale=0.125, key_padding_mask=None if km is None else torch.from_numpy(km).to("cuda:0"),
+              p_drop=drop, seed=9)
+    O, LSE = bb.bigbird_attn_fwd_dropout(Q, K, V, ridx, **kw)
+    grads = bb.bigbird_attn_bwd_dropout(Q, K, V, O, LSE, dO, ridx, **kw)
+    torch.cuda.synchronize()
+    ref = oracle.attn_bwd_dropout(t["Q"], t["K"], t["V"], t["dO"], ridx_h, 64, g, w, 0.125, drop, 9, key_mask=km)
+    for x, y in zip(grads, ref):
+        err = np.abs(to_host(x) - y).max()
+        assert err <= TOL, err
