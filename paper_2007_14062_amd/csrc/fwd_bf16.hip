@@ -541,7 +541,7 @@ __device__ __forceinline__ const char* query_tile(const FwdParams& p, int bh, in
 }
 
 // kMode (here and below): the instance of the kernel.  kPlain knows no padding mask, kMasked does,
-// kOptions also serves attention dropout and skipped query blocks.  An instance holds no code of the
+// kOptions also skipped query blocks, kDrop also attention dropout.  An instance holds no code of the
 // others, so its registers and schedule are its own.
 template <int kMode>
 __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
