@@ -20,7 +20,8 @@
 //     reference of 0 is exact as long as the row sum stays inside [2^-40, 2^60]; a wave
 //     checks that at the end of its item and, if a row left the range (logits beyond about
 //     +-28 in natural units), puts the item on a list that it works off afterwards with the
-//     classical running-maximum recurrence (slow_item).  Both paths give the same un-normalised (reference, sum,
+//     classical running-maximum recurrence (slow_item), as it does with items that have
+//     padded keys inside a block.  Both paths give the same un-normalised (reference, sum,
 //     O~) triple to the common epilogue.  (Folding the factor into the query operand would
 //     save the multiplication, but the operand would have to be rounded to bf16 again: that
 //     perturbs a logit by up to 2^-9 of its size, four times the error of everything else in
@@ -43,12 +44,14 @@
 //     three quarters of a block pair to land.
 //   * V^T operands come from the transposing LDS read; the LDS layout is swizzled so
 //     that neither read pattern has bank conflicts.
-//   * A block with padded keys inside takes the same body: after the conversion the padded keys'
-//     probabilities are cleared (drop_padded_keys), behind a scalar branch per slot.  What bounds
-//     such batches is the pipelined body as ever: 8 sequences of 1024 .. 4096 valid positions
-//     (12 heads, n = 4096) 72 us against 84 when items with such a block went to the per-item list,
-//     57 against 101 with their padded query blocks skipped; 230 leading global tokens (every row
-//     attends a cut block, 4 sequences) 47 against 75.
+//   * Items with a block that has padded keys inside take the recurrence: its row sums are fp32 sums of
+//     the probabilities before their rounding, and the largest probability of a row is 1 and not rounded.
+//     (The pipelined body with the padded probabilities cleared is faster but less exact: 8 sequences of
+//     1024 .. 4096 valid positions, 12 heads, n = 4096, 69 against 84 us, with padded query blocks skipped
+//     56 against 87, 230 leading global tokens 47 against 73; its LSE is off by up to 2^-8 where one key holds
+//     a row, and its O by 2.33e-3 (2-norm, normal inputs, rows of 454 keys) where the recurrence has 2.19e-3.)
+//     The list builder leaves the validity bits of such blocks in LDS, so that no pair of the recurrence
+//     waits for the mask.
 //   * The two waves of a SIMD get their issue priority from the pairs they still have to
 //     do, so that they finish together (set_issue_priority).
 //   * Instances of the kernel: without a padding mask (everything above and nothing else); with
@@ -127,7 +130,7 @@ __device__ __forceinline__ void set_issue_priority(int remaining_pairs) {
 // was requested three slots earlier; the request for the half after that follows as soon as the
 // read has returned.  Tile loads outstanding at the start of a pair, oldest first:
 // K(i+1).t0 and V(i).t1 (8 instructions).
-// A block with padded keys inside comes with the validity bits of its keys (key_bits, LDS).
+// Blocks with padded keys inside never come here: such items take the recurrence (but see pair_step_drop).
 struct PairCtx {
   const char* lds_k;   // this wave's K and V tile buffers
   const char* lds_v;
@@ -332,13 +335,11 @@ __device__ __forceinline__ void pair_step_drop(const PairCtx& cx, const Straight
 // delivers a tile nobody uses (see TileStreams).
 // k1 / v1: global address of the tile that follows this pair's in the K / V stream; k2: the one
 // after that in the K stream.
-template <int kMode>
 __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
                                           const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], bf16x8 (&va)[2][2][2],
                                           f32x16& sA, bf16x8 (&p3)[2], f32x16 (&o)[2][2],
                                           const RowSumOperand& ones, f32x4 (&ls)[2],
-                                          const char* k1, const char* v1, const char* k2,
-                                          const uint32_t* key_bits = nullptr) {
+                                          const char* k1, const char* v1, const char* k2) {
   f32x16 sB, sC, sD;
   bf16x8 p0[2], p1[2], p2[2];
 
@@ -350,7 +351,6 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   unit_pv(va[1], p3, o[1], ones, ls[1]);
   unit_probs(sA, cx.c, p0);
   pin_slot<0>();
-  if (kMode != kPlain && key_bits) drop_padded_keys(key_bits[0], cx.hf, p0);
 
   // ---- slot 1: K(i+1).t0 and V(i).t1 have landed
   wait_tile_loads<8>();
@@ -360,7 +360,6 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   unit_pv(va[0], p0, o[0], ones, ls[0]);
   unit_probs(sB, cx.c, p1);
   pin_slot<12>();
-  if (kMode != kPlain && key_bits) drop_padded_keys(key_bits[0], cx.hf, p1);
 
   // ---- slot 2
   wait_lds_reads();
@@ -370,7 +369,6 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   unit_pv(va[0], p1, o[1], ones, ls[1]);
   unit_probs(sC, cx.c, p2);
   pin_slot<0>();
-  if (kMode != kPlain && key_bits) drop_padded_keys(key_bits[1], cx.hf, p2);
 
   // ---- slot 3: K(i+1).t1 and V(i+1).t0 have landed
   wait_tile_loads<8>();
@@ -380,7 +378,6 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   unit_pv(va[1], p2, o[0], ones, ls[0]);
   unit_probs(sD, cx.c, p3);
   pin_slot<12>();
-  if (kMode != kPlain && key_bits) drop_padded_keys(key_bits[1], cx.hf, p3);
 }
 
 // LDS of a workgroup (at namespace scope: the cold paths below are separate functions).
@@ -389,7 +386,8 @@ __shared__ int klist_all[kFwdWaves][kGlobalWaveLen];
 // validity bits of the keys of listed blocks that have padded keys inside, for the three items a wave
 // knows at a time (the one in work, the next, the one after)
 __shared__ uint32_t key_bits_all[kFwdWaves][3][kGlobalWaveLen][2];
-__shared__ float mrg_m[kFwdWaves][kBlk], mrg_l[kFwdWaves][kBlk];  // global rows: per-wave exponent, sum
+__shared__ int row_cut[kFwdWaves];  // rows by a workgroup: does the wave's share hold a cut block?
+__shared__ float mrg_m[kFwdWaves][kBlk], mrg_l[kFwdWaves][kBlk];  // their per-wave exponents and sums
 __shared__ float mrg_lse[kFwdWaves][kBlk];  // (dropout) sum for LSE
 
 // What a wave knows about itself and its LDS.
@@ -573,11 +571,8 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
   it.cnt = kl.cnt;
   it.kl = kl.entry;
   it.partial = kl.partial;
-  it.per_item = false;
-  // No block without padded keys: a row may have a key or two, whose rounded probabilities are a
-  // row sum that is off by up to 2^-9 (over 64 keys and more the roundings average out) -- the
-  // recurrence sums them before the rounding.
-  if (kMode != kPlain && it.partial) it.per_item |= it.partial == (1u << it.cnt) - 1;
+  // (attention dropout: only items without a single full block)
+  it.per_item = kMode == kDrop ? it.partial && it.partial == (1u << it.cnt) - 1 : it.partial != 0;
   // all of these are wave uniform; saying so keeps them (and what is computed from them) in
   // scalar registers
   it.bh = __builtin_amdgcn_readfirstlane(it.bh);
@@ -708,12 +703,11 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
   unit_scores(ka[0], qb[0], sA);
 
   for (int i = 0; i < cnt; ++i) {
-    const uint32_t* const bits = (item.partial >> i) & 1 ? key_bits + 2 * i : nullptr;
     if constexpr (kMode == kDrop)
       pair_step_drop(cx, so, to, qb, ka, va, sA, p3, o, dc, __builtin_amdgcn_readlane(item.kl, i), ones, ls, sum,
-                     ts.k(i + 1), ts.v(i + 1), ts.k(i + 2), bits);
+                     ts.k(i + 1), ts.v(i + 1), ts.k(i + 2), (item.partial >> i) & 1 ? key_bits + 2 * i : nullptr);
     else
-      pair_step<kMode>(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2), bits);
+      pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
   }
   if (!next) wait_tile_loads<0>();  // requests past the end of the streams
   // the last unit's share of O and of the row sums
@@ -729,13 +723,15 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
 }
 
 // The classical recurrence (running maximum, rescale on every block), one block pair at a time
-// the path of items whose every block has padded keys inside and the
+// with the tiles of the next pair in flight: the path of items with padded keys inside a block (key_bits: the
+// validity bits of those blocks, as make_item leaves them) and the
 // fallback for items whose row sums left the safe range of the reference-free path.  Leaves m_ref (exponent
 // units), this lane's share of the row sums and O~.  Any load still in flight lands first.
 template <int kMode>
 __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
                                           const bf16x8 (&qb)[2][4], const FwdParams& p, const Item& item,
-                                          f32x16 (&o)[2][2], float (&l_run)[2], float (&m_ref)[2]) {
+                                          const uint32_t (*key_bits)[2], f32x16 (&o)[2][2], float (&l_run)[2],
+                                          float (&m_ref)[2]) {
   const ItemTiles it(p, item);
   zero_acc(o[0]);
   zero_acc(o[1]);
@@ -759,8 +755,11 @@ __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffse
   if (item.cnt > 0) request_tiles(0);
   for (int i = 0; i < item.cnt; ++i) {
     const int kblock = __builtin_amdgcn_readlane(item.kl, i);
-    uint64_t vbits = ~0ull;
-    if (p.kmask) vbits = key_valid_bits(p.kmask, item.bh / p.H, p.n, kblock);
+    uint32_t vbits[2] = {~0u, ~0u};
+    if (kMode != kPlain && (item.partial >> i) & 1) {
+      vbits[0] = key_bits[i][0];
+      vbits[1] = key_bits[i][1];
+    }
     wait_tile_loads<0>();
     bf16x8 ka[2][4], va[2][2][2];
     read_straight_half(so, cx.lds_k, 0, ka[0]);
@@ -777,7 +776,7 @@ __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffse
       float mloc = neg_inf();
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        const unsigned mine = static_cast<unsigned>(vbits >> (32 * t + cx.hf * 4));
+        const unsigned mine = vbits[t] >> (cx.hf * 4);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           s[t][r] = ((mine >> acc_row(r, 0)) & 1) ? s[t][r] * cx.c : neg_inf();  // base-2 exponent
@@ -930,7 +929,7 @@ __device__ __forceinline__ const void* kernel_kernargs() {
 }
 
 // One non-global item by the classical recurrence, from its first load to its last store: the path
-// of items without any key block or with padded keys inside every block, and of items whose row sums
+// of items without any key block or with padded keys inside a block, and of items whose row sums
 // left the safe range of the pipelined path.
 template <int kMode>
 __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
@@ -951,7 +950,7 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
     so.read(w.lds_v, qb);
     wait_lds_reads();
     }
-  slow_item<kMode>(w.cx, so, to, qb, p, it, o, l_run, m_ref);
+  slow_item<kMode>(w.cx, so, to, qb, p, it, key_bits_all[w.wv][0], o, l_run, m_ref);
 #pragma unroll
   for (int q = 0; q < 2; ++q) l_tot[q] = half_sum(l_run[q]);
   if (it.nchunks == 1) {
@@ -993,6 +992,14 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
 #endif
   Item cur;
   make_item<kMode>(p, w, sc, 0, cur, 0);
+  bool by_recurrence = cur.per_item;
+  if ((kMode == kMasked || kMode == kOptions) && (p.nb < 4 * kGlobalWaveLen || sc.row_idx >= p.g * p.geo.ng)) {
+    // A row with a cut block takes the recurrence in all four waves, as it does where one wave has the
+    // whole row.  (Global rows of 64 blocks and more are never one wave's: each share by itself.)
+    if (lane == 0) row_cut[wv] = by_recurrence;
+    __syncthreads();
+    by_recurrence = (row_cut[0] | row_cut[1] | row_cut[2] | row_cut[3]) != 0;
+  }
   bf16x8 qb[2][4], ka[2][4];
   f32x16 o[2][2];
   float m_ref[2] = {0.f, 0.f};  // reference exponents (base-2 units); halves agree
@@ -1003,14 +1010,14 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   if (cur.cnt > 0) {
     fresh_start(p, w, so, cur, qb);
     float l_run[2] = {0.f, 0.f};
-    bool bad = cur.per_item;
+    bool bad = by_recurrence;
     if (!bad) {
       fast_item<kMode>(w.cx, so, to, qb, ka, p, cur, nullptr, true, key_bits_all[w.wv][0][0], o, l_tot, l_lse);
 #pragma unroll
       for (int q = 0; q < 2; ++q) bad |= !(l_tot[q] >= kSumLo && l_tot[q] <= kSumHi);
     }
     if (__any(bad)) {
-      slow_item<kMode>(w.cx, so, to, qb, p, cur, o, l_run, m_ref);
+      slow_item<kMode>(w.cx, so, to, qb, p, cur, key_bits_all[wv][0], o, l_run, m_ref);
 #pragma unroll
       for (int q = 0; q < 2; ++q) l_lse[q] = l_tot[q] = half_sum(l_run[q]);
     }
@@ -1180,7 +1187,7 @@ void fwd_kernel_bf16(FwdParams p) {
 #define BB_STAMP(i)
 #endif
   // ---- persistent wave: the die's non-global items t_item, t_item + wave_stride, ...
-  // Items that cannot take the pipelined path (no key block at all, padded keys inside every block,
+  // Items that cannot take the pipelined path (no key block at all, padded keys inside a block,
   // or -- found out afterwards -- row sums outside the safe range) are put on a list and done
   // by the classical recurrence when the stream has ended; the host sizes the grid so that a
   // wave has at most 64 items (a lane of `redo` each).
@@ -1310,8 +1317,7 @@ void fwd_kernel_bf16(FwdParams p) {
                        ts.k(i + 1), ts.v(i + 1), ts.k(i + 2),
                        (cur.partial >> i) & 1 ? key_bits_all[w.wv][bits_cur][i] : nullptr);
       else
-        pair_step<kMode>(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2),
-                         (cur.partial >> i) & 1 ? key_bits_all[w.wv][bits_cur][i] : nullptr);
+        pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
       rem_pairs = __builtin_amdgcn_readfirstlane(rem_pairs - 1);
       i = __builtin_amdgcn_readfirstlane(i + 1);
       if (__builtin_expect(i < cnt, 1)) continue;  // (the register allocator should favour the pairs)
