@@ -144,8 +144,8 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
   // When query blocks may be skipped, a fixed share of the items can be anything from all skipped
   // to all computed: the waves of the bf16 kernel then claim their items from a counter per die.
   // (Without skipped blocks claiming measured no gain over fixed shares at the key-padding
-  // workload -- 60.6 against 61.1 us with its extra launch; with dropout a step of 48 slices of
-  // n = 3072 takes 155 us without and 158 with it.)
+  // workload -- 60.6 against 61.1 us with its extra launch; with dropout every item is the same
+  // slow path.)
   p.counters = L.has_counters ? reinterpret_cast<int*>(ws + L.counters) : nullptr;
   p.dyn = (dtype == BB_BF16 && p.skip_q && drop.thr == 0 && p.counters) ? 1 : 0;
   // (at up to 8 blocks no row is split and the forward needs no workspace: that stays so)

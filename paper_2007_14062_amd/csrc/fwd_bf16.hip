@@ -58,11 +58,11 @@
 //     one; kOptions, launched when a call asks for fully padded query blocks to be skipped
 //     (BB_SKIP_PADDED_QUERY_BLOCKS: their rows are written as zeros and the waves claim the
 //     other items from a counter per die, global-row waves included once their row is done); and
-//     kDrop for attention dropout, with or without these.  There the row sums are those of the undropped
-//     probabilities and the keep mask of dropout.h is applied to the converted
-//     pairs.  What bounds it is the vector port: a unit has 16 multiplications in 32 bits and some
-//     160 other instructions against ten of the matrix pipe.  48 slices of n = 3072, padded
-//     blocks skipped: 55 us when every item took the recurrence pair by pair, 41 here.
+//     kDrop for attention dropout, with or without these.  There every item takes the recurrence, in a
+//     plain loop, and the keep mask of dropout.h is applied to the converted pairs that multiply V.
+//     (A pipelined body with the mask inside measured 46 against 53 us at 48 slices of n = 3072, padded
+//     blocks skipped; against a fixed reference the largest probability of a row is rounded: O is off by
+//     2.33e-3 where the recurrence has 2.19e-3, and the slices of a cut row need two sums each.)
 // -DBB_STAMPS builds a development variant that writes per-wave time stamps into the
 // partial-result workspace (which must then hold 128 bytes per wave of the launch); the
 // library proper is built without it.
@@ -130,7 +130,7 @@ __device__ __forceinline__ void set_issue_priority(int remaining_pairs) {
 // was requested three slots earlier; the request for the half after that follows as soon as the
 // read has returned.  Tile loads outstanding at the start of a pair, oldest first:
 // K(i+1).t0 and V(i).t1 (8 instructions).
-// Blocks with padded keys inside never come here: such items take the recurrence (but see pair_step_drop).
+// Blocks with padded keys inside never come here: such items take the recurrence.
 struct PairCtx {
   const char* lds_k;   // this wave's K and V tile buffers
   const char* lds_v;
@@ -222,111 +222,6 @@ __device__ __forceinline__ void pin_slot() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// Attention dropout in the pipelined path: what a lane needs to know of the keep mask.
-struct DropCtx {
-  uint32_t rk[2];   // row keys of its two queries
-  uint32_t thr;     // see drop_keep_pair
-};
-
-// Probabilities of one unit under attention dropout: row sums of all, operands of the kept ones.  Two row
-// sums: `sum` in fp32 for LSE, `ls` of the rounded probabilities (on the matrix pipe) for the output, where a
-// row that one key dominates would otherwise keep the rounding of that key's probability.
-// word0: what the words of the unit's first key pair add to the row key.
-__device__ __forceinline__ void unit_probs_drop(const f32x16& s, float c, uint32_t rk, uint32_t word0, uint32_t thr,
-                                                bf16x8 (&pb)[2], float& sum, const RowSumOperand& ones, f32x4& ls) {
-#pragma unroll
-  for (int sgl = 0; sgl < 2; ++sgl) {
-    u32x4 all, keep;
-#pragma unroll
-    for (int kk = 0; kk < 8; kk += 2) {
-      const int r = sgl * 8 + kk;
-      const float p0 = fast_exp2(s[r] * c);
-      const float p1 = fast_exp2(s[r + 1] * c);
-      sum += p0 + p1;
-      const bf16x2 pk = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
-      // registers r, r + 1 are keys 2m, 2m + 1: one word of the mask
-      const uint32_t word = drop_mix(rk ^ (word0 + static_cast<uint32_t>(acc_row(r, 0) / 2) * kDropPairStep));
-      all[kk / 2] = __builtin_bit_cast(uint32_t, pk);
-      keep[kk / 2] = drop_keep_pair(word, thr);
-    }
-    ls = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.a, __builtin_bit_cast(bf16x8, all), ls, 0, 0, 0);
-    pb[sgl] = __builtin_bit_cast(bf16x8, all & keep);
-  }
-}
-
-// Scores of padded keys -> -inf (before the exponentials: the row sums leave them out).
-__device__ __forceinline__ void mask_scores(uint32_t bits, int hf, f32x16& s) {
-  const uint32_t mine = bits >> (hf * 4);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) s[r] = (mine >> acc_row(r, 0)) & 1 ? s[r] : neg_inf();
-}
-
-// Issue order of a slot under dropout: per MFMA two exponentials and an eighth of the other vector work.
-// (The results are named so that the compiler does not move them past the branch of the next slot.)
-template <int DS_READS>
-__device__ __forceinline__ void pin_slot_drop(bf16x8 (&pb)[2], float& sum) {
-  asm volatile("" : "+v"(pb[0]), "+v"(pb[1]), "+v"(sum));
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if (u * 2 < DS_READS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, 20, 0);
-    if (u == 3 || u == 7) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// pair_step under attention dropout: the same slots, requests and waits.
-__device__ __forceinline__ void pair_step_drop(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
-                                               const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], bf16x8 (&va)[2][2][2],
-                                               f32x16& sA, bf16x8 (&p3)[2], f32x16 (&o)[2][2], const DropCtx& dc,
-                                               int kblock, const RowSumOperand& ones, f32x4 (&ls)[2], float (&sum)[2],
-                                               const char* k1, const char* v1,
-                                               const char* k2, const uint32_t* key_bits) {
-  f32x16 sB, sC, sD;
-  bf16x8 p0[2], p1[2], p2[2];
-  // first key pair of this lane in the block, and 32 keys on
-  const uint32_t w0 = static_cast<uint32_t>(kblock * (kBlk / 2) + 2 * cx.hf) * kDropPairStep, w1 = w0 + 16u * kDropPairStep;
-  const float c = cx.c;
-
-  if (key_bits) mask_scores(key_bits[0], cx.hf, sA);
-  wait_lds_reads();
-  half_load_async(k1, cx.lds_k_a, 1, cx.voff);
-  half_load_async(v1, cx.lds_v_a, 0, cx.voff);
-  unit_scores(ka[0], qb[1], sB);
-  unit_pv(va[1], p3, o[1]);
-  unit_probs_drop(sA, c, dc.rk[0], w0, dc.thr, p0, sum[0], ones, ls[0]);
-  pin_slot_drop<0>(p0, sum[0]);
-
-  if (key_bits) mask_scores(key_bits[0], cx.hf, sB);
-  wait_tile_loads<8>();
-  read_straight_half(so, cx.lds_k, 0, ka[0]);
-  read_transposed_half(to, cx.lds_v, 1, va[1]);
-  unit_scores(ka[1], qb[0], sC);
-  unit_pv(va[0], p0, o[0]);
-  unit_probs_drop(sB, c, dc.rk[1], w0, dc.thr, p1, sum[1], ones, ls[1]);
-  pin_slot_drop<12>(p1, sum[1]);
-
-  if (key_bits) mask_scores(key_bits[1], cx.hf, sC);
-  wait_lds_reads();
-  half_load_async(k2, cx.lds_k_a, 0, cx.voff);
-  half_load_async(v1, cx.lds_v_a, 1, cx.voff);
-  unit_scores(ka[1], qb[1], sD);
-  unit_pv(va[0], p1, o[1]);
-  unit_probs_drop(sC, c, dc.rk[0], w1, dc.thr, p2, sum[0], ones, ls[0]);
-  pin_slot_drop<0>(p2, sum[0]);
-
-  if (key_bits) mask_scores(key_bits[1], cx.hf, sD);
-  wait_tile_loads<8>();
-  read_straight_half(so, cx.lds_k, 1, ka[1]);
-  read_transposed_half(to, cx.lds_v, 0, va[0]);
-  unit_scores(ka[0], qb[0], sA);
-  unit_pv(va[1], p2, o[0]);
-  unit_probs_drop(sD, c, dc.rk[1], w1, dc.thr, p3, sum[1], ones, ls[1]);
-  pin_slot_drop<12>(p3, sum[1]);
-}
-
 // One block pair.  The arithmetic and the memory requests are the same for every pair, so that
 // one straight-line body serves them all: the first pair of an item finishes a predecessor that
 // does not exist (p3 = 0 on entry, V fragments zeroed), the last one starts a successor that does
@@ -383,12 +278,10 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
 // LDS of a workgroup (at namespace scope: the cold paths below are separate functions).
 __shared__ __attribute__((aligned(1024))) char lds_all[kFwdWaves][2 * kTile];  // per wave: K tile, V tile
 __shared__ int klist_all[kFwdWaves][kGlobalWaveLen];
-// validity bits of the keys of listed blocks that have padded keys inside, for the three items a wave
-// knows at a time (the one in work, the next, the one after)
-__shared__ uint32_t key_bits_all[kFwdWaves][3][kGlobalWaveLen][2];
+// validity bits of the keys of listed blocks that have padded keys inside, of the list made last
+__shared__ uint32_t key_bits_all[kFwdWaves][kGlobalWaveLen][2];
 __shared__ int row_cut[kFwdWaves];  // rows by a workgroup: does the wave's share hold a cut block?
 __shared__ float mrg_m[kFwdWaves][kBlk], mrg_l[kFwdWaves][kBlk];  // their per-wave exponents and sums
-__shared__ float mrg_lse[kFwdWaves][kBlk];  // (dropout) sum for LSE
 
 // What a wave knows about itself and its LDS.
 struct WaveCtx {
@@ -462,7 +355,7 @@ struct Item {
   int slot;            // partial-result slot (nchunks > 1)
   int cnt;             // key blocks in this slice
   int kl;              // the list: lane t holds entry t % 16
-  unsigned partial;    // bit t: entry t has padded keys inside (its validity bits are in the wave's key_bits)
+  unsigned partial;    // bit t: entry t has padded keys inside (until the next list: its validity bits are in the wave's key_bits)
   bool per_item;       // not for the pipelined path (see make_item)
   bool skipped;        // query block without a valid position, not to be computed (cnt = 0)
 };
@@ -539,11 +432,10 @@ __device__ __forceinline__ const char* query_tile(const FwdParams& p, int bh, in
 }
 
 // kMode (here and below): the instance of the kernel.  kPlain knows no padding mask, kMasked does,
-// kOptions also skipped query blocks, kDrop also attention dropout.  An instance holds no code of the
+// kOptions also skipped query blocks, kDrop attention dropout with or without these.  An instance holds no code of the
 // others, so its registers and schedule are its own.
 template <int kMode>
-__device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
-                                          int bits_slot) {
+__device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   const int lane = lane_again(w.lane);
   int list_lo, list_len;
@@ -567,12 +459,11 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
     return;
   }
   const KeyList kl = item_key_list<kMode != kPlain>(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, row_global, list_lo,
-                                                    list_len, lane, w.klist, key_bits_all[w.wv][bits_slot]);
+                                                    list_len, lane, w.klist, key_bits_all[w.wv]);
   it.cnt = kl.cnt;
   it.kl = kl.entry;
   it.partial = kl.partial;
-  // (attention dropout: only items without a single full block)
-  it.per_item = kMode == kDrop ? it.partial && it.partial == (1u << it.cnt) - 1 : it.partial != 0;
+  it.per_item = kMode == kDrop || it.partial != 0;
   // all of these are wave uniform; saying so keeps them (and what is computed from them) in
   // scalar registers
   it.bh = __builtin_amdgcn_readfirstlane(it.bh);
@@ -646,15 +537,6 @@ struct TileStreams {
   }
 };
 
-__device__ __forceinline__ DropCtx drop_ctx(const FwdParams& p, const Item& it, int col) {
-  DropCtx dc;
-  const uint32_t row0 = static_cast<uint32_t>(it.bh) * static_cast<uint32_t>(p.n) + static_cast<uint32_t>(it.j * kBlk + col);
-#pragma unroll
-  for (int q = 0; q < 2; ++q) dc.rk[q] = drop_row_key(p.drop, row0 + q * 32);
-  dc.thr = drop_pair_threshold(p.drop);
-  return dc;
-}
-
 // The item's block pairs through the pipeline.
 // On entry, fresh: K(0) is in the K buffer, V(0).t0 is the only load outstanding.
 //           else : K(0)'s fragments are in `ka`, V(0).t0 and V(0).t1 are outstanding, in that order
@@ -663,12 +545,10 @@ __device__ __forceinline__ DropCtx drop_ctx(const FwdParams& p, const Item& it, 
 // one more tile of the K stream, its first K tile as one more of the V stream, so that both are
 // in LDS when this item's last pair is done (they are read as K / V fragments by the pairs'
 // regular reads, which nothing uses).
-template <int kMode>
 __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
                                           const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], const FwdParams& p,
                                           const Item& item, const Item* next, bool fresh,
-                                          const uint32_t* key_bits, f32x16 (&o)[2][2], float (&l_tot)[2],
-                                          float (&l_lse)[2]) {
+                                          f32x16 (&o)[2][2], float (&l_tot)[2]) {
   bf16x8 va[2][2][2], p3[2];
   f32x16 sA;
   const RowSumOperand ones(lane_id());
@@ -684,9 +564,6 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
   }
   const int cnt = item.cnt;
   const TileStreams ts(p, item, next, lane_id());
-  DropCtx dc;
-  float sum[2] = {0.f, 0.f};
-  if constexpr (kMode == kDrop) dc = drop_ctx(p, item, lane_id() & 31);
 
   // start of the streams: K(0) -> registers, then the loads a pair expects to find outstanding
   if (fresh) {
@@ -702,28 +579,17 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
   read_transposed_half(to, cx.lds_v, 0, va[0]);
   unit_scores(ka[0], qb[0], sA);
 
-  for (int i = 0; i < cnt; ++i) {
-    if constexpr (kMode == kDrop)
-      pair_step_drop(cx, so, to, qb, ka, va, sA, p3, o, dc, __builtin_amdgcn_readlane(item.kl, i), ones, ls, sum,
-                     ts.k(i + 1), ts.v(i + 1), ts.k(i + 2), (item.partial >> i) & 1 ? key_bits + 2 * i : nullptr);
-    else
-      pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
-  }
+  for (int i = 0; i < cnt; ++i)
+    pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
   if (!next) wait_tile_loads<0>();  // requests past the end of the streams
   // the last unit's share of O and of the row sums
-  if constexpr (kMode == kDrop)
-    unit_pv(va[1], p3, o[1]);
-  else
-    unit_pv(va[1], p3, o[1], ones, ls[1]);
+  unit_pv(va[1], p3, o[1], ones, ls[1]);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    l_tot[q] = row_total(ls[q], lane_id() & 31);
-    l_lse[q] = kMode == kDrop ? half_sum(sum[q]) : l_tot[q];
-  }
+  for (int q = 0; q < 2; ++q) l_tot[q] = row_total(ls[q], lane_id() & 31);
 }
 
 // The classical recurrence (running maximum, rescale on every block), one block pair at a time
-// with the tiles of the next pair in flight: the path of items with padded keys inside a block (key_bits: the
+// with the tiles of the next pair in flight: the path of attention dropout, of items with padded keys inside a block (key_bits: the
 // validity bits of those blocks, as make_item leaves them) and the
 // fallback for items whose row sums left the safe range of the reference-free path.  Leaves m_ref (exponent
 // units), this lane's share of the row sums and O~.  Any load still in flight lands first.
@@ -740,8 +606,14 @@ __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffse
     m_ref[q] = neg_inf();
     l_run[q] = 0.f;
   }
-  DropCtx dc;
-  if constexpr (kMode == kDrop) dc = drop_ctx(p, item, lane_id() & 31);
+  // attention dropout: the keys of this lane's two rows of the keep mask
+  uint32_t drop_rk[2] = {0u, 0u};
+  const uint32_t drop_thr = kMode == kDrop ? drop_pair_threshold(p.drop) : 0u;
+  if constexpr (kMode == kDrop) {
+    const uint32_t row0 = static_cast<uint32_t>(item.bh) * static_cast<uint32_t>(p.n) + static_cast<uint32_t>(item.j * kBlk + (lane_id() & 31));
+#pragma unroll
+    for (int q = 0; q < 2; ++q) drop_rk[q] = drop_row_key(p.drop, row0 + q * 32);
+  }
   // The tiles of pair i + 1 are requested as soon as those of pair i sit in registers, and land
   // under pair i's arithmetic.
   auto request_tiles = [&](int i) {
@@ -806,7 +678,7 @@ __device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffse
             l_run[q] += p0 + p1;  // (the row sums are those of the undropped probabilities)
             if constexpr (kMode == kDrop) {
               const uint32_t key = static_cast<uint32_t>(kblock * kBlk + t * 32 + acc_row(r, cx.hf));
-              pk = __builtin_bit_cast(bf16x2, __builtin_bit_cast(uint32_t, pk) & drop_keep_pair(drop_word(dc.rk[q], key >> 1), dc.thr));
+              pk = __builtin_bit_cast(bf16x2, __builtin_bit_cast(uint32_t, pk) & drop_keep_pair(drop_word(drop_rk[q], key >> 1), drop_thr));
             }
             pb[sgl][kk] = pk[0];
             pb[sgl][kk + 1] = pk[1];
@@ -929,8 +801,8 @@ __device__ __forceinline__ const void* kernel_kernargs() {
 }
 
 // One non-global item by the classical recurrence, from its first load to its last store: the path
-// of items without any key block or with padded keys inside a block, and of items whose row sums
-// left the safe range of the pipelined path.
+// of items without any key block or with padded keys inside a block, of items whose row sums
+// left the safe range of the pipelined path, and of every item under attention dropout.
 template <int kMode>
 __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
   const WaveCtx w(p.c);
@@ -939,7 +811,7 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
   const StraightOffsets so(w.lane);
   const TransposedOffsets to(w.lane);
   Item it;
-  make_item<kMode>(p, w, sc, t, it, 0);
+  make_item<kMode>(p, w, sc, t, it);
   wait_tile_loads<0>();
   bf16x8 qb[2][4];
   f32x16 o[2][2];
@@ -950,7 +822,7 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
     so.read(w.lds_v, qb);
     wait_lds_reads();
     }
-  slow_item<kMode>(w.cx, so, to, qb, p, it, key_bits_all[w.wv][0], o, l_run, m_ref);
+  slow_item<kMode>(w.cx, so, to, qb, p, it, key_bits_all[w.wv], o, l_run, m_ref);
 #pragma unroll
   for (int q = 0; q < 2; ++q) l_tot[q] = half_sum(l_run[q]);
   if (it.nchunks == 1) {
@@ -991,7 +863,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   const long long rt0 = __builtin_amdgcn_s_memrealtime();
 #endif
   Item cur;
-  make_item<kMode>(p, w, sc, 0, cur, 0);
+  make_item<kMode>(p, w, sc, 0, cur);
   bool by_recurrence = cur.per_item;
   if ((kMode == kMasked || kMode == kOptions) && (p.nb < 4 * kGlobalWaveLen || sc.row_idx >= p.g * p.geo.ng)) {
     // A row with a cut block takes the recurrence in all four waves, as it does where one wave has the
@@ -1004,22 +876,21 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   f32x16 o[2][2];
   float m_ref[2] = {0.f, 0.f};  // reference exponents (base-2 units); halves agree
   float l_tot[2] = {0.f, 0.f};  // row sums of 2^(s - m_ref)
-  float l_lse[2] = {0.f, 0.f};  // the same, those for LSE (under dropout: see unit_probs_drop)
   zero_acc(o[0]);
   zero_acc(o[1]);
   if (cur.cnt > 0) {
     fresh_start(p, w, so, cur, qb);
     float l_run[2] = {0.f, 0.f};
     bool bad = by_recurrence;
-    if (!bad) {
-      fast_item<kMode>(w.cx, so, to, qb, ka, p, cur, nullptr, true, key_bits_all[w.wv][0][0], o, l_tot, l_lse);
+    if (kMode != kDrop && !bad) {
+      fast_item(w.cx, so, to, qb, ka, p, cur, nullptr, true, o, l_tot);
 #pragma unroll
       for (int q = 0; q < 2; ++q) bad |= !(l_tot[q] >= kSumLo && l_tot[q] <= kSumHi);
     }
     if (__any(bad)) {
-      slow_item<kMode>(w.cx, so, to, qb, p, cur, key_bits_all[wv][0], o, l_run, m_ref);
+      slow_item<kMode>(w.cx, so, to, qb, p, cur, key_bits_all[wv], o, l_run, m_ref);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) l_lse[q] = l_tot[q] = half_sum(l_run[q]);
+      for (int q = 0; q < 2; ++q) l_tot[q] = half_sum(l_run[q]);
     }
   } else {
     m_ref[0] = m_ref[1] = neg_inf();
@@ -1042,7 +913,6 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
     if (hf == 0) {
       mrg_m[wv][q * 32 + col] = !(l_tot[q] > 0.f) ? neg_inf() : m_ref[q];
       mrg_l[wv][q * 32 + col] = l_tot[q];
-      if constexpr (kMode == kDrop) mrg_lse[wv][q * 32 + col] = l_lse[q];
     }
 #ifdef BB_STAMPS
   if (lane == 0) {  // (nchunks == 1 only: the partial-result area is otherwise in use)
@@ -1063,14 +933,13 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   f32x4 acc[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float L = 0.f, L_lse = 0.f;
+  float L = 0.f;
   if (M != neg_inf()) {
 #pragma unroll
     for (int v = 0; v < kFwdWaves; ++v) {
       const float mv = mrg_m[v][q];
       const float wgt = (mv == neg_inf()) ? 0.f : fast_exp2(mv - M);
       L += mrg_l[v][q] * wgt;
-      if constexpr (kMode == kDrop) L_lse += mrg_lse[v][q] * wgt;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int cc = part * 4 + e;
@@ -1080,11 +949,10 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
       }
     }
   }
-  if constexpr (kMode != kDrop) L_lse = L;
   const size_t row = row_blk + q;
   if (cur.nchunks == 1) {
     const float inv = L > 0.f ? (kMode == kDrop ? p.drop.rs : 1.f) / L : 0.f;  // (rs: 1, or the dropout scale)
-    if (part == 0) p.LSE[row] = L > 0.f ? (M + fast_log2(L_lse)) * kLn2 : neg_inf();
+    if (part == 0) p.LSE[row] = L > 0.f ? (M + fast_log2(L)) * kLn2 : neg_inf();
     bf16x8 v0, v1;
 #pragma unroll
     for (int z = 0; z < 4; ++z) {
@@ -1101,7 +969,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
     float* pml = p.part_ml + static_cast<size_t>(cur.slot) * (2 * kBlk);
     if (part == 0) {
       pml[q] = L > 0.f ? M : neg_inf();
-      pml[kBlk + q] = L_lse;
+      pml[kBlk + q] = L;
     }
     f32x4* dst =
         reinterpret_cast<f32x4*>(p.part_o + static_cast<size_t>(cur.slot) * (kBlk * kDim) + q * kDim + part * 16);
@@ -1135,7 +1003,7 @@ void fwd_kernel_bf16(FwdParams p) {
   // the launch) instead of taking every wave_stride-th one: with a padding mask items differ in
   // length and some are not computed at all.  The waves of a global-row workgroup then join in
   // when their row is done.
-  const bool dyn = kMode >= kOptions && p.dyn != 0;
+  const bool dyn = kMode == kOptions && p.dyn != 0;
   const bool was_global = sc.global_wg;
   if (sc.global_wg) {
     if (sc.row_ok) global_row_workgroup<kMode>(p, sc);
@@ -1164,6 +1032,12 @@ void fwd_kernel_bf16(FwdParams p) {
     return c < n_items_die ? wave_stride + c : n_items_die;
   };
   int t_first = static_cast<int>(sc.wg - sc.n_gpart) * kFwdWaves + w.wv;  // first item of this wave
+  if constexpr (kMode == kDrop) {
+    // every item takes the recurrence: no stream to run and no list to keep
+    for (int t = t_first; t < n_items_die; t += wave_stride)
+      item_by_recurrence<kMode>(p, __builtin_amdgcn_readfirstlane(t));
+    return;
+  }
   if (dyn && was_global) t_first = claim();
   const int t_item = __builtin_amdgcn_readfirstlane(t_first);
   if (t_item >= n_items_die) return;
@@ -1198,15 +1072,15 @@ void fwd_kernel_bf16(FwdParams p) {
     n_redo = __builtin_amdgcn_readfirstlane(n_redo + 1);
   };
   // the next item at or after t that takes the pipelined path (others go to the list)
-  auto next_fast = [&](int t, Item& it, int bits_slot) {
+  auto next_fast = [&](int t, Item& it) {
     int found = -1;
     while (t < n_items_die) {
-      make_item<kMode>(p, w, sc, t, it, bits_slot);
+      make_item<kMode>(p, w, sc, t, it);
       if (it.cnt > 0 && !it.per_item) {
         found = t;
         break;
       }
-      if (kMode >= kOptions && it.skipped && it.nchunks == 1) {  // nothing to compute: its rows are written here
+      if (kMode == kOptions && it.skipped && it.nchunks == 1) {  // nothing to compute: its rows are written here
         store_zero_rows_bf16(p, it);
       } else {
         push_redo(t);
@@ -1235,7 +1109,7 @@ void fwd_kernel_bf16(FwdParams p) {
     tile_load_async_wave(query_tile(p, __builtin_amdgcn_readfirstlane(cur.bh), __builtin_amdgcn_readfirstlane(cur.j)),
                          cx.lds_k_a, cx.voff);
   }
-  int t_cur = next_fast(t_item, cur, 0);
+  int t_cur = next_fast(t_item, cur);
   int t_nxt = -1;
 #ifdef BB_STAMPS
   st_t[0] = __builtin_readcyclecounter() - tprev;
@@ -1246,16 +1120,10 @@ void fwd_kernel_bf16(FwdParams p) {
     f32x16 sA;
     const RowSumOperand ones(lane_again(lane));
     f32x4 ls[2];
-    DropCtx dc;     // (kDrop)
-    float sum[2];   // (kDrop: this lane's share of the row sums for LSE)
     // what the first pair of an item "finishes": nothing
     auto reset_item_state = [&]() {
       zero_acc(o[0]);
       zero_acc(o[1]);
-      if constexpr (kMode == kDrop) {
-        dc = drop_ctx(p, cur, w.col);
-        sum[0] = sum[1] = 0.f;
-      }
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
         ls[a] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1291,7 +1159,7 @@ void fwd_kernel_bf16(FwdParams p) {
 #ifdef BB_STAMPS
     st_t[2] = __builtin_readcyclecounter() - tprev;
 #endif
-    t_nxt = next_fast(successor(t_cur), nxt, 1);  // (scalar loads only, unless there is a padding mask)
+    t_nxt = next_fast(successor(t_cur), nxt);  // (scalar loads only, unless there is a padding mask)
     TileStreams ts(p, cur, t_nxt >= 0 ? &nxt : nullptr, lane_again(lane));
     int cnt = __builtin_amdgcn_readfirstlane(cur.cnt);  // pairs of the item in work
       reset_item_state();
@@ -1308,35 +1176,25 @@ void fwd_kernel_bf16(FwdParams p) {
     unit_scores(ka[0], qb[0], sA);
     BB_STAMP(0);
 
-    int bits_cur = 0;  // where cur's validity bits are (nxt's: the next of the three places, cyclically)
     for (int i = 0;;) {
       if ((rem_pairs & 3) == 3 || i == 0) set_issue_priority(rem_pairs);
-      // (the address of the bits is written out in the calls: named, it is kept in vector registers)
-      if constexpr (kMode == kDrop)
-        pair_step_drop(cx, so, to, qb, ka, va, sA, p3, o, dc, __builtin_amdgcn_readlane(cur.kl, i), ones, ls, sum,
-                       ts.k(i + 1), ts.v(i + 1), ts.k(i + 2),
-                       (cur.partial >> i) & 1 ? key_bits_all[w.wv][bits_cur][i] : nullptr);
-      else
-        pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
+      pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
       rem_pairs = __builtin_amdgcn_readfirstlane(rem_pairs - 1);
       i = __builtin_amdgcn_readfirstlane(i + 1);
       if (__builtin_expect(i < cnt, 1)) continue;  // (the register allocator should favour the pairs)
 
       // ---- item boundary.  The last unit's share of O, the row sums, the range check.
       BB_STAMP(1);
-      if constexpr (kMode == kDrop)
-        unit_pv(va[1], p3, o[1]);
-      else
-        unit_pv(va[1], p3, o[1], ones, ls[1]);
+      unit_pv(va[1], p3, o[1], ones, ls[1]);
       bool bad = false;
       float inv[2], lse[2], lsum[2];
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const float l = row_total(ls[q], w.col);
         bad |= !(l >= kSumLo && l <= kSumHi);
-        lsum[q] = kMode == kDrop ? half_sum(sum[q]) : l;
-        inv[q] = (kMode == kDrop ? p.drop.rs : 1.f) / l;
-        lse[q] = fast_log2(lsum[q]) * kLn2;
+        lsum[q] = l;
+        inv[q] = 1.f / l;
+        lse[q] = fast_log2(l) * kLn2;
       }
       const bool redo_cur = __any(bad);
       if (redo_cur) push_redo(t_cur);
@@ -1346,7 +1204,7 @@ void fwd_kernel_bf16(FwdParams p) {
       int t_nn = -1;
       BB_STAMP(2);
       if (t_nxt >= 0) {
-        t_nn = next_fast(successor(t_nxt), nn, bits_cur == 0 ? 2 : bits_cur - 1);
+        t_nn = next_fast(successor(t_nxt), nn);
         BB_STAMP(3);
         // The next item's query tile is in the K buffer, its first K tile in the V buffer (the
         // second half may still be landing).  Both go to registers, its first V tile is requested,
@@ -1380,7 +1238,6 @@ void fwd_kernel_bf16(FwdParams p) {
 
       // ---- the next item's stream starts (its K(0) fragments are in registers, V(0) is in flight)
       cur = nxt;
-      bits_cur = __builtin_amdgcn_readfirstlane(bits_cur == 2 ? 0 : bits_cur + 1);
       t_cur = t_nxt;
       nxt = nn;
       t_nxt = t_nn;

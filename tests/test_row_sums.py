@@ -1,5 +1,5 @@
 """GPU test: row sums of the bf16 forward on calls whose softmax is summed in fp32 before the
-probabilities are rounded: rows that attend a block with padded keys inside.
+probabilities are rounded: rows that attend a block with padded keys inside, and all rows under dropout.
 
 One key holds nearly all of every row, with a probability of another size in every row, so that the
 rounding of that probability to bf16 (up to 2^-8 of it) shows in whatever is summed or divided after it.
@@ -57,3 +57,28 @@ def test_lse_of_rows_with_a_cut_block(B, H, n, w, r, skip, cut):
         m = A.sum(axis=1) - A[:, cut:cut + 20].sum(axis=1)
         err = np.abs(got[:, h] - np.log(np.exp(l[:, h]) + m - 1)).max()
         assert err <= 2e-5, (h, err)
+
+
+@pytest.mark.parametrize("B,H,n,w,r", [
+    (1, 2, 1024, 3, 3),    # a workgroup per row
+    (2, 10, 1664, 3, 3),   # non-global rows by single waves
+    (1, 10, 2048, 15, 4),  # cut rows: non-global rows of more than 16 blocks,
+    (1, 2, 8192, 3, 3),    # global rows of more than 64,
+    (2, 12, 4096, 3, 3),   # global rows of 64 at a size where they are cut finer
+])
+def test_dropout_output_of_dominated_rows(B, H, n, w, r):
+    """Attention dropout at its smallest rate (2^-15): wherever k* is kept, O is V[k*] but for 1e-4 (the other
+    keys: up to 8191 e^-18), so that its bf16 value is +-1 exactly; a numerator and a divisor that round the
+    probability of k* differently would give 1 -+ 2^-8.  LSE in fp32 as without dropout."""
+    import torch
+    (Q, K, V), l = dominated(B, H, n, 18.0, 21.0, 6)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, 2, w, r, 4)
+    O, LSE = bb.bigbird_attn_fwd_dropout(Q, K, V, torch.from_numpy(ridx).to("cuda:0"), g=2, w=w, scale=0.125,
+                                         p_drop=2.0 ** -15, seed=99)
+    want = V[:, :, KEY:KEY + 1, :].float()
+    wrong = (O.float() != want).any(dim=3).cpu().numpy()  # [B, H, n]
+    for b, h, i in zip(*np.nonzero(wrong)):  # few: the rows that dropped k*
+        keep, _ = bb.bigbird_dropout_keep_mask(2.0 ** -15, 99, b * H + h, n, int(i), 1)
+        assert not keep[0, KEY], (b, h, i, O[b, h, i, :4])
+    assert wrong.sum() <= 16 + wrong.size // 4096
+    assert np.abs(to_host(LSE) - l).max() <= 2e-4
