@@ -203,10 +203,11 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
       int avail = slots_per_die - n_global;
       if (avail < 16) avail = 32;  // the global rows alone fill the die: queue behind them
       q.p_wgs = want < avail ? want : avail;
-      // a wave lists the items it has to redo by the exact recurrence in one register, a lane per
-      // item: no wave may be given more than 64 items, whatever that does to residency
-      const int per_wave_cap = 64;
-      const int floor_wgs = (q.bh_rounds * q.n_sitems + 4 * per_wave_cap - 1) / (4 * per_wave_cap);
+      // a wave lists the items it has to redo by the exact recurrence in one register: no wave may be
+      // given more than the list takes, and together the lists have to take every item, whatever that
+      // does to residency
+      const int per_wg = 4 * bb::kListedItems;
+      const int floor_wgs = (q.bh_rounds * q.n_sitems + per_wg - 1) / per_wg;
       if (q.p_wgs < floor_wgs) q.p_wgs = floor_wgs;
     }
     p.cmb_g_rows = q.ng > 1 ? g : 0;

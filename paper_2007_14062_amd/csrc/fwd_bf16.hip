@@ -1063,8 +1063,9 @@ void fwd_kernel_bf16(FwdParams p) {
   // ---- persistent wave: the die's non-global items t_item, t_item + wave_stride, ...
   // Items that cannot take the pipelined path (no key block at all, padded keys inside a block,
   // or -- found out afterwards -- row sums outside the safe range) are put on a list and done
-  // by the classical recurrence when the stream has ended; the host sizes the grid so that a
-  // wave has at most 64 items (a lane of `redo` each).
+  // by the classical recurrence when the stream has ended (a lane of `redo` each).  Items dealt out: the
+  // host sizes the grid so that a wave has at most kListedItems.  Items claimed: a wave with that many
+  // on its list takes no more; the one or two it still has in flight find room behind them.
   int redo = 0;       // the list: lane t holds the number of the t-th such item
   int n_redo = 0;
   auto push_redo = [&](int t) {
@@ -1086,7 +1087,7 @@ void fwd_kernel_bf16(FwdParams p) {
         push_redo(t);
       }
       if (dyn) {
-        if (n_redo >= 64) break;  // the list is full: this wave takes no more items, the others do
+        if (n_redo >= kListedItems) break;  // this wave takes no more items, the others do
         t = claim();
       } else {
         t += wave_stride;
@@ -1095,7 +1096,7 @@ void fwd_kernel_bf16(FwdParams p) {
     return __builtin_amdgcn_readfirstlane(found);
   };
   // where the search for the item after item t begins
-  auto successor = [&](int t) { return dyn ? (n_redo < 64 ? claim() : n_items_die) : t + wave_stride; };
+  auto successor = [&](int t) { return dyn ? (n_redo < kListedItems ? claim() : n_items_die) : t + wave_stride; };
 
   // cur: the item in work; nxt: the one after it (its list is needed before cur's last pairs,
   // which fetch its first tiles); nn: the one after that, built while few loads are in flight.

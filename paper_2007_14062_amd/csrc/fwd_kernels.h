@@ -14,6 +14,9 @@ namespace bb {
 // A global row longer than 64 key blocks takes several workgroups whose merged partial
 // results go through the merge kernel, as do sparse rows with more than one slice.
 constexpr int kGlobalWaveLen = 16;  // most key blocks a wave of a global workgroup takes
+// Items a wave may put on its list of items to redo before it stops taking others: a lane of one register
+// each, less the two that can still be in flight (the item in work and the next).
+constexpr int kListedItems = 62;
 constexpr int kCounterStride = 32;  // ints between the item counters of two dies (a 128-byte line each)
 struct Bf16Geom {
   int by_row;    // small launches: every row is done the way global rows are, a workgroup per row; no

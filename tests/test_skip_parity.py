@@ -131,3 +131,34 @@ def test_cfg3_shape_per_batch_entry():
         worst_l = max(worst_l, np.abs(Lh[fin] - Lo[0, 0][fin]).max())
     print(f"cfg3 with skipped query blocks: max|dO|={worst_o:.3e} max|dLSE|={worst_l:.3e}")
     assert worst_o <= TOL["bf16"] and worst_l <= TOL["bf16"]
+
+
+def test_lists_of_claimed_items_keep_room_for_the_items_in_flight():
+    """Claimed items, more than the resident waves' lists hold (520 slices of 256 blocks, two key blocks a
+    row), every one of them for the list: three rows of four attend a cut block, the others leave the
+    range of the fixed reference, which a wave finds out after it has taken them.  Each row is written, and
+    right: fp32 attention of every row but those of the global block."""
+    import torch
+    assert torch.cuda.is_available()
+    B, H, n = 65, 8, 16384
+    nb = n // 64
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    Q, K, V = (torch.randn((B, H, n, 64), generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(3))
+    Q *= 8
+    K *= 8
+    km = torch.ones((B, n), dtype=torch.uint8, device="cuda:0")
+    km.view(B, nb, 64)[:, torch.arange(nb, device="cuda:0") % 4 != 0, 5] = 0
+    O = torch.full_like(Q, float("nan"))
+    LSE = torch.full((B, H, n), float("nan"), device="cuda:0")
+    bb.bigbird_attn_fwd(Q, K, V, None, g=1, w=1, scale=0.125, key_padding_mask=km, O=O, LSE=LSE,
+                        global_mode=bb.BB_GLOBAL_LEADING | bb.BB_SKIP_PADDED_QUERY_BLOCKS)
+    assert not torch.isnan(LSE).any() and not torch.isnan(O).any()
+    for b in range(B):
+        q, k, v = (x[b].float().view(H, nb, 64, 64) for x in (Q, K, V))
+        keys, values = (torch.cat((x[:, :1].expand(-1, nb - 1, -1, -1), x[:, 1:]), dim=2) for x in (k, v))
+        s = torch.matmul(q[:, 1:], keys.transpose(2, 3).contiguous()) * 0.125
+        m = km[b].view(nb, 64)
+        s.masked_fill_((torch.cat((m[:1].expand(nb - 1, -1), m[1:]), dim=1) == 0)[None, :, None, :], float("-inf"))
+        assert (torch.softmax(s, dim=3).matmul(values) - O[b].float().view(H, nb, 64, 64)[:, 1:]).abs().max() <= 5e-2
+        assert (torch.logsumexp(s, dim=3) - LSE[b].view(H, nb, 64)[:, 1:]).abs().max() <= 2e-2
