@@ -86,7 +86,7 @@ struct BwdParams {
   const uint8_t* kmask;
   // written by the dQ kernel for the dK/dV kernel
   float* Dvec;     // [B*H*n]  bf16: -D_i, D_i = sum_c dO_ic O_ic; fp32: D_i
-  float* Lvec;     // [B*H*n]  bf16: -LSE_i / scale, -inf for rows without a valid key; fp32: LSE_i * log2(e), +inf
+  float* Lvec;     // [B*H*n]  LSE_i * log2(e), +inf for rows without a valid key
   int* key_order;  // bf16: [H][nb] non-global key blocks by falling length of their query-block lists
   uint32_t* query_sets;  // bf16: [H][nb][kSetWords] query blocks that attend a non-global key block, as bits
   unsigned inverse_wgs;  // bf16: workgroups of the dQ launch that make these (a multiple of the dies)

@@ -302,7 +302,7 @@ void bwd_dq_kernel(BwdParams p) {
   asm volatile("" ::: "memory");
   if (it.chunk == 0 && wv == 0) {
     p.Dvec[row0 + lane] = -dvals[lane];  // negated: the other kernel starts its dP accumulators from it
-    p.Lvec[row0 + lane] = lse == __builtin_inff() ? neg_inf() : -lse / p.c;  // (its S accumulators: from this)
+    p.Lvec[row0 + lane] = lse;
   }
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
@@ -464,10 +464,11 @@ void bwd_dq_kernel(BwdParams p) {
 // ---------------------------------------------------------------------------------------
 // Wave wv owns 32 keys of the block; the list's Q and dO tiles come in halves of 32 queries through a ring
 // of four places in LDS that both waves read, one barrier per half.  Stages of half h, in issue order:
-//   A(h)  dK^T += Q^T dS of half h-1 and dP = dO V^T (8 MFMAs), beside P = 2^(S c) and its conversion
+//   A(h)  dK^T += Q^T dS of half h-1 and dP = dO V^T (8 MFMAs), beside P = 2^(S c - LSE log2e) and its conversion
 //   B(h)  dV^T += dO^T P and S = Q K^T of half h+1 (8 MFMAs), beside dS = P o dP and its conversion
-// S starts from -LSE / scale and dP from -D, staged with the tiles (element r of an accumulator belongs to
-// query row acc_row(r)), so neither subtraction costs a vector instruction.  Operands are read from LDS one
+// dP starts from -D, staged with the tiles (element r of an accumulator belongs to query row acc_row(r)), and
+// LSE log2(e) rides in the fma that scales S, so neither subtraction costs a vector instruction.  (S does not
+// start from -LSE / scale: that rounds every product at the size of LSE / scale, and overflows for small scales.)  Operands are read from LDS one
 // stage before their use; a half is requested three halves ahead.
 // What bounds it: issue slots of the vector port, where an MFMA takes 17 cycles, an exponential 7 to 9, a
 // conversion 5 and other instructions 3 (measured, two waves per SIMD): 2340 cycles per block pair and
@@ -505,7 +506,7 @@ template <bool kDrop, int kTeams>
 __global__ __launch_bounds__(kDkvThreads * kTeams) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_dkv_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(1024))) char ring_all[kTeams][kRing][2][kHalfTile];  // Q half, dO half
-  __shared__ __attribute__((aligned(256))) float lds_l_all[kTeams][kRing][kBlk];         // -LSE / scale of the whole block
+  __shared__ __attribute__((aligned(256))) float lds_l_all[kTeams][kRing][kBlk];         // LSE log2(e) of the whole block
   __shared__ __attribute__((aligned(256))) float lds_d_all[kTeams][kRing][kBlk];         // -D
   __shared__ __attribute__((aligned(256))) uint32_t lds_rk_all[kTeams][kDrop ? kRing : 1][kBlk];
   __shared__ int jlist[kMaxBwdBlocks];
@@ -593,8 +594,8 @@ void bwd_dkv_kernel(BwdParams p) {
 
     const float c = p.c;
     bf16x8 qs[4], dos[4], qt[2][2], dot[2][2], pb[2], dsb[2];
-    f32x16 s, dp;
-    // rows of an accumulator that starts from a staged vector
+    f32x16 s, dp, lse;  // (lse: the elements of the staged vector that belong to s)
+    // the rows of an accumulator, from a staged vector
     auto start_from = [&](const float* vec, f32x16& acc) {
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
@@ -620,7 +621,9 @@ void bwd_dkv_kernel(BwdParams p) {
     };
     // S of half 0; what A(0) "finishes": nothing
     read_straight_half(so, ring[0][0], 0, qs);
-    start_from(lds_l[0], s);
+    start_from(lds_l[0], lse);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
     add_products(qs, kb, s);
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
@@ -672,7 +675,7 @@ void bwd_dkv_kernel(BwdParams p) {
       add_transposed(qt, dsb, dk);
       add_products(dos, vb, dp);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = fast_exp2(s[r] * c);
+      for (int r = 0; r < 16; ++r) s[r] = fast_exp2(__builtin_fmaf(s[r], c, -lse[r]));
       if constexpr (kDrop) {
         // this lane's key against the queries of its accumulator rows: the kept probabilities go to dV,
         // and dP becomes M / (1 - p) o dP - D  (the staged vector holds -D)
@@ -700,7 +703,9 @@ void bwd_dkv_kernel(BwdParams p) {
       // ---- B(h)
       f32x16 s_new;
       read_straight_half(so, ring[next][0], 0, qs);
-      start_from(lds_l[next] + row1, s_new);
+      start_from(lds_l[next] + row1, lse);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_new[r] = 0.f;
       read_transposed_half(to, ring[here][0], 0, qt);
       j_next = entry(hh + 4);
       add_transposed(dot, pb, dv);

@@ -372,3 +372,13 @@ def test_small_launches_by_blocks_bf16(B, H, n, g, w, r, drop, padded):
     for x, y in zip(grads, ref):
         err = np.abs(to_host(x) - y).max()
         assert err <= TOL, err
+
+
+@pytest.mark.parametrize("scale", [1e-38, 1e-44, 1e-30])
+@pytest.mark.parametrize("B,H,n", [(1, 2, 640), (2, 10, 1088)])  # a workgroup per block; past that
+def test_scales_whose_lse_quotient_overflows(B, H, n, scale):
+    """Any finite scale > 0: LSE (about 6) over these scales is past the fp32 range, or close to it.  The
+    probabilities are uniform, dV their sums of dO rows (bf16 tolerance), dQ and dK vanish."""
+    t = inp.make_tensors(B, H, n, 64, 19, "bf16", with_dO=True)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, 2, 3, 3, 5)
+    check_full(t, ridx, 64, 2, 3, scale, tag=f"scale {scale}")
