@@ -72,9 +72,10 @@ def test_full_coverage_long_lists():
     check_full(t, empty, 64, nb, 1, 0.125, tag="bwd full coverage (all global)")
 
 
+@pytest.mark.parametrize("H", [2, 20])  # a workgroup per block; a wave (two waves) per item (here and below)
 @pytest.mark.parametrize("g,w,r", [(0, 1, 0), (1, 1, 0), (0, 3, 2), (2, 3, 0), (1, 7, 4)])
-def test_degenerate_patterns(g, w, r):
-    B, H, n = 1, 2, 1024
+def test_degenerate_patterns(g, w, r, H):
+    B, n = 1, 1024
     t = inp.make_tensors(B, H, n, 64, 19, "bf16", with_dO=True)
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 3)
     check_full(t, ridx, 64, g, w, 0.125, tag=f"bwd g{g} w{w} r{r}")
@@ -116,8 +117,9 @@ def test_single_block_sequence():
     check_full(t, empty, 64, 0, 1, 0.125, tag="bwd nb=1 window")
 
 
-def test_table_with_duplicates_and_negative_entries():
-    B, H, n, g, w, r = 1, 2, 1024, 2, 3, 4
+@pytest.mark.parametrize("H", [2, 20])
+def test_table_with_duplicates_and_negative_entries(H):
+    B, n, g, w, r = 1, 1024, 2, 3, 4
     t = inp.make_tensors(B, H, n, 64, 21, "bf16", with_dO=True)
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 5)
     ridx[0, 5] = [-1, 9, 9, 12]
@@ -127,8 +129,9 @@ def test_table_with_duplicates_and_negative_entries():
     check_full(t, ridx, 64, g, w, 0.125, tag="bwd dirty table")
 
 
-def test_key_padding_gradients():
-    B, H, n, g, w, r = 3, 2, 1024, 2, 3, 3
+@pytest.mark.parametrize("H", [2, 8])
+def test_key_padding_gradients(H):
+    B, n, g, w, r = 3, 1024, 2, 3, 3
     t = inp.make_tensors(B, H, n, 64, 22, "bf16", with_dO=True)
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 6)
     km = np.ones((B, n), dtype=np.uint8)
@@ -145,10 +148,11 @@ def test_key_padding_gradients():
     assert (dQh[2] == 0).all()
 
 
-def test_runs_are_bit_reproducible():
+@pytest.mark.parametrize("H", [3, 6])
+def test_runs_are_bit_reproducible(H):
     torch = torch_mod()
-    t = inp.make_tensors(2, 3, 2048, 64, 23, "bf16", with_dO=True)
-    ridx = bb.bigbird_make_rand_idx(3, 2048, 64, 2, 3, 3, 2)
+    t = inp.make_tensors(2, H, 2048, 64, 23, "bf16", with_dO=True)
+    ridx = bb.bigbird_make_rand_idx(H, 2048, 64, 2, 3, 3, 2)
     a = run_fwd_bwd(t, ridx, 2, 3, 0.125)
     b_ = run_fwd_bwd(t, ridx, 2, 3, 0.125)
     for x, y in zip(a, b_):
@@ -324,10 +328,11 @@ def test_fp32_slices(B, H, nb, g, w, r):
 
 
 @pytest.mark.parametrize("nb,g,w,r", [(1, 0, 1, 0), (2, 1, 1, 0), (3, 0, 3, 0), (7, 0, 1, 1), (65, 2, 3, 3), (66, 1, 5, 17)])
-def test_list_lengths(nb, g, w, r):
+@pytest.mark.parametrize("H", [3, 6])
+def test_list_lengths(nb, g, w, r, H):
     """Key lists of 1, 2, 3 ... blocks and across a 16-block slice, inverse lists of 0 .. nb blocks: every row
     of one head names the same blocks, in another head no row names any."""
-    B, H, n = 1, 3, nb * 64
+    B, n = 1, nb * 64
     t = inp.make_tensors(B, H, n, 64, 60 + nb, "bf16", with_dO=True)
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 5)
     if r:

@@ -20,7 +20,7 @@ from gpu_util import to_host
 
 pytestmark = pytest.mark.gpu
 
-B, H, n, b, g, w, r = 1, 2, 1024, 64, 2, 3, 3
+B, n, b, g, w, r = 1, 1024, 64, 2, 3, 3
 SCALE, P_DROP, SEED = 0.125, 0.1, 0xC0FFEE1234
 
 
@@ -30,7 +30,7 @@ def _dev(x):
     return torch.from_numpy(bits.view(np.int16)).to("cuda:0").view(torch.bfloat16)
 
 
-def _onehot():
+def _onehot(H):
     x = np.zeros((B, H, n, 64), dtype=np.float32)
     x[:, :, np.arange(n), np.arange(n) % 64] = 1.0
     return x
@@ -49,7 +49,8 @@ def _run(Q, K, V, dO, ridx_h):
     return to_host(O), [to_host(x) for x in grads], Oo, ref
 
 
-def test_every_mask_bit_shows_in_the_outputs():
+@pytest.mark.parametrize("H", [2, 20])  # a workgroup per row and block; a wave (two waves) per item
+def test_every_mask_bit_shows_in_the_outputs(H):
     import torch
     assert torch.cuda.is_available()
     ridx_h = bb.bigbird_make_rand_idx(H, n, b, g, w, r, 21)
@@ -61,17 +62,17 @@ def test_every_mask_bit_shows_in_the_outputs():
     rnd = rng.standard_normal((B, H, n, 64)).astype(np.float32)
 
     # forward and dV: Q = 0; V and dO one-hot by position modulo 64
-    O, G, Oo, ref = _run(zeros, rnd, _onehot(), _onehot(), ridx_h)
+    O, G, Oo, ref = _run(zeros, rnd, _onehot(H), _onehot(H), ridx_h)
     assert np.abs(O - Oo).max() < 0.25 * step, np.abs(O - Oo).max() / step
     assert np.abs(G[2] - ref[2]).max() < 0.25 * step, np.abs(G[2] - ref[2]).max() / step
     # the steps are really there: the oracle without dropout differs by many of them
-    O_plain, _ = oracle.attn_fwd(zeros, rnd, _onehot(), ridx_h, b, g, w, SCALE)
+    O_plain, _ = oracle.attn_fwd(zeros, rnd, _onehot(H), ridx_h, b, g, w, SCALE)
     assert np.abs(Oo - O_plain * rs).max() > 2 * step
 
     # dQ: Q = 0, K one-hot, dO . V = 1 for every pair
-    O, G, Oo, ref = _run(zeros, _onehot(), ones, ones / 64.0, ridx_h)
+    O, G, Oo, ref = _run(zeros, _onehot(H), ones, ones / 64.0, ridx_h)
     assert np.abs(G[0] - ref[0]).max() < 0.25 * SCALE * step, np.abs(G[0] - ref[0]).max() / (SCALE * step)
 
     # dK: K = 0, Q one-hot, dO . V = 1 for every pair
-    O, G, Oo, ref = _run(_onehot(), zeros, ones, ones / 64.0, ridx_h)
+    O, G, Oo, ref = _run(_onehot(H), zeros, ones, ones / 64.0, ridx_h)
     assert np.abs(G[1] - ref[1]).max() < 0.25 * SCALE * step, np.abs(G[1] - ref[1]).max() / (SCALE * step)

@@ -89,10 +89,11 @@ def test_long_rows_and_wide_patterns_bf16():
     t = inp.make_tensors(B, H, n, 64, 303, "bf16", with_dO=True)
     ridx = bb.bigbird_make_rand_idx(H, n, 64, 2, 3, 3, 11)
     check(t, ridx, 64, 2, 3, 0.125, 0.1, 42, "bf16", tag="dropout n=8192")
-    B, H, n, g, w, r = 1, 2, 2048, 2, 15, 4
-    t = inp.make_tensors(B, H, n, 64, 304, "bf16", with_dO=True)
-    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 12)
-    check(t, ridx, 64, g, w, 0.125, 0.5, 43, "bf16", tag="dropout wide pattern")
+    for H in (2, 10):  # a workgroup per row or block; waves' items, cut into slices of 16 blocks
+        B, n, g, w, r = 1, 2048, 2, 15, 4
+        t = inp.make_tensors(B, H, n, 64, 304, "bf16", with_dO=True)
+        ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 12)
+        check(t, ridx, 64, g, w, 0.125, 0.5, 43, "bf16", tag=f"dropout wide pattern H{H}")
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -166,7 +167,7 @@ def test_training_shape_sampled_rows_and_gradient_properties():
     (1664, True, 1.0),
     (1664, False, 40.0),  # row sums that leave the range of the fixed reference: the recurrence
 ])
-def test_pipelined_forward_with_padding(n, skip, spread):
+def test_forward_with_padding(n, skip, spread):
     """Forward under dropout on masked batches: a block cut inside, holes, a single valid key, against the
     oracle; rows of every query block."""
     torch = torch_mod()

@@ -199,28 +199,36 @@ def _scaled_key_blocks(t, factors):
     return out
 
 
+@pytest.mark.parametrize("H,mask", [(2, ""), (20, ""), (20, "masked"), (20, "skip")])  # a workgroup per row; waves' streams
 @pytest.mark.parametrize("case", ["growing", "decreasing", "growing_hot", "decreasing_hot"])
-def test_row_maxima_that_move_along_the_key_list(case):
+def test_row_maxima_that_move_along_the_key_list(case, H, mask):
     """Logits whose size changes from key block to key block, so that a row's maximum moves (up or
     down) several times along its key list.  At scale 0.125 the sums stay in the range of the
     fixed-reference path; the `hot` cases (scale 1.0: logits up to about +-150) leave it, the
     items are redone by the running-maximum recurrence, block after block with a finite running
     maximum, and the backward has to reproduce probabilities from LSE values of that size.
-    Forward and backward compared in full."""
-    B, H, n, g, w, r = 1, 2, 1024, 2, 3, 3
+    Forward and backward compared in full.  Masked: a cut block, a padded tail and whole blocks in front."""
+    B, n, g, w, r = 1, 1024, 2, 3, 3
     nb = n // 64
     t = inp.make_tensors(B, H, n, 64, 77, "bf16", with_dO=True)
     up = [1.0 + k / 4.0 for k in range(nb)]
     t = _scaled_key_blocks(t, up if case.startswith("growing") else up[::-1])
     scale = 1.0 if case.endswith("hot") else 0.125
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 5)
-    dev, O, LSE = _fwd(t, ridx, g, w, scale)
-    Oref, Lref = oracle.attn_fwd(t["Q"], t["K"], t["V"], ridx, 64, g, w, scale)
+    km, mode, ref_kw = None, 0, {}
+    if mask:
+        km = np.ones((B, n), dtype=np.uint8)
+        km[0, 128:256] = 0
+        km[0, 900:] = 0
+        mode = bb.BB_SKIP_PADDED_QUERY_BLOCKS if mask == "skip" else 0
+        ref_kw = dict(key_mask=km, skip_padded_query_blocks=mask == "skip")
+    dev, O, LSE = _fwd(t, ridx, g, w, scale, km, mode)
+    Oref, Lref = oracle.attn_fwd(t["Q"], t["K"], t["V"], ridx, 64, g, w, scale, **ref_kw)
     eo, el = _fwd_errors(to_host(O), to_host(LSE), Oref, Lref)
     print(f"{case}: |LSE|max={np.abs(Lref).max():.1f} max|dO|={eo:.3e} max|dLSE|={el:.3e}")
     assert eo <= TOL and el <= TOL
-    hQ, hK, hV = _bwd(dev, O, LSE, t, g, w, scale)
-    ref = oracle.attn_bwd(t["Q"], t["K"], t["V"], t["dO"], ridx, 64, g, w, scale)
+    hQ, hK, hV = _bwd(dev, O, LSE, t, g, w, scale, mode)
+    ref = oracle.attn_bwd(t["Q"], t["K"], t["V"], t["dO"], ridx, 64, g, w, scale, **ref_kw)
     errs = [np.abs(got - want).max() for got, want in zip((hQ, hK, hV), ref)]
     mags = [np.abs(want).max() for want in ref]
     print(f"{case}: max|ddQ|={errs[0]:.3e} max|ddK|={errs[1]:.3e} max|ddV|={errs[2]:.3e} "

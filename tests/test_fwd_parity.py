@@ -86,9 +86,10 @@ def test_full_coverage_equals_full_attention(dtype):
     assert np.abs(to_host(O) - to_host(O2)).max() <= TOL[dtype]
 
 
+@pytest.mark.parametrize("H", [2, 20])  # a workgroup per row; waves' streams (here and below)
 @pytest.mark.parametrize("g,w,r", [(0, 1, 0), (1, 1, 0), (0, 3, 2), (2, 3, 0), (1, 7, 4)])
-def test_degenerate_patterns(g, w, r):
-    B, H, n = 1, 2, 1024
+def test_degenerate_patterns(g, w, r, H):
+    B, n = 1, 1024
     t = inp.make_tensors(B, H, n, 64, 9, "bf16")
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 3)
     check_full(t, ridx, "bf16", 64, g, w, 0.125, tag=f"g{g} w{w} r{r}")
@@ -120,9 +121,10 @@ def test_single_block_sequence():
     check_full(t, empty, "f32", 64, 0, 1, 0.125, tag="nb=1 window")
 
 
-def test_table_with_duplicates_and_negative_entries():
+@pytest.mark.parametrize("H", [2, 20])
+def test_table_with_duplicates_and_negative_entries(H):
     """Entries < 0 are ignored; entries repeating the window, a global block or each other count once."""
-    B, H, n, g, w, r = 1, 2, 1024, 2, 3, 4
+    B, n, g, w, r = 1, 1024, 2, 3, 4
     t = inp.make_tensors(B, H, n, 64, 11, "bf16")
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 5)
     ridx[0, 5] = [-1, 9, 9, 12]
@@ -149,12 +151,13 @@ def test_key_padding_unaligned_and_empty_rows(dtype):
 
 @pytest.mark.parametrize("tail", [1, 2, 31, 32, 33, 63])
 @pytest.mark.parametrize("mode,g,r", [(bb.BB_GLOBAL_FIRST_LAST, 2, 3), (bb.BB_GLOBAL_LEADING, 3, 0)])
-def test_blocks_with_padded_keys_inside(tail, mode, g, r):
+@pytest.mark.parametrize("H", [2, 8])
+def test_blocks_with_padded_keys_inside(tail, mode, g, r, H):
     """bf16: validity ends `tail` keys into a block, at the edges of the 32-key units; a hole of every
     residue; a whole sequence of `tail` keys (rows with no full block); mask bytes of any non-zero value;
     K rows of padded keys hold NaN.  (Same tolerance as everywhere: the keys left out change nothing else.)"""
     torch = torch_mod()
-    B, H, n, w = 3, 2, 1024, 3
+    B, n, w = 3, 1024, 3
     t = inp.make_tensors(B, H, n, 64, 40 + tail, "bf16")
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 6, mode)
     km = np.full((B, n), 0x80, dtype=np.uint8)
@@ -221,11 +224,11 @@ def test_zero_queries_closed_form_and_pattern_readback():
             assert np.abs(Lh[0, h, j * 64:(j + 1) * 64] - math.log(cnt)).max() < 1e-5
 
 
-def test_runs_are_bit_reproducible():
+@pytest.mark.parametrize("H", [3, 6])
+def test_runs_are_bit_reproducible(H):
     torch = torch_mod()
-    wl = inp.WORKLOADS["cfg1_fp32_small"]
-    t = inp.make_tensors(2, 3, 2048, 64, 13, "bf16")
-    ridx = bb.bigbird_make_rand_idx(3, 2048, 64, 2, 3, 3, 2)
+    t = inp.make_tensors(2, H, 2048, 64, 13, "bf16")
+    ridx = bb.bigbird_make_rand_idx(H, 2048, 64, 2, 3, 3, 2)
     O1, L1 = run_fwd(t, ridx, "bf16", 2, 3, 0.125)
     O2, L2 = run_fwd(t, ridx, "bf16", 2, 3, 0.125)
     assert torch.equal(O1.view(torch.int16), O2.view(torch.int16)) and torch.equal(L1, L2)

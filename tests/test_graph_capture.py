@@ -13,11 +13,12 @@ from gpu_util import device_qkv
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("H", [3, 6])  # 192 rows: a workgroup each; 384: waves' streams, items claimed
 @pytest.mark.parametrize("masked", [False, True])
-def test_replays_equal_eager_calls(masked):
+def test_replays_equal_eager_calls(masked, H):
     import torch
     assert torch.cuda.is_available()
-    B, H, n, g, w, r = 2, 3, 2048, 2, 3, 3
+    B, n, g, w, r = 2, 2048, 2, 3, 3
     sets = [device_qkv(inp.make_tensors(B, H, n, 64, 500 + i, "bf16"), "bf16") for i in range(3)]
     ridx = torch.from_numpy(bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 8)).to("cuda:0")
     km = None

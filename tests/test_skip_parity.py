@@ -73,10 +73,11 @@ def test_suffix_padding_and_holes(dtype):
     check(t, ridx, 64, 2, 3, 0.125, dtype, km, tag=f"skip {dtype}")
 
 
-def test_leading_globals_wide_pattern_bf16():
+@pytest.mark.parametrize("H", [2, 5])  # a workgroup per row or block; waves' items
+def test_leading_globals_wide_pattern_bf16(H):
     """Non-global rows of more than 16 key blocks (partial results + merge) and leading global
     blocks, one of which is fully padded in one batch entry."""
-    B, H, n, g, w, r = 2, 2, 2048, 3, 15, 4
+    B, n, g, w, r = 2, 2048, 3, 15, 4
     t = inp.make_tensors(B, H, n, 64, 402, "bf16", with_dO=True)
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 6, bb.BB_GLOBAL_LEADING)
     km = inp.lengths_to_key_mask(np.array([1500, n]), n)
@@ -84,8 +85,9 @@ def test_leading_globals_wide_pattern_bf16():
     check(t, ridx, 64, g, w, 0.125, "bf16", km, mode=bb.BB_GLOBAL_LEADING, tag="skip wide")
 
 
-def test_with_dropout_bf16():
-    B, H, n = 2, 2, 1024
+@pytest.mark.parametrize("H", [2, 10])
+def test_with_dropout_bf16(H):
+    B, n = 2, 1024
     t = inp.make_tensors(B, H, n, 64, 403, "bf16", with_dO=True)
     ridx = bb.bigbird_make_rand_idx(H, n, 64, 2, 3, 3, 7)
     km = inp.lengths_to_key_mask(np.array([700, 320]), n)
