@@ -230,6 +230,23 @@ def test_binding_validator_refuses_wrong_dtypes_and_shapes():
         chk(Q[0], Q[0], Q[0], ridx, km, b)                   # Q not [B, H, n, d]
 
 
+def test_workspace_size_of_a_plain_call_follows_the_values():
+    """The remembered size goes by the values of b, g and w, whatever holds them."""
+    import torch
+    from paper_2007_14062_amd.binding import _workspace_bytes
+    for make in (torch.tensor, np.array):
+        g, w = make(2), make(3)
+        for _ in range(2):
+            assert _workspace_bytes(1, 2, 1024, 64, 64, g, w, 3, True) == \
+                bb.bigbird_attn_workspace_bytes(1, 2, 1024, 64, 64, int(g), int(w), 3, True)
+            g += 5
+            w += 2
+    assert _workspace_bytes(1, 2, 1024, 64, 64, ctypes.c_int(2), 3, 3, False) == \
+        bb.bigbird_attn_workspace_bytes(1, 2, 1024, 64, 64, 2, 3, 3, False)
+    with pytest.raises(ctypes.ArgumentError):
+        _workspace_bytes(1, 2, 1024, 64, 64, 2.0, 3, 3, False)
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures one GPU; any other --gpus value exits with a message and status 2."""
     import subprocess
