@@ -111,11 +111,18 @@ inline int longest_sparse_list(int nb, int g, int w, int r) {
 // 2 .. 4 us there, so a launch that would have fewer than two 8-block slices per compute unit is cut finer,
 // down to one pair per workgroup (n = 1024, 2 heads: forward 42 us with slices of 8, backward kernels
 // 38 and 52; 13, 18 and 27 with slices of one).  0: use the standard slices.
+// A length of 5 and more leaves a rest of one to three blocks of the usual list of 8, in a slice that costs
+// nearly as much as a full one: 5 only where these slices still fit the chip at once (8 slices of n = 1792: forward
+// and backward 37 and 115 us, 44 and 134 with 4), else 4 (8 of n = 2048: 55 and 166 us with 5, 44 and 147 with 4);
+// from 6 on the standard ones (24 of n = 1024: 81 and 215 us with 7, 55 and 175 with 4, 47 and 162 with these).
 inline int fine_slice_f32(int BH, int nb, int g, int w, int r) {
-  const long long pairs =
-      static_cast<long long>(BH) * (static_cast<long long>(g) * nb + static_cast<long long>(nb - g) * longest_sparse_list(nb, g, w, r));
+  const int sparse = longest_sparse_list(nb, g, w, r);
+  const long long pairs = static_cast<long long>(BH) * (static_cast<long long>(g) * nb + static_cast<long long>(nb - g) * sparse);
   const long long len = (pairs + 511) / 512;
-  return len < kChunkGlobal ? static_cast<int>(len < 1 ? 1 : len) : 0;
+  if (len > 5) return 0;
+  if (len == 5)
+    return static_cast<long long>(BH) * (static_cast<long long>(g) * ((nb + 4) / 5) + static_cast<long long>(nb - g) * ((sparse + 4) / 5)) <= 512 ? 5 : 4;
+  return static_cast<int>(len < 1 ? 1 : len);
 }
 
 // len: key blocks per slice of every row; 0: kChunkGlobal / kSparseChunk.

@@ -309,8 +309,13 @@ def test_seeded_sweep_of_small_configurations():
     (1, 1, 1, 0, 1, 0),     # a single pair
     (1, 1, 9, 2, 3, 3),     # one pair per slice, one slice of batch * heads
     (1, 6, 17, 2, 3, 3),    # two pairs per slice, odd number of blocks
-    (2, 9, 21, 3, 5, 2),    # slices of 7: remainders in every list
-    (3, 10, 16, 2, 3, 3),   # just past the fine slices
+    (1, 8, 17, 2, 3, 3),    # slices of 3: remainders in every list
+    (1, 12, 17, 2, 3, 3),   # of 4
+    (1, 8, 28, 2, 3, 3),    # of 5: the launch holds 512 workgroups
+    (2, 9, 13, 3, 5, 2),    # of 4 instead of 5: it would hold more; lists of 10
+    (1, 16, 18, 2, 3, 3),   # the first ones past the fine slices
+    (2, 9, 21, 3, 5, 2),    # standard slices
+    (3, 10, 16, 2, 3, 3),
     (1, 2, 20, 1, 1, 17),   # lists of 19, inverse lists of any length
 ])
 def test_fp32_slices(B, H, nb, g, w, r):

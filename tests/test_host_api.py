@@ -119,6 +119,9 @@ def test_workspace_bytes():
     assert bb.bigbird_attn_workspace_bytes(4, 12, 4100, 64, 64, 2, 3, 3) == 0     # n % b
     small = bb.bigbird_attn_workspace_bytes(1, 1, 512, 64, 64, 2, 3, 3)           # nb = 8: nothing split
     assert small == 0
+    # 24 slices of 16 blocks: standard slices (8 blocks, 96 partial results), also of the fp32 kernels, to
+    # which finer ones of 7 blocks would be a loss
+    assert bb.bigbird_attn_workspace_bytes(2, 12, 1024, 64, 64, 2, 3, 3) < 97 * (64 * 64 + 2 * 64) * 4
     assert (bb.bigbird_attn_workspace_bytes(4, 12, 4096, 64, 64, 2, 3, 3, True)
             >= bb.bigbird_attn_workspace_bytes(4, 12, 4096, 64, 64, 2, 3, 3, False))
 
