@@ -376,6 +376,12 @@ int attn_bwd_impl(const void* Q, const void* K, const void* V, const void* O,
     p.split = bb::make_row_split_by_row(p.BH, p.nb, g, w, r);
     p.kv = bb::make_key_split_by_row(p.nb, g);
   }
+  p.dq_waves = p.by_row ? bb::kRowWaves : 1;
+  if (dtype == BB_BF16 && !p.by_row && bb::dq_two_waves(p.BH, p.split)) {
+    p.dq_waves = 2;
+    const int sparse_ub = bb::longest_sparse_list(p.nb, g, w, r);
+    if (sparse_ub <= p.split.ls) p.split.ls = 2 * ((sparse_ub + 1) / 2);  // whole rows in two equal shares
+  }
   if (dtype == BB_F32) return bb::launch_bwd_f32(p, static_cast<hipStream_t>(hip_stream));
   return bb::launch_bwd_bf16(p, static_cast<hipStream_t>(hip_stream));
 }

@@ -70,6 +70,17 @@ inline bool bwd_by_row(int BH, int nb, int g, int w, int r) {
          longest_sparse_list(nb, g, w, r) <= kRowWaves * kChunkMax;
 }
 
+// Between the small launches and those that put two dQ items on every SIMD: two waves per item, which deal out its
+// list (blocks are lists and slices as before, a slice of up to 16 cut in half), from where a third of the SIMDs
+// would have a wave up to where all have two.  Whole backward, one wave / two: 24 slices of n = 1024 (432 items)
+// 36.7 / 35.4 us, 72 of n = 640 (864) 48 / 43, under dropout 70 / 59 (two waves shared every block of an item before: 49
+// and 70); 36 of n = 1536 (1008) 54 / 48.  Past 1024 items 58 / 58 (48 of n = 1280), 62 / 66 (72 of n = 1024); below 384
+// as often slower as faster (12 of n = 1536, 336 items: 34.2 / 35.4).
+inline bool dq_two_waves(int BH, const RowSplit& s) {
+  const long long items = static_cast<long long>(BH) * s.items_per_bh;
+  return items >= 384 && items <= 1024;
+}
+
 constexpr int kSetWords = kMaxBwdBlocks / 32;
 
 struct BwdParams {
@@ -97,6 +108,7 @@ struct BwdParams {
   float c;      // scale * log2(e)
   float scale;
   int by_row;      // bf16: a workgroup per block (bwd_by_row)
+  int dq_waves;    // bf16: waves of a dQ item: kRowWaves if by_row, else 1 or 2 (dq_two_waves)
   RowSplit split;  // query-row decomposition (dQ kernel), as in the forward
   KeySplit kv;     // key-block decomposition (dK/dV kernel)
   Dropout drop;    // attention dropout of the forward these gradients belong to (thr == 0: none)

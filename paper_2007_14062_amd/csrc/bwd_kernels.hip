@@ -206,8 +206,8 @@ __device__ __forceinline__ void pin_b() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// kWaves: waves of a workgroup.  Large launches: 1, every wave an item of its own.  Small ones: 4 (p.by_row),
-// which deal out the list of one item among themselves and add their shares of dQ in LDS.
+// kWaves: waves of a workgroup.  Large launches: 1, every wave an item of its own.  Smaller ones: 2 (dq_two_waves)
+// or 4 (p.by_row), which deal out the list of one item among themselves and add their shares of dQ in LDS.
 template <bool kDrop, int kWaves>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_dq_kernel(BwdParams p) {
@@ -864,9 +864,10 @@ bool launch_failed(const char* what) {
 int launch_bwd_bf16(const BwdParams& p, hipStream_t stream) {
   const unsigned qgrid = p.inverse_wgs + DieItems(p.BH, p.split.items_per_bh).grid();
   const bool drop = p.drop.thr != 0;
-  const auto dq = p.by_row ? (drop ? bwd_dq_kernel<true, kRowWaves> : bwd_dq_kernel<false, kRowWaves>)
-                           : (drop ? bwd_dq_kernel<true, 1> : bwd_dq_kernel<false, 1>);
-  hipLaunchKernelGGL(dq, dim3(qgrid), dim3(p.by_row ? 64 * kRowWaves : 64), 0, stream, p);
+  const auto dq = p.dq_waves == kRowWaves ? (drop ? bwd_dq_kernel<true, kRowWaves> : bwd_dq_kernel<false, kRowWaves>)
+                  : p.dq_waves == 2       ? (drop ? bwd_dq_kernel<true, 2> : bwd_dq_kernel<false, 2>)
+                                          : (drop ? bwd_dq_kernel<true, 1> : bwd_dq_kernel<false, 1>);
+  hipLaunchKernelGGL(dq, dim3(qgrid), dim3(64 * p.dq_waves), 0, stream, p);
   if (launch_failed("bwd_dq_kernel")) return BB_ERR_LAUNCH;
   const unsigned kvgrid = DieItems(p.BH, p.kv.items_per_bh).grid();
   const auto dkv = p.by_row ? (drop ? bwd_dkv_kernel<true, kRowWaves> : bwd_dkv_kernel<false, kRowWaves>)

@@ -72,7 +72,7 @@ def test_full_coverage_long_lists():
     check_full(t, empty, 64, nb, 1, 0.125, tag="bwd full coverage (all global)")
 
 
-@pytest.mark.parametrize("H", [2, 20])  # a workgroup per block; a wave (two waves) per item (here and below)
+@pytest.mark.parametrize("H", [2, 20, 30])  # a workgroup per block; a wave per dQ item; two waves (here and below)
 @pytest.mark.parametrize("g,w,r", [(0, 1, 0), (1, 1, 0), (0, 3, 2), (2, 3, 0), (1, 7, 4)])
 def test_degenerate_patterns(g, w, r, H):
     B, n = 1, 1024
@@ -117,7 +117,7 @@ def test_single_block_sequence():
     check_full(t, empty, 64, 0, 1, 0.125, tag="bwd nb=1 window")
 
 
-@pytest.mark.parametrize("H", [2, 20])
+@pytest.mark.parametrize("H", [2, 20, 30])
 def test_table_with_duplicates_and_negative_entries(H):
     B, n, g, w, r = 1, 1024, 2, 3, 4
     t = inp.make_tensors(B, H, n, 64, 21, "bf16", with_dO=True)
@@ -358,6 +358,9 @@ def test_list_lengths(nb, g, w, r, H):
     (1, 1, 4160, 2, 3, 3, 0.0),    # 65 blocks: the list of a global block by several workgroups
     (1, 2, 1536, 3, 13, 8, 0.0),   # lists of up to 24 blocks: six per wave
     (1, 12, 1600, 2, 3, 3, 0.0),   # 300 blocks: past the line, a wave or a pair of waves per item
+    (3, 7, 1088, 2, 3, 3, 0.1),    # 441 dQ items: two waves each
+    (1, 32, 640, 1, 5, 2, 0.0),    # 352: one again (32 x 11 items)
+    (4, 32, 320, 1, 1, 0, 0.0),    # 640 with lists of 2, and of 5 for the global rows
 ])
 @pytest.mark.parametrize("padded", [False, True])
 def test_small_launches_by_blocks_bf16(B, H, n, g, w, r, drop, padded):

@@ -49,7 +49,7 @@ def _run(Q, K, V, dO, ridx_h):
     return to_host(O), [to_host(x) for x in grads], Oo, ref
 
 
-@pytest.mark.parametrize("H", [2, 20])  # a workgroup per row and block; a wave (two waves) per item
+@pytest.mark.parametrize("H", [2, 20, 24])  # a workgroup per row and block; a wave per dQ item; two waves
 def test_every_mask_bit_shows_in_the_outputs(H):
     import torch
     assert torch.cuda.is_available()

@@ -89,7 +89,7 @@ def test_long_rows_and_wide_patterns_bf16():
     t = inp.make_tensors(B, H, n, 64, 303, "bf16", with_dO=True)
     ridx = bb.bigbird_make_rand_idx(H, n, 64, 2, 3, 3, 11)
     check(t, ridx, 64, 2, 3, 0.125, 0.1, 42, "bf16", tag="dropout n=8192")
-    for H in (2, 10):  # a workgroup per row or block; waves' items, cut into slices of 16 blocks
+    for H in (2, 10, 16):  # a workgroup per row or block; items cut into slices of 16 blocks, dQ by two waves; by one
         B, n, g, w, r = 1, 2048, 2, 15, 4
         t = inp.make_tensors(B, H, n, 64, 304, "bf16", with_dO=True)
         ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 12)

@@ -73,7 +73,7 @@ def test_suffix_padding_and_holes(dtype):
     check(t, ridx, 64, 2, 3, 0.125, dtype, km, tag=f"skip {dtype}")
 
 
-@pytest.mark.parametrize("H", [2, 5])  # a workgroup per row or block; waves' items
+@pytest.mark.parametrize("H", [2, 5, 8])  # a workgroup per row or block; waves' items, dQ by two waves; by one
 def test_leading_globals_wide_pattern_bf16(H):
     """Non-global rows of more than 16 key blocks (partial results + merge) and leading global
     blocks, one of which is fully padded in one batch entry."""
