@@ -166,7 +166,7 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
     // workgroup of the launch is resident at once (two per CU, 32 CUs per die) the longest
     // workgroup sets the run time, so the global rows are then cut twice as fine, into
     // workgroups whose partial results the merge kernel combines -- if that finer grid still fits.
-    q.gw_len = p.nb < 4 * bb::kGlobalWaveLen ? (p.nb + 3) / 4 : bb::kGlobalWaveLen;
+    q.gw_len = bb::kGlobalWaveLen;
     q.ng = (p.nb + 4 * q.gw_len - 1) / (4 * q.gw_len);
     {
       const int slots_per_die = 64;
@@ -194,6 +194,11 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
         p.dyn = 0;  // (nothing is claimed)
       }
     }
+    // A global row of one workgroup: a quarter for each wave in small launches and for short rows (96 slices of
+    // n = 512 15.5 -> 14.1 us, 144 of n = 768 26.2 -> 25.1); longer ones keep 16 blocks per wave, which leaves
+    // other waves a SIMD of their own meanwhile (96 of n = 1024 27.0 against 27.6 in quarters, 72 of n = 1536 26.6
+    // against 26.9, 36 of n = 3072 26.9 against 27.2).
+    if (q.ng == 1 && (q.by_row || p.nb < bb::kGlobalWaveLen)) q.gw_len = (p.nb + 3) / 4;
     {
       // Persistent workgroups: as many as stay resident beside the global-row workgroups (a die
       // holds 64 workgroups of this kernel: two per CU), at most one wave per item.

@@ -865,9 +865,10 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   Item cur;
   make_item<kMode>(p, w, sc, 0, cur);
   bool by_recurrence = cur.per_item;
-  if ((kMode == kMasked || kMode == kOptions) && (p.nb < 4 * kGlobalWaveLen || sc.row_idx >= p.g * p.geo.ng)) {
-    // A row with a cut block takes the recurrence in all four waves, as it does where one wave has the
-    // whole row.  (Global rows of 64 blocks and more are never one wave's: each share by itself.)
+  const bool dealt_out = (p.geo.ng == 1 && p.geo.gw_len < kGlobalWaveLen) || sc.row_idx >= p.g * p.geo.ng;
+  if ((kMode == kMasked || kMode == kOptions) && dealt_out) {
+    // A row with a cut block takes the recurrence in all four waves, as the same blocks do in one wave's
+    // item.  (Shares of 16 blocks, and of rows of several workgroups: each by itself.)
     if (lane == 0) row_cut[wv] = by_recurrence;
     __syncthreads();
     by_recurrence = (row_cut[0] | row_cut[1] | row_cut[2] | row_cut[3]) != 0;

@@ -22,8 +22,8 @@ struct Bf16Geom {
   int by_row;    // small launches: every row is done the way global rows are, a workgroup per row; no
                  // persistent workgroups
   int sw_len;    // by_row: key blocks per wave of a non-global row
-  int gw_len;    // key blocks per wave of a global workgroup: a quarter of the row, at most 16, or 8 when the
-                 // whole grid fits the chip at once (then the global rows alone would set the run time)
+  int gw_len;    // key blocks per wave of a global workgroup: 16; 8 when the whole grid fits the chip at once (then
+                 // the global rows alone would set the run time); a quarter of the row in small launches and for short rows
   int ng;        // workgroups per global row: ceil(nb / (4 * gw_len))
   int cs;        // slices per non-global row: ceil(min(g + w + r, nb) / 16)
   int n_sitems;  // (nb - g) * cs
