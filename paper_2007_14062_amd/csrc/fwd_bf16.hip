@@ -355,7 +355,7 @@ struct Item {
   int slot;            // partial-result slot (nchunks > 1)
   int cnt;             // key blocks in this slice
   int kl;              // the list: lane t holds entry t % 16
-  unsigned partial;    // bit t: entry t has padded keys inside (until the next list: its validity bits are in the wave's key_bits)
+  unsigned partial;    // bit t: entry t has padded keys inside (make_item with bits: its validity bits are in the wave's key_bits)
   bool per_item;       // not for the pipelined path (see make_item)
   bool skipped;        // query block without a valid position, not to be computed (cnt = 0)
 };
@@ -435,7 +435,8 @@ __device__ __forceinline__ const char* query_tile(const FwdParams& p, int bh, in
 // kOptions also skipped query blocks, kDrop attention dropout with or without these.  An instance holds no code of the
 // others, so its registers and schedule are its own.
 template <int kMode>
-__device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it) {
+__device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
+                                          bool bits = true) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   const int lane = lane_again(w.lane);
   int list_lo, list_len;
@@ -459,7 +460,7 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
     return;
   }
   const KeyList kl = item_key_list<kMode != kPlain>(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, row_global, list_lo,
-                                                    list_len, lane, w.klist, key_bits_all[w.wv]);
+                                                    list_len, lane, w.klist, bits ? key_bits_all[w.wv] : nullptr);
   it.cnt = kl.cnt;
   it.kl = kl.entry;
   it.partial = kl.partial;
@@ -1077,7 +1078,7 @@ void fwd_kernel_bf16(FwdParams p) {
   auto next_fast = [&](int t, Item& it) {
     int found = -1;
     while (t < n_items_die) {
-      make_item<kMode>(p, w, sc, t, it);
+      make_item<kMode>(p, w, sc, t, it, false);  // (items with cut blocks are only told from others here)
       if (it.cnt > 0 && !it.per_item) {
         found = t;
         break;

@@ -97,10 +97,11 @@ __device__ __forceinline__ bool block_any_valid_scalar(const uint8_t* kmask, int
 struct KeyList {
   int cnt;
   int entry;         // lane t holds entry t % 16
-  unsigned partial;  // bit t: entry t has padded keys inside; its validity bits are in key_bits[t]
+  unsigned partial;  // bit t: entry t has padded keys inside; its validity bits are in key_bits[t].
+                     // Without key_bits: not 0 if any has
 };
 
-// Entries [lo, lo + len), len <= 16, of row j's list.  klist[16] and key_bits[16][2]: this wave's, in LDS.
+// Entries [lo, lo + len), len <= 16, of row j's list.  klist[16] and key_bits[16][2] (or NULL): this wave's, in LDS.
 //
 // Non-global rows: the list is made without a vector memory access.  A padding mask is then applied to
 // the finished list, lane i looking at block i (one round trip to memory for the whole list) -- for rows
@@ -146,7 +147,9 @@ __device__ __forceinline__ KeyList item_key_list(const Pattern& pat, const int32
       out.cnt = static_cast<int>(__popcll(m));
     }
     const bool cut = any_valid && any_padded;
-    if (__any(cut)) {
+    if (!key_bits) {
+      out.partial = __any(cut);
+    } else if (__any(cut)) {
       if (cut) {
         uint32_t bits[2];
         block_key_bits(kmask, bi, n, kb, bits);
