@@ -34,14 +34,15 @@ def dominated(B, H, n, lo, hi, seed):
 
 @pytest.mark.parametrize("B,H,n,w,r,skip,cut", [
     (1, 2, 1024, 3, 3, False, 980),    # a workgroup per row; the cut block and k* in different waves
-    (2, 10, 1664, 3, 3, False, 1620),  # items in the waves' streams
-    (2, 10, 1664, 3, 3, True, 1620),
+    (2, 10, 1664, 3, 3, False, 20),    # items in the waves' streams, global rows in shares of 16 blocks
+    (2, 10, 1664, 3, 3, True, 20),
     (1, 10, 2048, 15, 4, False, 20),   # non-global rows of more than 16 blocks
     (1, 2, 8192, 3, 3, False, 20),     # global rows of several workgroups
 ])
 def test_lse_of_rows_with_a_cut_block(B, H, n, w, r, skip, cut):
-    """20 keys from `cut` on are padded, in the first or in the last block: every row attends both (and
-    where a row's list is cut into slices of its own, k* is in the slice of the cut block).
+    """20 keys from `cut` on are padded, in the first or in the last block: every row attends both.  (Where the
+    waves' shares of a row, or its slices, are 16 blocks, those without a cut block are summed as without a mask:
+    k* is in the share of the cut block there.)
     LSE = ln(e^l + m - 1), m the number of attended valid keys; fp32 sums leave an error of some 2^-22 of l
     and of the sum: 2e-5 here."""
     import torch
