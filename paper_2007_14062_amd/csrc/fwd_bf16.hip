@@ -385,7 +385,6 @@ struct ItemTiles {
 // the row).  All loads here are waited for before the function returns (scalar loads inside
 // their asm statement, the others by the compiler), so tile loads in flight are at most delayed.
 // Its first part: which row, which slice of the row's list (arithmetic only, no memory access).
-template <int kMode>
 __device__ __forceinline__ void item_coords(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
                                             int& list_lo, int& list_len, bool& row_global) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
@@ -441,7 +440,7 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
   const int lane = lane_again(w.lane);
   int list_lo, list_len;
   bool row_global;
-  item_coords<kMode>(p, w, sc, t, it, list_lo, list_len, row_global);
+  item_coords(p, w, sc, t, it, list_lo, list_len, row_global);
   const int bi = it.bh / p.H, h = it.bh % p.H;
   it.skipped = false;
   if (kMode >= kOptions && p.skip_q && !block_any_valid_scalar(p.kmask, __builtin_amdgcn_readfirstlane(bi), p.n, __builtin_amdgcn_readfirstlane(it.j))) {
@@ -538,18 +537,11 @@ struct TileStreams {
   }
 };
 
-// The item's block pairs through the pipeline.
-// On entry, fresh: K(0) is in the K buffer, V(0).t0 is the only load outstanding.
-//           else : K(0)'s fragments are in `ka`, V(0).t0 and V(0).t1 are outstanding, in that order
-//                  (the previous item's last pairs fetched this one's first tiles, see below).
-// If `nx` is given, the item after this one rides at the end of the streams: its query tile as
-// one more tile of the K stream, its first K tile as one more of the V stream, so that both are
-// in LDS when this item's last pair is done (they are read as K / V fragments by the pairs'
-// regular reads, which nothing uses).
+// The block pairs of a single item through the pipeline (a wave's share of a row).  On entry K(0) is in the K buffer
+// and V(0).t0 the only load outstanding (fresh_start).
 __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
                                           const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], const FwdParams& p,
-                                          const Item& item, const Item* next, bool fresh,
-                                          f32x16 (&o)[2][2], float (&l_tot)[2]) {
+                                          const Item& item, f32x16 (&o)[2][2], float (&l_tot)[2]) {
   bf16x8 va[2][2][2], p3[2];
   f32x16 sA;
   const RowSumOperand ones(lane_id());
@@ -564,25 +556,21 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
       for (int e = 0; e < 8; ++e) va[1][a][b][e] = static_cast<__bf16>(0.f);
   }
   const int cnt = item.cnt;
-  const TileStreams ts(p, item, next, lane_id());
+  const TileStreams ts(p, item, nullptr, lane_id());
 
   // start of the streams: K(0) -> registers, then the loads a pair expects to find outstanding
-  if (fresh) {
-    read_straight_half(so, cx.lds_k, 0, ka[0]);
-    read_straight_half(so, cx.lds_k, 1, ka[1]);
-    wait_lds_reads();
-    half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
-    half_load_async(ts.v(0), cx.lds_v_a, 1, cx.voff);
-  } else {
-    half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
-  }
+  read_straight_half(so, cx.lds_k, 0, ka[0]);
+  read_straight_half(so, cx.lds_k, 1, ka[1]);
+  wait_lds_reads();
+  half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
+  half_load_async(ts.v(0), cx.lds_v_a, 1, cx.voff);
   wait_tile_loads<8>();
   read_transposed_half(to, cx.lds_v, 0, va[0]);
   unit_scores(ka[0], qb[0], sA);
 
   for (int i = 0; i < cnt; ++i)
     pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
-  if (!next) wait_tile_loads<0>();  // requests past the end of the streams
+  wait_tile_loads<0>();  // requests past the end of the streams
   // the last unit's share of O and of the row sums
   unit_pv(va[1], p3, o[1], ones, ls[1]);
 #pragma unroll
@@ -885,7 +873,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
     float l_run[2] = {0.f, 0.f};
     bool bad = by_recurrence;
     if (kMode != kDrop && !bad) {
-      fast_item(w.cx, so, to, qb, ka, p, cur, nullptr, true, o, l_tot);
+      fast_item(w.cx, so, to, qb, ka, p, cur, o, l_tot);
 #pragma unroll
       for (int q = 0; q < 2; ++q) bad |= !(l_tot[q] >= kSumLo && l_tot[q] <= kSumHi);
     }
@@ -1108,7 +1096,7 @@ void fwd_kernel_bf16(FwdParams p) {
   {
     int lo_, len_;
     bool rg_;
-    item_coords<kMode>(p, w, sc, t_item, cur, lo_, len_, rg_);
+    item_coords(p, w, sc, t_item, cur, lo_, len_, rg_);
     tile_load_async_wave(query_tile(p, __builtin_amdgcn_readfirstlane(cur.bh), __builtin_amdgcn_readfirstlane(cur.j)),
                          cx.lds_k_a, cx.voff);
   }

@@ -1,4 +1,4 @@
-// End of a forward work item: normalise and store O and LSE, or hand the partial
+// End of a work item of the fp32 forward: normalise and store O and LSE, or hand the partial
 // (max, sum, un-normalised O) triple of a split row to the merge kernel.
 #ifndef BB_FWD_EPILOGUE_H_
 #define BB_FWD_EPILOGUE_H_
@@ -9,7 +9,6 @@ namespace bb {
 
 // o[dt][r]: accumulator of O^T, rows d = 32*dt + acc_row(r, hf), column = query `qi`.
 // m_ref: reference exponent (raw score units) the sums are relative to; l_tot: full row sum.
-template <bool BF16>
 __device__ __forceinline__ void fwd_store(const FwdParams& p, const WorkItem& it, const f32x16 (&o)[2],
                                           float m_ref, float l_tot, float c, size_t qrow, int qi,
                                           int hf) {
@@ -22,17 +21,10 @@ __device__ __forceinline__ void fwd_store(const FwdParams& p, const WorkItem& it
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
         const int d0 = dt * 32 + acc_row(r4 * 4, hf);
-        if constexpr (BF16) {
-          bf16x4 v;
+        f32x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = static_cast<__bf16>(o[dt][r4 * 4 + e] * inv);
-          *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.O) + qrow * kDim + d0) = v;
-        } else {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = o[dt][r4 * 4 + e] * inv;
-          *reinterpret_cast<f32x4*>(static_cast<float*>(p.O) + qrow * kDim + d0) = v;
-        }
+        for (int e = 0; e < 4; ++e) v[e] = o[dt][r4 * 4 + e] * inv;
+        *reinterpret_cast<f32x4*>(static_cast<float*>(p.O) + qrow * kDim + d0) = v;
       }
   } else {
     float* po = p.part_o + static_cast<size_t>(it.slot) * (kBlk * kDim);

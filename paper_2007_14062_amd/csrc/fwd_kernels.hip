@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kThreadsF32) void fwd_kernel_f32(FwdParams p) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[dt][r] = o[dt][r] * w0 + slot[(dt * 16 + r) * 64 + lane] * w1;
   l_tot = l_tot * w0 + l1 * w1;
-  fwd_store<false>(p, it, o, m_all, l_tot, c, qrow, qh * 32 + col, hf);
+  fwd_store(p, it, o, m_all, l_tot, c, qrow, qh * 32 + col, hf);
 }
 
 // Merge the slices of a split row: M = max m_c, L = sum l_c 2^(m_c - M),
