@@ -250,6 +250,20 @@ def test_workspace_size_of_a_plain_call_follows_the_values():
         _workspace_bytes(1, 2, 1024, 64, 64, 2.0, 3, 3, False)
 
 
+def test_current_stream_without_the_private_torch_functions(monkeypatch):
+    """The stream of a plain call comes from the public torch function where the short way is missing."""
+    import torch
+    from paper_2007_14062_amd import binding
+    binding._current_raw_stream.cache_clear()
+    try:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+        monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 0x77})())
+        assert binding._stream_ptr(None) == 0x77
+        assert binding._stream_ptr(type("S", (), {"cuda_stream": 0x99})()) == 0x99
+    finally:
+        binding._current_raw_stream.cache_clear()
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures one GPU; any other --gpus value exits with a message and status 2."""
     import subprocess
