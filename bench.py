@@ -254,8 +254,8 @@ def time_fwd_bwd(bb, torch, dev, batches: int):
         out[name] = {"ms_per_step_median": med, "ms_per_step_min": mn,
                      "useful_tflops": fl / (med * 1e-3) / 1e12,
                      "pct_of_bf16_mfma_peak": 100.0 * fl / (med * 1e-3) / 1e12 / BF16_MFMA_PEAK_TFLOPS}
-    # the same step with attention dropout 0.1 (App. E.1): the bf16 forward then runs its per-item
-    # path; the outputs of the timed calls are checked against the dropout oracle on sampled rows
+    # the same step with attention dropout 0.1 (App. E.1): the bf16 forward then takes every
+    # row by the running-maximum recurrence; the outputs of the timed calls are checked against the dropout oracle on sampled rows
     p_drop, seed = 0.1, 20200728
     fwd_d = bb.prepare_attn_fwd(dv["Q"], dv["K"], dv["V"], ridx, O, LSE, ws, g=wl.g, w=wl.w, scale=wl.scale,
                                 p_drop=p_drop, seed=seed)

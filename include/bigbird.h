@@ -198,8 +198,9 @@ int bigbird_attn_bwd(const void* Q, const void* K, const void* V, const void* O,
  * else); p_drop == 0 is the plain call, bit for bit.  Use a new seed for every step and layer.
  *
  * bigbird_attn_fwd_dropout: arguments, checks and outputs of bigbird_attn_fwd, plus p_drop and
- * seed.  The bf16 path applies the mask on its per-item path, not in the pipelined one: expect
- * about half the throughput of the plain call.
+ * seed.  The bf16 path takes every row by the running-maximum recurrence, where the mask is applied, not
+ * by the pipelined form of the plain call: expect half to two thirds of its throughput.  (Rows that attend
+ * a block with padded keys inside go that way in bigbird_attn_fwd too.)
  */
 int bigbird_attn_fwd_dropout(const void* Q, const void* K, const void* V, void* O, float* LSE,
                              const int32_t* rand_idx, const uint8_t* key_padding_mask,

@@ -12,8 +12,9 @@
 //   * bwd_dkv_kernel walks the query-block list of a key block -- the inverse of the
 //     pattern (invert_pattern, part of the dQ launch) -- with S, dP, dS as
 //     [queries x keys] tiles, one lane per key, dV^T += dO^T P and dK^T += Q^T dS.
-// Rows / columns of global blocks are cut into slices of 8 blocks whose partial sums
-// are added in slice order by bwd_reduce_kernel (bit-reproducible).
+// Lists longer than an item takes are cut into slices -- those of global blocks into 8 blocks each in large launches,
+// longer or none in small ones (RowSplit, KeySplit) -- whose partial sums are added in slice order by
+// bwd_reduce_kernel (bit-reproducible).
 #include "bwd_kernels.h"
 #include "key_list.h"
 #include "tile_ops.h"
@@ -146,7 +147,8 @@ __device__ __forceinline__ int query_list(const BwdParams& p, const Pattern& pat
 // a conversion 5, other instructions 3, measured with two waves per SIMD: 2080 per block pair and SIMD
 // against 1536 of the matrix pipe; 2300 are reached) and, with all waves of a launch of 1872 items resident
 // at once, the start: Q, dO, O tiles of every item together, 9 k of a wave's 41 k cycles.
-// 24 slices, n = 4096: 40 -> 35 us; 16 of n = 16384: 97 -> 82; n = 3072, 48 slices, dropout: 53 -> 47.
+// In back-to-back steps, 24 slices, n = 4096: 37 -> 34 us; 16 of n = 16384: 92 -> 83; n = 3072, 48 slices,
+// dropout: 49 -> 47.
 struct DqState {
   bf16x8 qb[2][4], dob[2][4];  // B operands of the item: Q^T, dO^T (lane = query, d = 16ks + 8hf .. +8)
   f32x16 dq[2][2];             // [query tile][d tile]
@@ -476,9 +478,9 @@ void bwd_dq_kernel(BwdParams p) {
 // 1950, two on a SIMD 2700 (per pair; 3220 when a pair was one stage after the other).
 // Items run longest list first (key_order of the workspace): the lists of the non-global key blocks hold 5
 // to 16 query blocks at the base pattern, and in the order of the sequence the launch ended on whichever
-// came last.  24 slices, n = 4096: 50 -> 42 us; 16 of n = 16384: 124 -> 104; 48 of n = 3072 with padding and
-// dropout: 64 -> 60; there
-// two neighbouring keys share the words of the keep mask (one per 2 x 1 elements): 63 -> 59.
+// came last.  In back-to-back steps, 24 slices, n = 4096: 46 -> 40 us; 16 of n = 16384: 120 -> 103; 48 of n = 3072
+// with padding and dropout, where two neighbouring keys share the words of the keep mask (one per 2 x 1
+// elements): 61 -> 50.
 //
 // kDrop: attention dropout (see bwd_dq_kernel): dV takes the kept probabilities (rescaled at the
 // end), dP is masked and rescaled before D is subtracted.  The row keys of the mask for the queries of a

@@ -24,7 +24,7 @@
 //     padded keys inside a block.  Both paths give the same un-normalised (reference, sum,
 //     O~) triple to the common epilogue.  (Folding the factor into the query operand would
 //     save the multiplication, but the operand would have to be rounded to bf16 again: that
-//     perturbs a logit by up to 2^-9 of its size, four times the error of everything else in
+//     perturbs a logit by up to 2^-8 of its size, four times the error of everything else in
 //     LSE, and the backward pass, which recomputes the logits exactly, then sees rows whose
 //     probabilities do not sum to one -- measured: gradient errors three times as large.)
 //   * Row sums come from the matrix pipe as well: one small MFMA per 16 keys multiplies

@@ -190,6 +190,6 @@ def test_forward_with_padding(n, skip, spread):
                                      skip_padded_query_blocks=skip)
     fin = np.isfinite(Lo)
     assert (to_host(LSE)[~fin] == -np.inf).all() and (to_host(O)[~fin] == 0).all()
-    # (one key can hold all of a row: its probability and the output are rounded to 2^-9 of at most 5)
+    # (one key can hold all of a row: the output, at most 5, is rounded by up to 2^-8 of itself)
     assert np.abs(to_host(O) - Oo).max() <= TOL["bf16"]
     assert np.abs(to_host(LSE)[fin] - Lo[fin]).max() <= (1e-4 if spread == 1.0 else TOL["bf16"])
