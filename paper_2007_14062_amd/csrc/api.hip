@@ -34,11 +34,12 @@ int check_attn_shape(int B, int H, int n, int d, int b, int g, int w, int r, int
   return BB_OK;
 }
 
-WorkspaceLayout make_layout(int B, int H, int n, int b, int g, int w, int r, int need_bwd) {
+// fine_slices: with room for the finer slices of small fp32 launches (bigbird_attn_workspace_bytes does not know the
+// storage type: the larger need counts there).
+WorkspaceLayout make_layout(int B, int H, int n, int b, int g, int w, int r, int need_bwd, bool fine_slices = true) {
   WorkspaceLayout L;
   const int BH = B * H, nb = n / b;
-  // (the same buffer serves both storage types: the larger need counts)
-  const int fine = bb::fine_slice_f32(BH, nb, g, w, r);
+  const int fine = fine_slices ? bb::fine_slice_f32(BH, nb, g, w, r) : 0;
   const int fwd_fine = nb > bb::kChunkGlobal ? fine : 0;
   size_t slots = static_cast<size_t>(BH) * bb::make_row_split(BH, nb, g, w, r).slots_per_bh;
   if (fwd_fine)
@@ -123,7 +124,10 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
                              reinterpret_cast<uintptr_t>(V) | reinterpret_cast<uintptr_t>(O) |
                              reinterpret_cast<uintptr_t>(key_padding_mask);
   if (align_or & 15) return BB_ERR_SHAPE;
-  const WorkspaceLayout L = make_layout(B, H, n, b, g, w, r, 0);
+  // A forward with less than the finer slices need, as it was enough before there were any, takes the standard ones.
+  // (At up to 8 blocks no row is split and the forward needs no workspace.)
+  const bool fine = dtype == BB_F32 && n / b > bb::kChunkGlobal && workspace_bytes >= make_layout(B, H, n, b, g, w, r, 0).fwd_total;
+  const WorkspaceLayout L = make_layout(B, H, n, b, g, w, r, 0, fine);
   if (L.fwd_total > 0) {
     if (!workspace || workspace_bytes < L.fwd_total ||
         (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)))
@@ -148,8 +152,6 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
   // slow path.)
   p.counters = L.has_counters ? reinterpret_cast<int*>(ws + L.counters) : nullptr;
   p.dyn = (dtype == BB_BF16 && p.skip_q && drop.thr == 0 && p.counters) ? 1 : 0;
-  // (at up to 8 blocks no row is split and the forward needs no workspace: that stays so)
-  const bool fine = dtype == BB_F32 && p.nb > bb::kChunkGlobal;
   p.split = bb::make_row_split(p.BH, p.nb, g, w, r, fine ? bb::fine_slice_f32(p.BH, p.nb, g, w, r) : 0);
   if (dtype == BB_BF16) {
     bb::Bf16Geom& q = p.geo;

@@ -328,3 +328,24 @@ def test_seeded_sweep_of_small_configurations():
         check_full(t, ridx, dtype, 64, g, w, scale, key_mask=km, mode=mode,
                    tag=f"sweep {done}: B{B} H{H} nb{nb} g{g} w{w} r{r} mode{mode} {dtype} pad{km is not None}")
         done += 1
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_workspace_of_the_standard_slices(dtype):
+    """A small launch whose fp32 form cuts rows finer where the workspace has room for it: with room for
+    the standard slices alone (8 blocks: 2 global rows x 2 slices x 2 heads, and the item counters) both types run."""
+    torch = torch_mod()
+    B, H, n, g, w, r = 1, 2, 1024, 2, 3, 3
+    t = inp.make_tensors(B, H, n, 64, 14, dtype)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 7)
+    nbytes = 8 * (64 * 64 + 2 * 64) * 4 + 8 * 128
+    assert nbytes < bb.bigbird_attn_workspace_bytes(B, H, n, 64, 64, g, w, r)
+    # the buffer ends where its size says: what lies behind it stays as it was
+    buf = torch.full((nbytes + 4096,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    Q, K, V = device_qkv(t, dtype)
+    O, LSE = bb.bigbird_attn_fwd(Q, K, V, torch.from_numpy(ridx).to("cuda:0"), g=g, w=w, scale=0.125, workspace=buf[:nbytes])
+    Oref, Lref = oracle.attn_fwd(t["Q"], t["K"], t["V"], ridx, 64, g, w, 0.125)
+    assert np.abs(to_host(O) - Oref).max() <= TOL[dtype] and np.abs(to_host(LSE) - Lref).max() <= TOL[dtype]
+    assert (buf[nbytes:] == 0xA5).all()
+    with pytest.raises(bb.BigBirdError):
+        bb.bigbird_attn_fwd(Q, K, V, torch.from_numpy(ridx).to("cuda:0"), g=g, w=w, scale=0.125, workspace=buf[:nbytes - 256])
