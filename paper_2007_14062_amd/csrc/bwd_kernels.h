@@ -71,11 +71,10 @@ inline bool bwd_by_row(int BH, int nb, int g, int w, int r) {
 }
 
 // Between the small launches and those that put two dQ items on every SIMD: two waves per item, which deal out its
-// list (blocks are lists and slices as before, a slice of up to 16 cut in half), from where a third of the SIMDs
-// would have a wave up to where all have two.  Whole backward, one wave / two: 24 slices of n = 1024 (432 items)
-// 36.7 / 35.4 us, 72 of n = 640 (864) 48 / 43, under dropout 70 / 59 (two waves shared every block of an item before: 49
-// and 70); 36 of n = 1536 (1008) 54 / 48.  Past 1024 items 58 / 58 (48 of n = 1280), 62 / 66 (72 of n = 1024); below 384
-// as often slower as faster (12 of n = 1536, 336 items: 34.2 / 35.4).
+// list (or its slice of up to 16 blocks) in halves.  From 384 items, where single waves would leave most SIMDs empty, up to
+// 1024, where two per item fill them.  Whole backward, one wave / two: 24 slices of n = 1024 (432 items) 36.7 / 35.4 us,
+// 72 of n = 640 (864) 48 / 43 and under dropout 70 / 59, 36 of n = 1536 (1008) 54 / 48.  Past 1024 items 58 / 58 (48
+// of n = 1280) and 62 / 66 (72 of n = 1024); below 384 as often slower as faster (12 of n = 1536, 336 items: 34.2 / 35.4).
 inline bool dq_two_waves(int BH, const RowSplit& s) {
   const long long items = static_cast<long long>(BH) * s.items_per_bh;
   return items >= 384 && items <= 1024;
