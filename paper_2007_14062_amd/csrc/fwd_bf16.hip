@@ -20,8 +20,7 @@
 //     reference of 0 is exact as long as the row sum stays inside [2^-40, 2^60]; a wave
 //     checks that at the end of its item and, if a row left the range (logits beyond about
 //     +-28 in natural units), puts the item on a list that it works off afterwards with the
-//     classical running-maximum recurrence (slow_item), as it does with items that have
-//     padded keys inside a block.  Both paths give the same un-normalised (reference, sum,
+//     classical running-maximum recurrence (running_item).  Both paths give the same un-normalised (reference, sum,
 //     O~) triple to the common epilogue.  (Folding the factor into the query operand would
 //     save the multiplication, but the operand would have to be rounded to bf16 again: that
 //     perturbs a logit by up to 2^-8 of its size, four times the error of everything else in
@@ -44,22 +43,26 @@
 //     three quarters of a block pair to land.
 //   * V^T operands come from the transposing LDS read; the LDS layout is swizzled so
 //     that neither read pattern has bank conflicts.
-//   * Items with a block that has padded keys inside take the recurrence: its row sums are fp32 sums of
-//     the probabilities before their rounding, and the largest probability of a row is 1 and not rounded.
-//     (The pipelined body with the padded probabilities cleared is faster but less exact: 8 sequences of
-//     1024 .. 4096 valid positions, 12 heads, n = 4096, 69 against 84 us, with padded query blocks skipped
-//     56 against 87, 230 leading global tokens 47 against 73; its LSE is off by up to 2^-8 where one key holds
-//     a row, and its O by 2.33e-3 (2-norm, normal inputs, rows of 454 keys) where the recurrence has 2.19e-3.)
-//     The list builder leaves the validity bits of such blocks in LDS, so that no pair of the recurrence
-//     waits for the mask.
+//   * Items with a block that has padded keys inside take the recurrence, in the same streams and with a pipelined
+//     body of its own (running_pair): its row sums are fp32 sums of the probabilities before their rounding, and
+//     the largest probability of a row is 1 and not rounded.  (Against the fixed reference LSE is off by up
+//     to 2^-8 where one key holds a row, and O by 2.33e-3 -- 2-norm, normal inputs, rows of 454 keys -- where the
+//     recurrence has 2.18e-3.  A maximum of the whole row found in a pass of its own gives 2.23e-3: the maxima on
+//     the way there are exact too.)  What bounds it is the vector port, 415 instructions a pair where the
+//     body without a maximum has 206: 230 leading global tokens, where every item has such a block, 73 -> 57 us (42 with
+//     256); 8 sequences of 1024 .. 4096 valid positions, 12 heads, n = 4096, 75 -> 70 us, and with padded query
+//     blocks skipped 87 -> 58.  (The recurrence had been one pair after another and its items a list worked off
+//     at the end, while other waves had nothing left to do.)  The order of issue inside its slots, pinned in
+//     six ways, made no difference beyond 1 us and is left to the compiler.
+//     The list builder leaves the validity bits of such blocks in LDS, so that no pair waits for the mask.
 //   * The two waves of a SIMD get their issue priority from the pairs they still have to
 //     do, so that they finish together (set_issue_priority).
 //   * Instances of the kernel: without a padding mask (everything above and nothing else); with
 //     one; kOptions, launched when a call asks for fully padded query blocks to be skipped
 //     (BB_SKIP_PADDED_QUERY_BLOCKS: their rows are written as zeros and the waves claim the
 //     other items from a counter per die, global-row waves included once their row is done); and
-//     kDrop for attention dropout, with or without these.  There every item takes the recurrence, in a
-//     plain loop, and the keep mask of dropout.h is applied to the converted pairs that multiply V.
+//     kDrop for attention dropout, with or without these.  There every item takes the recurrence,
+//     and the keep mask of dropout.h is applied to the converted pairs that multiply V.
 //     (A pipelined body with the mask inside measured 46 against 53 us at 48 slices of n = 3072, padded
 //     blocks skipped; against a fixed reference the largest probability of a row is rounded: O is off by
 //     2.33e-3 where the recurrence has 2.19e-3, and the slices of a cut row need two sums each.)
@@ -130,7 +133,7 @@ __device__ __forceinline__ void set_issue_priority(int remaining_pairs) {
 // was requested three slots earlier; the request for the half after that follows as soon as the
 // read has returned.  Tile loads outstanding at the start of a pair, oldest first:
 // K(i+1).t0 and V(i).t1 (8 instructions).
-// Blocks with padded keys inside never come here: such items take the recurrence.
+// Blocks with padded keys inside never come here: such items take the recurrence (running_pair).
 struct PairCtx {
   const char* lds_k;   // this wave's K and V tile buffers
   const char* lds_v;
@@ -275,11 +278,187 @@ __device__ __forceinline__ void pair_step(const PairCtx& cx, const StraightOffse
   pin_slot<12>();
 }
 
+// The same pair with the classical softmax recurrence: every probability is taken against the running maximum
+// of its row, the sums are fp32 sums of the probabilities before their rounding.  For items with a block
+// that has padded keys inside, for attention dropout, and for items whose row sums left the safe range of the
+// reference-free path.
+//
+// The maximum of a row over the 64 keys of the pair has to be known before the first exponential, so the
+// units go (0,A) (1,A) (0,B) (1,B) and the scores run two units ahead: slot k of the stream issues S(k+2), E(k), P(k-1).
+// Entering a pair, s0 and s1 are the scores of (0,A) and (1,A), ka its K fragments, and outstanding are V(i) and
+// K(i+1) (V(i).t0 oldest).
+// Operand reads from two registers instead of the eight of StraightOffsets and TransposedOffsets: the others differ
+// from them in single bits of the address (see tile_off_bf16), and three scores in flight leave no registers.
+struct LeanOffsets {
+  int s0, t0;
+  __device__ __forceinline__ explicit LeanOffsets(int lane) : s0(StraightOffsets(lane).off[0]), t0(TransposedOffsets(lane).off[0][0]) {}
+  __device__ __forceinline__ void straight_half(const char* tile, int t, bf16x8 (&f)[4]) const {
+    const int base = lane_again(s0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) f[ks] = *reinterpret_cast<const bf16x8*>(tile + (base ^ (ks << 5)) + t * kHalfTile);
+  }
+  __device__ __forceinline__ void transposed_half(const char* tile, int t, bf16x8 (&f)[2][2]) const {
+    const int base = lane_again(t0);
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+      for (int sgl = 0; sgl < 2; ++sgl) {
+        union { s16x4 half[2]; bf16x8 v; } u;
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+          u.half[half] = lds_read_tr16(tile + (base ^ (dt << 6) ^ (half << 5)) + half * 1024 + (2 * t + sgl) * 2048);
+        f[dt][sgl] = u.v;
+      }
+  }
+};
+
+struct RowState {
+  float m[2], l[2];  // per query tile: reference exponent (base 2; the lane halves agree), this lane's share of the row sum
+};
+
+// Padded keys of a half block never count: selected, not added to (their scores may be anything).
+__device__ __forceinline__ void drop_padded_scores(uint32_t bits, int hf, f32x16& s) {
+  const uint32_t mine = bits >> (hf * 4);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] = ((mine >> acc_row(r, 0)) & 1) ? s[r] : neg_inf();
+}
+
+// Running maximum of the rows of a query tile over another 64 keys; what is summed so far is rescaled to it.
+__device__ __forceinline__ float raise_reference(const f32x16& s0, const f32x16& s1, float c, float& m, float& l,
+                                                 f32x16 (&o)[2]) {
+  // (the maximum that keeps a NaN: one instruction for three values, where fmaxf first quiets the scores; a row with a
+  // NaN among its scores has a NaN among its probabilities either way)
+  float x[2] = {s0[0], s1[0]};
+#pragma unroll
+  for (int r = 1; r < 15; r += 2) {
+    x[0] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[0], s0[r]), s0[r + 1]);
+    x[1] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[1], s1[r]), s1[r + 1]);
+  }
+  x[0] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x[0], s0[15]), s1[15]);
+  const float mloc = half_max(__builtin_elementwise_maximum(x[0], x[1])) * c;
+  const float m_new = fmaxf(m, mloc);
+  const float m_use = m_new == neg_inf() ? 0.f : m_new;
+  const float alpha = fast_exp2(m - m_use);  // 0 while m is still -inf
+  m = m_new;
+  l *= alpha;
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+  return m_use;
+}
+
+// What attention dropout needs of an item: the keys of this lane's two rows of the keep mask.
+struct DropRows {
+  uint32_t rk[2];
+  uint32_t thr;
+};
+
+// Probabilities of one unit against a reference, as two B operands; their sum before rounding goes to l.
+// first_key: number of the unit's first key.
+template <bool kDropout, class Reads>
+__device__ __forceinline__ void unit_probs_against(const f32x16& s, float c, float m_use, float& l, bf16x8 (&pb)[2],
+                                                   uint32_t drop_rk, uint32_t drop_thr, uint32_t first_key, int hf, Reads reads) {
+  if (!kDropout) reads();
+  float sum[2] = {0.f, 0.f};
+#pragma unroll
+  for (int sgl = 0; sgl < 2; ++sgl) {
+    if (kDropout && sgl) {
+      __builtin_amdgcn_sched_barrier(0);
+      reads();
+    }
+#pragma unroll
+    for (int kk = 0; kk < 8; kk += 2) {
+      const int r = sgl * 8 + kk;
+      const float p0 = fast_exp2(__builtin_fmaf(s[r], c, -m_use));
+      const float p1 = fast_exp2(__builtin_fmaf(s[r + 1], c, -m_use));
+      sum[0] += p0;  // (the row sums are those of the undropped probabilities)
+      sum[1] += p1;
+      bf16x2 pk = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
+      if constexpr (kDropout) {
+        const uint32_t key = first_key + acc_row(r, hf);
+        pk = __builtin_bit_cast(bf16x2, __builtin_bit_cast(uint32_t, pk) & drop_keep_pair(drop_word(drop_rk, key >> 1), drop_thr));
+      }
+      pb[sgl][kk] = pk[0];
+      pb[sgl][kk + 1] = pk[1];
+    }
+  }
+  l += sum[0] + sum[1];
+}
+
+// key_bits: validity bits of the pair's keys if `cut`, else not read.  kblock: its key block (dropout only).
+template <bool kMask, bool kDropout>
+__device__ __forceinline__ void running_pair(const PairCtx& cx, const LeanOffsets& lo,
+                                             const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], bf16x8 (&va)[2][2][2],
+                                             f32x16& s0, f32x16& s1, bf16x8 (&p3)[2], f32x16 (&o)[2][2], RowState& rs,
+                                             const DropRows& drop, uint32_t kblock, bool cut, const uint32_t* key_bits,
+                                             const char* k2, const char* v1) {
+  f32x16 sB0, sB1;
+  bf16x8 p0[2], p1[2], p2[2];
+  uint32_t vb[2] = {~0u, ~0u};
+  const uint32_t key0 = kblock * kBlk;
+  if (kMask && cut) {
+    vb[0] = key_bits[0];
+    vb[1] = key_bits[1];
+    drop_padded_scores(vb[0], cx.hf, s0);
+    drop_padded_scores(vb[1], cx.hf, s1);
+  }
+  // ---- slot 0: (0,A).  V.t0 has landed; K.t1 of this pair (read in the previous pair) is in registers
+  wait_lds_reads();
+  wait_tile_loads<12>();
+  unit_pv(va[1], p3, o[1]);
+  unit_scores(ka[0], qb[1], sB0);
+  float mu = raise_reference(s0, s1, cx.c, rs.m[0], rs.l[0], o[0]);
+  if (kDropout) __builtin_amdgcn_sched_barrier(0);
+  unit_probs_against<kDropout>(s0, cx.c, mu, rs.l[0], p0, drop.rk[0], drop.thr, key0, cx.hf,
+                               [&]() { lo.transposed_half(cx.lds_v, 0, va[0]); });
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- slot 1: (1,A).  V.t1 and K(i+1).t0 have landed
+  wait_lds_reads();
+  half_load_async(v1, cx.lds_v_a, 0, cx.voff);
+  wait_tile_loads<8>();
+  unit_scores(ka[1], qb[1], sB1);
+  unit_pv(va[0], p0, o[0]);
+  unit_probs_against<kDropout>(s1, cx.c, mu, rs.l[0], p1, drop.rk[0], drop.thr, key0 + 32, cx.hf, [&]() {
+    lo.straight_half(cx.lds_k, 0, ka[0]);
+    lo.transposed_half(cx.lds_v, 1, va[1]);
+  });
+  asm volatile("" : "+v"(p1[0]), "+v"(p1[1]), "+v"(rs.l[0]));  // (made here, not behind the branch)
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- slot 2: (0,B).  K(i+1).t1 has landed
+  if (kMask && cut) {
+    drop_padded_scores(vb[0], cx.hf, sB0);
+    drop_padded_scores(vb[1], cx.hf, sB1);
+  }
+  wait_lds_reads();
+  half_load_async(k2, cx.lds_k_a, 0, cx.voff);
+  half_load_async(v1, cx.lds_v_a, 1, cx.voff);
+  wait_tile_loads<12>();
+  unit_pv(va[1], p1, o[0]);
+  unit_scores(ka[0], qb[0], s0);
+  mu = raise_reference(sB0, sB1, cx.c, rs.m[1], rs.l[1], o[1]);
+  if (kDropout) __builtin_amdgcn_sched_barrier(0);
+  unit_probs_against<kDropout>(sB0, cx.c, mu, rs.l[1], p2, drop.rk[1], drop.thr, key0, cx.hf,
+                               [&]() { lo.straight_half(cx.lds_k, 1, ka[1]); });
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- slot 3: (1,B)
+  wait_lds_reads();
+  half_load_async(k2, cx.lds_k_a, 1, cx.voff);
+  unit_scores(ka[1], qb[0], s1);
+  unit_pv(va[0], p2, o[1]);
+  unit_probs_against<kDropout>(sB1, cx.c, mu, rs.l[1], p3, drop.rk[1], drop.thr, key0 + 32, cx.hf, []() {});
+  asm volatile("" : "+v"(p3[0]), "+v"(p3[1]), "+v"(rs.l[1]));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // LDS of a workgroup (at namespace scope: the cold paths below are separate functions).
 __shared__ __attribute__((aligned(1024))) char lds_all[kFwdWaves][2 * kTile];  // per wave: K tile, V tile
 __shared__ int klist_all[kFwdWaves][kGlobalWaveLen];
-// validity bits of the keys of listed blocks that have padded keys inside, of the list made last
-__shared__ uint32_t key_bits_all[kFwdWaves][kGlobalWaveLen][2];
+// validity bits of the keys of listed blocks that have padded keys inside, of the item in work and of the next one
+__shared__ uint32_t key_bits_all[kFwdWaves][2][kGlobalWaveLen][2];
 __shared__ int row_cut[kFwdWaves];  // rows by a workgroup: does the wave's share hold a cut block?
 __shared__ float mrg_m[kFwdWaves][kBlk], mrg_l[kFwdWaves][kBlk];  // their per-wave exponents and sums
 
@@ -355,8 +534,9 @@ struct Item {
   int slot;            // partial-result slot (nchunks > 1)
   int cnt;             // key blocks in this slice
   int kl;              // the list: lane t holds entry t % 16
-  unsigned partial;    // bit t: entry t has padded keys inside (make_item with bits: its validity bits are in the wave's key_bits)
-  bool per_item;       // not for the pipelined path (see make_item)
+  unsigned partial;    // bit t: entry t has padded keys inside; its validity bits are in the wave's key_bits
+  bool running;        // takes the running maximum (running_pair)
+  int bits;            // which of the wave's two sets of key_bits is its
   bool skipped;        // query block without a valid position, not to be computed (cnt = 0)
 };
 
@@ -435,7 +615,7 @@ __device__ __forceinline__ const char* query_tile(const FwdParams& p, int bh, in
 // others, so its registers and schedule are its own.
 template <int kMode>
 __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
-                                          bool bits = true) {
+                                          int bits = 0) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   const int lane = lane_again(w.lane);
   int list_lo, list_len;
@@ -443,12 +623,13 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
   item_coords(p, w, sc, t, it, list_lo, list_len, row_global);
   const int bi = it.bh / p.H, h = it.bh % p.H;
   it.skipped = false;
+  it.bits = bits;
   if (kMode >= kOptions && p.skip_q && !block_any_valid_scalar(p.kmask, __builtin_amdgcn_readfirstlane(bi), p.n, __builtin_amdgcn_readfirstlane(it.j))) {
     // the caller reads the mask as a query mask too, and no position of this block is valid:
     // an item without key blocks (O = 0, LSE = -inf)
     it.skipped = true;
     it.partial = 0;
-    it.per_item = false;
+    it.running = false;
     it.kl = 0;
     it.bh = __builtin_amdgcn_readfirstlane(it.bh);
     it.j = __builtin_amdgcn_readfirstlane(it.j);
@@ -459,11 +640,11 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
     return;
   }
   const KeyList kl = item_key_list<kMode != kPlain>(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, row_global, list_lo,
-                                                    list_len, lane, w.klist, bits ? key_bits_all[w.wv] : nullptr);
+                                                    list_len, lane, w.klist, key_bits_all[w.wv][bits]);
   it.cnt = kl.cnt;
   it.kl = kl.entry;
   it.partial = kl.partial;
-  it.per_item = kMode == kDrop || it.partial != 0;
+  it.running = kMode == kDrop || it.partial != 0;
   // all of these are wave uniform; saying so keeps them (and what is computed from them) in
   // scalar registers
   it.bh = __builtin_amdgcn_readfirstlane(it.bh);
@@ -473,7 +654,7 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
   it.slot = __builtin_amdgcn_readfirstlane(it.slot);
   it.cnt = __builtin_amdgcn_readfirstlane(it.cnt);
   it.partial = __builtin_amdgcn_readfirstlane(it.partial);
-  it.per_item = __builtin_amdgcn_readfirstlane(static_cast<int>(it.per_item)) != 0;
+  it.running = __builtin_amdgcn_readfirstlane(static_cast<int>(it.running)) != 0;
 }
 
 // First tiles of an item that nobody has fetched ahead.  The query block takes the same road as a
@@ -537,6 +718,58 @@ struct TileStreams {
   }
 };
 
+// The same streams without their four vector registers: entries picked by scalar arithmetic, for items with the
+// running maximum.
+struct ScalarStreams {
+  const char* kbase;
+  const char* vbase;
+  const char* k_tail;
+  const char* v_tail;
+  int kl, cnt;
+  __device__ __forceinline__ ScalarStreams(const FwdParams& p, const Item& it, const Item* next) {
+    const ItemTiles ct(p, it);
+    kbase = ct.kbase;
+    vbase = ct.vbase;
+    kl = it.kl;
+    cnt = it.cnt;
+    if (next) {
+      const ItemTiles nx(p, *next);
+      k_tail = uniform_ptr(nx.qtile);
+      v_tail = uniform_ptr(nx.ktile(0));
+    } else {
+      k_tail = uniform_ptr(ct.ktile(0));
+      v_tail = uniform_ptr(ct.vtile(0));
+    }
+  }
+  __device__ __forceinline__ const char* k(int m) const {
+    return m < cnt ? kbase + static_cast<size_t>(__builtin_amdgcn_readlane(kl, m)) * kTile : k_tail;
+  }
+  __device__ __forceinline__ const char* v(int m) const {
+    return m < cnt ? vbase + static_cast<size_t>(__builtin_amdgcn_readlane(kl, m)) * kTile : v_tail;
+  }
+};
+
+// Operands that nobody reads again, said to the register allocator, which would carry them past the pairs otherwise.
+__device__ __forceinline__ void forget(bf16x8 (&f)[2][4]) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) asm volatile("" : "=v"(f[t][ks]));
+}
+
+// What the first pair of an item "finishes": nothing.
+__device__ __forceinline__ void no_predecessor(bf16x8 (&va1)[2][2], bf16x8 (&p3)[2]) {
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) p3[a][e] = static_cast<__bf16>(0.f);
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) va1[a][b][e] = static_cast<__bf16>(0.f);
+  }
+}
+
 // The block pairs of a single item through the pipeline (a wave's share of a row).  On entry K(0) is in the K buffer
 // and V(0).t0 the only load outstanding (fresh_start).
 __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
@@ -546,15 +779,7 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
   f32x16 sA;
   const RowSumOperand ones(lane_id());
   f32x4 ls[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};  // per query tile
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {  // what the first pair "finishes": nothing
-#pragma unroll
-    for (int e = 0; e < 8; ++e) p3[a][e] = static_cast<__bf16>(0.f);
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) va[1][a][b][e] = static_cast<__bf16>(0.f);
-  }
+  no_predecessor(va[1], p3);
   const int cnt = item.cnt;
   const TileStreams ts(p, item, nullptr, lane_id());
 
@@ -577,104 +802,52 @@ __device__ __forceinline__ void fast_item(const PairCtx& cx, const StraightOffse
   for (int q = 0; q < 2; ++q) l_tot[q] = row_total(ls[q], lane_id() & 31);
 }
 
-// The classical recurrence (running maximum, rescale on every block), one block pair at a time
-// with the tiles of the next pair in flight: the path of attention dropout, of items with padded keys inside a block (key_bits: the
-// validity bits of those blocks, as make_item leaves them) and the
-// fallback for items whose row sums left the safe range of the reference-free path.  Leaves m_ref (exponent
-// units), this lane's share of the row sums and O~.  Any load still in flight lands first.
 template <int kMode>
-__device__ __forceinline__ void slow_item(const PairCtx& cx, const StraightOffsets& so, const TransposedOffsets& to,
-                                          const bf16x8 (&qb)[2][4], const FwdParams& p, const Item& item,
-                                          const uint32_t (*key_bits)[2], f32x16 (&o)[2][2], float (&l_run)[2],
-                                          float (&m_ref)[2]) {
-  const ItemTiles it(p, item);
+__device__ __forceinline__ DropRows drop_rows(const FwdParams& p, const Item& item, int lane) {
+  DropRows d = {{0u, 0u}, 0u};
+  if constexpr (kMode == kDrop) {
+    d.thr = drop_pair_threshold(p.drop);
+    const uint32_t row0 = static_cast<uint32_t>(item.bh) * static_cast<uint32_t>(p.n) + static_cast<uint32_t>(item.j * kBlk + (lane & 31));
+#pragma unroll
+    for (int q = 0; q < 2; ++q) d.rk[q] = drop_row_key(p.drop, row0 + q * 32);
+  }
+  return d;
+}
+
+// The same with the running maximum, on the same entry.  Leaves the reference exponents (base 2) in m_ref.
+template <int kMode>
+__device__ __forceinline__ void running_item(const WaveCtx& w, const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], const FwdParams& p,
+                                             const Item& item, f32x16 (&o)[2][2], float (&m_ref)[2], float (&l_tot)[2]) {
+  const PairCtx& cx = w.cx;
+  const LeanOffsets lo(lane_again(w.lane));
+  bf16x8 va[2][2][2], p3[2];
+  f32x16 s0, s1;
+  RowState rs = {{neg_inf(), neg_inf()}, {0.f, 0.f}};
+  no_predecessor(va[1], p3);
   zero_acc(o[0]);
   zero_acc(o[1]);
+  const DropRows drop = drop_rows<kMode>(p, item, lane_id());
+  const int cnt = item.cnt;
+  const ScalarStreams ts(p, item, nullptr);
+
+  lo.straight_half(cx.lds_k, 0, ka[0]);
+  lo.straight_half(cx.lds_k, 1, ka[1]);
+  wait_lds_reads();
+  half_load_async(ts.v(0), cx.lds_v_a, 1, cx.voff);
+  half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
+  half_load_async(ts.k(1), cx.lds_k_a, 1, cx.voff);
+  unit_scores(ka[0], qb[0], s0);
+  unit_scores(ka[1], qb[0], s1);
+  for (int i = 0; i < cnt; ++i)
+    running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, s0, s1, p3, o, rs, drop,
+                                                  __builtin_amdgcn_readlane(item.kl, i), (item.partial >> i) & 1,
+                                                  key_bits_all[w.wv][item.bits][i], ts.k(i + 2), ts.v(i + 1));
+  wait_tile_loads<0>();  // requests past the end of the streams
+  unit_pv(va[1], p3, o[1]);
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    m_ref[q] = neg_inf();
-    l_run[q] = 0.f;
-  }
-  // attention dropout: the keys of this lane's two rows of the keep mask
-  uint32_t drop_rk[2] = {0u, 0u};
-  const uint32_t drop_thr = kMode == kDrop ? drop_pair_threshold(p.drop) : 0u;
-  if constexpr (kMode == kDrop) {
-    const uint32_t row0 = static_cast<uint32_t>(item.bh) * static_cast<uint32_t>(p.n) + static_cast<uint32_t>(item.j * kBlk + (lane_id() & 31));
-#pragma unroll
-    for (int q = 0; q < 2; ++q) drop_rk[q] = drop_row_key(p.drop, row0 + q * 32);
-  }
-  // The tiles of pair i + 1 are requested as soon as those of pair i sit in registers, and land
-  // under pair i's arithmetic.
-  auto request_tiles = [&](int i) {
-    const char* kt = it.ktile(i);
-    const char* vt = it.vtile(i);
-    half_load_async(kt, cx.lds_k_a, 0, cx.voff);
-    half_load_async(kt, cx.lds_k_a, 1, cx.voff);
-    half_load_async(vt, cx.lds_v_a, 0, cx.voff);
-    half_load_async(vt, cx.lds_v_a, 1, cx.voff);
-  };
-  if (item.cnt > 0) request_tiles(0);
-  for (int i = 0; i < item.cnt; ++i) {
-    const int kblock = __builtin_amdgcn_readlane(item.kl, i);
-    uint32_t vbits[2] = {~0u, ~0u};
-    if (kMode != kPlain && (item.partial >> i) & 1) {
-      vbits[0] = key_bits[i][0];
-      vbits[1] = key_bits[i][1];
-    }
-    wait_tile_loads<0>();
-    bf16x8 ka[2][4], va[2][2][2];
-    read_straight_half(so, cx.lds_k, 0, ka[0]);
-    read_straight_half(so, cx.lds_k, 1, ka[1]);
-    read_transposed_half(to, cx.lds_v, 0, va[0]);
-    read_transposed_half(to, cx.lds_v, 1, va[1]);
-    wait_lds_reads();  // the buffers are free again
-    if (i + 1 < item.cnt) request_tiles(i + 1);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      f32x16 s[2];
-      unit_scores(ka[0], qb[q], s[0]);
-      unit_scores(ka[1], qb[q], s[1]);
-      float mloc = neg_inf();
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const unsigned mine = vbits[t] >> (cx.hf * 4);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          s[t][r] = ((mine >> acc_row(r, 0)) & 1) ? s[t][r] * cx.c : neg_inf();  // base-2 exponent
-          mloc = fmaxf(mloc, s[t][r]);
-        }
-      }
-      mloc = half_max(mloc);
-      const float m_new = fmaxf(m_ref[q], mloc);
-      const float m_use = (m_new == neg_inf()) ? 0.f : m_new;
-      const float alpha = fast_exp2(m_ref[q] - m_use);  // 0 while m_ref is still -inf
-      l_run[q] *= alpha;
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[q][dt][r] *= alpha;
-      m_ref[q] = m_new;
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        bf16x8 pb[2];
-#pragma unroll
-        for (int sgl = 0; sgl < 2; ++sgl)
-#pragma unroll
-          for (int kk = 0; kk < 8; kk += 2) {
-            const int r = sgl * 8 + kk;
-            const float p0 = fast_exp2(s[t][r] - m_use), p1 = fast_exp2(s[t][r + 1] - m_use);
-            bf16x2 pk = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
-            l_run[q] += p0 + p1;  // (the row sums are those of the undropped probabilities)
-            if constexpr (kMode == kDrop) {
-              const uint32_t key = static_cast<uint32_t>(kblock * kBlk + t * 32 + acc_row(r, cx.hf));
-              pk = __builtin_bit_cast(bf16x2, __builtin_bit_cast(uint32_t, pk) & drop_keep_pair(drop_word(drop_rk[q], key >> 1), drop_thr));
-            }
-            pb[sgl][kk] = pk[0];
-            pb[sgl][kk + 1] = pk[1];
-          }
-        unit_pv(va[t], pb, o[q]);
-      }
-    }
+    m_ref[q] = rs.m[q];
+    l_tot[q] = half_sum(rs.l[q]);
   }
 }
 
@@ -802,18 +975,15 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
   Item it;
   make_item<kMode>(p, w, sc, t, it);
   wait_tile_loads<0>();
-  bf16x8 qb[2][4];
+  bf16x8 qb[2][4], ka[2][4];
   f32x16 o[2][2];
-  float l_run[2], m_ref[2], l_tot[2];
+  float m_ref[2] = {neg_inf(), neg_inf()}, l_tot[2] = {0.f, 0.f};
+  zero_acc(o[0]);
+  zero_acc(o[1]);
   if (it.cnt > 0) {
-    tile_load_async_wave(ItemTiles(p, it).qtile, w.cx.lds_v_a, w.cx.voff);
-    wait_tile_loads<0>();
-    so.read(w.lds_v, qb);
-    wait_lds_reads();
-    }
-  slow_item<kMode>(w.cx, so, to, qb, p, it, key_bits_all[w.wv], o, l_run, m_ref);
-#pragma unroll
-  for (int q = 0; q < 2; ++q) l_tot[q] = half_sum(l_run[q]);
+    fresh_start(p, w, so, it, qb);
+    running_item<kMode>(w, qb, ka, p, it, o, m_ref, l_tot);
+  }
   if (it.nchunks == 1) {
     float inv[2], lse[2];
 #pragma unroll
@@ -853,7 +1023,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
 #endif
   Item cur;
   make_item<kMode>(p, w, sc, 0, cur);
-  bool by_recurrence = cur.per_item;
+  bool by_recurrence = cur.running;
   const bool dealt_out = (p.geo.ng == 1 && p.geo.gw_len < kGlobalWaveLen) || sc.row_idx >= p.g * p.geo.ng;
   if ((kMode == kMasked || kMode == kOptions) && dealt_out) {
     // A row with a cut block takes the recurrence in all four waves, as the same blocks do in one wave's
@@ -870,18 +1040,19 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   zero_acc(o[1]);
   if (cur.cnt > 0) {
     fresh_start(p, w, so, cur, qb);
-    float l_run[2] = {0.f, 0.f};
     bool bad = by_recurrence;
     if (kMode != kDrop && !bad) {
       fast_item(w.cx, so, to, qb, ka, p, cur, o, l_tot);
 #pragma unroll
       for (int q = 0; q < 2; ++q) bad |= !(l_tot[q] >= kSumLo && l_tot[q] <= kSumHi);
+      if (__any(bad)) {  // its first tiles again
+        const ItemTiles ct(p, cur);
+        tile_load_async_wave(ct.ktile(0), w.cx.lds_k_a, w.cx.voff);
+        wait_tile_loads<0>();
+        half_load_async(ct.vtile(0), w.cx.lds_v_a, 0, w.cx.voff);
+      }
     }
-    if (__any(bad)) {
-      slow_item<kMode>(w.cx, so, to, qb, p, cur, key_bits_all[wv], o, l_run, m_ref);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) l_tot[q] = half_sum(l_run[q]);
-    }
+    if (__any(bad)) running_item<kMode>(w, qb, ka, p, cur, o, m_ref, l_tot);
   } else {
     m_ref[0] = m_ref[1] = neg_inf();
   }
@@ -1006,8 +1177,11 @@ void fwd_kernel_bf16(FwdParams p) {
   const int lane = w.lane;
   char* const lds_k = w.lds_k;
   char* const lds_v = w.lds_v;
-  const StraightOffsets so(lane);
-  const TransposedOffsets to(lane);
+  const StraightOffsets so_plain(lane);
+  const TransposedOffsets to_plain(lane);
+  // (kept in registers where they are all there is to keep)
+  auto straight = [&]() { return kMode == kPlain ? so_plain : StraightOffsets(lane_again(lane)); };
+  auto transposed = [&]() { return kMode == kPlain ? to_plain : TransposedOffsets(lane_again(lane)); };
   const int n_items_die = sc.n_items_die, wave_stride = sc.wave_stride;
   // the die's next unclaimed item (tickets start after the items the persistent waves begin with)
   auto claim = [&]() {
@@ -1022,12 +1196,6 @@ void fwd_kernel_bf16(FwdParams p) {
     return c < n_items_die ? wave_stride + c : n_items_die;
   };
   int t_first = static_cast<int>(sc.wg - sc.n_gpart) * kFwdWaves + w.wv;  // first item of this wave
-  if constexpr (kMode == kDrop) {
-    // every item takes the recurrence: no stream to run and no list to keep
-    for (int t = t_first; t < n_items_die; t += wave_stride)
-      item_by_recurrence<kMode>(p, __builtin_amdgcn_readfirstlane(t));
-    return;
-  }
   if (dyn && was_global) t_first = claim();
   const int t_item = __builtin_amdgcn_readfirstlane(t_first);
   if (t_item >= n_items_die) return;
@@ -1051,9 +1219,9 @@ void fwd_kernel_bf16(FwdParams p) {
 #define BB_STAMP(i)
 #endif
   // ---- persistent wave: the die's non-global items t_item, t_item + wave_stride, ...
-  // Items that cannot take the pipelined path (no key block at all, padded keys inside a block,
-  // or -- found out afterwards -- row sums outside the safe range) are put on a list and done
-  // by the classical recurrence when the stream has ended (a lane of `redo` each).  Items dealt out: the
+  // Items with a cut block (and all under dropout) take their pairs with the running maximum.  Items without
+  // any key block, and those whose row sums turn out to be outside the safe range, are put on a list and done
+  // by item_by_recurrence when the stream has ended (a lane of `redo` each).  Items dealt out: the
   // host sizes the grid so that a wave has at most kListedItems.  Items claimed: a wave with that many
   // on its list takes no more; the one or two it still has in flight find room behind them.
   int redo = 0;       // the list: lane t holds the number of the t-th such item
@@ -1062,16 +1230,16 @@ void fwd_kernel_bf16(FwdParams p) {
     if (lane == n_redo) redo = t;
     n_redo = __builtin_amdgcn_readfirstlane(n_redo + 1);
   };
-  // the next item at or after t that takes the pipelined path (others go to the list)
-  auto next_fast = [&](int t, Item& it) {
+  // the next item at or after t that has a key block (others go to the list); bits: its set of key_bits
+  auto next_item = [&](int t, Item& it, int bits) {
     int found = -1;
     while (t < n_items_die) {
-      make_item<kMode>(p, w, sc, t, it, false);  // (items with cut blocks are only told from others here)
-      if (it.cnt > 0 && !it.per_item) {
+      make_item<kMode>(p, w, sc, t, it, bits);
+      if (it.cnt > 0) {
         found = t;
         break;
       }
-      if (kMode == kOptions && it.skipped && it.nchunks == 1) {  // nothing to compute: its rows are written here
+      if (kMode >= kOptions && it.skipped && it.nchunks == 1) {  // nothing to compute: its rows are written here
         store_zero_rows_bf16(p, it);
       } else {
         push_redo(t);
@@ -1100,32 +1268,13 @@ void fwd_kernel_bf16(FwdParams p) {
     tile_load_async_wave(query_tile(p, __builtin_amdgcn_readfirstlane(cur.bh), __builtin_amdgcn_readfirstlane(cur.j)),
                          cx.lds_k_a, cx.voff);
   }
-  int t_cur = next_fast(t_item, cur);
+  int t_cur = next_item(t_item, cur, 0);
   int t_nxt = -1;
 #ifdef BB_STAMPS
   st_t[0] = __builtin_readcyclecounter() - tprev;
 #endif
   if (t_cur < 0) wait_tile_loads<0>();  // nothing for the pipelined path: let the request land
   if (t_cur >= 0) {
-    bf16x8 va[2][2][2], p3[2];
-    f32x16 sA;
-    const RowSumOperand ones(lane_again(lane));
-    f32x4 ls[2];
-    // what the first pair of an item "finishes": nothing
-    auto reset_item_state = [&]() {
-      zero_acc(o[0]);
-      zero_acc(o[1]);
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        ls[a] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p3[a][e] = static_cast<__bf16>(0.f);
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) va[1][a][b][e] = static_cast<__bf16>(0.f);
-      }
-    };
     // pairs this wave still has to do, roughly (for its issue priority)
     const int pairs_per_item = p.geo.cs > 1 ? kGlobalWaveLen : (p.g + p.w + p.r < kGlobalWaveLen ? p.g + p.w + p.r : kGlobalWaveLen);
     int rem_pairs = dyn ? 0  // (unknown when items are claimed: every wave at the same priority)
@@ -1137,7 +1286,7 @@ void fwd_kernel_bf16(FwdParams p) {
       tile_load_async_wave(query_tile(p, cur.bh, cur.j), cx.lds_k_a, cx.voff);
       wait_tile_loads<0>();
     }
-    so.read(lds_k, qb);
+    straight().read(lds_k, qb);
     wait_lds_reads();
     {
       // K(0) and V(0) together; the next item's list is made while they fly
@@ -1150,43 +1299,89 @@ void fwd_kernel_bf16(FwdParams p) {
 #ifdef BB_STAMPS
     st_t[2] = __builtin_readcyclecounter() - tprev;
 #endif
-    t_nxt = next_fast(successor(t_cur), nxt);  // (scalar loads only, unless there is a padding mask)
-    TileStreams ts(p, cur, t_nxt >= 0 ? &nxt : nullptr, lane_again(lane));
+    t_nxt = next_item(successor(t_cur), nxt, 1);  // (scalar loads only, unless there is a padding mask)
     int cnt = __builtin_amdgcn_readfirstlane(cur.cnt);  // pairs of the item in work
-      reset_item_state();
 #ifdef BB_STAMPS
     st_t[1] = __builtin_readcyclecounter() - tprev;
 #endif
     wait_tile_loads<8>();  // K(0)
-    read_straight_half(so, lds_k, 0, ka[0]);
-    read_straight_half(so, lds_k, 1, ka[1]);
+    straight().read(lds_k, ka);
     wait_lds_reads();
-    half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
-    wait_tile_loads<8>();  // V(0).t0
-    read_transposed_half(to, lds_v, 0, va[0]);
-    unit_scores(ka[0], qb[0], sA);
     BB_STAMP(0);
 
-    for (int i = 0;;) {
-      if ((rem_pairs & 3) == 3 || i == 0) set_issue_priority(rem_pairs);
-      pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
-      rem_pairs = __builtin_amdgcn_readfirstlane(rem_pairs - 1);
-      i = __builtin_amdgcn_readfirstlane(i + 1);
-      if (__builtin_expect(i < cnt, 1)) continue;  // (the register allocator should favour the pairs)
-
-      // ---- item boundary.  The last unit's share of O, the row sums, the range check.
-      BB_STAMP(1);
-      unit_pv(va[1], p3, o[1], ones, ls[1]);
+    bool rows_written = false;
+    for (;;) {
       bool bad = false;
-      float inv[2], lse[2], lsum[2];
+      float inv[2], lse[2], lsum[2], m_ref[2] = {0.f, 0.f};
+      bf16x8 va[2][2][2], p3[2];
+      f32x16 sA;
+      no_predecessor(va[1], p3);
+      zero_acc(o[0]);
+      zero_acc(o[1]);
+      // (said to be uniform here: otherwise one kind's operands are kept through the pairs of the other)
+      if (kMode == kDrop || (kMode != kPlain && __builtin_amdgcn_readfirstlane(static_cast<int>(cur.running)) != 0)) {
+        const ScalarStreams ts(p, cur, t_nxt >= 0 ? &nxt : nullptr);
+        const LeanOffsets lo(lane_again(lane));
+        f32x16 s1;
+        RowState rs = {{neg_inf(), neg_inf()}, {0.f, 0.f}};
+        const DropRows drop = drop_rows<kMode>(p, cur, lane_again(lane));
+        half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
+        half_load_async(ts.k(1), cx.lds_k_a, 1, cx.voff);
+        unit_scores(ka[0], qb[0], sA);
+        unit_scores(ka[1], qb[0], s1);
+        for (int i = 0; i < cnt;) {
+          if ((rem_pairs & 3) == 3 || i == 0) set_issue_priority(rem_pairs);
+          running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, sA, s1, p3, o, rs, drop,
+                                                        __builtin_amdgcn_readlane(cur.kl, i), (cur.partial >> i) & 1,
+                                                        key_bits_all[w.wv][cur.bits][i], ts.k(i + 2), ts.v(i + 1));
+          rem_pairs = __builtin_amdgcn_readfirstlane(rem_pairs - 1);
+          i = __builtin_amdgcn_readfirstlane(i + 1);
+        }
+        BB_STAMP(1);
+        unit_pv(va[1], p3, o[1]);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const float l = row_total(ls[q], w.col);
-        bad |= !(l >= kSumLo && l <= kSumHi);
-        lsum[q] = l;
-        inv[q] = 1.f / l;
-        lse[q] = fast_log2(l) * kLn2;
+        for (int q = 0; q < 2; ++q) {
+          const float l = half_sum(rs.l[q]);
+          m_ref[q] = rs.m[q];
+          lsum[q] = l;
+          inv[q] = l > 0.f ? (kMode == kDrop ? p.drop.rs : 1.f) / l : 0.f;
+          lse[q] = l > 0.f ? (rs.m[q] + fast_log2(l)) * kLn2 : neg_inf();
+        }
+      } else {
+        const StraightOffsets so = straight();
+        const TransposedOffsets to = transposed();
+        const RowSumOperand ones(lane_again(lane));
+        f32x4 ls[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        const TileStreams ts(p, cur, t_nxt >= 0 ? &nxt : nullptr, lane_again(lane));
+        half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
+        // V(0).t0.  Behind it are V(0).t1, K(1).t0 and the eight 16-byte stores (at least) of rows just written, which
+        // it need not wait for (infer of 48 slices, n = 4096: 41.0 -> 40.6 us)
+        if (rows_written)
+          wait_tile_loads<16>();
+        else
+          wait_tile_loads<8>();
+        read_transposed_half(to, lds_v, 0, va[0]);
+        unit_scores(ka[0], qb[0], sA);
+        for (int i = 0;;) {
+          if ((rem_pairs & 3) == 3 || i == 0) set_issue_priority(rem_pairs);
+          pair_step(cx, so, to, qb, ka, va, sA, p3, o, ones, ls, ts.k(i + 1), ts.v(i + 1), ts.k(i + 2));
+          rem_pairs = __builtin_amdgcn_readfirstlane(rem_pairs - 1);
+          i = __builtin_amdgcn_readfirstlane(i + 1);
+          if (__builtin_expect(i >= cnt, 0)) break;  // (the register allocator should favour the pairs)
+        }
+        // the last unit's share of O, the row sums, the range check
+        BB_STAMP(1);
+        unit_pv(va[1], p3, o[1], ones, ls[1]);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float l = row_total(ls[q], w.col);
+          bad |= !(l >= kSumLo && l <= kSumHi);
+          lsum[q] = l;
+          inv[q] = 1.f / l;
+          lse[q] = fast_log2(l) * kLn2;
+        }
       }
+      // ---- item boundary
       const bool redo_cur = __any(bad);
       if (redo_cur) push_redo(t_cur);
 
@@ -1195,15 +1390,15 @@ void fwd_kernel_bf16(FwdParams p) {
       int t_nn = -1;
       BB_STAMP(2);
       if (t_nxt >= 0) {
-        t_nn = next_fast(successor(t_nxt), nn);
+        t_nn = next_item(successor(t_nxt), nn, cur.bits);  // (cur is done with its bits)
         BB_STAMP(3);
         // The next item's query tile is in the K buffer, its first K tile in the V buffer (the
         // second half may still be landing).  Both go to registers, its first V tile is requested,
         // and this item's output is written under that flight.
         wait_tile_loads<0>();
+        const StraightOffsets so = straight();
         so.read(lds_k, qb);
-        read_straight_half(so, lds_v, 0, ka[0]);
-        read_straight_half(so, lds_v, 1, ka[1]);
+        so.read(lds_v, ka);
         wait_lds_reads();
         const char* v0 = uniform_ptr(ItemTiles(p, nxt).vtile(0));
         half_load_async(v0, cx.lds_v_a, 0, cx.voff);
@@ -1211,14 +1406,19 @@ void fwd_kernel_bf16(FwdParams p) {
       }
 
       BB_STAMP(4);
-      if (t_nxt < 0) wait_tile_loads<0>();  // requests past the end of the streams
+      if (t_nxt < 0) {
+        wait_tile_loads<0>();  // requests past the end of the streams
+        // (no instruction: nothing of the last item's operands is kept for a next one)
+        forget(qb);
+        forget(ka);
+      }
       // ---- output, through the K buffer (free now)
+      rows_written = !redo_cur && cur.nchunks == 1;
       if (!redo_cur) {
         if (cur.nchunks == 1) {
           store_rows_bf16(p, w, cur, o, inv, lse);
         } else {
-          const float zero[2] = {0.f, 0.f};
-          store_partial(p, w, cur, o, zero, lsum);
+          store_partial(p, w, cur, o, m_ref, lsum);
         }
       }
       BB_STAMP(5);
@@ -1232,14 +1432,7 @@ void fwd_kernel_bf16(FwdParams p) {
       t_cur = t_nxt;
       nxt = nn;
       t_nxt = t_nn;
-      ts = TileStreams(p, cur, t_nxt >= 0 ? &nxt : nullptr, lane_again(lane));
-      reset_item_state();
       cnt = __builtin_amdgcn_readfirstlane(cur.cnt);
-      half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
-      wait_tile_loads<8>();
-      read_transposed_half(to, lds_v, 0, va[0]);
-      unit_scores(ka[0], qb[0], sA);
-      i = 0;
       BB_STAMP(6);
     }
   }

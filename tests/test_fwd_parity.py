@@ -180,6 +180,46 @@ def test_blocks_with_padded_keys_inside(tail, mode, g, r, H):
     assert err_o <= TOL["bf16"] and err_l <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("H,nb,g,w,r", [(2, 9, 2, 3, 3), (40, 9, 1, 3, 0), (40, 10, 2, 5, 3), (24, 20, 1, 15, 4)])
+@pytest.mark.parametrize("skip", [False, True])
+@pytest.mark.parametrize("gain", [1.0, 40.0])
+def test_running_maximum_in_the_streams(H, nb, g, w, r, skip, gain):
+    """bf16: items with and without padded keys inside a block side by side in a wave's stream (rows by a workgroup
+    at H = 2), lists of one block up to two slices of 16; blocks whose first or second 32 keys, or all but one, are
+    padded.  LSE is an fp32 sum there: 1e-5 of its size, where rounding the probabilities first would give 2^-9."""
+    torch = torch_mod()
+    B, n = 3, nb * 64
+    t = inp.make_tensors(B, H, n, 64, 300 + nb, "bf16")
+    Qg = t["Q"] * np.float32(gain)          # a power of two times the rounded values would be exact; round again
+    u = np.ascontiguousarray(Qg, dtype=np.float32).view(np.uint32)
+    bits = ((u + 0x7fff + ((u >> 16) & 1)) >> 16).astype(np.uint16)
+    t["Q_bits"], t["Q"] = bits, (bits.astype(np.uint32) << 16).view(np.float32)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 5)
+    km = np.ones((B, n), dtype=np.uint8)
+    km[0, :32] = 0                          # first half of the first global block
+    km[0, 3 * 64 + 32:4 * 64] = 0           # second half of block 3
+    km[0, 5 * 64:5 * 64 + 63] = 0           # all but the last key of block 5
+    km[1, (nb - 2) * 64 + 1:] = 0           # one key of the last block that has any
+    km[2] = np.random.default_rng(nb).integers(0, 2, n)  # every block cut
+    mode = bb.BB_SKIP_PADDED_QUERY_BLOCKS if skip else 0
+    kw = dict(key_mask=km)
+    Oref, Lref = oracle.attn_fwd(t["Q"], t["K"], t["V"], ridx, 64, g, w, 0.125, **kw)
+    Q, K, V = device_qkv(t, "bf16")
+    O, LSE = bb.bigbird_attn_fwd(Q, K, V, torch.from_numpy(ridx).to("cuda:0"), g=g, w=w, scale=0.125,
+                                 key_padding_mask=torch.from_numpy(km).to("cuda:0"), global_mode=mode)
+    Oh, Lh = to_host(O), to_host(LSE)
+    if skip:
+        dead = ~km.reshape(B, nb, 64).any(axis=2).repeat(64, axis=1)
+        Oref = np.where(dead[:, None, :, None], 0.0, Oref)
+        Lref = np.where(dead[:, None, :], -np.inf, Lref)
+    fin = np.isfinite(Lref)
+    assert (np.isneginf(Lh) == ~fin).all()
+    assert np.abs(Oh - Oref).max() <= TOL["bf16"]
+    # batch entry 2: every list has a cut block; others: items without one sum the rounded probabilities
+    err = np.abs(np.where(fin, Lh, 0) - np.where(fin, Lref, 0)) / np.maximum(1.0, np.abs(np.where(fin, Lref, 0)))
+    assert err[2].max() <= 1e-5 and err.max() <= 2.0 ** -8
+
+
 @pytest.mark.parametrize("B,H,nb,g,w,r", [
     (1, 1, 1, 1, 1, 0), (1, 1, 3, 0, 1, 0), (1, 3, 9, 2, 3, 3), (1, 16, 18, 2, 3, 3), (1, 17, 17, 2, 3, 3),
     (1, 2, 66, 1, 3, 60), (1, 2, 70, 1, 3, 61), (1, 1, 130, 2, 3, 12)])
