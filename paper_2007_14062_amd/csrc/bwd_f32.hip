@@ -8,12 +8,13 @@
 //
 // fp32 MFMA 32x32x2 throughout, four waves per item, a wave per 32x32 quarter of every block pair
 // (f32_ops.h).  What bounds them is the fp32 matrix rate (a block pair is 96 / 128 MFMAs of 64 cycles per
-// wave) and, at small sizes, the longest slice: hence slices down to a single pair (fine_slice_f32).
-// n = 1024, 2 heads: dQ 18 us, dK/dV 27 us, reduction 4 us, where one workgroup per block with vector
-// arithmetic took 313 and 358; n = 4096, 24 slices, forward and backward: 0.73 ms against 10.7.
+// wave) and, at small sizes, the longest slice: hence slices down to a single pair (fine_slice_f32), and for the
+// smallest launches the kernels at the end of this file.
+// n = 4096, 24 slices, forward and backward: 0.73 ms, where one workgroup per block with vector arithmetic took 10.7.
 // (dK/dV is held to two waves per SIMD: 29 registers spilled, but 0.73 against 0.78 ms.)
 #include "bwd_kernels.h"
 #include "f32_ops.h"
+#include "f32_rows.h"
 
 #include <cstdio>
 
@@ -267,7 +268,266 @@ __global__ __launch_bounds__(kThreadsF32) __attribute__((amdgpu_waves_per_eu(2))
   store_rows_f32((it.nchunks == 1 ? p.dV : p.part_dv) + off, dv, hf);
 }
 
+// ---------------------------------------------------------------------------------------
+// Small launches (rows_f32_bwd): a workgroup per eight queries (dQ) or eight keys (dK, dV), see f32_rows.h.  Tiles come
+// as a stream of quarters (sixteen rows of both), one ahead.
+// ---------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kRowsThreadsF32) __attribute__((amdgpu_waves_per_eu(2))) void bwd_rows_f32_dq_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(1024))) char ring_all[kRowsWavesF32][2][2][kQuarterF32];  // a wave's K and V quarters; then its dQ
+  __shared__ int klist_all[kRowsWavesF32][kMaxListLen];
+  __shared__ uint32_t key_bits_all[kRowsWavesF32][kMaxListLen][2];
+
+  const Pattern pat{p.nb, p.g, p.w, p.global_mode};
+  OwnItem it;
+  if (!decode_own(pat, p.BH, blockIdx.x, &it)) return;
+  const int bi = it.bh / p.H, h = it.bh % p.H;
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const RowsLane l(lane);
+  const size_t bh_row0 = static_cast<size_t>(it.bh) * p.n;
+  const size_t row0 = bh_row0 + static_cast<size_t>(it.j) * kBlk + it.first;
+  const float* Kp = static_cast<const float*>(p.K) + bh_row0 * kDim;
+  const float* Vp = static_cast<const float*>(p.V) + bh_row0 * kDim;
+
+  f32x4 qf[2][4], gf[2][4];
+  own_rows(static_cast<const float*>(p.Q) + row0 * kDim, l, qf);
+  own_rows(static_cast<const float*>(p.dO) + row0 * kDim, l, gf);
+  float dsum[2], lse2[2];
+  {
+    f32x4 of[2][4];
+    own_rows(static_cast<const float*>(p.O) + row0 * kDim, l, of);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float part = 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part = __builtin_fmaf(gf[q][u][e], of[q][u][e], part);
+      dsum[q] = part;
+      lse2[q] = p.LSE[row0 + 4 * q + l.t];
+    }
+  }
+  // a query block that was skipped (no valid position) behaves like rows without a valid key
+  const bool skip = p.skip_q && !block_any_valid_scalar(p.kmask, bi, p.n, it.j);
+  int cnt = 0;
+  KeyList list = {0, 0, 0u};
+  if (!skip) {
+    list = own_key_list(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it, wv, lane, klist_all[wv], key_bits_all[wv]);
+    cnt = __builtin_amdgcn_readfirstlane(list.cnt);
+  }
+  uint32_t drop_rk[2] = {0u, 0u};
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    dsum[q] = skip ? 0.f : add_over_groups(dsum[q]);
+    lse2[q] = (skip || lse2[q] == neg_inf()) ? __builtin_inff() : lse2[q] * kLog2e;  // no valid key: every P is 0
+    if (wv == 0 && lane < 4) {
+      p.Dvec[row0 + 4 * q + lane] = dsum[q];
+      p.Lvec[row0 + 4 * q + lane] = lse2[q];
+    }
+    if (p.drop.thr) drop_rk[q] = drop_row_key(p.drop, static_cast<uint32_t>(row0 + 4 * q + l.t));
+  }
+
+  const float c = p.c;
+  f32x4 dq[2][4];
+  clear_own(dq);
+  const QuarterLoads ql(lane);
+  const QuarterForms qforms(l);
+  const unsigned ring_a = lds_addr(ring_all[wv]);
+  // quarters of the list's K and V tiles, one ahead
+  auto request = [&](int i, int kt) {
+    const size_t off = static_cast<size_t>(__builtin_amdgcn_readlane(list.entry, i)) * (kBlk * kDim) + kt * 16 * kDim;
+    ql.request(Kp + off, ring_a + (kt & 1) * (2 * kQuarterF32));
+    ql.request(Vp + off, ring_a + (kt & 1) * (2 * kQuarterF32) + kQuarterF32);
+  };
+  if (cnt > 0) request(0, 0);
+  for (int i = 0; i < cnt; ++i) {
+    const int kb = __builtin_amdgcn_readlane(list.entry, i);
+    const bool cut = (list.partial >> i) & 1;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+      wait_lds_reads();  // the other place of the ring is free
+      if (kt < 3 || i + 1 < cnt) {
+        request(kt < 3 ? i : i + 1, (kt + 1) & 3);
+        wait_tile_loads<2 * kQuarterLoads>();
+      } else {
+        wait_tile_loads<0>();
+      }
+      const char (*quarter)[kQuarterF32] = ring_all[wv][kt & 1];
+      f32x4 x[4], y[4];
+      float s[2], dp[2];
+      qforms.row_form(quarter[0], x);
+      qforms.row_form(quarter[1], y);
+      row_products(x, qf, s, y, gf, dp);
+      const uint32_t key = static_cast<uint32_t>(kb * kBlk + l.row(kt));
+      const bool valid = !cut || row_valid(key_bits_all[wv][i], l, kt);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (p.drop.thr) {  // dP = M / (1 - p) o (dO V^T), M the keep mask
+          const uint32_t wd = drop_word(drop_rk[q], key >> 1);
+          dp[q] = ((key & 1u) ? drop_keep_odd(wd, p.drop.thr) : drop_keep_even(wd, p.drop.thr)) ? dp[q] * p.drop.rs : 0.f;
+        }
+        const float ds = fast_exp2(__builtin_fmaf(s[q], c, -lse2[q])) * (dp[q] - dsum[q]);
+        s[q] = valid ? ds : 0.f;  // (selected: the K row of a padded key may hold anything)
+      }
+      qforms.column_form(quarter[0], x);
+      add_rows(x, s, dq);
+    }
+  }
+
+  wait_lds_reads();
+  auto dq_of = [&](int v) { return reinterpret_cast<float (*)[kDim]>(ring_all[v][0][0]); };
+  store_own(dq_of(wv), l, dq);
+  __syncthreads();
+  float acc = 0.f;
+#pragma unroll
+  for (int v = 0; v < kRowsWavesF32; ++v) acc += dq_of(v)[wv][lane];
+  p.dQ[(row0 + wv) * kDim + lane] = acc * p.scale;
+}
+
+// Query blocks that attend key block k, one in kRowsWavesF32 of them (those of wave wv) into jlist, by that wave; returns how many.
+// A lane looks at query block j0 + lane: one trip to memory for up to four random blocks a row.
+__device__ __forceinline__ int own_query_list(const BwdParams& p, const Pattern& pat, int bi, int h, int k, bool key_global,
+                                              int wv, int lane, int* jlist) {
+  const int32_t* tbl = p.rand_idx ? p.rand_idx + static_cast<size_t>(h) * p.nb * p.r : nullptr;
+  int cnt = 0;
+  for (int j0 = 0; j0 < p.nb; j0 += 64) {
+    const int j = j0 + lane;
+    bool valid = j < p.nb;
+    if (valid && !key_global && !pat.is_global(j) && !pat.in_window(j, k)) {
+      valid = false;
+      for (int t0 = 0; tbl && t0 < p.r; t0 += 4) {
+        int e[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) e[t] = tbl[static_cast<size_t>(j) * p.r + (t0 + t < p.r ? t0 + t : p.r - 1)];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) valid |= e[t] == k;
+      }
+    }
+    if (p.skip_q && valid) valid = block_has_valid_key(p.kmask, bi, p.n, j);
+    const uint64_t mask = __ballot(valid);
+    const int rank = cnt + mask_rank(mask);
+    if (valid && rank % kRowsWavesF32 == wv) jlist[rank / kRowsWavesF32] = j;
+    cnt += static_cast<int>(__popcll(mask));
+  }
+  asm volatile("" ::: "memory");  // the same wave reads the list: LDS keeps a wave's accesses in order, the compiler must too
+  return cnt > wv ? (cnt - wv + kRowsWavesF32 - 1) / kRowsWavesF32 : 0;
+}
+
+__global__ __launch_bounds__(kRowsThreadsF32) __attribute__((amdgpu_waves_per_eu(2))) void bwd_rows_f32_dkv_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(1024))) char ring_all[kRowsWavesF32][2][2][kQuarterF32];  // a wave's Q and dO quarters; then its dK, dV
+  __shared__ __attribute__((aligned(256))) float vec_all[kRowsWavesF32][2][2][kBlk];          // LSE log2(e) and D of the rows of an entry
+  __shared__ int jlist_all[kRowsWavesF32][kMaxListLen];
+
+  const Pattern pat{p.nb, p.g, p.w, p.global_mode};
+  OwnItem it;
+  if (!decode_own(pat, p.BH, blockIdx.x, &it)) return;
+  const int bi = it.bh / p.H, h = it.bh % p.H;
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const RowsLane l(lane);
+  const size_t bh_row0 = static_cast<size_t>(it.bh) * p.n;
+  const size_t key0 = bh_row0 + static_cast<size_t>(it.j) * kBlk + it.first;  // first own key
+  const float* Qp = static_cast<const float*>(p.Q) + bh_row0 * kDim;
+  const float* Gp = static_cast<const float*>(p.dO) + bh_row0 * kDim;
+
+  f32x4 kf[2][4], vf[2][4];
+  own_rows(static_cast<const float*>(p.K) + key0 * kDim, l, kf);
+  own_rows(static_cast<const float*>(p.V) + key0 * kDim, l, vf);
+  const int cnt = __builtin_amdgcn_readfirstlane(own_query_list(p, pat, bi, h, it.j, it.global, wv, lane, jlist_all[wv]));
+
+  const float c = p.c;
+  f32x4 dk[2][4], dv[2][4];
+  clear_own(dk);
+  clear_own(dv);
+  const QuarterLoads ql(lane);
+  const QuarterForms qforms(l);
+  const unsigned ring_a = __builtin_amdgcn_readfirstlane(lds_addr(ring_all[wv]));
+  const unsigned vec_a = __builtin_amdgcn_readfirstlane(lds_addr(vec_all[wv]));
+  // quarters of the list's Q and dO tiles, one ahead; LSE and D of an entry come with its first
+  auto entry = [&](int i) { return __builtin_amdgcn_readfirstlane(jlist_all[wv][i]); };
+  auto request = [&](int i, int j, int kt) {
+    const size_t off = static_cast<size_t>(j) * (kBlk * kDim) + kt * 16 * kDim;
+    ql.request(Qp + off, ring_a + (kt & 1) * (2 * kQuarterF32));
+    ql.request(Gp + off, ring_a + (kt & 1) * (2 * kQuarterF32) + kQuarterF32);
+    if (kt == 0) {
+      const size_t row = bh_row0 + static_cast<size_t>(j) * kBlk;
+      vec_load_async(p.Lvec + row, vec_a + (i & 1) * (2 * kBlk * 4), lane);
+      vec_load_async(p.Dvec + row, vec_a + (i & 1) * (2 * kBlk * 4) + kBlk * 4, lane);
+    }
+  };
+  if (cnt > 0) request(0, entry(0), 0);
+  for (int i = 0; i < cnt; ++i) {
+    const int j = entry(i);
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+      wait_lds_reads();  // the other place of the ring is free
+      if (kt < 3) {
+        request(i, j, kt + 1);
+        wait_tile_loads<2 * kQuarterLoads>();
+      } else if (i + 1 < cnt) {
+        request(i + 1, entry(i + 1), 0);
+        wait_tile_loads<2 * kQuarterLoads + 2>();
+      } else {
+        wait_tile_loads<0>();
+      }
+      const char (*quarter)[kQuarterF32] = ring_all[wv][kt & 1];
+      f32x4 x[4], y[4];
+      float s[2], dp[2];
+      qforms.row_form(quarter[0], x);
+      qforms.row_form(quarter[1], y);
+      row_products(x, kf, s, y, vf, dp);
+      const float lse2 = vec_all[wv][i & 1][0][l.row(kt)], dsum = vec_all[wv][i & 1][1][l.row(kt)];
+      const uint32_t rk = p.drop.thr ? drop_row_key(p.drop, static_cast<uint32_t>(bh_row0 + static_cast<size_t>(j) * kBlk + l.row(kt))) : 0u;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const float pr = fast_exp2(__builtin_fmaf(s[q], c, -lse2));
+        float mr = 1.f;  // attention dropout: dV takes the kept, rescaled probabilities; dP is masked the same way
+        if (p.drop.thr) {
+          const uint32_t key = static_cast<uint32_t>(it.j * kBlk + it.first + 4 * q + l.t);
+          const uint32_t wd = drop_word(rk, key >> 1);
+          mr = ((key & 1u) ? drop_keep_odd(wd, p.drop.thr) : drop_keep_even(wd, p.drop.thr)) ? p.drop.rs : 0.f;
+        }
+        s[q] = pr * mr;
+        dp[q] = pr * (dp[q] * mr - dsum);
+      }
+      qforms.column_form(quarter[1], y);
+      qforms.column_form(quarter[0], x);
+      add_rows(y, s, dv);
+      add_rows(x, dp, dk);
+    }
+  }
+
+  wait_lds_reads();
+  auto dk_of = [&](int v) { return reinterpret_cast<float (*)[kDim]>(ring_all[v][0][0]); };
+  auto dv_of = [&](int v) { return reinterpret_cast<float (*)[kDim]>(ring_all[v][0][1]); };
+  store_own(dk_of(wv), l, dk);
+  store_own(dv_of(wv), l, dv);
+  const bool key_valid = !p.kmask || p.kmask[static_cast<size_t>(bi) * p.n + it.j * kBlk + it.first + wv] != 0;
+  __syncthreads();
+  float a = 0.f, b = 0.f;
+#pragma unroll
+  for (int v = 0; v < kRowsWavesF32; ++v) {
+    a += dk_of(v)[wv][lane];
+    b += dv_of(v)[wv][lane];
+  }
+  // gradients of a padded key are exactly 0 (selected, not multiplied: its K row may hold anything)
+  p.dK[(key0 + wv) * kDim + lane] = key_valid ? a * p.scale : 0.f;
+  p.dV[(key0 + wv) * kDim + lane] = key_valid ? b : 0.f;
+}
+
 int launch_bwd_f32(const BwdParams& p, hipStream_t stream) {
+  if (rows_f32_bwd(p.BH, p.nb)) {
+    const unsigned grid = own_grid(p.BH, p.nb);
+    hipLaunchKernelGGL(bwd_rows_f32_dq_kernel, dim3(grid), dim3(kRowsThreadsF32), 0, stream, p);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) {
+      hipLaunchKernelGGL(bwd_rows_f32_dkv_kernel, dim3(grid), dim3(kRowsThreadsF32), 0, stream, p);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) {
+      fprintf(stderr, "bigbird: launch of the fp32 backward kernels failed: %s\n", hipGetErrorString(e));
+      return BB_ERR_LAUNCH;
+    }
+    return BB_OK;
+  }
   const unsigned qgrid = DieItems(p.BH, p.split.items_per_bh).grid();
   const unsigned kvgrid = DieItems(p.BH, p.kv.items_per_bh).grid();
   hipLaunchKernelGGL(bwd_f32_dq_kernel, dim3(qgrid), dim3(kThreadsF32), 0, stream, p);

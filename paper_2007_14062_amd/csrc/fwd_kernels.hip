@@ -11,6 +11,7 @@
 // wants its B operand (the contraction order over keys is free, so V^T is read
 // from LDS in the matching permuted key order).
 #include "f32_ops.h"
+#include "f32_rows.h"
 #include "fwd_epilogue.h"
 
 #include <cstdio>
@@ -21,8 +22,8 @@ namespace bb {
 // 32 of the 64 keys of every block with an online softmax of its own, and the two key halves are merged
 // in LDS at the end.  What bounds it is the fp32 matrix rate (a block pair is 64 MFMAs of 64 cycles per
 // wave: 2 us) and, at small sizes, the length of the longest slice: hence the fine slices
-// (fine_slice_f32).  n = 1024, 2 heads: 20 us a call with the merge launch; two waves over slices of 8
-// blocks took 44.  n = 2048, 12 heads: 50 against 92.
+// (fine_slice_f32).  n = 2048, 12 heads: 50 us a call, where two waves over slices of 8 blocks took 92.  The smallest
+// launches take fwd_rows_f32.
 __global__ __launch_bounds__(kThreadsF32) void fwd_kernel_f32(FwdParams p) {
   __shared__ __attribute__((aligned(16))) float lds_k[kBlk * kF32Stride];
   __shared__ __attribute__((aligned(16))) float lds_v[kBlk * kF32Stride];
@@ -163,6 +164,158 @@ __global__ __launch_bounds__(kThreadsF32) void fwd_kernel_f32(FwdParams p) {
   fwd_store(p, it, o, m_all, l_tot, c, qrow, qh * 32 + col, hf);
 }
 
+// Small fp32 launches (rows_f32_fwd): a workgroup per eight queries (f32_rows.h), an online softmax per wave over its share
+// of the key blocks, the waves merged in LDS: one launch.  (K and V as one stream of quarters through a ring, three
+// ahead, took 12.1 us where this takes 11.7: 2 slices of n = 1024.)
+__global__ __launch_bounds__(kRowsThreadsF32) __attribute__((amdgpu_waves_per_eu(2))) void fwd_rows_f32(FwdParams p) {
+  __shared__ __attribute__((aligned(1024))) char k_all[kRowsWavesF32][4][kQuarterF32];  // a wave's K tile; then its O
+  __shared__ float m_all[kRowsWavesF32][kOwn], l_all[kRowsWavesF32][kOwn];
+  __shared__ int klist_all[kRowsWavesF32][kMaxListLen];
+  __shared__ uint32_t key_bits_all[kRowsWavesF32][kMaxListLen][2];
+
+  const Pattern pat{p.nb, p.g, p.w, p.global_mode};
+  OwnItem it;
+  if (!decode_own(pat, p.BH, blockIdx.x, &it)) return;
+  const int bi = it.bh / p.H, h = it.bh % p.H;
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const RowsLane l(lane);
+  const size_t bh_row0 = static_cast<size_t>(it.bh) * p.n;
+  const size_t row0 = bh_row0 + static_cast<size_t>(it.j) * kBlk + it.first;  // first own query
+  const float* Kp = static_cast<const float*>(p.K) + bh_row0 * kDim;
+  const float* Vp = static_cast<const float*>(p.V) + bh_row0 * kDim;
+
+  f32x4 qf[2][4];
+  own_rows(static_cast<const float*>(p.Q) + row0 * kDim, l, qf);
+  // (a query block without a valid position, if the caller asked for those to be skipped, is an empty row)
+  const bool skip = p.skip_q && !block_any_valid_scalar(p.kmask, bi, p.n, it.j);
+  int cnt = 0;
+  KeyList list = {0, 0, 0u};
+  if (!skip) {
+    list = own_key_list(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it, wv, lane, klist_all[wv], key_bits_all[wv]);
+    cnt = __builtin_amdgcn_readfirstlane(list.cnt);
+  }
+
+  const float c = p.c;
+  f32x4 o[2][4];
+  clear_own(o);
+  float m_run[2] = {neg_inf(), neg_inf()};  // running maxima of the raw scores of queries 4 q + t
+  float l_run[2] = {0.f, 0.f};              // this lane's share of the sums of 2^((q.k - m) c)
+  uint32_t drop_rk[2] = {0u, 0u};
+  if (p.drop.thr) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) drop_rk[q] = drop_row_key(p.drop, static_cast<uint32_t>(row0 + 4 * q + l.t));
+  }
+  // K goes through LDS, V straight to registers in the form its product wants; both are requested while the entry
+  // before is in work
+  const QuarterLoads ql(lane);
+  const QuarterForms qforms(l);
+  const unsigned k_a = lds_addr(k_all[wv]);
+  f32x4 z[4][4];
+  auto request_k = [&](int i) {
+    const float* t = Kp + static_cast<size_t>(__builtin_amdgcn_readlane(list.entry, i)) * (kBlk * kDim);
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) ql.request(t + kt * 16 * kDim, k_a + kt * kQuarterF32);
+  };
+  auto request_v = [&](int i, int kt) {
+    const float* t = Vp + static_cast<size_t>(__builtin_amdgcn_readlane(list.entry, i)) * (kBlk * kDim);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) z[kt][s] = *reinterpret_cast<const f32x4*>(t + (16 * kt + 4 * s + l.g) * kDim + 4 * l.m);
+  };
+  if (cnt > 0) {
+    request_k(0);
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) request_v(0, kt);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  for (int i = 0; i < cnt; ++i) {
+    const int kb = __builtin_amdgcn_readlane(list.entry, i);
+    float s[4][2];
+    wait_tile_loads<16 + 2 * kQuarterLoads>();  // half of K(i): the sixteen loads of V(i) are younger
+#pragma unroll
+    for (int kt = 0; kt < 4; kt += 2) {
+      if (kt == 2) wait_tile_loads<16>();
+      f32x4 x0[4], x1[4];
+      qforms.row_form(k_all[wv][kt], x0);
+      qforms.row_form(k_all[wv][kt + 1], x1);
+      row_products(x0, qf, s[kt], x1, qf, s[kt + 1]);
+    }
+    wait_lds_reads();
+    const bool more = i + 1 < cnt;
+    if (more) request_k(i + 1);
+    if ((list.partial >> i) & 1) {  // padded keys -> -inf (selected: their scores may be anything)
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) {
+        const bool valid = row_valid(key_bits_all[wv][i], l, kt);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) s[kt][q] = valid ? s[kt][q] : neg_inf();
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float m_new = fmaxf(m_run[q], max_over_rows(fmaxf(fmaxf(s[0][q], s[1][q]), fmaxf(s[2][q], s[3][q]))));
+      const float m_use = m_new == neg_inf() ? 0.f : m_new;
+      const float alpha = fast_exp2((m_run[q] - m_use) * c);
+      const float mc = m_use * c;
+      float sum = 0.f;
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) {
+        s[kt][q] = fast_exp2(__builtin_fmaf(s[kt][q], c, -mc));
+        sum += s[kt][q];
+      }
+      l_run[q] = l_run[q] * alpha + sum;
+      m_run[q] = m_new;
+      const float al[4] = {of_position<0>(alpha), of_position<1>(alpha), of_position<2>(alpha), of_position<3>(alpha)};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[q][e][u] *= al[u];
+    }
+    if (p.drop.thr) {  // (the sums are those of the undropped probabilities)
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) {
+        const uint32_t key = static_cast<uint32_t>(kb * kBlk + l.row(kt));
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const uint32_t wd = drop_word(drop_rk[q], key >> 1);
+          if (!((key & 1u) ? drop_keep_odd(wd, p.drop.thr) : drop_keep_even(wd, p.drop.thr))) s[kt][q] = 0.f;
+        }
+      }
+    }
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+      add_rows(z[kt], s[kt], o);
+      if (more) request_v(i + 1, kt);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  auto o_of = [&](int v) { return reinterpret_cast<float (*)[kDim]>(k_all[v][0]); };
+  store_own(o_of(wv), l, o);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const float sum = add_over_rows(l_run[q]);
+    if (lane < 4) {
+      m_all[wv][4 * q + lane] = m_run[q];
+      l_all[wv][4 * q + lane] = sum;
+    }
+  }
+  __syncthreads();
+  // wave wv finishes query wv, lane d
+  float M = neg_inf();
+#pragma unroll
+  for (int v = 0; v < kRowsWavesF32; ++v) M = fmaxf(M, m_all[v][wv]);
+  const float ref = M == neg_inf() ? 0.f : M;
+  float L = 0.f, acc = 0.f;
+#pragma unroll
+  for (int v = 0; v < kRowsWavesF32; ++v) {
+    const float wgt = fast_exp2((m_all[v][wv] - ref) * c);  // 0 for a wave without a key
+    L += l_all[v][wv] * wgt;
+    acc += o_of(v)[wv][lane] * wgt;
+  }
+  static_cast<float*>(p.O)[(row0 + wv) * kDim + lane] = acc * (L > 0.f ? p.drop.rs / L : 0.f);  // (rs: 1, or the dropout scale)
+  if (lane == 0) p.LSE[row0 + wv] = L > 0.f ? (M * c + fast_log2(L)) * kLn2 : neg_inf();
+}
+
 // Merge the slices of a split row: M = max m_c, L = sum l_c 2^(m_c - M),
 // O = sum O~_c 2^(m_c - M) / L, LSE = (M + log2 L) ln 2.  Four workgroups per
 // (batch, head, split row), 16 queries each; thread t owns 4 d columns of query
@@ -253,6 +406,9 @@ int launch_fwd(const FwdParams& p, bool bf16, hipStream_t stream) {
   if (bf16) {
     const int st = launch_fwd_bf16_main(p, stream);
     if (st != BB_OK) return st;
+  } else if (rows_f32_fwd(p.BH, p.nb)) {
+    hipLaunchKernelGGL(fwd_rows_f32, dim3(own_grid(p.BH, p.nb)), dim3(kRowsThreadsF32), 0, stream, p);
+    return launch_failed("fwd_rows_f32") ? BB_ERR_LAUNCH : BB_OK;
   } else {
     const unsigned grid = DieItems(p.BH, p.split.items_per_bh).grid();
     if (grid == 0) return BB_OK;
