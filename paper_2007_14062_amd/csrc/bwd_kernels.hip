@@ -164,7 +164,7 @@ struct DqState {
 // dS of the previous unit (query tile q), packed as B operand.
 template <bool kDrop>
 __device__ __forceinline__ void dq_ds(const DqState& st, const f32x16& p, const f32x16& dp, int q,
-                                      const Dropout& drop, uint32_t drop_rk, uint32_t key0, int hf,
+                                      const Dropout& drop, uint32_t drop_rk, const uint32_t* drop_words,
                                       bf16x8 (&dsb)[2]) {
   const float d = st.d[q];
 #pragma unroll
@@ -172,9 +172,9 @@ __device__ __forceinline__ void dq_ds(const DqState& st, const f32x16& p, const 
     float x0, x1;
     if constexpr (kDrop) {
       // registers r, r + 1 are keys 2m, 2m + 1: one word of the mask
-      const uint32_t wd = drop_word(drop_rk, (key0 + acc_row(r, hf)) >> 1);
-      x0 = drop_keep_even(wd, drop.thr) ? __builtin_fmaf(dp[r], drop.rs, -d) : -d;
-      x1 = drop_keep_odd(wd, drop.thr) ? __builtin_fmaf(dp[r + 1], drop.rs, -d) : -d;
+      const uint32_t wd = drop_doubled(drop_rk ^ drop_words[r >> 1]);
+      x0 = drop_keep_low(wd, drop.thr) ? __builtin_fmaf(dp[r], drop.rs, -d) : -d;
+      x1 = drop_keep_high(wd, drop.thr) ? __builtin_fmaf(dp[r + 1], drop.rs, -d) : -d;
     } else {
       x0 = dp[r] - d;
       x1 = dp[r + 1] - d;
@@ -220,6 +220,7 @@ void bwd_dq_kernel(BwdParams p) {
   __shared__ int klist_all[kWaves][kChunkMax];
   __shared__ uint32_t key_bits_all[kWaves][kChunkMax][2];  // validity of the keys of blocks with padded keys inside
   __shared__ float dvals_all[kWaves][kBlk];
+  __shared__ __attribute__((aligned(16))) uint32_t drop_words_all[kDrop ? kWaves : 1][2][32];  // key words of two blocks in turn
   const int wv = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   char (&lds)[2][kTile] = lds_all[wv];
   int* const klist = klist_all[wv];
@@ -316,7 +317,7 @@ void bwd_dq_kernel(BwdParams p) {
   uint32_t drop_rk[2] = {0u, 0u};
   if constexpr (kDrop) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) drop_rk[q] = drop_row_key(p.drop, static_cast<uint32_t>(row0 + q * 32 + col));
+    for (int q = 0; q < 2; ++q) drop_rk[q] = drop_first(drop_row_key(p.drop, static_cast<uint32_t>(row0 + q * 32 + col)));
   }
 
   const TransposedOffsets to(lane);
@@ -376,22 +377,22 @@ void bwd_dq_kernel(BwdParams p) {
     // block i; its K tile is lds[X], its V tile lds[X ^ 1]
     auto block = [&](int i, auto X) {
       constexpr int kx = decltype(X)::value;
-      const int kb = __builtin_amdgcn_readlane(kl, i);
-      const int kprev = __builtin_amdgcn_readlane(kl, i > 0 ? i - 1 : 0);
+      if constexpr (kDrop)
+        drop_key_words(drop_words_all[wv][kx], static_cast<uint32_t>(__builtin_amdgcn_readlane(kl, i)), lane_again(lane));
       const size_t off1 = tile_off(i + 1);
       const char* k1 = kbase + off1;
       const char* v1 = vbase + off1;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
-        // key number of the first key of the previous unit's half (tile B of the half before this one)
-        const uint32_t key_prev = static_cast<uint32_t>((hh ? kb : kprev) * kBlk + (hh ^ 1) * 32);
-        const uint32_t key_cur = static_cast<uint32_t>(kb * kBlk + hh * 32);
+        // key words of the previous unit's half (tile B of the half before this one) and of this one
+        const uint32_t* const words_prev = drop_unit_words(drop_words_all[kDrop ? wv : 0][hh ? kx : kx ^ 1], hh ^ 1, hf);
+        const uint32_t* const words_cur = drop_unit_words(drop_words_all[kDrop ? wv : 0][kx], hh, hf);
         f32x16 s_new;
         // ---- a(A): V fragments of this half (the two requests after it are still out)
         wait_tile_loads<8>();
         read_straight_half(so, lds[kx ^ 1], hh, st.va);
         products(st.ka, st.qb[0], s_new);
-        dq_ds<kDrop>(st, st.s, st.dp, 1, p.drop, drop_rk[1], key_prev, hf, dsb);
+        dq_ds<kDrop>(st, st.s, st.dp, 1, p.drop, drop_rk[1], words_prev, dsb);
         pin_a<4, 10>();
         mask_ds(hh ? i : (i > 0 ? i - 1 : 0), hh ^ 1);
         st.s = s_new;
@@ -404,7 +405,7 @@ void bwd_dq_kernel(BwdParams p) {
         // ---- a(B)
         read_transposed_half(to, lds[kx], hh, st.kt);
         products(st.ka, st.qb[1], s_new);
-        dq_ds<kDrop>(st, st.s, st.dp, 0, p.drop, drop_rk[0], key_cur, hf, dsb);
+        dq_ds<kDrop>(st, st.s, st.dp, 0, p.drop, drop_rk[0], words_cur, dsb);
         pin_a<8, 10>();
         mask_ds(i, hh);
         st.s = s_new;
@@ -423,12 +424,9 @@ void bwd_dq_kernel(BwdParams p) {
       if (i + 1 < cnt) block(i + 1, std::integral_constant<int, 1>{});
     }
     // the last unit's dS and its share of dQ
-    {
-      const int kb = __builtin_amdgcn_readlane(kl, cnt - 1);
-      dq_ds<kDrop>(st, st.s, st.dp, 1, p.drop, drop_rk[1], static_cast<uint32_t>(kb * kBlk + 32), hf, dsb);
-      mask_ds(cnt - 1, 1);
-      dq_update(1);
-    }
+    dq_ds<kDrop>(st, st.s, st.dp, 1, p.drop, drop_rk[1], drop_unit_words(drop_words_all[kDrop ? wv : 0][(cnt - 1) & 1], 1, hf), dsb);
+    mask_ds(cnt - 1, 1);
+    dq_update(1);
     wait_tile_loads<0>();  // requests past the end of the list
   }
 
@@ -576,7 +574,7 @@ void bwd_dkv_kernel(BwdParams p) {
       vec_load_async(vecbase + static_cast<size_t>(j) * kBlk, vec_a + place * (kBlk * 4), lane);
       if constexpr (kDrop) {
         if (wv == 0)
-          lds_rk[place][lane] = drop_row_key(p.drop, static_cast<uint32_t>(bh_row0 + static_cast<size_t>(j) * kBlk + lane));
+          lds_rk[place][lane] = drop_first(drop_row_key(p.drop, static_cast<uint32_t>(bh_row0 + static_cast<size_t>(j) * kBlk + lane)));
       }
     };
     request(0, entry(0), 0);
@@ -637,7 +635,7 @@ void bwd_dkv_kernel(BwdParams p) {
         for (int e = 0; e < 8; ++e) qt[a][b][e] = static_cast<__bf16>(0.f);
     }
     // (dropout) this lane's key: its pair's share of the words' argument, its half of a word
-    const uint32_t my_pair = (static_cast<uint32_t>(k * kBlk + wv * 32 + col) >> 1) * kDropPairStep;
+    const uint32_t my_pair = drop_first((static_cast<uint32_t>(k * kBlk + wv * 32 + col) >> 1) * kDropPairStep);
     const int odd = col & 1, my_shift = odd * 16;
     const uint32_t drop_thr = kDrop ? drop_pair_threshold(p.drop) : 0u;
     // keep bits of this lane's key, bit r: the query of accumulator register r.  A word of the mask serves two
@@ -648,7 +646,8 @@ void bwd_dkv_kernel(BwdParams p) {
       for (int u = 0; u < 2; ++u) {
         const u32x4 k4 = *reinterpret_cast<const u32x4*>(row_keys + odd * 16 + acc_row(u * 4, hf));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) both |= drop_keep_pair(drop_mix(k4[e] ^ my_pair), drop_thr) & (0x00010001u << (u * 4 + e));
+        for (int e = 0; e < 4; ++e)
+          both |= drop_keep_pair(drop_doubled(k4[e] ^ my_pair), drop_thr) << (u * 4 + e);
       }
       const uint32_t other = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(both), 0xB1, 0xf, 0xf, true));  // quad_perm [1, 0, 3, 2]
       const uint32_t mine = (both >> my_shift) & 0xffu, theirs = (other >> my_shift) & 0xffu;

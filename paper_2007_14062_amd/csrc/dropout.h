@@ -54,16 +54,48 @@ BB_HD bool drop_keep(const Dropout& dr, uint32_t rowid, uint32_t key) {
 }
 
 #if defined(__HIPCC__)
-// The two keys of a word together: their keep bits as a mask for a register that holds the pair in 16 bits
-// each (even key low).  u >= T as the sign of T - 1 - u, both halves at once: four instructions
-// where two tests and two selections take six.
-typedef __attribute__((ext_vector_type(2))) short s16x2;
+// The same in the form the bf16 kernels use, with fewer instructions for a word:
+//   * the first step of mix is linear over xor, so it is done once for a row key and once for a pair of keys
+//     (drop_first) and not for every (row, pair); the pairs' side comes from a small table in LDS;
+//   * with twice the second factor the numbers end up doubled, in bits 1..15 and 17..31 of one word, each above a
+//     bit that does not matter: 2 u + (0 or 1) >= 2 T if and only if u >= T.  That saves masking them.
+// Words are what bounds the kernels under dropout (vector port; 32 of them a block pair and wave): 8 instructions each and 3
+// to apply one, where it were 9 and 3 and the two of the argument.  Step of 48 slices of n = 3072, padded: 150 -> 141 us.
 constexpr uint32_t kDropPairStep = 0x9E3779B9u;
-__device__ __forceinline__ uint32_t drop_pair_threshold(const Dropout& dr) { return (dr.thr - 1u) * 0x10001u; }
-__device__ __forceinline__ uint32_t drop_keep_pair(uint32_t w, uint32_t threshold) {
-  const s16x2 u = __builtin_bit_cast(s16x2, w & 0x7fff7fffu);
-  return __builtin_bit_cast(uint32_t, (__builtin_bit_cast(s16x2, threshold) - u) >> static_cast<short>(15));
+__device__ __forceinline__ uint32_t drop_first(uint32_t x) { return x ^ (x >> 16); }
+// x = drop_first(row key) ^ drop_first(pair * kDropPairStep): low half even key, upper half odd key
+__device__ __forceinline__ uint32_t drop_doubled(uint32_t x) {
+  x *= 0x7feb352du;
+  x ^= x >> 15;
+  x *= 2u * 0x846ca68bu;
+  // (x ^ x >> 16 in one instruction, whatever is made of the halves)
+  asm("v_xor_b32_sdwa %0, %0, %0 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "+v"(x));
+  return x;
 }
+__device__ __forceinline__ bool drop_keep_low(uint32_t doubled, uint32_t thr) { return static_cast<uint16_t>(doubled) >= static_cast<uint16_t>(2u * thr); }
+__device__ __forceinline__ bool drop_keep_high(uint32_t doubled, uint32_t thr) { return doubled >= thr << 17; }
+// Both keys at once: 1 in each half that is kept, else 0 (a packed subtraction that stops at 0, and a minimum; written
+// out, because the compiler knows them for comparisons and makes six instructions of those).
+__device__ __forceinline__ uint32_t drop_pair_threshold(const Dropout& dr) { return (2u * dr.thr - 1u) * 0x10001u; }
+__device__ __forceinline__ uint32_t drop_keep_pair(uint32_t doubled, uint32_t threshold) {
+  uint32_t keep;
+  asm("v_pk_sub_u16 %0, %1, %2 clamp\n\tv_pk_min_u16 %0, %0, 1 op_sel_hi:[1,0]" : "=v"(keep) : "v"(doubled), "s"(threshold));
+  return keep;
+}
+// Two packed 16-bit values, each of them or 0.
+__device__ __forceinline__ uint32_t drop_apply(uint32_t values, uint32_t keep) {
+  asm("v_pk_mul_lo_u16 %0, %0, %1" : "+v"(values) : "v"(keep));
+  return values;
+}
+
+// Kernels whose lanes own a query: drop_first of the 32 key pairs of a block, left in LDS by the wave that needs them.  A lane of
+// half hf reads those of a unit of 32 keys together: element m belongs to accumulator registers 2 m, 2 m + 1.
+__device__ __forceinline__ void drop_key_words(uint32_t* table, uint32_t kblock, int lane) {
+  const uint32_t i = static_cast<uint32_t>(lane) & 31u;  // (both halves of the wave write the same)
+  table[(i & 17u) | ((i & 2u) << 2) | ((i & 12u) >> 1)] = drop_first((kblock * 32u + i) * kDropPairStep);
+  asm volatile("" ::: "memory");  // read by the same wave: LDS keeps the order, the compiler must too
+}
+__device__ __forceinline__ const uint32_t* drop_unit_words(const uint32_t* table, int t, int hf) { return table + t * 16 + hf * 8; }
 #endif
 
 // Host: rate and seed -> parameters.  False if p is not in [0, 1) or rounds to 1.

@@ -348,25 +348,20 @@ __device__ __forceinline__ float raise_reference(const f32x16& s0, const f32x16&
   return m_use;
 }
 
-// What attention dropout needs of an item: the keys of this lane's two rows of the keep mask.
+// What attention dropout needs of an item: drop_first of the keys of this lane's two rows of the keep mask.
 struct DropRows {
   uint32_t rk[2];
   uint32_t thr;
 };
 
 // Probabilities of one unit against a reference, as two B operands; their sum before rounding goes to l.
-// first_key: number of the unit's first key.
-template <bool kDropout, class Reads>
+// drop_words: the unit's key words (drop_unit_words).
+template <bool kDropout>
 __device__ __forceinline__ void unit_probs_against(const f32x16& s, float c, float m_use, float& l, bf16x8 (&pb)[2],
-                                                   uint32_t drop_rk, uint32_t drop_thr, uint32_t first_key, int hf, Reads reads) {
-  if (!kDropout) reads();
+                                                   uint32_t drop_rk, uint32_t drop_thr, const uint32_t* drop_words) {
   float sum[2] = {0.f, 0.f};
 #pragma unroll
   for (int sgl = 0; sgl < 2; ++sgl) {
-    if (kDropout && sgl) {
-      __builtin_amdgcn_sched_barrier(0);
-      reads();
-    }
 #pragma unroll
     for (int kk = 0; kk < 8; kk += 2) {
       const int r = sgl * 8 + kk;
@@ -375,10 +370,8 @@ __device__ __forceinline__ void unit_probs_against(const f32x16& s, float c, flo
       sum[0] += p0;  // (the row sums are those of the undropped probabilities)
       sum[1] += p1;
       bf16x2 pk = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
-      if constexpr (kDropout) {
-        const uint32_t key = first_key + acc_row(r, hf);
-        pk = __builtin_bit_cast(bf16x2, __builtin_bit_cast(uint32_t, pk) & drop_keep_pair(drop_word(drop_rk, key >> 1), drop_thr));
-      }
+      if constexpr (kDropout)
+        pk = __builtin_bit_cast(bf16x2, drop_apply(__builtin_bit_cast(uint32_t, pk), drop_keep_pair(drop_doubled(drop_rk ^ drop_words[r >> 1]), drop_thr)));
       pb[sgl][kk] = pk[0];
       pb[sgl][kk + 1] = pk[1];
     }
@@ -391,12 +384,12 @@ template <bool kMask, bool kDropout>
 __device__ __forceinline__ void running_pair(const PairCtx& cx, const LeanOffsets& lo,
                                              const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], bf16x8 (&va)[2][2][2],
                                              f32x16& s0, f32x16& s1, bf16x8 (&p3)[2], f32x16 (&o)[2][2], RowState& rs,
-                                             const DropRows& drop, uint32_t kblock, bool cut, const uint32_t* key_bits,
+                                             const DropRows& drop, uint32_t* drop_table, uint32_t kblock, bool cut, const uint32_t* key_bits,
                                              const char* k2, const char* v1) {
   f32x16 sB0, sB1;
   bf16x8 p0[2], p1[2], p2[2];
   uint32_t vb[2] = {~0u, ~0u};
-  const uint32_t key0 = kblock * kBlk;
+  if constexpr (kDropout) drop_key_words(drop_table, kblock, lane_again(lane_id()));
   if (kMask && cut) {
     vb[0] = key_bits[0];
     vb[1] = key_bits[1];
@@ -409,9 +402,8 @@ __device__ __forceinline__ void running_pair(const PairCtx& cx, const LeanOffset
   unit_pv(va[1], p3, o[1]);
   unit_scores(ka[0], qb[1], sB0);
   float mu = raise_reference(s0, s1, cx.c, rs.m[0], rs.l[0], o[0]);
-  if (kDropout) __builtin_amdgcn_sched_barrier(0);
-  unit_probs_against<kDropout>(s0, cx.c, mu, rs.l[0], p0, drop.rk[0], drop.thr, key0, cx.hf,
-                               [&]() { lo.transposed_half(cx.lds_v, 0, va[0]); });
+  lo.transposed_half(cx.lds_v, 0, va[0]);
+  unit_probs_against<kDropout>(s0, cx.c, mu, rs.l[0], p0, drop.rk[0], drop.thr, drop_unit_words(drop_table, 0, cx.hf));
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- slot 1: (1,A).  V.t1 and K(i+1).t0 have landed
@@ -420,10 +412,9 @@ __device__ __forceinline__ void running_pair(const PairCtx& cx, const LeanOffset
   wait_tile_loads<8>();
   unit_scores(ka[1], qb[1], sB1);
   unit_pv(va[0], p0, o[0]);
-  unit_probs_against<kDropout>(s1, cx.c, mu, rs.l[0], p1, drop.rk[0], drop.thr, key0 + 32, cx.hf, [&]() {
-    lo.straight_half(cx.lds_k, 0, ka[0]);
-    lo.transposed_half(cx.lds_v, 1, va[1]);
-  });
+  lo.straight_half(cx.lds_k, 0, ka[0]);
+  lo.transposed_half(cx.lds_v, 1, va[1]);
+  unit_probs_against<kDropout>(s1, cx.c, mu, rs.l[0], p1, drop.rk[0], drop.thr, drop_unit_words(drop_table, 1, cx.hf));
   asm volatile("" : "+v"(p1[0]), "+v"(p1[1]), "+v"(rs.l[0]));  // (made here, not behind the branch)
   __builtin_amdgcn_sched_barrier(0);
 
@@ -439,9 +430,8 @@ __device__ __forceinline__ void running_pair(const PairCtx& cx, const LeanOffset
   unit_pv(va[1], p1, o[0]);
   unit_scores(ka[0], qb[0], s0);
   mu = raise_reference(sB0, sB1, cx.c, rs.m[1], rs.l[1], o[1]);
-  if (kDropout) __builtin_amdgcn_sched_barrier(0);
-  unit_probs_against<kDropout>(sB0, cx.c, mu, rs.l[1], p2, drop.rk[1], drop.thr, key0, cx.hf,
-                               [&]() { lo.straight_half(cx.lds_k, 1, ka[1]); });
+  lo.straight_half(cx.lds_k, 1, ka[1]);
+  unit_probs_against<kDropout>(sB0, cx.c, mu, rs.l[1], p2, drop.rk[1], drop.thr, drop_unit_words(drop_table, 0, cx.hf));
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- slot 3: (1,B)
@@ -449,7 +439,7 @@ __device__ __forceinline__ void running_pair(const PairCtx& cx, const LeanOffset
   half_load_async(k2, cx.lds_k_a, 1, cx.voff);
   unit_scores(ka[1], qb[0], s1);
   unit_pv(va[0], p2, o[1]);
-  unit_probs_against<kDropout>(sB1, cx.c, mu, rs.l[1], p3, drop.rk[1], drop.thr, key0 + 32, cx.hf, []() {});
+  unit_probs_against<kDropout>(sB1, cx.c, mu, rs.l[1], p3, drop.rk[1], drop.thr, drop_unit_words(drop_table, 1, cx.hf));
   asm volatile("" : "+v"(p3[0]), "+v"(p3[1]), "+v"(rs.l[1]));
   __builtin_amdgcn_sched_barrier(0);
 }
@@ -459,6 +449,13 @@ __shared__ __attribute__((aligned(1024))) char lds_all[kFwdWaves][2 * kTile];  /
 __shared__ int klist_all[kFwdWaves][kGlobalWaveLen];
 // validity bits of the keys of listed blocks that have padded keys inside, of the item in work and of the next one
 __shared__ uint32_t key_bits_all[kFwdWaves][2][kGlobalWaveLen][2];
+__shared__ __attribute__((aligned(16))) uint32_t drop_words_all[kFwdWaves][32];  // dropout: key words of the pair in work
+// (referenced by that instance alone, so that the others do not hold the memory)
+template <int kMode>
+__device__ __forceinline__ uint32_t* drop_words_of(int wv) {
+  if constexpr (kMode == kDrop) return drop_words_all[wv];
+  return nullptr;
+}
 __shared__ int row_cut[kFwdWaves];  // rows by a workgroup: does the wave's share hold a cut block?
 __shared__ float mrg_m[kFwdWaves][kBlk], mrg_l[kFwdWaves][kBlk];  // their per-wave exponents and sums
 
@@ -809,7 +806,7 @@ __device__ __forceinline__ DropRows drop_rows(const FwdParams& p, const Item& it
     d.thr = drop_pair_threshold(p.drop);
     const uint32_t row0 = static_cast<uint32_t>(item.bh) * static_cast<uint32_t>(p.n) + static_cast<uint32_t>(item.j * kBlk + (lane & 31));
 #pragma unroll
-    for (int q = 0; q < 2; ++q) d.rk[q] = drop_row_key(p.drop, row0 + q * 32);
+    for (int q = 0; q < 2; ++q) d.rk[q] = drop_first(drop_row_key(p.drop, row0 + q * 32));
   }
   return d;
 }
@@ -839,7 +836,7 @@ __device__ __forceinline__ void running_item(const WaveCtx& w, const bf16x8 (&qb
   unit_scores(ka[0], qb[0], s0);
   unit_scores(ka[1], qb[0], s1);
   for (int i = 0; i < cnt; ++i)
-    running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, s0, s1, p3, o, rs, drop,
+    running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, s0, s1, p3, o, rs, drop, drop_words_of<kMode>(w.wv),
                                                   __builtin_amdgcn_readlane(item.kl, i), (item.partial >> i) & 1,
                                                   key_bits_all[w.wv][item.bits][i], ts.k(i + 2), ts.v(i + 1));
   wait_tile_loads<0>();  // requests past the end of the streams
@@ -1331,7 +1328,7 @@ void fwd_kernel_bf16(FwdParams p) {
         unit_scores(ka[1], qb[0], s1);
         for (int i = 0; i < cnt;) {
           if ((rem_pairs & 3) == 3 || i == 0) set_issue_priority(rem_pairs);
-          running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, sA, s1, p3, o, rs, drop,
+          running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, sA, s1, p3, o, rs, drop, drop_words_of<kMode>(w.wv),
                                                         __builtin_amdgcn_readlane(cur.kl, i), (cur.partial >> i) & 1,
                                                         key_bits_all[w.wv][cur.bits][i], ts.k(i + 2), ts.v(i + 1));
           rem_pairs = __builtin_amdgcn_readfirstlane(rem_pairs - 1);
