@@ -376,10 +376,16 @@ int attn_bwd_impl(const void* Q, const void* K, const void* V, const void* O,
   p.drop = drop;
   p.skip_q = (skip_q && key_padding_mask) ? 1 : 0;
   const int fine = dtype == BB_F32 ? bb::fine_slice_f32(p.BH, p.nb, g, w, r) : 0;
-  p.split = bb::make_row_split(p.BH, p.nb, g, w, r, fine);
-  p.kv = bb::make_key_split(p.nb, g, w, r, fine);
+  if (dtype == BB_F32) {
+    p.split = bb::make_row_split(p.BH, p.nb, g, w, r, fine);
+    p.kv = bb::make_key_split(p.nb, g, w, r, fine);
+  } else {  // (never more slots than the workspace is sized for: slices as long or longer)
+    const bool masked = key_padding_mask != nullptr;
+    p.split = bb::make_row_split(p.BH, p.nb, g, w, r, 0, bb::dq_global_slice(p.BH, p.nb, g, w, r, masked));
+    p.kv = bb::make_key_split(p.nb, g, w, r, 0, bb::dkv_global_slice(p.BH, p.nb, g, w, r, masked));
+  }
   p.by_row = dtype == BB_BF16 && bb::bwd_by_row(p.BH, p.nb, g, w, r);
-  if (p.by_row) {  // (never more slots than the workspace is sized for: longer slices)
+  if (p.by_row) {
     p.split = bb::make_row_split_by_row(p.BH, p.nb, g, w, r);
     p.kv = bb::make_key_split_by_row(p.nb, g);
   }

@@ -19,10 +19,10 @@ struct KeySplit {
 };
 
 // len: list entries per slice of every key block (of an average list where its length is not known);
-// 0: kChunk for a global key block, one slice for the others.
-inline KeySplit make_key_split(int nb, int g, int w, int r, int len = 0) {
+// 0: global_len for a global key block, one slice for the others.
+inline KeySplit make_key_split(int nb, int g, int w, int r, int len = 0, int global_len = kChunk) {
   KeySplit s;
-  s.cg = (nb + (len > 0 ? len : kChunk) - 1) / (len > 0 ? len : kChunk);
+  s.cg = (nb + (len > 0 ? len : global_len) - 1) / (len > 0 ? len : global_len);
   s.cs = len > 0 ? (longest_sparse_list(nb, g, w, r) + len - 1) / len : 1;
   if (s.cs < 1) s.cs = 1;
   s.items_per_bh = g * s.cg + (nb - g) * s.cs;
@@ -78,6 +78,29 @@ inline bool bwd_by_row(int BH, int nb, int g, int w, int r) {
 inline bool dq_two_waves(int BH, const RowSplit& s) {
   const long long items = static_cast<long long>(BH) * s.items_per_bh;
   return items >= 384 && items <= 1024;
+}
+
+// Large bf16 launches: slices of global blocks longer than the standard 8, where the launch is long enough that
+// they still end with the others (the longest items start first).  Every slice costs 16 KB (dQ) or 32 KB (dK/dV) written
+// and read again by the reduction.  The lines lie by the pairs each resident workgroup gets on average: 1024 of the dK/dV
+// kernel, 2048 of the dQ kernel.  Forward and backward in us, dK/dV slices of 8 / 16 / 24 / 32:
+//   40 pairs: 16 slices of n = 16384   263 / 260 / 257 / 255; 32 of n = 8192  257 / 255 / 251 / 247
+//   29: 48 of n = 4096  191 / 187 / 184 / 187; 96 of n = 2048  191 / 186 / 184 / 187; 64 of n = 3072  193 / 188 / 187 / 187
+//   14..20: 16 of n = 8192  134 / 133 / 130 / 132; 24 of n = 4096  100.5 / 99.8 / 99.4 / 101.7; 64 of n = 1536  98.5 / 98.6 / 95.5 / 95.4
+//   9..10: 8 of n = 8192  79 / 80 / 80 / 87; 20 of n = 3072  82 / 81 / 89 / 90
+// Where slices of a launch are left over and cut into runs (DieItems), longer items make the runs uneven: 12 of n = 12288
+// (22 pairs, slices of 8 / 12 / 16 / 24) 160 / 159 / 158 / 164, 36 of n = 2560 (14) 99.5 / 99.6 / 100.5 / 103.3.  Under a mask
+// lists are shorter than counted: 48 padded ones of n = 3072, dropout (8 / 16 / 24) 139.9 / 138.8 / 144.5.
+inline int dkv_global_slice(int BH, int nb, int g, int w, int r, bool masked) {
+  const long long each = most_pairs(BH, nb, g, w, r) / 1024;
+  if (each < 14) return kChunk;
+  if (BH % kXcd != 0) return 12;
+  return masked ? 16 : each < 32 ? 24 : 32;
+}
+// dQ slices of 8 / 16 (the most a wave lists): 20 pairs: 16 slices of n = 16384  255 / 248, 32 of n = 8192  247 / 246; 15: 48 of
+// n = 4096  187 / 188, 64 of n = 3072  187 / 189; 7: 24 of n = 4096  102 / 106.
+inline int dq_global_slice(int BH, int nb, int g, int w, int r, bool masked) {
+  return !masked && most_pairs(BH, nb, g, w, r) / 2048 >= 18 ? 2 * kChunkGlobal : kChunkGlobal;
 }
 
 constexpr int kSetWords = kMaxBwdBlocks / 32;

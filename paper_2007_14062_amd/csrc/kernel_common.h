@@ -107,6 +107,11 @@ inline int longest_sparse_list(int nb, int g, int w, int r) {
   return ub < nb ? static_cast<int>(ub) : nb;
 }
 
+// Block pairs of a launch, at most.
+inline long long most_pairs(int BH, int nb, int g, int w, int r) {
+  return BH * (static_cast<long long>(g) * nb + static_cast<long long>(nb - g) * longest_sparse_list(nb, g, w, r));
+}
+
 // Key blocks per slice of the fp32 kernels.  A block pair keeps a workgroup's matrix pipes busy for
 // 2 .. 4 us there, so a launch that would have fewer than two 8-block slices per compute unit is cut finer,
 // down to one pair per workgroup (n = 1024, 2 heads: forward 42 us with slices of 8, backward kernels
@@ -117,19 +122,18 @@ inline int longest_sparse_list(int nb, int g, int w, int r) {
 // from 6 on the standard ones (24 of n = 1024: 81 and 215 us with 7, 55 and 175 with 4, 47 and 162 with these).
 inline int fine_slice_f32(int BH, int nb, int g, int w, int r) {
   const int sparse = longest_sparse_list(nb, g, w, r);
-  const long long pairs = static_cast<long long>(BH) * (static_cast<long long>(g) * nb + static_cast<long long>(nb - g) * sparse);
-  const long long len = (pairs + 511) / 512;
+  const long long len = (most_pairs(BH, nb, g, w, r) + 511) / 512;
   if (len > 5) return 0;
   if (len == 5)
     return static_cast<long long>(BH) * (static_cast<long long>(g) * ((nb + 4) / 5) + static_cast<long long>(nb - g) * ((sparse + 4) / 5)) <= 512 ? 5 : 4;
   return static_cast<int>(len < 1 ? 1 : len);
 }
 
-// len: key blocks per slice of every row; 0: kChunkGlobal / kSparseChunk.
-inline RowSplit make_row_split(int BH, int nb, int g, int w, int r, int len = 0) {
+// len: key blocks per slice of every row; 0: global_len / kSparseChunk.
+inline RowSplit make_row_split(int BH, int nb, int g, int w, int r, int len = 0, int global_len = kChunkGlobal) {
   RowSplit s;
   const int sparse_ub = longest_sparse_list(nb, g, w, r);
-  s.lg = len > 0 ? len : kChunkGlobal;
+  s.lg = len > 0 ? len : global_len;
   s.ls = len > 0 ? len : kSparseChunk;
   s.cg = (nb + s.lg - 1) / s.lg;
   s.cs = (sparse_ub + s.ls - 1) / s.ls;

@@ -188,6 +188,35 @@ def test_cfg4_sampled_heads():
     assert np.abs(qdq - kdk).max() <= 1e-3 * max(1.0, np.abs(qdq).max()) + 0.5
 
 
+@pytest.mark.parametrize("B,H,nb,masked", [
+    (8, 8, 24, False),    # slices of 24: a global key block whole, no partial sums of dK and dV
+    (8, 8, 25, True),     # of 16 under a mask
+    (7, 12, 33, False),   # of 12 where slices of the launch are left over
+    (16, 12, 27, False),  # of 32 (one) for dK/dV, dQ rows of 27 in slices of 16
+    (16, 10, 35, False),  # of 32 and a rest of 3 (dealt out: 18 and 17)
+])
+def test_long_slices_of_global_blocks(B, H, nb, masked):
+    """Large launches take longer slices of global rows and columns: sampled (batch, head) slices against the oracle."""
+    n, g, w, r = nb * 64, 2, 3, 3
+    rng = np.random.default_rng(nb)
+    t = inp.make_tensors(B, H, n, 64, 500 + nb, "bf16", with_dO=True)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 4)
+    km = None
+    if masked:
+        km = np.ones((B, n), dtype=np.uint8)
+        for bi in range(B):
+            km[bi, int(rng.integers(n // 2, n + 1)):] = 0
+    grads = [to_host(x) for x in run_fwd_bwd(t, ridx, g, w, 0.125, km)]
+    assert all(np.isfinite(x).all() for x in grads)
+    for (bi, h) in [(0, 0), (B - 1, H - 1), (B // 2, 3)]:
+        sl = (slice(bi, bi + 1), slice(h, h + 1))
+        ref = oracle.attn_bwd(t["Q"][sl], t["K"][sl], t["V"][sl], t["dO"][sl], ridx[h:h + 1], 64, g, w, 0.125,
+                              key_mask=None if km is None else km[bi:bi + 1])
+        errs = [float(np.abs(x[sl] - y).max()) for x, y in zip(grads, ref)]
+        print(f"B{B} H{H} nb{nb} (b={bi}, h={h}): {errs}")
+        assert max(errs) <= TOL
+
+
 def test_cfg3_shape_backward_with_padding_sampled_heads():
     """The key-padding workload (B = 8, lengths 1024..4096) through forward + backward; the
     oracle is run on three (batch, head) slices, among them the shortest and the longest row."""
