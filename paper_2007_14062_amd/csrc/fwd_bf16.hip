@@ -79,9 +79,6 @@ namespace bb {
 
 namespace {
 
-constexpr int kFwdWaves = 4;
-constexpr int kFwdThreads = 64 * kFwdWaves;  // four independent wavefronts, one work item each
-
 // Instances of the kernel: no padding mask; a padding mask; a padding mask and skipped query blocks;
 // attention dropout with any of these.
 enum { kPlain = 0, kMasked = 1, kOptions = 2, kDrop = 3 };
@@ -444,22 +441,52 @@ __device__ __forceinline__ void running_pair(const PairCtx& cx, const LeanOffset
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// LDS of a workgroup (at namespace scope: the cold paths below are separate functions).
-__shared__ __attribute__((aligned(1024))) char lds_all[kFwdWaves][2 * kTile];  // per wave: K tile, V tile
-__shared__ int klist_all[kFwdWaves][kGlobalWaveLen];
+// LDS of a workgroup of W waves (the cold paths below are separate functions; an instance holds the arrays it names).
+template <int W>
+__device__ __forceinline__ auto tiles_of(int wv) -> char (&)[2 * kTile] {  // per wave: K tile, V tile
+  __shared__ __attribute__((aligned(1024))) char tiles[W][2 * kTile];
+  return tiles[wv];
+}
+template <int W>
+__device__ __forceinline__ int* klist_of(int wv) {
+  __shared__ int klist[W][kGlobalWaveLen];
+  return klist[wv];
+}
 // validity bits of the keys of listed blocks that have padded keys inside, of the item in work and of the next one
-__shared__ uint32_t key_bits_all[kFwdWaves][2][kGlobalWaveLen][2];
-__shared__ __attribute__((aligned(16))) uint32_t drop_words_all[kFwdWaves][32];  // dropout: key words of the pair in work
-// (referenced by that instance alone, so that the others do not hold the memory)
-template <int kMode>
+template <int W>
+__device__ __forceinline__ auto key_bits_of(int wv, int set) -> uint32_t (&)[kGlobalWaveLen][2] {
+  __shared__ uint32_t key_bits[W][2][kGlobalWaveLen][2];
+  return key_bits[wv][set];
+}
+// dropout: key words of the pair in work
+template <int kMode, int W>
 __device__ __forceinline__ uint32_t* drop_words_of(int wv) {
-  if constexpr (kMode == kDrop) return drop_words_all[wv];
+  if constexpr (kMode == kDrop) {
+    __shared__ __attribute__((aligned(16))) uint32_t words[W][32];
+    return words[wv];
+  }
   return nullptr;
 }
-__shared__ int row_cut[kFwdWaves];  // rows by a workgroup: does the wave's share hold a cut block?
-__shared__ float mrg_m[kFwdWaves][kBlk], mrg_l[kFwdWaves][kBlk];  // their per-wave exponents and sums
+// rows by a workgroup: does a wave's share hold a cut block?
+template <int W>
+__device__ __forceinline__ int* row_cut() {
+  __shared__ int cut[W];
+  return cut;
+}
+// their per-wave exponents and sums
+template <int W>
+__device__ __forceinline__ float* merge_m(int wv) {
+  __shared__ float m[W][kBlk];
+  return m[wv];
+}
+template <int W>
+__device__ __forceinline__ float* merge_l(int wv) {
+  __shared__ float l[W][kBlk];
+  return l[wv];
+}
 
 // What a wave knows about itself and its LDS.
+template <int W>
 struct WaveCtx {
   int lane, wv, hf, col;
   char* lds_kv;  // this wave's 16 KB: K buffer, then V buffer
@@ -472,10 +499,10 @@ struct WaveCtx {
     wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform, and the compiler should know
     hf = lane >> 5;
     col = lane & 31;
-    lds_kv = lds_all[wv];
+    lds_kv = tiles_of<W>(wv);
     lds_k = lds_kv;
     lds_v = lds_kv + kTile;
-    klist = klist_all[wv];
+    klist = klist_of<W>(wv);
     cx.lds_k = lds_k;
     cx.lds_v = lds_v;
     cx.hf = hf;
@@ -492,6 +519,7 @@ struct WaveCtx {
 // The others stay for the whole launch: wave w of the die's persistent waves takes the
 // non-global items w, w + wave_stride, ... of the die, in (slice, query block) order, so that
 // all waves start at once and nearly all end together.
+template <int W>
 struct Sched {
   int xcd;
   unsigned wg;        // workgroup number inside the die
@@ -520,7 +548,7 @@ struct Sched {
     }
     const int n_bh_die = xcd < p.BH ? (p.BH - xcd + kXcd - 1) / kXcd : 0;
     n_items_die = n_bh_die * p.geo.n_sitems;
-    wave_stride = p.geo.p_wgs * kFwdWaves;
+    wave_stride = p.geo.p_wgs * W;
   }
 };
 
@@ -562,7 +590,8 @@ struct ItemTiles {
 // the row).  All loads here are waited for before the function returns (scalar loads inside
 // their asm statement, the others by the compiler), so tile loads in flight are at most delayed.
 // Its first part: which row, which slice of the row's list (arithmetic only, no memory access).
-__device__ __forceinline__ void item_coords(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
+template <int W>
+__device__ __forceinline__ void item_coords(const FwdParams& p, const WaveCtx<W>& w, const Sched<W>& sc, int t, Item& it,
                                             int& list_lo, int& list_len, bool& row_global) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   const Bf16Geom& geo = p.geo;
@@ -585,7 +614,7 @@ __device__ __forceinline__ void item_coords(const FwdParams& p, const WaveCtx& w
     it.chunk = u;
     it.nchunks = geo.ng;
     it.slot = it.bh * p.slots_per_bh + row * geo.ng + u;
-    list_lo = (u * kFwdWaves + w.wv) * geo.gw_len;
+    list_lo = (u * W + w.wv) * geo.gw_len;
     list_len = geo.gw_len;
   } else {
     // (item order inside a die: slice by slice, so that a slice's K and V stay in the L2 while its
@@ -610,8 +639,8 @@ __device__ __forceinline__ const char* query_tile(const FwdParams& p, int bh, in
 // kMode (here and below): the instance of the kernel.  kPlain knows no padding mask, kMasked does,
 // kOptions also skipped query blocks, kDrop attention dropout with or without these.  An instance holds no code of the
 // others, so its registers and schedule are its own.
-template <int kMode>
-__device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, const Sched& sc, int t, Item& it,
+template <int kMode, int W>
+__device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx<W>& w, const Sched<W>& sc, int t, Item& it,
                                           int bits = 0) {
   const Pattern pat{p.nb, p.g, p.w, p.global_mode};
   const int lane = lane_again(w.lane);
@@ -637,7 +666,7 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
     return;
   }
   const KeyList kl = item_key_list<kMode != kPlain>(pat, p.rand_idx, p.r, p.kmask, p.n, bi, h, it.j, row_global, list_lo,
-                                                    list_len, lane, w.klist, key_bits_all[w.wv][bits]);
+                                                    list_len, lane, w.klist, key_bits_of<W>(w.wv, bits));
   it.cnt = kl.cnt;
   it.kl = kl.entry;
   it.partial = kl.partial;
@@ -659,7 +688,8 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx& w, 
 // arrives), then operand reads.  Register loads of the operand layout would touch every row of
 // the tile in each instruction and cost the address unit four times as many cache-line requests.
 // Leaves: K(0) in the K buffer, the scaled Q fragments in qb, V(0).t0 as the only load in flight.
-__device__ __forceinline__ void fresh_start(const FwdParams& p, const WaveCtx& w, const StraightOffsets& so,
+template <int W>
+__device__ __forceinline__ void fresh_start(const FwdParams& p, const WaveCtx<W>& w, const StraightOffsets& so,
                                             const Item& item, bf16x8 (&qb)[2][4]) {
   const ItemTiles ct(p, item);
   tile_load_async_wave(ct.ktile(0), w.cx.lds_k_a, w.cx.voff);
@@ -812,8 +842,8 @@ __device__ __forceinline__ DropRows drop_rows(const FwdParams& p, const Item& it
 }
 
 // The same with the running maximum, on the same entry.  Leaves the reference exponents (base 2) in m_ref.
-template <int kMode>
-__device__ __forceinline__ void running_item(const WaveCtx& w, const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], const FwdParams& p,
+template <int kMode, int W>
+__device__ __forceinline__ void running_item(const WaveCtx<W>& w, const bf16x8 (&qb)[2][4], bf16x8 (&ka)[2][4], const FwdParams& p,
                                              const Item& item, f32x16 (&o)[2][2], float (&m_ref)[2], float (&l_tot)[2]) {
   const PairCtx& cx = w.cx;
   const LeanOffsets lo(lane_again(w.lane));
@@ -836,9 +866,9 @@ __device__ __forceinline__ void running_item(const WaveCtx& w, const bf16x8 (&qb
   unit_scores(ka[0], qb[0], s0);
   unit_scores(ka[1], qb[0], s1);
   for (int i = 0; i < cnt; ++i)
-    running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, s0, s1, p3, o, rs, drop, drop_words_of<kMode>(w.wv),
+    running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, s0, s1, p3, o, rs, drop, drop_words_of<kMode, W>(w.wv),
                                                   __builtin_amdgcn_readlane(item.kl, i), (item.partial >> i) & 1,
-                                                  key_bits_all[w.wv][item.bits][i], ts.k(i + 2), ts.v(i + 1));
+                                                  key_bits_of<W>(w.wv, item.bits)[i], ts.k(i + 2), ts.v(i + 1));
   wait_tile_loads<0>();  // requests past the end of the streams
   unit_pv(va[1], p3, o[1]);
 #pragma unroll
@@ -851,7 +881,8 @@ __device__ __forceinline__ void running_item(const WaveCtx& w, const bf16x8 (&qb
 // Normalised bf16 output and LSE of a non-global item.  The accumulators hold O^T (a lane owns one
 // query and scattered groups of four d); they are turned through LDS (the K buffer) so that global
 // memory sees whole rows: 16 bytes per lane, consecutive lanes on consecutive addresses.
-__device__ __forceinline__ void store_rows_bf16(const FwdParams& p, const WaveCtx& w, const Item& it,
+template <int W>
+__device__ __forceinline__ void store_rows_bf16(const FwdParams& p, const WaveCtx<W>& w, const Item& it,
                                                 const f32x16 (&o)[2][2], const float (&inv)[2],
                                                 const float (&lse)[2]) {
   const size_t row_blk = static_cast<size_t>(it.bh) * p.n + it.j * kBlk;  // first row of the query block
@@ -889,7 +920,8 @@ __device__ __forceinline__ void store_rows_bf16(const FwdParams& p, const WaveCt
 
 // Partial triple (reference exponent, row sums, un-normalised O in fp32) of one slice of a row
 // that has several, for the merge kernel; O goes through the K buffer in two passes of 32 d.
-__device__ __forceinline__ void store_partial(const FwdParams& p, const WaveCtx& w, const Item& it,
+template <int W>
+__device__ __forceinline__ void store_partial(const FwdParams& p, const WaveCtx<W>& w, const Item& it,
                                               const f32x16 (&o)[2][2], const float (&m_ref)[2],
                                               const float (&l_tot)[2]) {
   const int lane = lane_again(w.lane), hf = lane >> 5, col = lane & 31;
@@ -962,15 +994,15 @@ __device__ __forceinline__ const void* kernel_kernargs() {
 // One non-global item by the classical recurrence, from its first load to its last store: the path
 // of items without any key block or with padded keys inside a block, of items whose row sums
 // left the safe range of the pipelined path, and of every item under attention dropout.
-template <int kMode>
+template <int kMode, int W>
 __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
-  const WaveCtx w(p.c);
-  Sched sc(p, false);
+  const WaveCtx<W> w(p.c);
+  Sched<W> sc(p, false);
   sc.global_wg = false;  // (a wave of a global-row workgroup that went on to claim other items)
   const StraightOffsets so(w.lane);
   const TransposedOffsets to(w.lane);
   Item it;
-  make_item<kMode>(p, w, sc, t, it);
+  make_item<kMode, W>(p, w, sc, t, it);
   wait_tile_loads<0>();
   bf16x8 qb[2][4], ka[2][4];
   f32x16 o[2][2];
@@ -979,7 +1011,7 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
   zero_acc(o[1]);
   if (it.cnt > 0) {
     fresh_start(p, w, so, it, qb);
-    running_item<kMode>(w, qb, ka, p, it, o, m_ref, l_tot);
+    running_item<kMode, W>(w, qb, ka, p, it, o, m_ref, l_tot);
   }
   if (it.nchunks == 1) {
     float inv[2], lse[2];
@@ -998,10 +1030,10 @@ __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
 // function: its registers are not that loop's problem.  One call for the whole list: a call saves
 // and restores the callee-saved registers in scratch memory, about 50 KB per wave, which per item
 // was most of the time of launches in which many items come here.
-template <int kMode>
+template <int kMode, int W>
 __device__ __attribute__((noinline)) void redo_items(const void* kernargs, int redo, int n_redo) {
   const FwdParams p = params_from(kernargs);
-  for (int u = 0; u < n_redo; ++u) item_by_recurrence<kMode>(p, __builtin_amdgcn_readlane(redo, u));
+  for (int u = 0; u < n_redo; ++u) item_by_recurrence<kMode, W>(p, __builtin_amdgcn_readlane(redo, u));
 }
 
 // One query block by a whole workgroup: its key list dealt out to the four waves (up to 16 key blocks
@@ -1009,9 +1041,9 @@ __device__ __attribute__((noinline)) void redo_items(const void* kernargs, int r
 // real call would start by saving a hundred callee-saved vector registers to scratch memory
 // (11 MB of HBM writes per launch at the BERT-base size, measured) for a caller that has nothing
 // in them.
-template <int kMode>
-__device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const Sched& sc) {
-  const WaveCtx w(p.c);
+template <int kMode, int W>
+__device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const Sched<W>& sc) {
+  const WaveCtx<W> w(p.c);
   const StraightOffsets so(w.lane);
   const TransposedOffsets to(w.lane);
   const int lane = w.lane, wv = w.wv, hf = w.hf, col = w.col;
@@ -1019,15 +1051,18 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   const long long rt0 = __builtin_amdgcn_s_memrealtime();
 #endif
   Item cur;
-  make_item<kMode>(p, w, sc, 0, cur);
+  make_item<kMode, W>(p, w, sc, 0, cur);
   bool by_recurrence = cur.running;
   const bool dealt_out = (p.geo.ng == 1 && p.geo.gw_len < kGlobalWaveLen) || sc.row_idx >= p.g * p.geo.ng;
   if ((kMode == kMasked || kMode == kOptions) && dealt_out) {
     // A row with a cut block takes the recurrence in all four waves, as the same blocks do in one wave's
     // item.  (Shares of 16 blocks, and of rows of several workgroups: each by itself.)
-    if (lane == 0) row_cut[wv] = by_recurrence;
+    if (lane == 0) row_cut<W>()[wv] = by_recurrence;
     __syncthreads();
-    by_recurrence = (row_cut[0] | row_cut[1] | row_cut[2] | row_cut[3]) != 0;
+    int any_cut = 0;
+#pragma unroll
+    for (int v = 0; v < W; ++v) any_cut |= row_cut<W>()[v];
+    by_recurrence = any_cut != 0;
   }
   bf16x8 qb[2][4], ka[2][4];
   f32x16 o[2][2];
@@ -1049,7 +1084,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
         half_load_async(ct.vtile(0), w.cx.lds_v_a, 0, w.cx.voff);
       }
     }
-    if (__any(bad)) running_item<kMode>(w, qb, ka, p, cur, o, m_ref, l_tot);
+    if (__any(bad)) running_item<kMode, W>(w, qb, ka, p, cur, o, m_ref, l_tot);
   } else {
     m_ref[0] = m_ref[1] = neg_inf();
   }
@@ -1069,39 +1104,40 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
 #pragma unroll
   for (int q = 0; q < 2; ++q)
     if (hf == 0) {
-      mrg_m[wv][q * 32 + col] = !(l_tot[q] > 0.f) ? neg_inf() : m_ref[q];
-      mrg_l[wv][q * 32 + col] = l_tot[q];
+      merge_m<W>(wv)[q * 32 + col] = !(l_tot[q] > 0.f) ? neg_inf() : m_ref[q];
+      merge_l<W>(wv)[q * 32 + col] = l_tot[q];
     }
 #ifdef BB_STAMPS
   if (lane == 0) {  // (nchunks == 1 only: the partial-result area is otherwise in use)
-    long long* dst = reinterpret_cast<long long*>(p.part_o) + (static_cast<size_t>(blockIdx.x) * kFwdWaves + wv) * 16;
+    long long* dst = reinterpret_cast<long long*>(p.part_o) + (static_cast<size_t>(blockIdx.x) * W + wv) * 16;
     dst[0] = rt0;
     dst[1] = __builtin_amdgcn_s_memrealtime();
     dst[2] = -1;
     dst[15] = __builtin_amdgcn_s_getreg((4) | (0 << 6) | (31 << 11));  // HW_ID: where the wave ran
   }
 #endif
-  __syncthreads();  // all four waves of a global workgroup arrive here
-  // wave w now owns query rows 16w .. 16w+15; a lane owns 16 d columns of one row
+  __syncthreads();  // all waves of a global workgroup arrive here
+  // a wave now owns 64 / W query rows, a lane 64 / W columns of one of them
+  constexpr int kCols = kDim / W;
   const size_t row_blk = static_cast<size_t>(cur.bh) * p.n + cur.j * kBlk;
-  const int q = wv * 16 + (lane >> 2), part = lane & 3;
+  const int q = wv * kCols + lane / W, part = lane % W;
   float M = neg_inf();
 #pragma unroll
-  for (int v = 0; v < kFwdWaves; ++v) M = fmaxf(M, mrg_m[v][q]);
-  f32x4 acc[4];
+  for (int v = 0; v < W; ++v) M = fmaxf(M, merge_m<W>(v)[q]);
+  f32x4 acc[kCols / 4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < kCols / 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
   float L = 0.f;
   if (M != neg_inf()) {
 #pragma unroll
-    for (int v = 0; v < kFwdWaves; ++v) {
-      const float mv = mrg_m[v][q];
+    for (int v = 0; v < W; ++v) {
+      const float mv = merge_m<W>(v)[q];
       const float wgt = (mv == neg_inf()) ? 0.f : fast_exp2(mv - M);
-      L += mrg_l[v][q] * wgt;
+      L += merge_l<W>(v)[q] * wgt;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int cc = part * 4 + e;
-        const f32x4 x = *reinterpret_cast<const f32x4*>(lds_all[v] + (cc >> 3) * kTile + tile_off_bf16(q, cc & 7));
+      for (int e = 0; e < kCols / 4; ++e) {
+        const int cc = part * (kCols / 4) + e;
+        const f32x4 x = *reinterpret_cast<const f32x4*>(tiles_of<W>(v) + (cc >> 3) * kTile + tile_off_bf16(q, cc & 7));
 #pragma unroll
         for (int z = 0; z < 4; ++z) acc[e][z] += x[z] * wgt;
       }
@@ -1111,17 +1147,17 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   if (cur.nchunks == 1) {
     const float inv = L > 0.f ? (kMode == kDrop ? p.drop.rs : 1.f) / L : 0.f;  // (rs: 1, or the dropout scale)
     if (part == 0) p.LSE[row] = L > 0.f ? (M + fast_log2(L)) * kLn2 : neg_inf();
-    bf16x8 v0, v1;
+    bf16x8* dst = reinterpret_cast<bf16x8*>(static_cast<__bf16*>(p.O) + row * kDim + part * kCols);
 #pragma unroll
-    for (int z = 0; z < 4; ++z) {
-      v0[z] = static_cast<__bf16>(acc[0][z] * inv);
-      v0[4 + z] = static_cast<__bf16>(acc[1][z] * inv);
-      v1[z] = static_cast<__bf16>(acc[2][z] * inv);
-      v1[4 + z] = static_cast<__bf16>(acc[3][z] * inv);
+    for (int e = 0; e < kCols / 8; ++e) {
+      bf16x8 v;
+#pragma unroll
+      for (int z = 0; z < 4; ++z) {
+        v[z] = static_cast<__bf16>(acc[2 * e][z] * inv);
+        v[4 + z] = static_cast<__bf16>(acc[2 * e + 1][z] * inv);
+      }
+      dst[e] = v;
     }
-    bf16x8* dst = reinterpret_cast<bf16x8*>(static_cast<__bf16*>(p.O) + row * kDim + part * 16);
-    dst[0] = v0;
-    dst[1] = v1;
   } else {
     // one of several workgroups of a long global row: merged partial triple for the merge kernel
     float* pml = p.part_ml + static_cast<size_t>(cur.slot) * (2 * kBlk);
@@ -1130,9 +1166,9 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
       pml[kBlk + q] = L;
     }
     f32x4* dst =
-        reinterpret_cast<f32x4*>(p.part_o + static_cast<size_t>(cur.slot) * (kBlk * kDim) + q * kDim + part * 16);
+        reinterpret_cast<f32x4*>(p.part_o + static_cast<size_t>(cur.slot) * (kBlk * kDim) + q * kDim + part * kCols);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) dst[e] = acc[e];
+    for (int e = 0; e < kCols / 4; ++e) dst[e] = acc[e];
   }
 }
 
@@ -1144,19 +1180,21 @@ __global__ void zero_counters_kernel(int* counters) {
   if (threadIdx.x < kXcd) counters[threadIdx.x * kCounterStride] = 0;
 }
 
+// (Eight waves to a row: 12 heads, n = 1024 7.7 -> 8.8 us.)
+constexpr int kRowWaves = 4;
 // Small launches: a workgroup per row (a kernel of its own, so that the other one keeps its registers
 // and schedule).
 template <int kMode>
-__global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(64 * kRowWaves) __attribute__((amdgpu_waves_per_eu(2)))
 void fwd_rows_bf16(FwdParams p) {
-  const Sched sc(p, true);
-  if (sc.row_ok) global_row_workgroup<kMode>(p, sc);
+  const Sched<kRowWaves> sc(p, true);
+  if (sc.row_ok) global_row_workgroup<kMode, kRowWaves>(p, sc);
 }
 
-template <int kMode>
-__global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2)))
+template <int kMode, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2)))
 void fwd_kernel_bf16(FwdParams p) {
-  Sched sc(p, false);
+  Sched<W> sc(p, false);
   // dyn: after its first piece of work a wave claims items from its die's counter (zeroed before
   // the launch) instead of taking every wave_stride-th one: with a padding mask items differ in
   // length and some are not computed at all.  The waves of a global-row workgroup then join in
@@ -1164,12 +1202,12 @@ void fwd_kernel_bf16(FwdParams p) {
   const bool dyn = kMode == kOptions && p.dyn != 0;
   const bool was_global = sc.global_wg;
   if (sc.global_wg) {
-    if (sc.row_ok) global_row_workgroup<kMode>(p, sc);
+    if (sc.row_ok) global_row_workgroup<kMode, W>(p, sc);
     if (!dyn) return;
     __syncthreads();  // the merge has read the other waves' LDS regions; from here on each wave's is its own
     sc.global_wg = false;
   }
-  const WaveCtx w(p.c);
+  const WaveCtx<W> w(p.c);
   const PairCtx& cx = w.cx;
   const int lane = w.lane;
   char* const lds_k = w.lds_k;
@@ -1192,7 +1230,7 @@ void fwd_kernel_bf16(FwdParams p) {
     // (a counter that has run far past the end must not wrap the sum)
     return c < n_items_die ? wave_stride + c : n_items_die;
   };
-  int t_first = static_cast<int>(sc.wg - sc.n_gpart) * kFwdWaves + w.wv;  // first item of this wave
+  int t_first = static_cast<int>(sc.wg - sc.n_gpart) * W + w.wv;  // first item of this wave
   if (dyn && was_global) t_first = claim();
   const int t_item = __builtin_amdgcn_readfirstlane(t_first);
   if (t_item >= n_items_die) return;
@@ -1231,7 +1269,7 @@ void fwd_kernel_bf16(FwdParams p) {
   auto next_item = [&](int t, Item& it, int bits) {
     int found = -1;
     while (t < n_items_die) {
-      make_item<kMode>(p, w, sc, t, it, bits);
+      make_item<kMode, W>(p, w, sc, t, it, bits);
       if (it.cnt > 0) {
         found = t;
         break;
@@ -1328,9 +1366,9 @@ void fwd_kernel_bf16(FwdParams p) {
         unit_scores(ka[1], qb[0], s1);
         for (int i = 0; i < cnt;) {
           if ((rem_pairs & 3) == 3 || i == 0) set_issue_priority(rem_pairs);
-          running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, sA, s1, p3, o, rs, drop, drop_words_of<kMode>(w.wv),
+          running_pair<kMode != kPlain, kMode == kDrop>(cx, lo, qb, ka, va, sA, s1, p3, o, rs, drop, drop_words_of<kMode, W>(w.wv),
                                                         __builtin_amdgcn_readlane(cur.kl, i), (cur.partial >> i) & 1,
-                                                        key_bits_all[w.wv][cur.bits][i], ts.k(i + 2), ts.v(i + 1));
+                                                        key_bits_of<W>(w.wv, cur.bits)[i], ts.k(i + 2), ts.v(i + 1));
           rem_pairs = __builtin_amdgcn_readfirstlane(rem_pairs - 1);
           i = __builtin_amdgcn_readfirstlane(i + 1);
         }
@@ -1435,7 +1473,7 @@ void fwd_kernel_bf16(FwdParams p) {
   }
 #ifdef BB_STAMPS
   if (lane == 0) {
-    long long* dst = reinterpret_cast<long long*>(p.part_o) + (static_cast<size_t>(blockIdx.x) * kFwdWaves + w.wv) * 16;
+    long long* dst = reinterpret_cast<long long*>(p.part_o) + (static_cast<size_t>(blockIdx.x) * W + w.wv) * 16;
     dst[0] = rt0;
     dst[1] = __builtin_amdgcn_s_memrealtime();
     dst[2] = n_done;
@@ -1448,7 +1486,7 @@ void fwd_kernel_bf16(FwdParams p) {
 #endif
 
   // ---- the listed items, by the classical recurrence
-  if (n_redo > 0) redo_items<kMode>(kernel_kernargs(), redo, n_redo);
+  if (n_redo > 0) redo_items<kMode, W>(kernel_kernargs(), redo, n_redo);
 }
 
 int launch_fwd_bf16_main(const FwdParams& p, hipStream_t stream) {
@@ -1460,10 +1498,12 @@ int launch_fwd_bf16_main(const FwdParams& p, hipStream_t stream) {
     if (hipGetLastError() != hipSuccess) return BB_ERR_LAUNCH;
   }
   const int mode = p.drop.thr != 0 ? kDrop : p.skip_q ? kOptions : p.kmask ? kMasked : kPlain;
-  static constexpr void (*kRows[])(FwdParams) = {fwd_rows_bf16<kPlain>, fwd_rows_bf16<kMasked>, fwd_rows_bf16<kOptions>, fwd_rows_bf16<kDrop>};
-  static constexpr void (*kItems[])(FwdParams) = {fwd_kernel_bf16<kPlain>, fwd_kernel_bf16<kMasked>, fwd_kernel_bf16<kOptions>, fwd_kernel_bf16<kDrop>};
-  const auto kernel = (p.geo.by_row ? kRows : kItems)[mode];
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kFwdThreads), 0, stream, p);
+  static constexpr void (*kRows[4])(FwdParams) = {fwd_rows_bf16<kPlain>, fwd_rows_bf16<kMasked>, fwd_rows_bf16<kOptions>, fwd_rows_bf16<kDrop>};
+  static constexpr void (*kItems[2][4])(FwdParams) = {
+      {fwd_kernel_bf16<kPlain, 4>, fwd_kernel_bf16<kMasked, 4>, fwd_kernel_bf16<kOptions, 4>, fwd_kernel_bf16<kDrop, 4>},
+      {fwd_kernel_bf16<kPlain, 8>, fwd_kernel_bf16<kMasked, 8>, fwd_kernel_bf16<kOptions, 8>, fwd_kernel_bf16<kDrop, 8>}};
+  const auto kernel = p.geo.by_row ? kRows[mode] : kItems[p.geo.waves == 8][mode];
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * p.geo.waves), 0, stream, p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     fprintf(stderr, "bigbird: launch of fwd_kernel_bf16 failed: %s\n", hipGetErrorString(e));

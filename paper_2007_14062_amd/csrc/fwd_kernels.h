@@ -7,8 +7,8 @@
 
 namespace bb {
 
-// Work decomposition of the bf16 forward.  Workgroups have four independent waves.
-//   global workgroup: one global query block x up to 64 key blocks, 16 per wave, merged in LDS;
+// Work decomposition of the bf16 forward.  Workgroups have four independent waves (eight in launches of medium size).
+//   global workgroup: one global query block x up to 64 key blocks, 16 (8) per wave, merged in LDS;
 //   persistent workgroup: its waves take the die's other items (non-global query block x slice
 //   of up to 16 key blocks: 8 at the ITC base pattern) in turn, wave w the items w, w + W, ...
 // A global row longer than 64 key blocks takes several workgroups whose merged partial
@@ -19,15 +19,15 @@ constexpr int kGlobalWaveLen = 16;  // most key blocks a wave of a global workgr
 constexpr int kListedItems = 62;
 constexpr int kCounterStride = 32;  // ints between the item counters of two dies (a 128-byte line each)
 struct Bf16Geom {
+  int waves;     // of a workgroup: 4, or 8
   int by_row;    // small launches: every row is done the way global rows are, a workgroup per row; no
                  // persistent workgroups
   int sw_len;    // by_row: key blocks per wave of a non-global row
   int gw_len;    // key blocks per wave of a global workgroup: 16; 8 when the whole grid fits the chip at once (then
                  // the global rows alone would set the run time); a quarter of the row in small launches and for short rows
-  int ng;        // workgroups per global row: ceil(nb / (4 * gw_len))
+  int ng;        // workgroups per global row: ceil(nb / (waves * gw_len))
   int cs;        // slices per non-global row: ceil(min(g + w + r, nb) / 16)
   int n_sitems;  // (nb - g) * cs
-  int s_wgs;     // ceil(n_sitems / 4): workgroups the non-global items of one (batch, head) would fill
   int p_wgs;     // persistent workgroups per die: their waves share out the die's non-global items
   int g_wgs;     // row workgroups per (batch, head): g * ng of global rows, then, by_row, the other rows
   int bh_rounds; // ceil(B*H / 8)

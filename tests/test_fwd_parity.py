@@ -238,6 +238,44 @@ def test_rows_by_workgroup(B, H, nb, g, w, r, masked):
     check_full(t, ridx, "bf16", 64, g, w, 0.125, key_mask=km, tag=f"rows B{B} H{H} nb{nb} r{r} mask{masked}")
 
 
+@pytest.mark.parametrize("B,H,nb,g,w,r", [
+    (5, 16, 9, 2, 3, 3),    # eight waves to a workgroup: a block or two of a global row each
+    (3, 16, 16, 2, 3, 3),
+    (3, 11, 20, 1, 17, 2),  # non-global rows in two slices
+    (1, 9, 66, 2, 3, 3),    # global rows by two workgroups of eight waves
+    (4, 8, 32, 2, 3, 3),
+    (5, 8, 33, 2, 3, 3),    # too many for a workgroup of eight waves per compute unit
+])
+@pytest.mark.parametrize("case", ["plain", "masked", "skip", "drop"])
+def test_launches_of_medium_size(B, H, nb, g, w, r, case):
+    n = nb * 64
+    t = inp.make_tensors(B, H, n, 64, 600 + nb, "bf16")
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 8)
+    torch = torch_mod()
+    km = None
+    if case in ("masked", "skip"):
+        km = np.ones((B, n), dtype=np.uint8)
+        km[0, n // 2 + 5:] = 0
+        km[B - 1, 3:40] = 0
+        km[B - 1, n - 130:n - 64] = 0
+    args = (t["Q"], t["K"], t["V"], ridx, 64, g, w, 0.125)
+    kw = dict(g=g, w=w, scale=0.125, key_padding_mask=None if km is None else torch.from_numpy(km).to("cuda:0"),
+              global_mode=bb.BB_SKIP_PADDED_QUERY_BLOCKS if case == "skip" else 0)
+    Q, K, V = device_qkv(t, "bf16")
+    rd = torch.from_numpy(ridx).to("cuda:0")
+    if case == "drop":
+        O, LSE = bb.bigbird_attn_fwd_dropout(Q, K, V, rd, p_drop=0.25, seed=3, **kw)
+        Oref, Lref = oracle.attn_fwd_dropout(*args, 0.25, 3)
+    else:
+        O, LSE = bb.bigbird_attn_fwd(Q, K, V, rd, **kw)
+        Oref, Lref = oracle.attn_fwd(*args, key_mask=km, skip_padded_query_blocks=case == "skip")
+    fin = np.isfinite(Lref)
+    assert (np.isneginf(to_host(LSE)) == ~fin).all()
+    err_o, err_l = np.abs(to_host(O) - Oref).max(), np.abs(to_host(LSE)[fin] - Lref[fin]).max()
+    print(f"B{B} H{H} nb{nb} {case}: max|dO|={err_o:.3e} max|dLSE|={err_l:.3e}")
+    assert err_o <= TOL["bf16"] and err_l <= TOL["bf16"]
+
+
 def test_zero_queries_closed_form_and_pattern_readback():
     """Q = 0 => O_i = mean of V over N(i), LSE_i = ln|N(i)|; V one-hot per key block spells out
     the neighbour set the kernel used, which must be the table's."""
