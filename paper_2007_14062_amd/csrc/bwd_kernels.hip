@@ -12,8 +12,8 @@
 //   * bwd_dkv_kernel walks the query-block list of a key block -- the inverse of the
 //     pattern (invert_pattern, part of the dQ launch) -- with S, dP, dS as
 //     [queries x keys] tiles, one lane per key, dV^T += dO^T P and dK^T += Q^T dS.
-// Lists longer than an item takes are cut into slices -- those of global blocks into 8 blocks each in large launches,
-// longer or none in small ones (RowSplit, KeySplit) -- whose partial sums are added in slice order by
+// Lists longer than an item takes are cut into slices -- those of global blocks into 8 to 32 blocks each in large
+// launches, longer or none in small ones (RowSplit, KeySplit) -- whose partial sums are added in slice order by
 // bwd_reduce_kernel (bit-reproducible).
 #include "bwd_kernels.h"
 #include "key_list.h"

@@ -9,7 +9,9 @@
 //     loop.  Per die, the first workgroups take one global query block each (key list
 //     dealt out 16 blocks per wave, the four waves' results merged in LDS: no partial
 //     results in HBM and no second kernel for up to 64 key blocks; longer rows take
-//     several workgroups plus the merge kernel).  The other workgroups stay for the whole
+//     several workgroups plus the merge kernel; launches of medium size: 8 blocks per wave and
+//     workgroups of eight waves, which took 24 slices of n = 4096 from 24.0 us, a merge launch in them,
+//     to 19.7).  The other workgroups stay for the whole
 //     launch: their waves share out the die's non-global items round robin and run them
 //     as one uninterrupted stream of block pairs -- the next item's query tile and first
 //     K tile ride at the end of this item's K and V tile streams, so the matrix pipe
@@ -991,9 +993,8 @@ __device__ __forceinline__ const void* kernel_kernargs() {
 #endif
 }
 
-// One non-global item by the classical recurrence, from its first load to its last store: the path
-// of items without any key block or with padded keys inside a block, of items whose row sums
-// left the safe range of the pipelined path, and of every item under attention dropout.
+// One non-global item with the running maximum, from its first load to its last store: the path of items
+// without any key block and of those whose row sums left the safe range of the fixed reference.
 template <int kMode, int W>
 __device__ __forceinline__ void item_by_recurrence(const FwdParams& p, int t) {
   const WaveCtx<W> w(p.c);
@@ -1036,7 +1037,7 @@ __device__ __attribute__((noinline)) void redo_items(const void* kernargs, int r
   for (int u = 0; u < n_redo; ++u) item_by_recurrence<kMode, W>(p, __builtin_amdgcn_readlane(redo, u));
 }
 
-// One query block by a whole workgroup: its key list dealt out to the four waves (up to 16 key blocks
+// One query block by a whole workgroup: its key list dealt out to the waves (up to 16 key blocks
 // each), their (m, l, O~) merged in LDS.  Inlined into the kernel, as the branch taken by the die's first workgroups: a
 // real call would start by saving a hundred callee-saved vector registers to scratch memory
 // (11 MB of HBM writes per launch at the BERT-base size, measured) for a caller that has nothing
@@ -1055,7 +1056,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
   bool by_recurrence = cur.running;
   const bool dealt_out = (p.geo.ng == 1 && p.geo.gw_len < kGlobalWaveLen) || sc.row_idx >= p.g * p.geo.ng;
   if ((kMode == kMasked || kMode == kOptions) && dealt_out) {
-    // A row with a cut block takes the recurrence in all four waves, as the same blocks do in one wave's
+    // A row with a cut block takes the running maximum in all waves, as the same blocks do in one wave's
     // item.  (Shares of 16 blocks, and of rows of several workgroups: each by itself.)
     if (lane == 0) row_cut<W>()[wv] = by_recurrence;
     __syncthreads();
