@@ -80,6 +80,13 @@ inline bool dq_two_waves(int BH, const RowSplit& s) {
   return items >= 384 && items <= 1024;
 }
 
+// The same for dK/dV: two pairs of waves per item up to 512 items, all resident at once (four waves each). Past that
+// they queue.  Forward and backward in us, one pair / two: 24 slices of n = 1024 (432 items) 50.8 / 49.9 and under dropout
+// 84 / 78, 12 of n = 2048 (456) 53.1 / 50.7, with w = 7 62 / 58, padded 56.5 / 53.0, under dropout 90 / 81, 48 of n = 512 (384)
+// 42.0 / 39.8, 4 of n = 4096 (312) 50.2 / 48.6; 8 of n = 2048 (304) and 16 of n = 1024 (288) the same.  Past 512 items:
+// 12 of n = 2048 with four global blocks (528) 63.3 / 67.1, 24 of n = 1536 (672) 57.3 / 58.5, 12 of n = 4096 (936) 67 / 72, 24 (1872) 101.5 / 111.
+inline bool dkv_two_teams(int BH, const KeySplit& s) { return static_cast<long long>(BH) * s.items_per_bh <= 512; }
+
 // Large bf16 launches: slices of global blocks longer than the standard 8, where the launch is long enough that
 // they still end with the others (the longest items start first).  Every slice costs 16 KB (dQ) or 32 KB (dK/dV) written
 // and read again by the reduction.  The lines lie by the pairs each resident workgroup gets on average: 1024 of the dK/dV
@@ -131,6 +138,7 @@ struct BwdParams {
   float scale;
   int by_row;      // bf16: a workgroup per block (bwd_by_row)
   int dq_waves;    // bf16: waves of a dQ item: kRowWaves if by_row, else 1 or 2 (dq_two_waves)
+  int dkv_teams;   // bf16: pairs of waves of a dK/dV item: kRowWaves if by_row, else 1 or 2 (dkv_two_teams)
   RowSplit split;  // query-row decomposition (dQ kernel), as in the forward
   KeySplit kv;     // key-block decomposition (dK/dV kernel)
   Dropout drop;    // attention dropout of the forward these gradients belong to (thr == 0: none)

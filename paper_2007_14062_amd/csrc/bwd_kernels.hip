@@ -500,8 +500,8 @@ __device__ __forceinline__ void pin_half_stage() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// kTeams: pairs of waves of a workgroup, each with a ring of its own.  Large launches: 1.  Small ones: 4
-// (p.by_row), which deal out the item's list and add their shares of dK and dV in LDS.
+// kTeams: pairs of waves of a workgroup, each with a ring of its own.  Large launches: 1.  Smaller ones: 2 (dkv_two_teams)
+// or 4 (p.by_row), which deal out the item's list and add their shares of dK and dV in LDS.
 template <bool kDrop, int kTeams>
 __global__ __launch_bounds__(kDkvThreads * kTeams) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_dkv_kernel(BwdParams p) {
@@ -871,9 +871,10 @@ int launch_bwd_bf16(const BwdParams& p, hipStream_t stream) {
   hipLaunchKernelGGL(dq, dim3(qgrid), dim3(64 * p.dq_waves), 0, stream, p);
   if (launch_failed("bwd_dq_kernel")) return BB_ERR_LAUNCH;
   const unsigned kvgrid = DieItems(p.BH, p.kv.items_per_bh).grid();
-  const auto dkv = p.by_row ? (drop ? bwd_dkv_kernel<true, kRowWaves> : bwd_dkv_kernel<false, kRowWaves>)
-                            : (drop ? bwd_dkv_kernel<true, 1> : bwd_dkv_kernel<false, 1>);
-  hipLaunchKernelGGL(dkv, dim3(kvgrid), dim3(p.by_row ? kDkvThreads * kRowWaves : kDkvThreads), 0, stream, p);
+  const auto dkv = p.dkv_teams == kRowWaves ? (drop ? bwd_dkv_kernel<true, kRowWaves> : bwd_dkv_kernel<false, kRowWaves>)
+                   : p.dkv_teams == 2       ? (drop ? bwd_dkv_kernel<true, 2> : bwd_dkv_kernel<false, 2>)
+                                            : (drop ? bwd_dkv_kernel<true, 1> : bwd_dkv_kernel<false, 1>);
+  hipLaunchKernelGGL(dkv, dim3(kvgrid), dim3(kDkvThreads * p.dkv_teams), 0, stream, p);
   if (launch_failed("bwd_dkv_kernel")) return BB_ERR_LAUNCH;
 
   return launch_bwd_reduce(p, stream);

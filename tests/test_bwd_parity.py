@@ -416,6 +416,51 @@ def test_small_launches_by_blocks_bf16(B, H, n, g, w, r, drop, padded):
         assert err <= TOL, err
 
 
+@pytest.mark.parametrize("B,H,nb,g,w,r", [
+    (3, 10, 9, 2, 3, 3),     # two pairs of waves to a key block, 330 items: slices of 8 and of 1 (one pair has none)
+    (2, 16, 14, 2, 3, 3),    # 512 items
+    (3, 11, 14, 2, 3, 3),    # 528: one pair
+    (1, 7, 41, 1, 5, 3),     # odd lists, a rest of one
+    (1, 2, 70, 2, 65, 1),    # few items, lists of more than 64 blocks
+    (1, 257, 1, 0, 1, 0),    # lists of one: the second pair has none
+])
+@pytest.mark.parametrize("case", ["plain", "skip", "drop"])
+def test_two_pairs_of_waves_per_key_block(B, H, nb, g, w, r, case):
+    torch = torch_mod()
+    n = nb * 64
+    t = inp.make_tensors(B, H, n, 64, 700 + nb, "bf16", with_dO=True)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 9)
+    km = None
+    if case == "skip":
+        km = np.ones((B, n), dtype=np.uint8)
+        km[0, n // 2 + 5:] = 0
+        km[B - 1, 3:40] = 0
+    Q, K, V = device_qkv(t, "bf16")
+    dO = device_tensor(t, "dO", "bf16")
+    rd = torch.from_numpy(ridx).to("cuda:0")
+    kw = dict(g=g, w=w, scale=0.125, key_padding_mask=None if km is None else torch.from_numpy(km).to("cuda:0"),
+              global_mode=bb.BB_SKIP_PADDED_QUERY_BLOCKS if case == "skip" else 0)
+    args = (t["Q"], t["K"], t["V"], t["dO"])
+    if case == "drop":
+        O, LSE = bb.bigbird_attn_fwd_dropout(Q, K, V, rd, p_drop=0.1, seed=5, **kw)
+        grads = bb.bigbird_attn_bwd_dropout(Q, K, V, O, LSE, dO, rd, p_drop=0.1, seed=5, **kw)
+    else:
+        O, LSE = bb.bigbird_attn_fwd(Q, K, V, rd, **kw)
+        grads = bb.bigbird_attn_bwd(Q, K, V, O, LSE, dO, rd, **kw)
+    torch.cuda.synchronize()
+    grads = [to_host(x) for x in grads]
+    assert all(np.isfinite(x).all() for x in grads)
+    if case == "drop":  # the mask is drawn by (batch, head): the whole call
+        ref = oracle.attn_bwd_dropout(*args, ridx, 64, g, w, 0.125, 0.1, 5)
+        assert max(float(np.abs(x - y).max()) for x, y in zip(grads, ref)) <= TOL
+        return
+    for (bi, h) in sorted({(0, 0), (B - 1, H - 1), (B // 2, H // 2)}):
+        sl = (slice(bi, bi + 1), slice(h, h + 1))
+        ref = oracle.attn_bwd(*(x[sl] for x in args), ridx[h:h + 1], 64, g, w, 0.125, key_mask=None if km is None else km[bi:bi + 1],
+                              skip_padded_query_blocks=case == "skip")
+        assert max(float(np.abs(x[sl] - y).max()) for x, y in zip(grads, ref)) <= TOL
+
+
 @pytest.mark.parametrize("scale", [1e-38, 1e-44, 1e-30])
 @pytest.mark.parametrize("B,H,n", [(1, 2, 640), (2, 10, 1088)])  # a workgroup per block; past that
 def test_scales_whose_lse_quotient_overflows(B, H, n, scale):
