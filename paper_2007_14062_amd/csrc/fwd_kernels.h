@@ -33,6 +33,73 @@ struct Bf16Geom {
   int bh_rounds; // ceil(B*H / 8)
 };
 
+// The decomposition of a launch.
+inline Bf16Geom make_bf16_geom(int BH, int nb, int g, int w, int r) {
+  Bf16Geom q;
+  const int sparse_ub = longest_sparse_list(nb, g, w, r);
+  auto cut = [](int n, int by) { return (n + by - 1) / by; };
+  // a wave takes up to 16 key blocks of a non-global row; wider patterns are sliced
+  q.cs = sparse_ub > kGlobalWaveLen ? cut(sparse_ub, kGlobalWaveLen) : 1;
+  q.n_sitems = (nb - g) * q.cs;
+  q.bh_rounds = cut(BH, kXcd);
+  q.waves = 4;
+  q.by_row = 0;
+  q.sw_len = 0;
+  // Global rows: 16 key blocks per wave (up to 64 per workgroup, merged in LDS).
+  q.gw_len = kGlobalWaveLen;
+  q.ng = cut(nb, 4 * kGlobalWaveLen);
+  constexpr int kHalfLen = kGlobalWaveLen / 2;
+  // the workgroups a die gets with half as many blocks per wave
+  auto wgs = [&](int waves) { return q.bh_rounds * (g * cut(nb, waves * kHalfLen) + cut(q.n_sitems, waves)); };
+  if (static_cast<long long>(BH) * (g * q.ng + nb - g) <= 288 && sparse_ub <= 4 * kGlobalWaveLen) {
+    // Small launches, about a workgroup per CU: all rows that way, the key list of each dealt out to four
+    // waves.  12 heads, n = 512 / 1024 / 1536: 12.2 -> 7.2, 12.4 -> 8.7, 12.5 -> 11.9 us; past that CUs have
+    // two such workgroups and single waves with whole rows win (n = 2048, 384 rows: 12.7 against 17.5).
+    q.by_row = 1;
+  } else if (wgs(8) <= 32 && wgs(4) > 32) {
+    // Every workgroup resident at once (a die has 32 CUs of eight waves), more than one to a CU: the longest wave sets the
+    // run time, so a global row's list is dealt out to eight waves, up to 64 blocks without a merge launch.  us,
+    // against workgroups of four waves with 16 blocks each, or with 8, several to a row, and a merge launch: 24 slices of
+    // n = 4096 24.0 -> 19.7, 12 20.3 -> 16.6, 48 of n = 1024 19.7 -> 16.5, 24 of n = 2048 with 230 global tokens 28.9 -> 23.1.
+    // With fewer workgroups eight waves share a CU while others idle (8 of n = 4096 14.6 -> 16.3); with more the global
+    // rows wait for each other (48 of n = 4096 38.2 -> 47.3).
+    q.waves = 8;
+    q.gw_len = kHalfLen;
+    q.ng = cut(nb, 8 * kHalfLen);
+  } else if (nb > 4 * kHalfLen && wgs(4) <= 64) {
+    // the same by several workgroups to a row, whose partial results the merge kernel combines
+    q.gw_len = kHalfLen;
+    q.ng = cut(nb, 4 * kHalfLen);
+  }
+  q.g_wgs = g * q.ng;
+  if (q.by_row) {
+    q.sw_len = sparse_ub > q.waves ? cut(sparse_ub, q.waves) : 1;
+    q.g_wgs += nb - g;
+    q.cs = 1;
+  }
+  // A global row of one workgroup: an equal share for each wave in small launches and for short rows (96 slices of
+  // n = 512 15.5 -> 14.1 us, 144 of n = 768 26.2 -> 25.1); longer ones keep 16 blocks per wave, which leaves
+  // other waves a SIMD of their own meanwhile (96 of n = 1024 27.0 against 27.6 in quarters, 72 of n = 1536 26.6
+  // against 26.9, 36 of n = 3072 26.9 against 27.2).
+  if (q.ng == 1 && (q.by_row || q.waves == 8 || nb < kGlobalWaveLen)) q.gw_len = cut(nb, q.waves);
+  {
+    // Persistent workgroups: as many as stay resident beside the global-row workgroups (a die
+    // holds 256 waves of this kernel: eight per CU), at most one wave per item.
+    const int slots_per_die = 256 / q.waves;
+    const int n_global = q.bh_rounds * q.g_wgs;
+    const int want = cut(q.bh_rounds * q.n_sitems, q.waves);
+    int avail = slots_per_die - n_global;
+    if (avail < slots_per_die / 4) avail = slots_per_die / 2;  // the global rows alone fill the die: queue behind them
+    q.p_wgs = want < avail ? want : avail;
+    // a wave lists the items it has to redo by the exact recurrence in one register: no wave may be
+    // given more than the list takes, and together the lists have to take every item, whatever that
+    // does to residency
+    const int floor_wgs = cut(q.bh_rounds * q.n_sitems, q.waves * kListedItems);
+    if (q.p_wgs < floor_wgs) q.p_wgs = floor_wgs;
+  }
+  return q;
+}
+
 struct FwdParams {
   const void* Q;
   const void* K;

@@ -1,0 +1,75 @@
+"""How launches are cut up, on the CPU: the host rules of the kernel headers, compiled into a small program.
+
+Every key block of a row is somebody's, lists fit where they are kept, partial results fit the workspace -- over all
+forms the entry points take, small and large, with many or no global blocks."""
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r"""
+#include "bwd_kernels.h"
+#include "fwd_kernels.h"
+#include <cstdio>
+int main() {
+  int BH, nb, g, w, r, masked, drop;
+  while (scanf("%d %d %d %d %d %d %d", &BH, &nb, &g, &w, &r, &masked, &drop) == 7) {
+    const bb::Bf16Geom q = bb::make_bf16_geom(BH, nb, g, w, r);
+    const bb::RowSplit s = bb::make_row_split(BH, nb, g, w, r);
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
+           q.g_wgs, q.bh_rounds, bb::longest_sparse_list(nb, g, w, r), bb::kListedItems, s.slots_per_bh);
+  }
+}
+"""
+FIELDS = "waves by_row sw_len gw_len ng cs n_sitems p_wgs g_wgs bh_rounds sparse listed slots_per_bh".split()
+
+
+@pytest.fixture(scope="module")
+def geometry(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("geometry")
+    src, exe = d / "geometry.hip", d / "geometry"
+    src.write_text(PROGRAM)
+    subprocess.run([hipcc, "--offload-host-only", "-std=c++17", "-O1", "-w", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2007_14062_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+
+    def ask(cases):
+        """cases: (BH, nb, g, w, r[, masked[, drop]]) each; a dict of the fields for each."""
+        text = "".join(" ".join(str(int(x)) for x in (tuple(c) + (0, 0))[:7]) + "\n" for c in cases)
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
+        return [dict(zip(FIELDS, map(int, line.split()))) for line in out.splitlines()]
+
+    return ask
+
+
+def any_forms(count, seed):
+    rng = random.Random(seed)
+    out = []
+    for _ in range(count):
+        nb = max(1, round(2 ** rng.uniform(0, 9)))
+        g = rng.choice((0, 1, 2, 2, 2, 4, 7, nb // 2, nb))
+        w = rng.choice((1, 3, 3, 3, 7, 15, 33, 2 * nb + 1))
+        out.append((max(1, round(2 ** rng.uniform(0, 9))), nb, min(g, nb), w, rng.choice((0, 2, 3, 3, 12)), rng.randrange(2), rng.randrange(2)))
+    return out
+
+
+def test_every_block_has_a_wave_and_every_list_a_place(geometry):
+    cases = any_forms(4000, 1)
+    for c, q in zip(cases, geometry(cases)):
+        BH, nb, g = c[:3]
+        assert q["waves"] in (4, 8) and 1 <= q["gw_len"] <= 16, (c, q)
+        assert q["waves"] * q["gw_len"] * q["ng"] >= nb, (c, q)                  # global rows
+        if q["by_row"]:
+            assert q["waves"] == 4 and q["sw_len"] <= 16 and 4 * q["sw_len"] >= q["sparse"], (c, q)
+            assert q["g_wgs"] == g * q["ng"] + nb - g and q["cs"] == 1, (c, q)
+        else:
+            assert 16 * q["cs"] >= q["sparse"] and q["g_wgs"] == g * q["ng"], (c, q)
+            assert q["n_sitems"] == (nb - g) * q["cs"], (c, q)
+            assert q["p_wgs"] * q["waves"] * q["listed"] >= q["bh_rounds"] * q["n_sitems"], (c, q)
+        slots = (g * q["ng"] if q["ng"] > 1 else 0) + ((nb - g) * q["cs"] if q["cs"] > 1 else 0)
+        assert slots <= q["slots_per_bh"], (c, q)
