@@ -24,7 +24,7 @@ struct Bf16Geom {
                  // persistent workgroups
   int sw_len;    // by_row: key blocks per wave of a non-global row
   int gw_len;    // key blocks per wave of a global workgroup: 16; 8 when the whole grid fits the chip at once (then
-                 // the global rows alone would set the run time); a quarter of the row in small launches and for short rows
+                 // the global rows alone would set the run time); an equal share of the row in small launches and for short rows
   int ng;        // workgroups per global row: ceil(nb / (waves * gw_len))
   int cs;        // slices per non-global row: ceil(min(g + w + r, nb) / 16)
   int n_sitems;  // (nb - g) * cs
@@ -49,24 +49,29 @@ inline Bf16Geom make_bf16_geom(int BH, int nb, int g, int w, int r) {
   q.gw_len = kGlobalWaveLen;
   q.ng = cut(nb, 4 * kGlobalWaveLen);
   constexpr int kHalfLen = kGlobalWaveLen / 2;
-  // the workgroups a die gets with half as many blocks per wave
-  auto wgs = [&](int waves) { return q.bh_rounds * (g * cut(nb, waves * kHalfLen) + cut(q.n_sitems, waves)); };
+  // the workgroups a die gets with half as many blocks per wave, as they are launched: the items of its slices together
+  auto wgs = [&](int waves) { return q.bh_rounds * g * cut(nb, waves * kHalfLen) + cut(q.bh_rounds * q.n_sitems, waves); };
   if (static_cast<long long>(BH) * (g * q.ng + nb - g) <= 288 && sparse_ub <= 4 * kGlobalWaveLen) {
     // Small launches, about a workgroup per CU: all rows that way, the key list of each dealt out to four
     // waves.  12 heads, n = 512 / 1024 / 1536: 12.2 -> 7.2, 12.4 -> 8.7, 12.5 -> 11.9 us; past that CUs have
     // two such workgroups and single waves with whole rows win (n = 2048, 384 rows: 12.7 against 17.5).
     q.by_row = 1;
-  } else if (wgs(8) <= 32 && wgs(4) > 32) {
+  } else if (nb >= kGlobalWaveLen && wgs(8) <= 32 && wgs(4) > 32) {
     // Every workgroup resident at once (a die has 32 CUs of eight waves), more than one to a CU: the longest wave sets the
     // run time, so a global row's list is dealt out to eight waves, up to 64 blocks without a merge launch.  us,
-    // against workgroups of four waves with 16 blocks each, or with 8, several to a row, and a merge launch: 24 slices of
-    // n = 4096 24.0 -> 19.7, 12 20.3 -> 16.6, 48 of n = 1024 19.7 -> 16.5, 24 of n = 2048 with 230 global tokens 28.9 -> 23.1.
-    // With fewer workgroups eight waves share a CU while others idle (8 of n = 4096 14.6 -> 16.3); with more the global
-    // rows wait for each other (48 of n = 4096 38.2 -> 47.3).
+    // four waves (16 blocks each; from 33 blocks on 8, several workgroups to a row and a merge launch) against eight, plain /
+    // padded / dropout:
+    //   wgs(4) = 33: 48 slices of n = 1024  20.4 / 23.0 / 40.8 and 17.1 / 21.8 / 31.4, 36 of n = 1280  16.6 / 21.6 / 34.4, 17.0 / 24.3 / 31.1
+    //   wgs(8) = 32: 36 of n = 2304  23.9 / 27.7 / 43.2 and 20.4 / 22.8 / 32.5, 48 of n = 1792  23.6 / 29.7 / 43.3, 20.4 / 23.3 / 33.1
+    //   24 of n = 4096  26.2 / 25.9 / 37.5 and 22.2 / 25.8 / 34.8, 12 of n = 4096  21.5 / 22.1 / 33.7, 17.8 / 23.5 / 31.2
+    // At a workgroup of four to a CU each wave has a SIMD, and eight waves share theirs while other CUs idle (wgs(4) = 32: 48 of
+    // n = 960 12.4 and 17.3, dropout 22.0 and 30.9); past the upper line the global rows wait for each other (wgs(8) = 34: 64
+    // of n = 1280 22.7 and 31.9, 35: 28 of n = 3584 27.7 and 35.1).  Rows below 16 blocks are dealt out in quarters to four waves, and
+    // eighths gain nothing there (64 of n = 896 16.0 / 19.0 / 25.6 and 17.9 / 22.1 / 31.0).
     q.waves = 8;
     q.gw_len = kHalfLen;
     q.ng = cut(nb, 8 * kHalfLen);
-  } else if (nb > 4 * kHalfLen && wgs(4) <= 64) {
+  } else if (nb > 4 * kHalfLen && q.bh_rounds * (g * cut(nb, 4 * kHalfLen) + cut(q.n_sitems, 4)) <= 64) {
     // the same by several workgroups to a row, whose partial results the merge kernel combines
     q.gw_len = kHalfLen;
     q.ng = cut(nb, 4 * kHalfLen);

@@ -49,7 +49,8 @@ def _run(Q, K, V, dO, ridx_h):
     return to_host(O), [to_host(x) for x in grads], Oo, ref
 
 
-@pytest.mark.parametrize("H", [2, 20, 24])  # a workgroup per row and block; a wave per dQ item; two waves
+# a workgroup per row and block; a wave per dQ item; two waves; workgroups of eight waves in the forward
+@pytest.mark.parametrize("H", [2, 20, 24, 44])
 def test_every_mask_bit_shows_in_the_outputs(H):
     import torch
     assert torch.cuda.is_available()

@@ -239,12 +239,15 @@ def test_rows_by_workgroup(B, H, nb, g, w, r, masked):
 
 
 @pytest.mark.parametrize("B,H,nb,g,w,r", [
-    (5, 16, 9, 2, 3, 3),    # eight waves to a workgroup: a block or two of a global row each
-    (3, 16, 16, 2, 3, 3),
+    (5, 16, 9, 2, 3, 3),    # four waves: rows of fewer than 16 blocks
+    (3, 16, 16, 2, 3, 3),   # eight waves to a workgroup: two blocks of a global row each
     (3, 11, 20, 1, 17, 2),  # non-global rows in two slices
     (1, 9, 66, 2, 3, 3),    # global rows by two workgroups of eight waves
     (4, 8, 32, 2, 3, 3),
-    (5, 8, 33, 2, 3, 3),    # too many for a workgroup of eight waves per compute unit
+    (5, 8, 33, 2, 3, 3),    # 30 workgroups of eight waves to a die
+    (6, 6, 36, 2, 3, 3),    # 32
+    (6, 8, 33, 2, 3, 3),    # 36 would not fit: four waves, 16 blocks of a global row each
+    (1, 8, 64, 2, 3, 3),    # a third of the units: four waves with 8 blocks, two workgroups to a global row and a merge launch
 ])
 @pytest.mark.parametrize("case", ["plain", "masked", "skip", "drop"])
 def test_launches_of_medium_size(B, H, nb, g, w, r, case):

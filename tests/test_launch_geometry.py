@@ -73,3 +73,19 @@ def test_every_block_has_a_wave_and_every_list_a_place(geometry):
             assert q["p_wgs"] * q["waves"] * q["listed"] >= q["bh_rounds"] * q["n_sitems"], (c, q)
         slots = (g * q["ng"] if q["ng"] > 1 else 0) + ((nb - g) * q["cs"] if q["cs"] > 1 else 0)
         assert slots <= q["slots_per_bh"], (c, q)
+
+
+@pytest.mark.parametrize("BH,nb,waves", [
+    (48, 15, 4), (56, 12, 4), (72, 8, 4),                # a workgroup of four waves to a compute unit
+    (64, 12, 4), (72, 10, 4), (56, 15, 4), (64, 15, 4),  # global rows of fewer than 16 blocks
+    (48, 16, 8), (64, 16, 8), (36, 20, 8), (24, 64, 8), (12, 64, 8), (40, 33, 8),
+    (36, 36, 8), (48, 28, 8),                            # 32 workgroups of eight waves to a die: every unit has one
+    (64, 20, 4), (48, 33, 4), (48, 64, 4), (8, 64, 4),   # past that; too few
+    (80, 9, 4), (9, 66, 8), (32, 32, 8), (44, 16, 8),    # (with the ones above: what the GPU tests of medium launches run)
+])
+def test_workgroups_of_eight_waves(geometry, BH, nb, waves):
+    """The count that decides is the one that is launched: the items of a die's slices together, not slice by slice."""
+    (q,) = geometry([(BH, nb, 2, 3, 3)])
+    assert q["waves"] == waves and not q["by_row"]
+    if waves == 8:
+        assert q["bh_rounds"] * q["g_wgs"] + q["p_wgs"] <= 32
