@@ -154,7 +154,7 @@ int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, float* L
   p.dyn = (dtype == BB_BF16 && p.skip_q && drop.thr == 0 && p.counters) ? 1 : 0;
   p.split = bb::make_row_split(p.BH, p.nb, g, w, r, fine ? bb::fine_slice_f32(p.BH, p.nb, g, w, r) : 0);
   if (dtype == BB_BF16) {
-    p.geo = bb::make_bf16_geom(p.BH, p.nb, g, w, r);
+    p.geo = bb::make_bf16_geom(p.BH, p.nb, g, w, r, key_padding_mask != nullptr);
     const bb::Bf16Geom& q = p.geo;
     if (q.by_row) p.dyn = 0;  // (nothing is claimed)
     p.cmb_g_rows = q.ng > 1 ? g : 0;

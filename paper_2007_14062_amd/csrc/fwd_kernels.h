@@ -33,8 +33,8 @@ struct Bf16Geom {
   int bh_rounds; // ceil(B*H / 8)
 };
 
-// The decomposition of a launch.
-inline Bf16Geom make_bf16_geom(int BH, int nb, int g, int w, int r) {
+// The decomposition of a launch.  masked: there is a padding mask.
+inline Bf16Geom make_bf16_geom(int BH, int nb, int g, int w, int r, bool masked) {
   Bf16Geom q;
   const int sparse_ub = longest_sparse_list(nb, g, w, r);
   auto cut = [](int n, int by) { return (n + by - 1) / by; };
@@ -45,17 +45,25 @@ inline Bf16Geom make_bf16_geom(int BH, int nb, int g, int w, int r) {
   q.waves = 4;
   q.by_row = 0;
   q.sw_len = 0;
-  // Global rows: 16 key blocks per wave (up to 64 per workgroup, merged in LDS).
-  q.gw_len = kGlobalWaveLen;
-  q.ng = cut(nb, 4 * kGlobalWaveLen);
+  // Global rows: 16 key blocks per wave (up to 64 per workgroup, merged in LDS).  When every workgroup of the launch is
+  // resident at once (two per CU, 32 CUs per die) the longest one sets the run time: then 8 per wave, by several workgroups
+  // to a row, whose partial results the merge kernel combines.
   constexpr int kHalfLen = kGlobalWaveLen / 2;
+  const bool halves = nb > 4 * kHalfLen && q.bh_rounds * (g * cut(nb, 4 * kHalfLen) + cut(q.n_sitems, 4)) <= 64;
+  q.gw_len = halves ? kHalfLen : kGlobalWaveLen;
+  q.ng = cut(nb, 4 * q.gw_len);
+  // With a workgroup for every row, up to 11 blocks per wave in one workgroup cost less than the merge launch (us, one workgroup
+  // to a global row and two: 4 slices of n = 2560 11.9 and 13.8, dropout 22.8 and 22.6; n = 3200 14.4 and 14.1, 28.1 and 22.7).  Under a mask
+  // the blocks that are left may all be the first wave's (4 of n = 3200, half of it padded, 21.1 and 14.5).
+  const int row_ng = masked || nb > 44 ? q.ng : 1;
   // the workgroups a die gets with half as many blocks per wave, as they are launched: the items of its slices together
   auto wgs = [&](int waves) { return q.bh_rounds * g * cut(nb, waves * kHalfLen) + cut(q.bh_rounds * q.n_sitems, waves); };
-  if (static_cast<long long>(BH) * (g * q.ng + nb - g) <= 288 && sparse_ub <= 4 * kGlobalWaveLen) {
+  if (static_cast<long long>(BH) * (g * row_ng + nb - g) <= 288 && sparse_ub <= 4 * kGlobalWaveLen) {
     // Small launches, about a workgroup per CU: all rows that way, the key list of each dealt out to four
     // waves.  12 heads, n = 512 / 1024 / 1536: 12.2 -> 7.2, 12.4 -> 8.7, 12.5 -> 11.9 us; past that CUs have
     // two such workgroups and single waves with whole rows win (n = 2048, 384 rows: 12.7 against 17.5).
     q.by_row = 1;
+    q.ng = row_ng;
   } else if (nb >= kGlobalWaveLen && wgs(8) <= 32 && wgs(4) > 32) {
     // Every workgroup resident at once (a die has 32 CUs of eight waves), more than one to a CU: the longest wave sets the
     // run time, so a global row's list is dealt out to eight waves, up to 64 blocks without a merge launch.  us,
@@ -71,10 +79,6 @@ inline Bf16Geom make_bf16_geom(int BH, int nb, int g, int w, int r) {
     q.waves = 8;
     q.gw_len = kHalfLen;
     q.ng = cut(nb, 8 * kHalfLen);
-  } else if (nb > 4 * kHalfLen && q.bh_rounds * (g * cut(nb, 4 * kHalfLen) + cut(q.n_sitems, 4)) <= 64) {
-    // the same by several workgroups to a row, whose partial results the merge kernel combines
-    q.gw_len = kHalfLen;
-    q.ng = cut(nb, 4 * kHalfLen);
   }
   q.g_wgs = g * q.ng;
   if (q.by_row) {

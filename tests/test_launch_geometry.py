@@ -17,7 +17,7 @@ PROGRAM = r"""
 int main() {
   int BH, nb, g, w, r, masked, drop;
   while (scanf("%d %d %d %d %d %d %d", &BH, &nb, &g, &w, &r, &masked, &drop) == 7) {
-    const bb::Bf16Geom q = bb::make_bf16_geom(BH, nb, g, w, r);
+    const bb::Bf16Geom q = bb::make_bf16_geom(BH, nb, g, w, r, masked != 0);
     const bb::RowSplit s = bb::make_row_split(BH, nb, g, w, r);
     printf("%d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
            q.g_wgs, q.bh_rounds, bb::longest_sparse_list(nb, g, w, r), bb::kListedItems, s.slots_per_bh);
@@ -89,3 +89,20 @@ def test_workgroups_of_eight_waves(geometry, BH, nb, waves):
     assert q["waves"] == waves and not q["by_row"]
     if waves == 8:
         assert q["bh_rounds"] * q["g_wgs"] + q["p_wgs"] <= 32
+
+
+@pytest.mark.parametrize("BH,nb,masked,ng,gw_len", [
+    (1, 128, 0, 4, 8), (2, 128, 0, 4, 8), (1, 200, 0, 7, 8), (3, 80, 0, 3, 8), (2, 65, 1, 3, 8),  # longer than 64 blocks
+    (4, 64, 0, 2, 8), (4, 50, 0, 2, 8), (4, 45, 0, 2, 8), (4, 50, 1, 2, 8), (8, 33, 1, 2, 8),
+    (4, 44, 0, 1, 11), (8, 35, 0, 1, 9), (8, 33, 0, 1, 9),                                        # dealt out in quarters
+    (12, 16, 0, 1, 4), (12, 16, 1, 1, 4), (4, 32, 1, 1, 8),
+])
+def test_global_rows_of_launches_by_rows(geometry, BH, nb, masked, ng, gw_len):
+    (q,) = geometry([(BH, nb, 2, 3, 3, masked)])
+    assert q["by_row"] and (q["ng"], q["gw_len"]) == (ng, gw_len), q
+
+
+@pytest.mark.parametrize("BH,nb,masked", [(5, 56, 0), (8, 35, 1), (7, 40, 1), (12, 24, 0)])
+def test_launches_just_past_those_by_rows(geometry, BH, nb, masked):
+    (q,) = geometry([(BH, nb, 2, 3, 3, masked)])
+    assert q["by_row"] == (BH == 12) and q["waves"] == 4, q
