@@ -561,8 +561,8 @@ struct Item {
   int slot;            // partial-result slot (nchunks > 1)
   int cnt;             // key blocks in this slice
   int kl;              // the list: lane t holds entry t % 16
-  unsigned partial;    // bit t: entry t has padded keys inside; its validity bits are in the wave's key_bits
-  bool running;        // takes the running maximum (running_pair)
+  unsigned partial;    // bit t: entry t has padded keys inside; its validity bits are in the wave's key_bits.  Not 0: takes the
+                       // running maximum (running_pair)
   int bits;            // which of the wave's two sets of key_bits is its
   bool skipped;        // query block without a valid position, not to be computed (cnt = 0)
 };
@@ -657,7 +657,6 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx<W>& 
     // an item without key blocks (O = 0, LSE = -inf)
     it.skipped = true;
     it.partial = 0;
-    it.running = false;
     it.kl = 0;
     it.bh = __builtin_amdgcn_readfirstlane(it.bh);
     it.j = __builtin_amdgcn_readfirstlane(it.j);
@@ -672,7 +671,6 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx<W>& 
   it.cnt = kl.cnt;
   it.kl = kl.entry;
   it.partial = kl.partial;
-  it.running = kMode == kDrop || it.partial != 0;
   // all of these are wave uniform; saying so keeps them (and what is computed from them) in
   // scalar registers
   it.bh = __builtin_amdgcn_readfirstlane(it.bh);
@@ -682,7 +680,6 @@ __device__ __forceinline__ void make_item(const FwdParams& p, const WaveCtx<W>& 
   it.slot = __builtin_amdgcn_readfirstlane(it.slot);
   it.cnt = __builtin_amdgcn_readfirstlane(it.cnt);
   it.partial = __builtin_amdgcn_readfirstlane(it.partial);
-  it.running = __builtin_amdgcn_readfirstlane(static_cast<int>(it.running)) != 0;
 }
 
 // First tiles of an item that nobody has fetched ahead.  The query block takes the same road as a
@@ -1053,7 +1050,7 @@ __device__ __forceinline__ void global_row_workgroup(const FwdParams& p, const S
 #endif
   Item cur;
   make_item<kMode, W>(p, w, sc, 0, cur);
-  bool by_recurrence = cur.running;
+  bool by_recurrence = kMode == kDrop || cur.partial != 0;
   const bool dealt_out = (p.geo.ng == 1 && p.geo.gw_len < kGlobalWaveLen) || sc.row_idx >= p.g * p.geo.ng;
   if ((kMode == kMasked || kMode == kOptions) && dealt_out) {
     // A row with a cut block takes the running maximum in all waves, as the same blocks do in one wave's
@@ -1352,10 +1349,15 @@ void fwd_kernel_bf16(FwdParams p) {
       bf16x8 va[2][2][2], p3[2];
       f32x16 sA;
       no_predecessor(va[1], p3);
-      zero_acc(o[0]);
-      zero_acc(o[1]);
-      // (said to be uniform here: otherwise one kind's operands are kept through the pairs of the other)
-      if (kMode == kDrop || (kMode != kPlain && __builtin_amdgcn_readfirstlane(static_cast<int>(cur.running)) != 0)) {
+      // Which kind of pairs: a scalar test (a flag in a vector register was reloaded from scratch memory at the start of every
+      // item, with a wait for all that was in flight).  Two ifs and not one with an else: the compiler lays the kinds
+      // out one behind the other, and what the second reads lives through the pairs of the first unless it is said
+      // not to.  33 and 32 spilled vector registers -> 3 and 7 (kMasked, kOptions; with the lists' lane numbers from lane_again):
+      // 8 sequences of n = 4096, 12 heads, padded at block ends, 61.4 -> 59.0 us, inside blocks 72.1 -> 70.1, 230 global tokens 57.8 -> 55.1.
+      unsigned running = kMode == kDrop ? 1u : kMode == kPlain ? 0u : cur.partial;
+      if (running != 0) {
+        zero_acc(o[0]);
+        zero_acc(o[1]);
         const ScalarStreams ts(p, cur, t_nxt >= 0 ? &nxt : nullptr);
         const LeanOffsets lo(lane_again(lane));
         f32x16 s1;
@@ -1383,7 +1385,12 @@ void fwd_kernel_bf16(FwdParams p) {
           inv[q] = l > 0.f ? (kMode == kDrop ? p.drop.rs : 1.f) / l : 0.f;
           lse[q] = l > 0.f ? (rs.m[q] + fast_log2(l)) * kLn2 : neg_inf();
         }
-      } else {
+        forget(ka);
+      }
+      if constexpr (kMode == kMasked || kMode == kOptions) asm volatile("" : "+s"(running));  // (or the two become one again)
+      if (running == 0) {
+        zero_acc(o[0]);
+        zero_acc(o[1]);
         const StraightOffsets so = straight();
         const TransposedOffsets to = transposed();
         const RowSumOperand ones(lane_again(lane));

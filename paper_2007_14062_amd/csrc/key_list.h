@@ -25,14 +25,13 @@ __device__ __forceinline__ int lane_again(int lane) {
 // rules as build_key_list_range: global blocks, window blocks, random blocks; a candidate is
 // dropped if an earlier component already holds it.  Entries [lo, lo+len) go to klist.
 __device__ __forceinline__ int finish_key_list_sparse(const Pattern& pat, int r, int j, int rnd, int lo,
-                                                       int len, int* klist) {
-  const int lane = lane_id();
+                                                       int len, int lane, int* klist) {
   const int nb = pat.nb;
   const int ncand = pat.g + pat.w + r;  // <= 64 (checked by the caller)
   bool valid = false;
   int k = -1;
   const int t = lane - pat.g - pat.w;
-  const int mine = __shfl(rnd, t < 0 ? 0 : t);  // entry t of the row, for the lanes that stand for it
+  const int mine = __builtin_amdgcn_ds_bpermute((t < 0 ? 0 : t) * 4, rnd);  // entry t of the row, for the lanes that stand for it
   if (lane < pat.g) {
     k = pat.global_block(lane);
     valid = true;
@@ -126,7 +125,8 @@ __device__ __forceinline__ KeyList item_key_list(const Pattern& pat, const int32
       for (int k = 0; k < 4; ++k)
         if (lane == u0 + k && u0 + k < r) rnd = e[k];
     }
-    out.cnt = finish_key_list_sparse(pat, r, j, rnd, lo, len, klist);
+    // (without a mask there are registers for what is made of the lane number to stay in)
+    out.cnt = finish_key_list_sparse(pat, r, j, rnd, lo, len, kMask ? lane : lane_id(), klist);
   } else {
     out.cnt = build_key_list_range(pat, rand_idx, r, kMask ? kmask : nullptr, n, bi, h, j, row_global, lo, len, klist);
   }
