@@ -260,8 +260,7 @@ __device__ __forceinline__ void block_key_bits(const uint8_t* kmask, int bi, int
 // dropped if an earlier component already holds it.
 __device__ __forceinline__ int build_key_list_range(const Pattern& pat, const int32_t* rand_idx, int r,
                                                     const uint8_t* kmask, int n, int bi, int h, int j,
-                                                    bool row_global, int lo, int len, int* klist) {
-  const int lane = lane_id();
+                                                    bool row_global, int lo, int len, int lane, int* klist) {
   const int nb = pat.nb;
   const int ncand = row_global ? nb : pat.g + pat.w + r;
   const int hi = lo + len;
@@ -303,7 +302,7 @@ __device__ __forceinline__ int build_key_list_range(const Pattern& pat, const in
 __device__ __forceinline__ int build_key_list(const Pattern& pat, const int32_t* rand_idx, int r,
                                               const uint8_t* kmask, int n, int bi, int h, const WorkItem& it,
                                               int* klist) {
-  return build_key_list_range(pat, rand_idx, r, kmask, n, bi, h, it.j, it.row_global, it.chunk * it.len, it.len, klist);
+  return build_key_list_range(pat, rand_idx, r, kmask, n, bi, h, it.j, it.row_global, it.chunk * it.len, it.len, lane_id(), klist);
 }
 
 // 64-bit validity mask of the keys of block k (bit t = key k*64+t is valid).

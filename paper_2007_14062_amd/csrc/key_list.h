@@ -128,7 +128,7 @@ __device__ __forceinline__ KeyList item_key_list(const Pattern& pat, const int32
     // (without a mask there are registers for what is made of the lane number to stay in)
     out.cnt = finish_key_list_sparse(pat, r, j, rnd, lo, len, kMask ? lane : lane_id(), klist);
   } else {
-    out.cnt = build_key_list_range(pat, rand_idx, r, kMask ? kmask : nullptr, n, bi, h, j, row_global, lo, len, klist);
+    out.cnt = build_key_list_range(pat, rand_idx, r, kMask ? kmask : nullptr, n, bi, h, j, row_global, lo, len, kMask ? lane : lane_id(), klist);
   }
   // same wave wrote and reads the list: LDS keeps a wave's accesses in order, the compiler must too
   asm volatile("" ::: "memory");
