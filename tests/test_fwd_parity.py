@@ -239,6 +239,38 @@ def test_rows_by_workgroup(B, H, nb, g, w, r, masked):
 
 
 @pytest.mark.parametrize("B,H,nb,g,w,r", [
+    (1, 2, 1, 1, 1, 0), (2, 3, 2, 1, 1, 0), (1, 4, 3, 2, 3, 0), (2, 2, 4, 2, 3, 0),  # a pair for a wave, or none
+    (1, 2, 8, 2, 3, 3), (1, 3, 12, 2, 3, 3), (1, 2, 17, 1, 5, 9),                    # two; three; five and four
+])
+@pytest.mark.parametrize("drop", [False, True])
+def test_short_rows_with_the_running_maximum(B, H, nb, g, w, r, drop):
+    """Rows by a workgroup whose waves have one to five pairs: every block holds padded keys (a pair's K rows of these are
+    NaN without dropout), and under dropout as well.  LSE is an fp32 sum: 1e-5 of its size."""
+    torch = torch_mod()
+    n = nb * 64
+    t = inp.make_tensors(B, H, n, 64, 900 + nb, "bf16")
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 3)
+    km = np.random.default_rng(nb).integers(0, 2, (B, n)).astype(np.uint8)
+    Q, K, V = device_qkv(t, "bf16")
+    kmd = torch.from_numpy(km).to("cuda:0")
+    rd = torch.from_numpy(ridx).to("cuda:0")
+    kw = dict(g=g, w=w, scale=0.125, key_padding_mask=kmd)
+    args = (t["Q"], t["K"], t["V"], ridx, 64, g, w, 0.125)
+    if drop:
+        O, LSE = bb.bigbird_attn_fwd_dropout(Q, K, V, rd, p_drop=0.25, seed=11, **kw)
+        Oref, Lref = oracle.attn_fwd_dropout(*args, 0.25, 11, key_mask=km)
+    else:
+        K.masked_fill_((kmd == 0)[:, None, :, None], float("nan"))
+        O, LSE = bb.bigbird_attn_fwd(Q, K, V, rd, **kw)
+        Oref, Lref = oracle.attn_fwd(*args, key_mask=km)
+    Oh, Lh = to_host(O), to_host(LSE)
+    fin = np.isfinite(Lref)
+    assert (np.isneginf(Lh) == ~fin).all()
+    assert np.abs(Oh - Oref).max() <= TOL["bf16"]
+    assert (np.abs(Lh[fin] - Lref[fin]) / np.maximum(1.0, np.abs(Lref[fin]))).max() <= 1e-5
+
+
+@pytest.mark.parametrize("B,H,nb,g,w,r", [
     (5, 16, 9, 2, 3, 3),    # four waves: rows of fewer than 16 blocks
     (3, 16, 16, 2, 3, 3),   # eight waves to a workgroup: two blocks of a global row each
     (3, 11, 20, 1, 17, 2),  # non-global rows in two slices
