@@ -210,10 +210,11 @@ inline bool rows_f32_bwd(int BH, int nb) {
   return blocks <= 32 && nb <= 2 * kRowsWavesF32 && (nb <= 12 || blocks > 16);
 }
 // A forward of up to eight blocks cuts no list (it needs no workspace): 3 us for every block in series there, while a
-// round of these workgroups takes 7 to 8 us (12 slices of n = 512: 25.8 and 23.9; 24 of n = 256: 14.8 and 18.4).
+// round of these workgroups takes 7 to 8 us (12 slices of n = 512: 25.8 and 23.9; 24 of n = 256: 14.8 and 18.4).  A single block
+// has nothing to deal out (plain 6.4 and 6.3 us, masked 7.3 and 7.4, masked with dropout 7.5 and 8.0).
 inline bool rows_f32_fwd(int BH, int nb) {
   const long long blocks = static_cast<long long>(BH) * nb;
-  return rows_f32_bwd(BH, nb) || (nb <= kChunkGlobal && blocks <= (nb == 8 ? 96 : nb >= 6 ? 64 : 32));
+  return nb > 1 && (rows_f32_bwd(BH, nb) || (nb <= kChunkGlobal && blocks <= (nb == 8 ? 96 : nb >= 6 ? 64 : 32)));
 }
 
 // This wave's share of a query block's key-block list.

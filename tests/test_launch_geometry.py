@@ -12,6 +12,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include "bwd_kernels.h"
+#include "f32_rows.h"
 #include "fwd_kernels.h"
 #include <cstdio>
 int main() {
@@ -19,12 +20,13 @@ int main() {
   while (scanf("%d %d %d %d %d %d %d", &BH, &nb, &g, &w, &r, &masked, &drop) == 7) {
     const bb::Bf16Geom q = bb::make_bf16_geom(BH, nb, g, w, r, masked != 0);
     const bb::RowSplit s = bb::make_row_split(BH, nb, g, w, r);
-    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
-           q.g_wgs, q.bh_rounds, bb::longest_sparse_list(nb, g, w, r), bb::kListedItems, s.slots_per_bh);
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
+           q.g_wgs, q.bh_rounds, bb::longest_sparse_list(nb, g, w, r), bb::kListedItems, s.slots_per_bh,
+           bb::rows_f32_fwd(BH, nb), bb::rows_f32_bwd(BH, nb));
   }
 }
 """
-FIELDS = "waves by_row sw_len gw_len ng cs n_sitems p_wgs g_wgs bh_rounds sparse listed slots_per_bh".split()
+FIELDS = "waves by_row sw_len gw_len ng cs n_sitems p_wgs g_wgs bh_rounds sparse listed slots_per_bh rows_f32_fwd rows_f32_bwd".split()
 
 
 @pytest.fixture(scope="module")
@@ -106,3 +108,12 @@ def test_global_rows_of_launches_by_rows(geometry, BH, nb, masked, ng, gw_len):
 def test_launches_just_past_those_by_rows(geometry, BH, nb, masked):
     (q,) = geometry([(BH, nb, 2, 3, 3, masked)])
     assert q["by_row"] == (BH == 12) and q["waves"] == 4, q
+
+
+@pytest.mark.parametrize("BH,nb,fwd,bwd", [
+    (1, 1, 0, 1), (32, 1, 0, 1), (2, 2, 1, 1), (4, 8, 1, 1), (5, 8, 1, 0), (12, 8, 1, 0), (13, 8, 0, 0), (10, 6, 1, 0), (11, 6, 0, 0),
+    (3, 9, 1, 1), (1, 12, 1, 1), (1, 13, 0, 0), (2, 16, 1, 1), (3, 11, 0, 0), (1, 17, 0, 0),
+])
+def test_fp32_launches_by_eight_positions(geometry, BH, nb, fwd, bwd):
+    (q,) = geometry([(BH, nb, min(2, nb), 3, 0)])
+    assert (q["rows_f32_fwd"], q["rows_f32_bwd"]) == (fwd, bwd)
