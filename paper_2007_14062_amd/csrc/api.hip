@@ -322,7 +322,7 @@ int attn_bwd_impl(const void* Q, const void* K, const void* V, const void* O,
   } else {  // (never more slots than the workspace is sized for: slices as long or longer)
     const bool masked = key_padding_mask != nullptr;
     p.split = bb::make_row_split(p.BH, p.nb, g, w, r, 0, bb::dq_global_slice(p.BH, p.nb, g, w, r, masked));
-    p.kv = bb::make_key_split(p.nb, g, w, r, 0, bb::dkv_global_slice(p.BH, p.nb, g, w, r, masked));
+    p.kv = bb::make_key_split(p.nb, g, w, r, 0, bb::dkv_global_slice(p.BH, p.nb, g, w, r, masked, drop.thr != 0));
   }
   p.by_row = dtype == BB_BF16 && bb::bwd_by_row(p.BH, p.nb, g, w, r);
   if (p.by_row) {

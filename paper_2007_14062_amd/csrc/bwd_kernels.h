@@ -87,6 +87,12 @@ inline bool dq_two_waves(int BH, const RowSplit& s) {
 // 12 of n = 2048 with four global blocks (528) 63.3 / 67.1, 24 of n = 1536 (672) 57.3 / 58.5, 12 of n = 4096 (936) 67 / 72, 24 (1872) 101.5 / 111.
 inline bool dkv_two_teams(int BH, const KeySplit& s) { return static_cast<long long>(BH) * s.items_per_bh <= 512; }
 
+// Slices of a die whose items alternate in the dK/dV kernels, in groups as equal as they come: as many as have their Q and
+// dO (256 n bytes each) in an L2 together.  With the longest lists of all of them first the bf16 kernel ends sooner (24
+// slices, n = 4096: 43 -> 42 us; 48 padded ones, n = 3072, dropout: 64 -> 60), but two slices of n = 16384 alternating
+// miss the L2 (104 -> 111).
+__host__ __device__ inline int key_slices_together(int n) { return n < 16384 ? 16384 / n : 1; }
+
 // Large bf16 launches: slices of global blocks longer than the standard 8, where the launch is long enough that
 // they still end with the others (the longest items start first).  Every slice costs 16 KB (dQ) or 32 KB (dK/dV) written
 // and read again by the reduction.  The lines lie by the pairs each resident workgroup gets on average: 1024 of the dK/dV
@@ -98,11 +104,18 @@ inline bool dkv_two_teams(int BH, const KeySplit& s) { return static_cast<long l
 // Where slices of a launch are left over and cut into runs (DieItems), longer items make the runs uneven: 12 of n = 12288
 // (22 pairs, slices of 8 / 12 / 16 / 24) 160 / 159 / 158 / 164, 36 of n = 2560 (14) 99.5 / 99.6 / 100.5 / 103.3.  Under a mask
 // lists are shorter than counted: 48 padded ones of n = 3072, dropout (8 / 16 / 24) 139.9 / 138.8 / 144.5.
-inline int dkv_global_slice(int BH, int nb, int g, int w, int r, bool masked) {
+// Under dropout, where a pair takes longest, the last of the groups of slices that are worked on together (key_slices_together)
+// may be smaller than the others, and its long items start late: whole backward, slices of 8 / 12 / 16 / 24, 24 of n = 6464 (groups
+// of 2 and 1 on a die) 150 / 148 / 149 / 166, 24 of n = 5760 144 / 143 / 145 / 151, 40 of n = 4608 (3 and 2) 182 / 177 / 179 / 185; with equal
+// groups 48 of n = 4096 (3 and 3) 196 / 192 / 192 / 192.
+inline int dkv_global_slice(int BH, int nb, int g, int w, int r, bool masked, bool drop) {
   const long long each = most_pairs(BH, nb, g, w, r) / 1024;
   if (each < 14) return kChunk;
   if (BH % kXcd != 0) return 12;
-  return masked ? 16 : each < 32 ? 24 : 32;
+  if (masked) return 16;
+  const int slices = BH / kXcd, together = key_slices_together(nb * kBlk), groups = (slices + together - 1) / together;
+  if (drop && slices % groups != 0) return 12;
+  return each < 32 ? 24 : 32;
 }
 // dQ slices of 8 / 16 (the most a wave lists): 20 pairs: 16 slices of n = 16384  255 / 248, 32 of n = 8192  247 / 246; 15: 48 of
 // n = 4096  187 / 188, 64 of n = 3072  187 / 189; 7: 24 of n = 4096  102 / 106.
@@ -152,13 +165,10 @@ struct KeyItem {
   bool key_global;
 };
 
-// Workgroup id -> item (see decode_item).  False: no such item.  As many slices at
-// a time as have their Q and dO (256 n bytes each) in an L2 together: with the longest lists of all of them
-// first the bf16 kernel ends sooner (24 slices, n = 4096: 43 -> 42 us; 48 padded ones, n = 3072, dropout: 64 -> 60),
-// but two slices of n = 16384 alternating miss the L2 (104 -> 111).
+// Workgroup id -> item (see decode_item).  False: no such item.
 __device__ __forceinline__ bool decode_key_item(const BwdParams& p, const Pattern& pat, unsigned wg, KeyItem* it) {
   int item;
-  if (!DieItems(p.BH, p.kv.items_per_bh).decode(wg, &it->bh, &item, p.n < 16384 ? 16384 / p.n : 1)) return false;
+  if (!DieItems(p.BH, p.kv.items_per_bh).decode(wg, &it->bh, &item, key_slices_together(p.n))) return false;
   const int nglob = p.g * p.kv.cg;
   it->key_global = item < nglob;
   if (it->key_global) {

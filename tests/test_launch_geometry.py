@@ -20,13 +20,14 @@ int main() {
   while (scanf("%d %d %d %d %d %d %d", &BH, &nb, &g, &w, &r, &masked, &drop) == 7) {
     const bb::Bf16Geom q = bb::make_bf16_geom(BH, nb, g, w, r, masked != 0);
     const bb::RowSplit s = bb::make_row_split(BH, nb, g, w, r);
-    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
            q.g_wgs, q.bh_rounds, bb::longest_sparse_list(nb, g, w, r), bb::kListedItems, s.slots_per_bh,
-           bb::rows_f32_fwd(BH, nb), bb::rows_f32_bwd(BH, nb));
+           bb::rows_f32_fwd(BH, nb), bb::rows_f32_bwd(BH, nb), bb::dkv_global_slice(BH, nb, g, w, r, masked != 0, drop != 0),
+           bb::dq_global_slice(BH, nb, g, w, r, masked != 0), bb::make_key_split(nb, g, w, r, 0, 8).slots_per_bh);
   }
 }
 """
-FIELDS = "waves by_row sw_len gw_len ng cs n_sitems p_wgs g_wgs bh_rounds sparse listed slots_per_bh rows_f32_fwd rows_f32_bwd".split()
+FIELDS = "waves by_row sw_len gw_len ng cs n_sitems p_wgs g_wgs bh_rounds sparse listed slots_per_bh rows_f32_fwd rows_f32_bwd dkv_slice dq_slice kv_slots_per_bh".split()
 
 
 @pytest.fixture(scope="module")
@@ -75,6 +76,10 @@ def test_every_block_has_a_wave_and_every_list_a_place(geometry):
             assert q["p_wgs"] * q["waves"] * q["listed"] >= q["bh_rounds"] * q["n_sitems"], (c, q)
         slots = (g * q["ng"] if q["ng"] > 1 else 0) + ((nb - g) * q["cs"] if q["cs"] > 1 else 0)
         assert slots <= q["slots_per_bh"], (c, q)
+        # backward: slices of global blocks as long as the standard 8 or longer, a query block's in a list of 16
+        assert q["dkv_slice"] >= 8 and 8 <= q["dq_slice"] <= 16, (c, q)
+        cut = -(-nb // q["dkv_slice"])
+        assert (g * cut if cut > 1 else 0) <= q["kv_slots_per_bh"], (c, q)
 
 
 @pytest.mark.parametrize("BH,nb,waves", [
@@ -117,3 +122,13 @@ def test_launches_just_past_those_by_rows(geometry, BH, nb, masked):
 def test_fp32_launches_by_eight_positions(geometry, BH, nb, fwd, bwd):
     (q,) = geometry([(BH, nb, min(2, nb), 3, 0)])
     assert (q["rows_f32_fwd"], q["rows_f32_bwd"]) == (fwd, bwd)
+
+
+@pytest.mark.parametrize("BH,nb,masked,drop,dkv", [
+    (24, 101, 0, 1, 12), (24, 90, 0, 1, 12), (24, 128, 0, 1, 12), (40, 72, 0, 1, 12),  # under dropout, a smaller last group
+    (48, 64, 0, 1, 24), (48, 48, 0, 1, 24), (24, 64, 0, 1, 24), (16, 256, 0, 1, 32),   # equal groups, or one
+    (24, 101, 0, 0, 24), (24, 101, 1, 1, 16), (24, 101, 1, 0, 16), (20, 128, 0, 1, 12), (20, 128, 0, 0, 12), (24, 48, 0, 0, 8),
+])
+def test_slices_of_global_key_blocks(geometry, BH, nb, masked, drop, dkv):
+    (q,) = geometry([(BH, nb, 2, 3, 3, masked, drop)])
+    assert q["dkv_slice"] == dkv
