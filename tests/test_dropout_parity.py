@@ -96,6 +96,17 @@ def test_long_rows_and_wide_patterns_bf16():
         check(t, ridx, 64, g, w, 0.125, 0.5, 43, "bf16", tag=f"dropout wide pattern H{H}")
 
 
+def test_streams_of_several_items_bf16():
+    """Forward: three whole rows for each wave, one after the other, with cut blocks in the lists of two batch entries."""
+    B, H, n = 3, 100, 768
+    t = inp.make_tensors(B, H, n, 64, 306, "bf16", with_dO=True)
+    ridx = bb.bigbird_make_rand_idx(H, n, 64, 2, 3, 3, 12)
+    km = np.ones((B, n), dtype=np.uint8)
+    km[1, n - 127:] = 0
+    km[2] = np.random.default_rng(6).integers(0, 2, n)
+    check(t, ridx, 64, 2, 3, 0.125, 0.25, 21, "bf16", key_mask=km, tag="dropout streams", backward=False)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_rate_zero_is_the_plain_call_bit_for_bit(dtype):
     torch = torch_mod()

@@ -180,12 +180,16 @@ def test_blocks_with_padded_keys_inside(tail, mode, g, r, H):
     assert err_o <= TOL["bf16"] and err_l <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("H,nb,g,w,r", [(2, 9, 2, 3, 3), (40, 9, 1, 3, 0), (40, 10, 2, 5, 3), (24, 20, 1, 15, 4)])
+@pytest.mark.parametrize("H,nb,g,w,r", [
+    (2, 9, 2, 3, 3), (40, 9, 1, 3, 0), (40, 10, 2, 5, 3),  # rows by a workgroup; an item for each wave
+    (24, 20, 1, 15, 4),                                    # two slices to a row, one or two for each wave
+    (100, 12, 2, 3, 3),                                    # whole rows, three for each wave: from either kind to either kind
+])
 @pytest.mark.parametrize("skip", [False, True])
 @pytest.mark.parametrize("gain", [1.0, 40.0])
 def test_running_maximum_in_the_streams(H, nb, g, w, r, skip, gain):
-    """bf16: items with and without padded keys inside a block side by side in a wave's stream (rows by a workgroup
-    at H = 2), lists of one block up to two slices of 16; blocks whose first or second 32 keys, or all but one, are
+    """bf16: items with and without padded keys inside a block, side by side in a wave's stream at the last shape (its batch
+    entry 1), lists of one block up to two slices of 16; blocks whose first or second 32 keys, or all but one, are
     padded.  LSE is an fp32 sum there: 1e-5 of its size, where rounding the probabilities first would give 2^-9."""
     torch = torch_mod()
     B, n = 3, nb * 64

@@ -132,3 +132,15 @@ def test_fp32_launches_by_eight_positions(geometry, BH, nb, fwd, bwd):
 def test_slices_of_global_key_blocks(geometry, BH, nb, masked, drop, dkv):
     (q,) = geometry([(BH, nb, 2, 3, 3, masked, drop)])
     assert q["dkv_slice"] == dkv
+
+
+@pytest.mark.parametrize("BH,nb,masked,items", [
+    (300, 12, 1, 2.5),       # the GPU tests of streams with several items to a wave
+    (520, 256, 1, 62),       # and of lists that are full
+])
+def test_items_of_a_wave(geometry, BH, nb, masked, items):
+    g = 2 if nb == 12 else 1
+    (q,) = geometry([(BH, nb, g, 3 if nb == 12 else 1, 3 if nb == 12 else 0, masked)])
+    assert not q["by_row"] and q["cs"] == 1 and q["waves"] == 4
+    resident = min(q["p_wgs"], 64) * q["waves"]
+    assert q["bh_rounds"] * q["n_sitems"] / resident > items, q
