@@ -30,7 +30,7 @@ pytestmark = pytest.mark.gpu
     (2, 1, 16, 4, 13, 0),   # of all 16, no random blocks
     (1, 3, 11, 2, 3, 3),    # 33 blocks
 ])
-@pytest.mark.parametrize("case", ["plain", "padded", "skip", "drop"])
+@pytest.mark.parametrize("case", ["plain", "padded", "skip", "drop", "drop padded"])
 def test_parity(B, H, nb, g, w, r, case):
     n = nb * 64
     rng = np.random.default_rng(nb * 100 + H)
@@ -43,7 +43,9 @@ def test_parity(B, H, nb, g, w, r, case):
     km = np.ones((B, n), dtype=np.uint8)
     km[0, n - n // 3 - 5:] = 0                      # ends inside a block; whole blocks after it
     km[B - 1, 7:7 + int(rng.integers(1, 50))] = 0   # a hole in the first block
-    if case == "skip":
+    if case == "drop padded":
+        test_dropout_parity.check(t, ridx, 64, g, w, 0.125, 0.25, 11, "f32", key_mask=km, tag=tag)
+    elif case == "skip":
         test_skip_parity.check(t, ridx, 64, g, w, 0.125, "f32", km, tag=tag)
     else:
         test_dropout_parity.check(t, ridx, 64, g, w, 0.125, 0.0, 11, "f32", key_mask=km, tag=tag)
