@@ -129,7 +129,10 @@ size_t bigbird_attn_workspace_bytes(int B, int H, int n, int d, int b, int g, in
  *           ignored; duplicates of window / global / earlier entries are dropped;
  * key_padding_mask  NULL, or device [B][n] bytes, non-zero = valid key.  Padded
  *           keys are removed for every query (global rows too); padded queries are
- *           still computed; a row with no valid key gives O = 0, LSE = -inf.
+ *           still computed; a row with no valid key gives O = 0, LSE = -inf.  K rows of
+ *           padded keys may hold anything here; their V rows, and in the backward call
+ *           their K rows as well, must be finite where the block has a valid key (they are
+ *           multiplied by 0).
  * Pointers must be 16-byte aligned.
  */
 int bigbird_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
@@ -198,9 +201,9 @@ int bigbird_attn_bwd(const void* Q, const void* K, const void* V, const void* O,
  * else); p_drop == 0 is the plain call, bit for bit.  Use a new seed for every step and layer.
  *
  * bigbird_attn_fwd_dropout: arguments, checks and outputs of bigbird_attn_fwd, plus p_drop and
- * seed.  The bf16 path takes every row by the running-maximum recurrence, where the mask is applied, not
- * by the pipelined form of the plain call: expect half to two thirds of its throughput.  (Rows that attend
- * a block with padded keys inside go that way in bigbird_attn_fwd too.)
+ * seed.  The bf16 path takes every row with a running maximum, not against the fixed reference of the plain call:
+ * expect half to two thirds of its throughput.  (Rows that attend a block with padded keys inside go
+ * that way in bigbird_attn_fwd too.)
  */
 int bigbird_attn_fwd_dropout(const void* Q, const void* K, const void* V, void* O, float* LSE,
                              const int32_t* rand_idx, const uint8_t* key_padding_mask,

@@ -254,7 +254,7 @@ __global__ __launch_bounds__(kThreadsF32) __attribute__((amdgpu_waves_per_eu(2))
   if (qh == 1) return;
   take_over(lds_q + kh * (32 * 64), lane, dk);
   take_over(lds_do + kh * (32 * 64), lane, dv);
-  // gradients of a padded key are exactly 0 (selected, not multiplied: its K row may hold anything)
+  // gradients of a padded key are exactly 0 (selected, not multiplied: what was summed for it may be anything)
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kRowsThreadsF32) __attribute__((amdgpu_waves_per_eu
           dp[q] = ((key & 1u) ? drop_keep_odd(wd, p.drop.thr) : drop_keep_even(wd, p.drop.thr)) ? dp[q] * p.drop.rs : 0.f;
         }
         const float ds = fast_exp2(__builtin_fmaf(s[q], c, -lse2[q])) * (dp[q] - dsum[q]);
-        s[q] = valid ? ds : 0.f;  // (selected: the K row of a padded key may hold anything)
+        s[q] = valid ? ds : 0.f;  // (its K row is multiplied by this 0 below, and has to be finite)
       }
       qforms.column_form(quarter[0], x);
       add_rows(x, s, dq);
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(kRowsThreadsF32) __attribute__((amdgpu_waves_per_eu
     a += dk_of(v)[wv][lane];
     b += dv_of(v)[wv][lane];
   }
-  // gradients of a padded key are exactly 0 (selected, not multiplied: its K row may hold anything)
+  // gradients of a padded key are exactly 0 (selected, not multiplied: what was summed for it may be anything)
   p.dK[(key0 + wv) * kDim + lane] = key_valid ? a * p.scale : 0.f;
   p.dV[(key0 + wv) * kDim + lane] = key_valid ? b : 0.f;
 }

@@ -734,7 +734,7 @@ void bwd_dkv_kernel(BwdParams p) {
   wait_tile_loads<0>();  // requests past the end of the list (with an empty one: K and V)
   __syncthreads();       // nobody reads the ring any more
 
-  // gradients of a padded key are exactly 0 (selected, not multiplied: its K row may hold anything); turned
+  // gradients of a padded key are exactly 0 (selected, not multiplied: what was summed for it may be anything); turned
   // through LDS so that memory sees whole rows: this wave's 32 rows of dK, then of dV, d 0 .. 31 and 32 .. 63
   const bool key_valid = (vbits >> (wv * 32 + col)) & 1;
   const float vscale = kDrop ? p.drop.rs : 1.f;

@@ -154,9 +154,9 @@ __device__ __forceinline__ void read_transposed_half(const TransposedOffsets& to
     for (int sgl = 0; sgl < 2; ++sgl) f[dt][sgl] = to.read_one(tile, dt, 2 * t + sgl);
 }
 
-// Padded keys of a unit (32 keys x 32 queries, a lane per query) leave its packed probabilities, or dS
-// values, here: after the conversion and before a product sees them (they may be anything, also not a
-// number).  bits: validity of the 32 keys of the unit, in key order.  Element kk of operand sgl belongs to key
+// Padded keys of a unit (32 keys x 32 queries, a lane per query) leave its packed dS values here: after the
+// conversion and before the product with K, whose rows have to be finite, sees them (the values may be anything, also
+// not a number).  bits: validity of the 32 keys of the unit, in key order.  Element kk of operand sgl belongs to key
 // 16 sgl + 8 (kk / 4) + 4 hf + kk % 4 (acc_row).  Three instructions per packed pair on the vector port --
 // only block pairs with padded keys inside pay them: the others take one scalar branch per unit.
 __device__ __forceinline__ void drop_padded_keys(uint32_t bits, int hf, bf16x8 (&pb)[2]) {
