@@ -1424,8 +1424,9 @@ void fwd_kernel_bf16(FwdParams p) {
         const TileStreams ts(p, cur, t_nxt >= 0 ? &nxt : nullptr, lane_again(lane));
         half_load_async(ts.k(1), cx.lds_k_a, 0, cx.voff);
         // V(0).t0.  Behind it are V(0).t1, K(1).t0 and the eight 16-byte stores (at least) of rows just written, which
-        // it need not wait for (infer of 48 slices, n = 4096: 41.0 -> 40.6 us)
-        if (rows_written)
+        // it need not wait for (48 slices of n = 3072 31.5 -> 31.2 us, of n = 4096 40.3 -> 40.2; with a mask, where the list builder
+        // has waited for them, the branch only costs: 33.0 -> 32.8, all keys valid)
+        if (kMode == kPlain && rows_written)
           wait_tile_loads<16>();
         else
           wait_tile_loads<8>();
