@@ -54,28 +54,41 @@ inline Bf16Geom make_bf16_geom(int BH, int nb, int g, int w, int r, bool masked)
   q.ng = cut(nb, 4 * q.gw_len);
   // With a workgroup for every row, up to 11 blocks per wave in one workgroup cost less than the merge launch (us, one workgroup
   // to a global row and two: 4 slices of n = 2560 11.9 and 13.8, dropout 22.8 and 22.6; n = 3200 14.4 and 14.1, 28.1 and 22.7).  Under a mask
-  // the blocks that are left may all be the first wave's (4 of n = 3200, half of it padded, 21.1 and 14.5).
-  const int row_ng = masked || nb > 44 ? q.ng : 1;
+  // the blocks that are left may all be the first wave's (4 of n = 3200, half of it padded, 21.1 and 14.5).  Where lists are long and
+  // only one workgroup to a global row leaves room for one to every row, dealing them out wins (6 of n = 3072, lists of 16: 16.4 and
+  // 21.9, dropout 29.1 and 39.6; 5 of n = 3200 with room for either 15.4 and 18.9, 28.5 and 28.8).
+  auto all_rows = [&](int ng) { return static_cast<long long>(BH) * (g * ng + nb - g) <= 288 && sparse_ub <= 4 * kGlobalWaveLen; };
+  const bool whole_rows = (!masked && nb <= (sparse_ub > 12 ? 52 : 44)) || (sparse_ub > 12 && nb <= 4 * kGlobalWaveLen && !all_rows(q.ng));
+  const int row_ng = whole_rows ? 1 : q.ng;
+  // Eight waves to a workgroup, where every workgroup is resident at once (a die has 32 CUs of eight waves) and the longest
+  // wave sets the run time: a global row's list is then dealt out to eight waves, up to 64 blocks without a merge launch.  us of
+  // four waves (16 blocks of a global row each; from 33 blocks on 8, several workgroups to a row and a merge launch) and what eight take
+  // of that, plain / dropout, by the lists of the other rows (lists of 4, 8, 12 and 16 blocks):
+  //   n = 1024 .. 2048, wgs(4) <= 32 (one wave to a SIMD)  16 / 34 us: 0.73 / 0.57, 1.03 / 0.91, 1.31 / 1.22, 1.45 / 1.44; 7 blocks 0.95 / 0.82
+  //   n = 1024 .. 2048, past that                          18 .. 25 / 35 .. 50 us: 0.66 / 0.55, 0.84 / 0.76, 0.95 / 0.92, 1.05 / 1.05
+  //     (just past it, 36 slices of n = 1280, wgs(4) = 33: 1.02 / 0.90 with 8 blocks, 1.24 / 1.15 with 11, 1.30 / 1.22 with 12)
+  //   n = 2304 .. 4096, wgs(4) <= 32                       14 .. 21 / 23 .. 40 us: 0.88 .. 1.13 / 0.95 .. 1.3, 1.09 / 1.23, 1.17 / 1.29, 1.22 / 1.33
+  //   n = 2304 .. 4096, past that                          15 .. 36 / 24 .. 59 us: 0.74 .. 0.97 / 0.79 .. 1.1, 0.83 / 0.9, 0.84 .. 0.97 / 0.92 .. 1.09,
+  //     0.98 .. 1.02 / 1.2 up to wgs(4) = 48 and 0.85 .. 0.95 / 0.91 .. 1.15 from 54 on
+  //   n > 4096 (a merge launch with either): 1.10 .. 1.16 / 1.25, 0.98 / 1.0, 0.96 .. 1.06 / 1.0 .. 1.15, and 1.0 .. 1.25 under a mask
+  // Past wgs(8) = 32 the global rows wait for each other (64 slices of n = 1280, 34: 22.7 and 31.9 us).  Rows below 16 blocks are
+  // dealt out in quarters to four waves, and eighths gain nothing (64 of n = 896 16.0 / 25.6 and 17.9 / 31.0 us, 48 of n = 960
+  // 12.4 / 22.0 and 17.3 / 30.9).  Under a mask short lists come out shorter, and fill four waves less (7 blocks 0.7 .. 1.3).
+  auto eight_waves = [&](int wgs4, int wgs8) {
+    if (g == 0 || nb < kGlobalWaveLen || wgs8 > 32) return false;
+    if (nb > 8 * kHalfLen) return !masked && sparse_ub >= 8 && sparse_ub <= 12 && wgs4 > 44;
+    if (sparse_ub > 12) return nb > 4 * kHalfLen && wgs4 > 52;
+    return wgs4 > (sparse_ub > 8 ? 33 : 32) || (nb <= 4 * kHalfLen && sparse_ub <= (masked ? 5 : 7));
+  };
   // the workgroups a die gets with half as many blocks per wave, as they are launched: the items of its slices together
   auto wgs = [&](int waves) { return q.bh_rounds * g * cut(nb, waves * kHalfLen) + cut(q.bh_rounds * q.n_sitems, waves); };
-  if (static_cast<long long>(BH) * (g * row_ng + nb - g) <= 288 && sparse_ub <= 4 * kGlobalWaveLen) {
+  if (all_rows(row_ng)) {
     // Small launches, about a workgroup per CU: all rows that way, the key list of each dealt out to four
     // waves.  12 heads, n = 512 / 1024 / 1536: 12.2 -> 7.2, 12.4 -> 8.7, 12.5 -> 11.9 us; past that CUs have
     // two such workgroups and single waves with whole rows win (n = 2048, 384 rows: 12.7 against 17.5).
     q.by_row = 1;
     q.ng = row_ng;
-  } else if (nb >= kGlobalWaveLen && wgs(8) <= 32 && wgs(4) > 32) {
-    // Every workgroup resident at once (a die has 32 CUs of eight waves), more than one to a CU: the longest wave sets the
-    // run time, so a global row's list is dealt out to eight waves, up to 64 blocks without a merge launch.  us,
-    // four waves (16 blocks each; from 33 blocks on 8, several workgroups to a row and a merge launch) against eight, plain /
-    // padded / dropout:
-    //   wgs(4) = 33: 48 slices of n = 1024  20.4 / 23.0 / 40.8 and 17.1 / 21.8 / 31.4, 36 of n = 1280  16.6 / 21.6 / 34.4, 17.0 / 24.3 / 31.1
-    //   wgs(8) = 32: 36 of n = 2304  23.9 / 27.7 / 43.2 and 20.4 / 22.8 / 32.5, 48 of n = 1792  23.6 / 29.7 / 43.3, 20.4 / 23.3 / 33.1
-    //   24 of n = 4096  26.2 / 25.9 / 37.5 and 22.2 / 25.8 / 34.8, 12 of n = 4096  21.5 / 22.1 / 33.7, 17.8 / 23.5 / 31.2
-    // At a workgroup of four to a CU each wave has a SIMD, and eight waves share theirs while other CUs idle (wgs(4) = 32: 48 of
-    // n = 960 12.4 and 17.3, dropout 22.0 and 30.9); past the upper line the global rows wait for each other (wgs(8) = 34: 64
-    // of n = 1280 22.7 and 31.9, 35: 28 of n = 3584 27.7 and 35.1).  Rows below 16 blocks are dealt out in quarters to four waves, and
-    // eighths gain nothing there (64 of n = 896 16.0 / 19.0 / 25.6 and 17.9 / 22.1 / 31.0).
+  } else if (eight_waves(wgs(4), wgs(8))) {
     q.waves = 8;
     q.gw_len = kHalfLen;
     q.ng = cut(nb, 8 * kHalfLen);

@@ -277,8 +277,11 @@ def test_short_rows_with_the_running_maximum(B, H, nb, g, w, r, drop):
 @pytest.mark.parametrize("B,H,nb,g,w,r", [
     (5, 16, 9, 2, 3, 3),    # four waves: rows of fewer than 16 blocks
     (3, 16, 16, 2, 3, 3),   # eight waves to a workgroup: two blocks of a global row each
-    (3, 11, 20, 1, 17, 2),  # non-global rows in two slices
-    (1, 9, 66, 2, 3, 3),    # global rows by two workgroups of eight waves
+    (4, 7, 16, 1, 3, 0),    # the same with short lists, a wave to a SIMD if there were four
+    (3, 11, 20, 1, 17, 2),  # four waves: non-global rows in two slices
+    (2, 10, 48, 4, 9, 3),   # eight: lists of a whole slice of 16
+    (1, 10, 80, 2, 3, 3),   # global rows by two workgroups of eight waves
+    (1, 9, 66, 2, 3, 3),    # by three of four
     (4, 8, 32, 2, 3, 3),
     (5, 8, 33, 2, 3, 3),    # 30 workgroups of eight waves to a die
     (6, 6, 36, 2, 3, 3),    # 32

@@ -85,10 +85,11 @@ def test_every_block_has_a_wave_and_every_list_a_place(geometry):
 @pytest.mark.parametrize("BH,nb,waves", [
     (48, 15, 4), (56, 12, 4), (72, 8, 4),                # a workgroup of four waves to a compute unit
     (64, 12, 4), (72, 10, 4), (56, 15, 4), (64, 15, 4),  # global rows of fewer than 16 blocks
-    (48, 16, 8), (64, 16, 8), (36, 20, 8), (24, 64, 8), (12, 64, 8), (40, 33, 8),
+    (44, 16, 8), (48, 16, 8), (64, 16, 8), (36, 20, 8), (24, 64, 8), (12, 64, 8), (40, 33, 8),
     (36, 36, 8), (48, 28, 8),                            # 32 workgroups of eight waves to a die: every unit has one
     (64, 20, 4), (48, 33, 4), (48, 64, 4), (8, 64, 4),   # past that; too few
-    (80, 9, 4), (9, 66, 8), (32, 32, 8), (44, 16, 8),    # (with the ones above: what the GPU tests of medium launches run)
+    (80, 9, 4), (32, 32, 8), (36, 36, 8),                # (with the ones above: what the GPU tests of medium launches run)
+    (10, 80, 8), (9, 66, 4),                             # longer than 64 blocks: 51 and 44 workgroups of four waves
 ])
 def test_workgroups_of_eight_waves(geometry, BH, nb, waves):
     """The count that decides is the one that is launched: the items of a die's slices together, not slice by slice."""
@@ -96,6 +97,21 @@ def test_workgroups_of_eight_waves(geometry, BH, nb, waves):
     assert q["waves"] == waves and not q["by_row"]
     if waves == 8:
         assert q["bh_rounds"] * q["g_wgs"] + q["p_wgs"] <= 32
+
+
+@pytest.mark.parametrize("BH,nb,g,w,r,masked,waves", [
+    (28, 16, 1, 3, 0, 0, 8), (28, 16, 1, 3, 0, 1, 8),    # lists of 4: also with a wave to a SIMD
+    (28, 20, 1, 3, 3, 0, 8), (28, 20, 1, 3, 3, 1, 4),    # of 7: not under a mask
+    (28, 20, 2, 3, 3, 0, 4), (28, 48, 1, 3, 0, 0, 8), (10, 36, 1, 3, 0, 0, 4),
+    (36, 20, 2, 1, 8, 0, 4), (44, 20, 2, 1, 8, 0, 8),    # of 11
+    (36, 24, 4, 9, 3, 0, 4), (20, 48, 4, 9, 3, 0, 8), (10, 48, 4, 9, 3, 0, 4),  # of 16
+    (10, 80, 2, 3, 3, 1, 4), (10, 80, 1, 3, 0, 0, 4),    # longer than 64 blocks: under a mask, short lists
+    (64, 24, 0, 3, 3, 0, 4),                             # no global rows
+    (33, 20, 1, 17, 2, 0, 4), (20, 56, 4, 9, 5, 0, 4),   # two slices to a row
+])
+def test_workgroups_of_eight_waves_by_lists(geometry, BH, nb, g, w, r, masked, waves):
+    (q,) = geometry([(BH, nb, g, w, r, masked)])
+    assert q["waves"] == waves and not q["by_row"], q
 
 
 @pytest.mark.parametrize("BH,nb,masked,ng,gw_len", [
@@ -109,10 +125,15 @@ def test_global_rows_of_launches_by_rows(geometry, BH, nb, masked, ng, gw_len):
     assert q["by_row"] and (q["ng"], q["gw_len"]) == (ng, gw_len), q
 
 
-@pytest.mark.parametrize("BH,nb,masked", [(5, 56, 0), (8, 35, 1), (7, 40, 1), (12, 24, 0)])
-def test_launches_just_past_those_by_rows(geometry, BH, nb, masked):
-    (q,) = geometry([(BH, nb, 2, 3, 3, masked)])
-    assert q["by_row"] == (BH == 12) and q["waves"] == 4, q
+@pytest.mark.parametrize("BH,nb,masked,wide,by_row", [
+    (5, 56, 0, 0, 0), (8, 35, 1, 0, 0), (7, 40, 1, 0, 0), (12, 24, 0, 0, 1),
+    (6, 48, 0, 1, 1), (6, 48, 1, 1, 1), (6, 49, 0, 1, 0), (4, 48, 0, 1, 1),  # lists of a whole slice
+])
+def test_launches_just_past_those_by_rows(geometry, BH, nb, masked, wide, by_row):
+    (q,) = geometry([(BH, nb, 4, 9, 3, masked) if wide else (BH, nb, 2, 3, 3, masked)])
+    assert q["by_row"] == by_row and q["waves"] == 4, q
+    if by_row and wide:
+        assert (q["ng"], q["gw_len"]) == ((1, 12) if BH == 6 else (2, 8)), q
 
 
 @pytest.mark.parametrize("BH,nb,fwd,bwd", [
