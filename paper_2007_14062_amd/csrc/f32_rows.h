@@ -210,11 +210,17 @@ inline bool rows_f32_bwd(int BH, int nb) {
   return blocks <= 32 && nb <= 2 * kRowsWavesF32 && (nb <= 12 || blocks > 16);
 }
 // A forward of up to eight blocks cuts no list (it needs no workspace): 3 us for every block in series there, while a
-// round of these workgroups takes 7 to 8 us (12 slices of n = 512: 25.8 and 23.9; 24 of n = 256: 14.8 and 18.4).  A single block
-// has nothing to deal out (plain 6.4 and 6.3 us, masked 7.3 and 7.4, masked with dropout 7.5 and 8.0).
-inline bool rows_f32_fwd(int BH, int nb) {
+// round of these workgroups takes 7 to 8 us (12 slices of n = 512: 25.8 and 23.9; 24 of n = 256: 14.8 and 18.4).  What counts
+// is the longest list there is: without global blocks n = 512 has lists of 6 (12 slices: 20.5 and 23.5).  A single block has
+// nothing to deal out (plain 6.4 and 6.2 us, masked 7.3 and 7.4, masked with dropout 7.5 and 8.0).  Past eight blocks the other
+// kernel cuts lists for several waves, and here one wave's share is two entries, which take longest under dropout (one slice
+// of n = 640, one global block: 11.0 and 11.5, dropout 11.5 and 12.9; two of n = 768, dropout: 12.6 and 13.1, n = 1024: 16.4 and 13.3).
+inline bool rows_f32_fwd(int BH, int nb, int g, int w, int r, bool drop) {
   const long long blocks = static_cast<long long>(BH) * nb;
-  return nb > 1 && (rows_f32_bwd(BH, nb) || (nb <= kChunkGlobal && blocks <= (nb == 8 ? 96 : nb >= 6 ? 64 : 32)));
+  const int longest = g > 0 ? nb : longest_sparse_list(nb, g, w, r);
+  if (nb == 1) return !drop && blocks <= 32;
+  if (longest > kRowsWavesF32 + 1 && blocks <= (drop ? 30 : 12)) return false;
+  return rows_f32_bwd(BH, nb) || (nb <= kChunkGlobal && blocks <= (longest == 8 ? 96 : longest >= 6 ? 64 : 32));
 }
 
 // This wave's share of a query block's key-block list.
