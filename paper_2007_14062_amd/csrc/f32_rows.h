@@ -211,16 +211,17 @@ inline bool rows_f32_bwd(int BH, int nb) {
 }
 // A forward of up to eight blocks cuts no list (it needs no workspace): 3 us for every block in series there, while a
 // round of these workgroups takes 7 to 8 us (12 slices of n = 512: 25.8 and 23.9; 24 of n = 256: 14.8 and 18.4).  What counts
-// is the longest list there is: without global blocks n = 512 has lists of 6 (12 slices: 20.5 and 23.5).  A single block has
-// nothing to deal out (plain 6.4 and 6.2 us, masked 7.3 and 7.4, masked with dropout 7.5 and 8.0).  Past eight blocks the other
-// kernel cuts lists for several waves, and here one wave's share is two entries, which take longest under dropout (one slice
-// of n = 640, one global block: 11.0 and 11.5, dropout 11.5 and 12.9; two of n = 768, dropout: 12.6 and 13.1, n = 1024: 16.4 and 13.3).
-inline bool rows_f32_fwd(int BH, int nb, int g, int w, int r, bool drop) {
+// is the longest list there is: without global blocks n = 512 has lists of 6 (12 slices: 20.5 and 23.5), and under a mask
+// they may be shorter (12 of n = 512, padded: 24.8 and 26.4).  A single block has nothing to deal out (plain 6.4 and 6.2 us,
+// masked 7.3 and 7.4, masked with dropout 7.5 and 8.0).  Past eight blocks the other kernel cuts lists for several waves, and
+// here a wave's share is two entries, which take longest under dropout (one slice of n = 640: 11.7 and 12.9, without dropout 11.5
+// and 11.5, padded 12.1 and 9.4; two of n = 768, dropout: 12.6 and 13.1, n = 1024: 16.4 and 13.3).
+inline bool rows_f32_fwd(int BH, int nb, int g, int w, int r, bool masked, bool drop) {
   const long long blocks = static_cast<long long>(BH) * nb;
   const int longest = g > 0 ? nb : longest_sparse_list(nb, g, w, r);
   if (nb == 1) return !drop && blocks <= 32;
-  if (longest > kRowsWavesF32 + 1 && blocks <= (drop ? 30 : 12)) return false;
-  return rows_f32_bwd(BH, nb) || (nb <= kChunkGlobal && blocks <= (longest == 8 ? 96 : longest >= 6 ? 64 : 32));
+  if (drop && !masked && longest > kRowsWavesF32 + 1 && blocks <= 30) return false;
+  return rows_f32_bwd(BH, nb) || (nb <= kChunkGlobal && blocks <= (longest == 8 && !masked ? 96 : longest >= 6 ? 64 : 32));
 }
 
 // This wave's share of a query block's key-block list.

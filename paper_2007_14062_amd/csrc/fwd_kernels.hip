@@ -406,7 +406,7 @@ int launch_fwd(const FwdParams& p, bool bf16, hipStream_t stream) {
   if (bf16) {
     const int st = launch_fwd_bf16_main(p, stream);
     if (st != BB_OK) return st;
-  } else if (rows_f32_fwd(p.BH, p.nb, p.g, p.w, p.r, p.drop.thr != 0)) {
+  } else if (rows_f32_fwd(p.BH, p.nb, p.g, p.w, p.r, p.kmask != nullptr, p.drop.thr != 0)) {
     hipLaunchKernelGGL(fwd_rows_f32, dim3(own_grid(p.BH, p.nb)), dim3(kRowsThreadsF32), 0, stream, p);
     return launch_failed("fwd_rows_f32") ? BB_ERR_LAUNCH : BB_OK;
   } else {

@@ -20,6 +20,9 @@ pytestmark = pytest.mark.gpu
     (1, 5, 8, 2, 3, 3),     # past it: forward alone
     (1, 12, 8, 2, 3, 2),    # last forward
     (1, 13, 8, 1, 3, 2),    # past it
+    (1, 8, 8, 0, 3, 3),     # lists of 6, no global block: last forward
+    (1, 12, 8, 0, 3, 2),    # of 5: past it
+    (2, 1, 10, 1, 3, 3),    # 20 blocks, lists of 10: past it under dropout
     (1, 10, 6, 1, 3, 1),    # 60 blocks of 6: forward alone
     (1, 3, 9, 2, 3, 3),     # two entries for wave 0 of a global block
     (2, 1, 12, 0, 5, 4),    # no global block

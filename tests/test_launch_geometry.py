@@ -22,7 +22,7 @@ int main() {
     const bb::RowSplit s = bb::make_row_split(BH, nb, g, w, r);
     printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
            q.g_wgs, q.bh_rounds, bb::longest_sparse_list(nb, g, w, r), bb::kListedItems, s.slots_per_bh,
-           bb::rows_f32_fwd(BH, nb, g, w, r, drop != 0), bb::rows_f32_bwd(BH, nb), bb::dkv_global_slice(BH, nb, g, w, r, masked != 0, drop != 0),
+           bb::rows_f32_fwd(BH, nb, g, w, r, masked != 0, drop != 0), bb::rows_f32_bwd(BH, nb), bb::dkv_global_slice(BH, nb, g, w, r, masked != 0, drop != 0),
            bb::dq_global_slice(BH, nb, g, w, r, masked != 0), bb::make_key_split(nb, g, w, r, 0, 8).slots_per_bh);
   }
 }
@@ -138,21 +138,22 @@ def test_launches_just_past_those_by_rows(geometry, BH, nb, masked, wide, by_row
 
 @pytest.mark.parametrize("BH,nb,fwd,bwd", [
     (1, 1, 1, 1), (32, 1, 1, 1), (33, 1, 0, 0), (2, 2, 1, 1), (4, 8, 1, 1), (5, 8, 1, 0), (12, 8, 1, 0), (13, 8, 0, 0), (10, 6, 1, 0), (11, 6, 0, 0),
-    (3, 9, 1, 1), (2, 12, 1, 1), (1, 12, 0, 1), (1, 10, 0, 1), (1, 9, 1, 1), (1, 13, 0, 0), (2, 16, 1, 1), (3, 11, 0, 0), (1, 17, 0, 0),
+    (3, 9, 1, 1), (1, 12, 1, 1), (1, 13, 0, 0), (2, 16, 1, 1), (3, 11, 0, 0), (1, 17, 0, 0),
 ])
 def test_fp32_launches_by_eight_positions(geometry, BH, nb, fwd, bwd):
     (q,) = geometry([(BH, nb, min(2, nb), 3, 0)])
     assert (q["rows_f32_fwd"], q["rows_f32_bwd"]) == (fwd, bwd)
 
 
-@pytest.mark.parametrize("BH,nb,g,r,drop,fwd", [
-    (12, 8, 0, 2, 0, 0), (12, 8, 1, 2, 0, 1), (8, 8, 0, 3, 0, 1), (10, 8, 0, 3, 0, 0), (5, 8, 0, 2, 0, 0),  # lists of 8, 6, 5
-    (1, 1, 1, 0, 1, 0), (32, 1, 0, 0, 1, 0), (2, 2, 1, 0, 1, 1),     # a single block under dropout
-    (2, 10, 1, 3, 0, 1), (2, 10, 1, 3, 1, 0), (3, 10, 2, 3, 1, 0), (2, 16, 2, 3, 1, 1), (3, 9, 2, 3, 1, 1),
-    (1, 12, 0, 3, 0, 1), (1, 12, 0, 3, 1, 1),                        # no list is that long without global blocks
+@pytest.mark.parametrize("BH,nb,g,r,masked,drop,fwd", [
+    (12, 8, 0, 2, 0, 0, 0), (12, 8, 1, 2, 0, 0, 1), (8, 8, 0, 3, 0, 0, 1), (10, 8, 0, 3, 0, 0, 0), (5, 8, 0, 2, 0, 0, 0),  # of 5, 6, 8
+    (12, 8, 1, 2, 1, 0, 0), (9, 8, 1, 2, 1, 0, 0), (8, 8, 1, 2, 1, 1, 1),                # under a mask
+    (1, 1, 1, 0, 0, 1, 0), (32, 1, 0, 0, 1, 1, 0), (32, 1, 0, 0, 1, 0, 1), (2, 2, 1, 0, 0, 1, 1),   # a single block under dropout
+    (2, 10, 1, 3, 0, 0, 1), (2, 10, 1, 3, 0, 1, 0), (2, 10, 1, 3, 1, 1, 1), (3, 10, 2, 3, 0, 1, 0), (2, 16, 2, 3, 0, 1, 1),
+    (3, 9, 2, 3, 0, 1, 1), (1, 12, 0, 3, 0, 1, 1),                   # no list is that long without global blocks
 ])
-def test_fp32_forward_launches_by_their_lists(geometry, BH, nb, g, r, drop, fwd):
-    (q,) = geometry([(BH, nb, g, 3, r, 0, drop)])
+def test_fp32_forward_launches_by_their_lists(geometry, BH, nb, g, r, masked, drop, fwd):
+    (q,) = geometry([(BH, nb, g, 3, r, masked, drop)])
     assert q["rows_f32_fwd"] == fwd, q
 
 
