@@ -330,7 +330,7 @@ int attn_bwd_impl(const void* Q, const void* K, const void* V, const void* O,
     p.kv = bb::make_key_split_by_row(p.nb, g);
   }
   p.dq_waves = p.by_row ? bb::kRowWaves : 1;
-  p.dkv_teams = p.by_row ? bb::kRowWaves : bb::dkv_two_teams(p.BH, p.kv) ? 2 : 1;
+  p.dkv_teams = p.by_row ? bb::kRowWaves : bb::dkv_two_teams(p.BH, p.nb, p.kv) ? 2 : 1;
   if (dtype == BB_BF16 && !p.by_row && bb::dq_two_waves(p.BH, p.split)) {
     p.dq_waves = 2;
     const int sparse_ub = bb::longest_sparse_list(p.nb, g, w, r);

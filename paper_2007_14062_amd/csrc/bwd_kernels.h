@@ -85,7 +85,13 @@ inline bool dq_two_waves(int BH, const RowSplit& s) {
 // 84 / 78, 12 of n = 2048 (456) 53.1 / 50.7, with w = 7 62 / 58, padded 56.5 / 53.0, under dropout 90 / 81, 48 of n = 512 (384)
 // 42.0 / 39.8, 4 of n = 4096 (312) 50.2 / 48.6; 8 of n = 2048 (304) and 16 of n = 1024 (288) the same.  Past 512 items:
 // 12 of n = 2048 with four global blocks (528) 63.3 / 67.1, 24 of n = 1536 (672) 57.3 / 58.5, 12 of n = 4096 (936) 67 / 72, 24 (1872) 101.5 / 111.
-inline bool dkv_two_teams(int BH, const KeySplit& s) { return static_cast<long long>(BH) * s.items_per_bh <= 512; }
+// Short lists leave the second pair one entry or none, and only gain where it lets a second workgroup onto a unit: one block
+// 15.8 / 16.4 (384 slices), 96 of n = 192 (288 items) 17.9 / 19.0, 72 of n = 256 (288) 19.2 / 20.1, 48 of n = 384 (288) 23.4 / 24.2,
+// but 64 of n = 384 (384) 26.7 / 25.6 and under dropout 40 / 35, 96 of n = 256 (384) 21.9 / 21.0 and 31 / 28.
+inline bool dkv_two_teams(int BH, int nb, const KeySplit& s) {
+  const long long items = static_cast<long long>(BH) * s.items_per_bh;
+  return items <= 512 && nb > 1 && (nb > 6 || items > 288);
+}
 
 // Slices of a die whose items alternate in the dK/dV kernels, in groups as equal as they come: as many as have their Q and
 // dO (256 n bytes each) in an L2 together.  With the longest lists of all of them first the bf16 kernel ends sooner (24

@@ -422,7 +422,8 @@ def test_small_launches_by_blocks_bf16(B, H, n, g, w, r, drop, padded):
     (3, 11, 14, 2, 3, 3),    # 528: one pair
     (1, 7, 41, 1, 5, 3),     # odd lists, a rest of one
     (1, 2, 70, 2, 65, 1),    # few items, lists of more than 64 blocks
-    (1, 257, 1, 0, 1, 0),    # lists of one: the second pair has none
+    (1, 257, 1, 0, 1, 0),    # lists of one: one pair
+    (2, 80, 2, 0, 1, 1),     # of at most two
 ])
 @pytest.mark.parametrize("case", ["plain", "skip", "drop"])
 def test_two_pairs_of_waves_per_key_block(B, H, nb, g, w, r, case):

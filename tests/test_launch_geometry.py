@@ -20,14 +20,15 @@ int main() {
   while (scanf("%d %d %d %d %d %d %d", &BH, &nb, &g, &w, &r, &masked, &drop) == 7) {
     const bb::Bf16Geom q = bb::make_bf16_geom(BH, nb, g, w, r, masked != 0);
     const bb::RowSplit s = bb::make_row_split(BH, nb, g, w, r);
-    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", q.waves, q.by_row, q.sw_len, q.gw_len, q.ng, q.cs, q.n_sitems, q.p_wgs,
            q.g_wgs, q.bh_rounds, bb::longest_sparse_list(nb, g, w, r), bb::kListedItems, s.slots_per_bh,
            bb::rows_f32_fwd(BH, nb, g, w, r, masked != 0, drop != 0), bb::rows_f32_bwd(BH, nb), bb::dkv_global_slice(BH, nb, g, w, r, masked != 0, drop != 0),
-           bb::dq_global_slice(BH, nb, g, w, r, masked != 0), bb::make_key_split(nb, g, w, r, 0, 8).slots_per_bh);
+           bb::dq_global_slice(BH, nb, g, w, r, masked != 0), bb::make_key_split(nb, g, w, r, 0, 8).slots_per_bh, bb::bwd_by_row(BH, nb, g, w, r),
+           bb::dkv_two_teams(BH, nb, bb::make_key_split(nb, g, w, r, 0, bb::dkv_global_slice(BH, nb, g, w, r, masked != 0, drop != 0))));
   }
 }
 """
-FIELDS = "waves by_row sw_len gw_len ng cs n_sitems p_wgs g_wgs bh_rounds sparse listed slots_per_bh rows_f32_fwd rows_f32_bwd dkv_slice dq_slice kv_slots_per_bh".split()
+FIELDS = "waves by_row sw_len gw_len ng cs n_sitems p_wgs g_wgs bh_rounds sparse listed slots_per_bh rows_f32_fwd rows_f32_bwd dkv_slice dq_slice kv_slots_per_bh bwd_by_row two_teams".split()
 
 
 @pytest.fixture(scope="module")
@@ -165,6 +166,16 @@ def test_fp32_forward_launches_by_their_lists(geometry, BH, nb, g, r, masked, dr
 def test_slices_of_global_key_blocks(geometry, BH, nb, masked, drop, dkv):
     (q,) = geometry([(BH, nb, 2, 3, 3, masked, drop)])
     assert q["dkv_slice"] == dkv
+
+
+@pytest.mark.parametrize("BH,nb,g,two", [
+    (384, 1, 0, 0), (512, 1, 1, 0),                                  # lists of one
+    (96, 3, 1, 0), (72, 4, 2, 0), (48, 6, 2, 0), (97, 3, 1, 1), (64, 6, 2, 1), (160, 2, 1, 1),   # short lists: 288 items, more
+    (48, 8, 2, 1), (32, 9, 0, 1), (32, 10, 2, 1), (24, 16, 2, 1), (32, 16, 0, 1), (33, 16, 0, 0),
+])
+def test_pairs_of_waves_per_key_block(geometry, BH, nb, g, two):
+    (q,) = geometry([(BH, nb, g, 3, 3)])
+    assert q["two_teams"] == two and not q["bwd_by_row"], q
 
 
 @pytest.mark.parametrize("BH,nb,masked,items", [
