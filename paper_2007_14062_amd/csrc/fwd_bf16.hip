@@ -9,9 +9,9 @@
 //     loop.  Per die, the first workgroups take one global query block each (key list
 //     dealt out 16 blocks per wave, the four waves' results merged in LDS: no partial
 //     results in HBM and no second kernel for up to 64 key blocks; longer rows take
-//     several workgroups plus the merge kernel; launches of medium size: 8 blocks per wave and
-//     workgroups of eight waves, which took 24 slices of n = 4096 from 24.0 us, a merge launch in them,
-//     to 19.7).  The other workgroups stay for the whole
+//     several workgroups plus the merge kernel; launches of medium size, where it pays
+//     (make_bf16_geom): 8 blocks per wave and workgroups of eight waves, which took 24 slices of
+//     n = 4096 from 24.0 us, a merge launch in them, to 19.7).  The other workgroups stay for the whole
 //     launch: their waves share out the die's non-global items round robin and run them
 //     as one uninterrupted stream of block pairs -- the next item's query tile and first
 //     K tile ride at the end of this item's K and V tile streams, so the matrix pipe
@@ -50,11 +50,11 @@
 //     the largest probability of a row is 1 and not rounded.  (Against the fixed reference LSE is off by up
 //     to 2^-8 where one key holds a row, and O by 2.33e-3 -- 2-norm, normal inputs, rows of 454 keys -- where the
 //     recurrence has 2.18e-3.  A maximum of the whole row found in a pass of its own gives 2.23e-3: the maxima on
-//     the way there are exact too.)  What bounds it is the vector port, 415 instructions a pair where the
-//     body without a maximum has 206: 230 leading global tokens, where every item has such a block, 73 -> 57 us (42 with
-//     256); 8 sequences of 1024 .. 4096 valid positions, 12 heads, n = 4096, 75 -> 70 us, and with padded query
-//     blocks skipped 87 -> 58.  (The recurrence had been one pair after another and its items a list worked off
-//     at the end, while other waves had nothing left to do.)  The order of issue inside its slots, pinned in
+//     the way there are exact too.)  What bounds it is the vector port, 410 instructions a pair (98 more where keys
+//     are padded) and the body without a maximum 206, matrix instructions included: 230 leading global tokens, where
+//     every item has such a block, 74.6 -> 55.1 us (42 with 256); 8 sequences of 1024 .. 4096 valid positions, 12 heads, n =
+//     4096, 85.8 -> 73.9 us, and with padded query blocks skipped 89.0 -> 58.8.  (The recurrence had been one pair
+//     after another and its items a list worked off at the end, while other waves had nothing left to do.)  The order of issue inside its slots, pinned in
 //     six ways, made no difference beyond 1 us and is left to the compiler.
 //     The list builder leaves the validity bits of such blocks in LDS, so that no pair waits for the mask.
 //   * The two waves of a SIMD get their issue priority from the pairs they still have to
@@ -1378,7 +1378,7 @@ void fwd_kernel_bf16(FwdParams p) {
       // Which kind of pairs: a scalar test (a flag in a vector register was reloaded from scratch memory at the start of every
       // item, with a wait for all that was in flight).  Two ifs and not one with an else: the compiler lays the kinds
       // out one behind the other, and what the second reads lives through the pairs of the first unless it is said
-      // not to.  33 and 32 spilled vector registers -> 3 and 7 (kMasked, kOptions; with the lists' lane numbers from lane_again):
+      // not to.  33 and 32 spilled vector registers -> 2 and 7 (kMasked, kOptions; with the lists' lane numbers handed on):
       // 8 sequences of n = 4096, 12 heads, padded at block ends, 61.4 -> 59.0 us, inside blocks 72.1 -> 70.1, 230 global tokens 57.8 -> 55.1.
       unsigned running = kMode == kDrop ? 1u : kMode == kPlain ? 0u : cur.partial;
       if (running != 0) {
