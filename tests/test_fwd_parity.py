@@ -226,12 +226,12 @@ def test_running_maximum_in_the_streams(H, nb, g, w, r, skip, gain):
 
 @pytest.mark.parametrize("B,H,nb,g,w,r", [
     (1, 1, 1, 1, 1, 0), (1, 1, 3, 0, 1, 0), (1, 3, 9, 2, 3, 3), (1, 16, 18, 2, 3, 3), (1, 17, 17, 2, 3, 3),
-    (1, 2, 66, 1, 3, 60), (1, 2, 70, 1, 3, 61), (1, 1, 130, 2, 3, 12)])
+    (1, 2, 66, 1, 3, 60), (1, 2, 70, 1, 3, 61), (1, 1, 130, 2, 3, 12), (1, 6, 48, 4, 9, 3)])
 @pytest.mark.parametrize("masked", [False, True])
 def test_rows_by_workgroup(B, H, nb, g, w, r, masked):
     """Small launches (a workgroup per row) and the first ones past the limit of 288 rows; key lists of 1, 2, 3,
-    9, 16, 64 and 65 blocks dealt out to four waves; global rows of one and of several workgroups; a mask
-    that leaves waves without a block."""
+    9, 16, 64 and 65 blocks dealt out to four waves; global rows of one and of several workgroups (48 blocks to one, where
+    lists of 16 leave no room for two); a mask that leaves waves without a block."""
     n = nb * 64
     t = inp.make_tensors(B, H, n, 64, 70 + nb, "bf16")
     ridx = bb.bigbird_make_rand_idx(H, n, 64, g, w, r, 8)
